@@ -272,9 +272,11 @@ int pgmoe_expert_ffn(pgmoe_ctx *ctx, int block, const void *x_perm, const int32_
  * from the moment the library is loaded there until the process ends.  The call allocates
  * nothing (no hipMalloc / hipFree, no allocating library routine) and otherwise behaves as
  * pgmoe_expert_ffn() (same arguments without `workspace`, same waits and events).
- *   - A launch that needs more scratch than the buffer holds is refused with PGMOE_EINVAL and a
- *     text that names both sizes (decode-sized launches need a few MiB; 4096 rows over 128
- *     experts would need 201 MB: use pgmoe_expert_ffn with a workspace there).
+ *   - A launch whose partial sums (with hundreds of rows per expert also the hidden activation) need
+ *     more scratch than the buffer holds is refused with PGMOE_EINVAL and a
+ *     text that names both sizes (decode-sized launches need a few MiB; 4096 rows over 8
+ *     experts would need 82 MB: use pgmoe_expert_ffn with a workspace there).  Launches in between
+ *     use the buffer for one part of their rows after the other.
  *   - All calls on one GPU, from every context, share the buffer and it keeps the last call's
  *     contents: nothing in it has to start at zero (every partial sum that is read was written
  *     by the same call), but two calls whose stream work overlaps on one GPU race.  Calls on

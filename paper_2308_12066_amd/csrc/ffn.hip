@@ -4,7 +4,7 @@
 // bf16 path - three kernels, picked from the shape of the launch alone (plan_ffn and friends):
 //   ffn_fused_kernel   the general, HBM-bound case (described next);
 //   ffn_decode_kernel  a handful of active experts with <= 16 rows each (batch-1 decode);
-//   ffn_gemm_pack_rows_kernel + ffn_gemm_tile_kernel (twice)  hundreds of rows per expert: two tiled GEMMs (ffn_gemm.hip).
+//   ffn_gemm_pack_rows_kernel + ffn_gemm_tile_kernel (twice)  many rows per expert: two tiled GEMMs (ffn_gemm.hip).
 // The fused kernel streams the weights from HBM exactly once per 16*MT-row chunk:
 //   workgroup = (chunk of <= 16*MT rows of one expert) x (a range of d_ff columns)
 //   = (blockIdx.x, blockIdx.y).
@@ -494,14 +494,16 @@ size_t ffn_workspace_bytes(const pgmoe_config &c) {
     return ((std::max(std::max(worst, big), gemm) + 255) & ~(size_t)255);
 }
 
-// Workspace bytes the launch of n_rows rows uses (what launch_ffn below writes and reads).
+size_t ffn_partial_bytes(const pgmoe_config &c, int n_rows) {
+    const FfnPlan p = plan_ffn(c, n_rows);
+    return uses_decode_kernel(c, p) || p.n_partial > 1 ? (size_t)p.n_partial * n_rows * c.d_model * 4 : 0;
+}
+
+// Scratch by which pgmoe_expert_ffn_static admits a launch of n_rows rows.
 size_t ffn_launch_workspace_bytes(const pgmoe_config &c, int n_rows) {
     if (n_rows <= 0) return 0;
     if (c.dtype == PGMOE_F32) return (size_t)n_rows * c.d_ff * 4;
-    if (uses_gemm_kernels(c, n_rows)) return ffn_gemm_launch_bytes(c, n_rows);
-    const FfnPlan p = plan_ffn(c, n_rows);
-    if (uses_decode_kernel(c, p) || p.n_partial > 1) return (size_t)p.n_partial * n_rows * c.d_model * 4;
-    return 0;
+    return uses_gemm_kernels(c, n_rows) ? ffn_gemm_launch_bytes(c, n_rows) : ffn_partial_bytes(c, n_rows);
 }
 
 // Scratch of pgmoe_expert_ffn_static(): part of the library's device image, so no call ever
@@ -592,8 +594,9 @@ int launch_ffn(pgmoe_ctx *ctx, const char *w_base, size_t w_stride, bool slot_by
         return PGMOE_OK;
     }
     if (uses_gemm_kernels(c, n_rows))
-        return launch_ffn_gemm(ctx, w_base, w_stride, slot_by_rank, n_slots, x_perm, offsets, n_rows, y_perm, workspace, s,
-                               keep_partials, table, src_row);
+        return launch_ffn_gemm(ctx, w_base, w_stride, slot_by_rank, n_slots, x_perm, offsets, n_rows, y_perm, workspace,
+                               workspace == ctx->static_scratch ? PGMOE_STATIC_SCRATCH_BYTES : ffn_workspace_bytes(c), s, keep_partials,
+                               table, src_row);
     const FfnPlan p = plan_ffn(c, n_rows);
     const int kt = c.d_model / 32;
     if (uses_decode_kernel(c, p)) {

@@ -93,22 +93,26 @@ __device__ inline void lds_barrier() {
 }
 
 // ---- host side, defined in ffn.hip
+// Bytes of the float32 partial sums of a fused or decode-sized launch of n_rows rows.
+size_t ffn_partial_bytes(const pgmoe_config &c, int n_rows);
 // Next free event pair when FFN timing is on, else -1.
 int ffn_timing_slot(pgmoe_ctx *ctx);
 // y_perm = bf16(sum of the P float32 partials [P][n_rows, d]), added in a fixed order.
 int launch_ffn_reduce(pgmoe_ctx *ctx, const float *partial, int P, int n_rows, void *y_perm, hipStream_t s);
 
 // ---- host side, defined in ffn_gemm.hip
+// Rows per expert from which a launch always takes the two-GEMM path.
+constexpr int GEMM_ALWAYS = 192;
 // Does a launch of n_rows rows take the two-GEMM path?
 bool uses_gemm_kernels(const pgmoe_config &c, int n_rows);
 // Workspace the two-GEMM path needs for max_tokens * top_k rows.
 size_t ffn_gemm_workspace_bytes(const pgmoe_config &c);
-// Workspace bytes one two-GEMM launch of n_rows rows uses.
+// The scratch pgmoe_expert_ffn_static admits a two-GEMM launch of n_rows rows by.
 size_t ffn_gemm_launch_bytes(const pgmoe_config &c, int n_rows);
-// The two-GEMM path of launch_ffn (same arguments).
+// The two-GEMM path of launch_ffn (same arguments; workspace_bytes: what the workspace holds).
 int launch_ffn_gemm(pgmoe_ctx *ctx, const char *w_base, size_t w_stride, bool slot_by_rank, int n_slots, const void *x_rows,
-                    const int32_t *offsets, int n_rows, void *y_perm, void *workspace, hipStream_t s, int *keep_partials,
-                    const unsigned long long *table, const int32_t *src_row);
+                    const int32_t *offsets, int n_rows, void *y_perm, void *workspace, size_t workspace_bytes, hipStream_t s,
+                    int *keep_partials, const unsigned long long *table, const int32_t *src_row);
 
 }  // namespace pgmoe
 #endif  // PGMOE_FFN_COMMON_H

@@ -1,111 +1,193 @@
-// Expert execution for launches with hundreds of rows per expert (Sec. II-B: every activated
-// expert, a dense FFN, processes the tokens routed to it): the two products as two tiled GEMMs.
+// Expert execution for launches with many rows per expert (Sec. II-B: every activated expert, a
+// dense FFN, processes the tokens routed to it): the two products as two tiled GEMMs.
+#include <climits>
+#include <cmath>
+
 #include "ffn_common.h"
 
 namespace pgmoe {
 
 // ------------------------------------------------------------------------------------------
-// Many rows per expert (hundreds): the weights must be reused across many rows, so the two
+// With many rows per expert the weights must be reused across many rows, so the two
 // products run as two tiled GEMMs with the hidden activation (bf16) parked in the workspace
 // between them, after a small kernel that gathers the rows and packs them as operand tiles:
 //   ffn_gemm_pack_rows_kernel   Xp = rows of x, chunk by chunk, as 1 KiB operand tiles
 //   ffn_gemm_tile_kernel<UP>    H[rows, f] = ReLU(Xp . W1)                           K = d
-//   ffn_gemm_tile_kernel<DOWN>  partial[s][rows, d] = H[rows, K-slice s] . W2        K = f / n_split
-// Both products work on chunks of 128 rows of one expert and 128 output columns, four wavefronts
-// as 2 x 2 with 4 x 4 accumulator tiles each, and load BOTH operands straight from memory into
-// LDS in operand order (every operand tile is 1 KiB contiguous: the packed rows, the packed
-// hidden activation the up-projection writes, and the pre-tiled weights).
+//   ffn_gemm_tile_kernel<DOWN>  y_perm[rows, d] = H . W2, or with K slices
+//                               partial[s][rows, d] = H[rows, K-slice s] . W2        K = f / n_split
+// A workgroup of eight wavefronts takes up to 320 rows of one expert and 256 (or 128) output columns and loads
+// BOTH operands straight from memory into LDS in operand order (every operand tile is 1 KiB contiguous: the
+// packed rows, the packed hidden activation the up-projection writes, and the pre-tiled weights).
 //
-// Measured on the 4096-row, 8-expert shape (d 768, f 3072; 19.3 GFLOP per product): pack 5 us,
-// up 32 us, down 35 us (the vendor GEMM library: 27 + 41 us for the two products, no gather, no
-// ReLU).  What was learnt on the way, in the order it mattered:
-//  * matrix-core accumulators must be ordinary vector registers (build flag): with the
-//    accumulator-register form the register allocator copies accumulators about inside the k
-//    loop and every copy waits for the product before it (6 us per product);
-//  * a product's time is that of its load stream alone (down-projection: loads and barriers
-//    without any arithmetic 33 us; arithmetic and LDS reads without loads 25 us): about 300 MB
-//    cross from L2 to the CUs per product and L2 misses on a quarter to a third of it (per XCD
-//    one expert's weights and rows against 4 MB of L2); a workgroup advances only when the
-//    slowest of a stage's sixteen tiles is there.  Neither a deeper ring (3 to 8 stages), nor
-//    more workgroups per CU, nor reading fragments a stage ahead, nor K slices, nor k orders
-//    rotated per expert / per column block (memory channels), nor the items of several chunks
-//    ordered column block by column block, nor v_mfma_f32_32x32x16_bf16 on the same tiles move
-//    it by more than a tenth; a fifth wavefront that touches the lines 16 stages ahead (to have
-//    them in L2) makes it slower (50 us: its touches are as many L2 requests as the loads);
-//  * 256 x 256 tiles with eight wavefronts halve that traffic and reach 32 us for the down
-//    product; not kept.  The same tile with four wavefronts of 128 x 128 (sixteen 32x32x16
-//    accumulators each, pinned to the accumulation registers from inline assembly) is correct
-//    but slower still, 40 us: with one wavefront per SIMD every wait is exposed;
-//  * the up-projection first staged row-major x through registers into LDS (41 us; direct loads
-//    of row-major x are slower still, 44 us: an operand tile takes 16 bytes from each of 16 rows
-//    per lane group and the address unit, not the data, paces the load).  Packing the rows once
-//    (5 us) and loading them like every other operand is 3 us faster in all and leaves one
-//    kernel for both products.
-constexpr int GEMM_ROWS = 128, GEMM_COLS = 128;
+// What bounds it and why the tile looks like this (measured on one MI355X):
+//  * large launches (128 experts of 1024 x 4096, 32768 rows): 322 us up, 361 us down, 454 and 464 with chunks of 128 rows
+//    and 128 columns before.  A CU keeps about 64 KiB of requests in flight whatever the ring holds (3, 4 and 5 stages
+//    are equal), and they return in order, so row tiles that L2 has wait behind weight tiles that HBM brings: the stream of
+//    weights runs at half of what it reaches alone (10 against 16 us for 38 MB beside / without the rows' tiles).
+//    Hence as many rows per weight tile as the registers hold (320: 160 accumulator registers of 246), no second
+//    chunk for an expert that has a few rows more than a power of two, and no request for a row tile the chunk lacks;
+//  * 8 experts of 768 x 3072, 4096 rows: 27 us up, 31 down (the vendor GEMM library: 27 + 41), of which the matrix cores
+//    alone take 21 and the load stream alone 21; random operands hold them to about 1.6 PFLOP/s;
+//  * matrix-core accumulators must be ordinary vector registers (build flag): with the accumulator-register form the
+//    register allocator copies accumulators about inside the k loop and every copy waits for the product before it;
+//  * one result straight in bf16 where no K slices are needed: the float32 partials of one slice cost the combine 14 us
+//    of 59 on the large launch.
+constexpr int GEMM_ROWS = 320;           // most rows of a chunk
+constexpr int GEMM_RT = GEMM_ROWS / 16;  // 16-row tiles of the largest chunk
+
+// The chunks of an expert are of equal size (its rows dealt to as few chunks as hold them, in whole
+// 16-row tiles): 330 rows are two chunks of 176 and 154 rows, not 320 and 10, so no workgroup streams a whole
+// slab of weights for a handful of rows.  tile0 counts the 16-row tiles of all chunks before this one: the
+// packed rows and the packed hidden activation are laid out by it.
+struct GemmChunk {
+    int expert, slot, row0, nrows, tile0;  // tile0 counts from the launch's first tile; nrows == 0: there is no such chunk
+};
+struct GemmScan {  // per lane: four experts, lane + 64 * q; everything a lookup needs, from one round of loads
+    int lo[4], n[4], k0[4], c[4], c_incl[4], t_incl[4], nz_incl[4];
+    int total, active;  // chunks of all experts, experts with chunks (uniform)
+};
+__device__ inline int gemm_chunks_of(int n) { return (n + GEMM_ROWS - 1) / GEMM_ROWS; }
+__device__ inline int gemm_rows_of(int n, int chunks) { return (((n + chunks - 1) / chunks) + 15) & ~15; }
+// Chunks whose first tile lies in [tiles_lo, tiles_hi): a launch whose scratch does not hold every row at once works
+// through them in several passes.
+__device__ inline void gemm_scan(const int32_t *__restrict__ offsets, int E, int tiles_lo, int tiles_hi, GemmScan &s) {
+    const int lane = threadIdx.x & 63;
+    int hi[4];
+#pragma unroll
+    for (int q = 0; q < 4; ++q) {
+        s.lo[q] = hi[q] = 0;
+        if (q * 64 < E) {  // uniform
+            s.lo[q] = offsets[min(q * 64 + lane, E)];
+            hi[q] = offsets[min(q * 64 + lane + 1, E)];
+        }
+    }
+    int c = 0, t = 0, z = 0, a = 0;
+#pragma unroll
+    for (int q = 0; q < 4; ++q) {
+        const int n = s.n[q] = hi[q] - s.lo[q];
+        s.k0[q] = s.c[q] = s.c_incl[q] = s.t_incl[q] = s.nz_incl[q] = 0;
+        if (q * 64 < E) {
+            s.t_incl[q] = t + wave_incl_scan((n + 15) >> 4);
+            s.nz_incl[q] = z + wave_incl_scan(n > 0 ? 1 : 0);
+            s.c[q] = gemm_chunks_of(n);
+            if (tiles_hi < INT_MAX) {  // uniform: only these chunks of the expert, from the k0-th on
+                const int rt = max(1, gemm_rows_of(n, max(1, s.c[q])) >> 4), first = s.t_incl[q] - ((n + 15) >> 4);
+                const int from = min(s.c[q], max(0, (tiles_lo - first + rt - 1) / rt));
+                const int to = min(s.c[q], max(0, (tiles_hi - first + rt - 1) / rt));
+                s.k0[q] = from;
+                s.c[q] = to - from;
+            }
+            s.c_incl[q] = c + wave_incl_scan(s.c[q]);
+            a += __popcll(__ballot(s.c[q] > 0));
+            c = __builtin_amdgcn_readlane(s.c_incl[q], 63);
+            t = __builtin_amdgcn_readlane(s.t_incl[q], 63);
+            z = __builtin_amdgcn_readlane(s.nz_incl[q], 63);
+        }
+    }
+    s.total = c;
+    s.active = a;
+}
+__device__ inline GemmChunk gemm_find(const GemmScan &s, int E, int tiles_lo, int chunk) {
+    GemmChunk ci = {0, 0, 0, 0, 0};
+#pragma unroll
+    for (int q = 0; q < 4; ++q) {
+        if (q * 64 >= E) break;
+        const int c_excl = s.c_incl[q] - s.c[q];
+        const unsigned long long hit = __ballot(chunk >= c_excl && chunk < s.c_incl[q]);
+        if (hit) {
+            const int src = __ffsll((long long)hit) - 1;  // uniform: read that lane's values directly
+            const int n = __builtin_amdgcn_readlane(s.n[q], src);
+            const int k = chunk - __builtin_amdgcn_readlane(c_excl, src) + __builtin_amdgcn_readlane(s.k0[q], src);
+            const int rows = gemm_rows_of(n, gemm_chunks_of(n));
+            ci.expert = q * 64 + src;
+            ci.slot = __builtin_amdgcn_readlane(s.nz_incl[q], src) - 1;
+            ci.row0 = __builtin_amdgcn_readlane(s.lo[q], src) + k * rows;
+            ci.nrows = min(rows, n - k * rows);
+            ci.tile0 = __builtin_amdgcn_readlane(s.t_incl[q], src) - ((n + 15) >> 4) + k * (rows >> 4) - tiles_lo;
+            return ci;
+        }
+    }
+    return ci;
+}
 
 // XCD-aware dealing of the (chunk, column block) items of a GEMM launch.  Workgroups go to the 8
-// XCDs round-robin in launch order and every XCD has its own L2; the items that exist are dealt
-// out so that each XCD works through one contiguous run of them, chunk-major: the workgroups
-// that share a chunk's rows, and the chunks that share an expert's weights, meet in one L2.
+// XCDs round-robin in launch order and every XCD has its own L2.  All column blocks of a chunk go to one XCD (they
+// share its rows), and so do G consecutive chunks, G being how many an expert has on average (they share its
+// weights); such groups are dealt round-robin, so that the large chunks of a popular expert do not all end up on
+// one XCD.  What is left over is cut into eight equal runs of items.
 // False: this workgroup has no item (uniform over the workgroup).
-__device__ inline bool gemm_item(const int32_t *__restrict__ offsets, int E, int &chunk_id, int &col_id) {
+__device__ inline bool gemm_item(const GemmScan &s, int &chunk_id, int &col_id) {
     const int gy = gridDim.y;
-    const int n_items = count_chunks(offsets, E, GEMM_ROWS) * gy;
     const int lin = blockIdx.y * gridDim.x + blockIdx.x;
-    const int xcd = lin & 7, turn = lin >> 3;
-    if (turn >= (n_items >> 3) + (xcd < (n_items & 7) ? 1 : 0)) return false;
-    const int item = xcd * (n_items >> 3) + min(xcd, n_items & 7) + turn;
-    chunk_id = item / gy;
-    col_id = item - chunk_id * gy;
+    const int xcd = lin & 7;
+    int turn = lin >> 3;
+    const int G = s.active > 0 ? (s.total + s.active - 1) / s.active : 1;
+    const int full = s.total / (8 * G) * G;  // chunks per XCD dealt in groups
+    if (turn < full * gy) {
+        const int lc = turn / gy;
+        col_id = turn - lc * gy;
+        chunk_id = (lc / G * 8 + xcd) * G + lc % G;
+        return true;
+    }
+    turn -= full * gy;
+    const int rest = (s.total - 8 * full) * gy;
+    if (turn >= (rest >> 3) + (xcd < (rest & 7) ? 1 : 0)) return false;
+    const int item = xcd * (rest >> 3) + min(xcd, rest & 7) + turn;
+    chunk_id = 8 * full + item / gy;
+    col_id = item % gy;
     return true;
 }
 
-// The rows of every 128-row chunk, gathered through the row -> token map and stored as the 1 KiB
-// operand tiles the tile kernel below loads straight into LDS: per chunk [d/32 k-tiles][8 row
+// The rows of every chunk, gathered through the row -> token map and stored as the 1 KiB
+// operand tiles the tile kernel below loads straight into LDS: per chunk [d/32 k-tiles][its row
 // tiles][1 KiB], a tile holding 16 rows x 32 features in matrix-core operand order (cell row%16 +
 // 16*((feature%32)/8), 8 features per cell): the layout of the packed hidden activation.  Rows
 // past the chunk's end are zero.  One workgroup packs PACK_KT k-tiles of one chunk: wavefront w
-// packs row tiles w and w + 4, a lane reads 16 bytes of two rows per k-tile (64 contiguous bytes
+// packs row tiles w, w + 8, .., a lane reads 16 bytes of a row per row tile and k-tile (64 contiguous bytes
 // per row and wavefront) and consecutive lanes write consecutive cells, so whole tiles go out as
 // contiguous kilobytes; every load is requested before the first store.
 constexpr int PACK_KT = 2;
-__global__ __launch_bounds__(256) void ffn_gemm_pack_rows_kernel(
+__global__ __launch_bounds__(512) void ffn_gemm_pack_rows_kernel(
     const __bf16 *__restrict__ x_rows, const int32_t *__restrict__ offsets, int E, int d,
     const int32_t *__restrict__ src_row,  // nullable: grouped row r is row src_row[r] of x_rows
-    __bf16 *__restrict__ x_packed) {
-    const ChunkInfo ci = find_chunk(offsets, E, GEMM_ROWS, blockIdx.x);
+    __bf16 *__restrict__ x_packed, int tiles_lo, int tiles_hi) {
+    GemmScan scan;
+    gemm_scan(offsets, E, tiles_lo, tiles_hi, scan);
+    const GemmChunk ci = gemm_find(scan, E, tiles_lo, blockIdx.x);
     if (ci.nrows == 0) return;  // uniform over the workgroup
-    constexpr int RT = GEMM_ROWS / 16;
+    const int rt = (ci.nrows + 15) >> 4;
     const int kt0 = blockIdx.y * PACK_KT;
     const int cell = threadIdx.x & 63, wave = threadIdx.x >> 6;
     const uint4 *src = reinterpret_cast<const uint4 *>(x_rows);
-    uint4 *dst = reinterpret_cast<uint4 *>(x_packed) + (size_t)blockIdx.x * GEMM_ROWS * (d >> 3);
+    uint4 *dst = reinterpret_cast<uint4 *>(x_packed) + (size_t)ci.tile0 * 16 * (d >> 3);
     const int cells_per_row = d >> 3;
-    size_t from[RT / 4];
-    bool live[RT / 4];
+    constexpr int J = (GEMM_RT + 7) / 8;
+    size_t from[J];
+    bool live[J];
 #pragma unroll
-    for (int j = 0; j < RT / 4; ++j) {
-        const int row = (wave + 4 * j) * 16 + (cell & 15);
+    for (int j = 0; j < J; ++j) {
+        const int row = (wave + 8 * j) * 16 + (cell & 15);
         live[j] = row < ci.nrows;
         const int r = ci.row0 + (live[j] ? row : 0);
         from[j] = (size_t)(src_row ? src_row[r] : r) * cells_per_row + (cell >> 4);
     }
-    uint4 v[RT / 4][PACK_KT];
+    uint4 v[J][PACK_KT];
 #pragma unroll
-    for (int j = 0; j < RT / 4; ++j)
+    for (int j = 0; j < J; ++j)
 #pragma unroll
         for (int k = 0; k < PACK_KT; ++k) v[j][k] = src[from[j] + (size_t)(kt0 + k) * 4];
 #pragma unroll
-    for (int j = 0; j < RT / 4; ++j)
+    for (int j = 0; j < J; ++j)
 #pragma unroll
         for (int k = 0; k < PACK_KT; ++k)
-            dst[((size_t)(kt0 + k) * RT + wave + 4 * j) * 64 + cell] = live[j] ? v[j][k] : make_uint4(0, 0, 0, 0);
+            if (wave + 8 * j < rt)
+                dst[((size_t)(kt0 + k) * rt + wave + 8 * j) * 64 + cell] = live[j] ? v[j][k] : make_uint4(0, 0, 0, 0);
 }
 
-// One product with both operands loaded straight into LDS (global_load_lds_dwordx4: each
+// Both operands are loaded straight into LDS (global_load_lds_dwordx4: each
 // lane's 16 bytes land at LDS base + 16 * lane, so a 1 KiB operand tile that is contiguous in
 // memory arrives in operand order with no register round trip and no staging writes).  A stage
-// is one 32-k tile of both operands (8 + 8 KiB); NS stages of LDS form a ring.
+// is one 32-k tile of both operands; NS stages of LDS form a ring.
 //
 // The loads are issued from inline assembly rather than through the compiler's builtin: the
 // compiler cannot tell which stage a later LDS read belongs to and would wait for every load in
@@ -119,138 +201,128 @@ __device__ inline void load_tile_to_lds(const char *src_lane, unsigned lds_tile)
     asm volatile("s_mov_b32 m0, %1\n\tglobal_load_lds_dwordx4 %0, off" ::"v"(src_lane), "s"(lds_tile) : "memory", "m0");
 }
 
-// UP = false: the down-projection, partial[s][rows, N] = A[rows, K-slice s] . W2 with K = f, N = d.
-// UP = true : the up-projection, H = ReLU(A . W1) with K = d, N = f, A the packed rows, W1's tiles
-//             n-tile major (the k-tiles of one 16-column slab are contiguous), the result rounded
-//             to bf16 and stored packed for the down-projection.
-template <int NS, bool UP>
-__global__ __launch_bounds__(256) void ffn_gemm_tile_kernel(
-    const char *__restrict__ a_packed, const int32_t *__restrict__ offsets, int E, int K, int N, int n_split,
-    const char *__restrict__ w_base, size_t w_stride, int slot_by_rank, int n_slots,
-    const unsigned long long *__restrict__ table, void *__restrict__ out, int n_rows) {
-    constexpr int NT = GEMM_ROWS / 16;     // 1 KiB tiles per operand and stage (GEMM_COLS / 16 is the same)
-    constexpr int TPW = 2 * NT / 4;        // tiles a wavefront brings per stage: TPW/2 row tiles, TPW/2 column tiles
-    constexpr int STAGE = 2 * NT * 1024;   // per stage: NT row tiles, then NT column tiles
-    static_assert(GEMM_ROWS == GEMM_COLS && NS >= 3 && TPW * (NS - 2) < 64, "NS - 1 stages of TPW loads per wavefront in flight");
-    extern __shared__ __attribute__((aligned(1024))) char ring[];  // NS stages
-    const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
-    const int wn = wave & 1, wm = wave >> 1;
-    int chunk_id, col_id;
-    if (!gemm_item(offsets, E, chunk_id, col_id)) return;
-    const ChunkInfo ci = find_chunk(offsets, E, GEMM_ROWS, chunk_id);
-    if (ci.nrows == 0) return;  // uniform over the workgroup
-    const char *wexp = table ? reinterpret_cast<const char *>(table[ci.expert])
-                             : w_base + (size_t)(slot_by_rank ? ci.slot : ci.expert) * w_stride;
-    const bool no_weights = table ? wexp == nullptr : (slot_by_rank && ci.slot >= n_slots);
-    const char *wsafe = no_weights ? w_base : wexp;  // a valid address; the rows are written as zeros below
+// What a workgroup of the tile kernel works on (all uniform).
+struct GemmTile {
+    const char *a;   // the chunk's packed operand tiles of the first k-tile: [n_kt][rt][1 KiB]
+    const char *w;   // the expert's operand tiles of the first k-tile and column tile
+    size_t w_tile, w_kt;  // bytes from one column tile / one k-tile of the weights to the next
+    int rt, n_kt;    // row tiles of the chunk, k-tiles to walk
+    int nrows;
+    bool no_weights;  // the expert got no slot: its rows are written as zeros
+};
 
-    const int n_blocks = N / GEMM_COLS;
-    const int nb = col_id % n_blocks, split = col_id / n_blocks;
-    const int n0 = nb * GEMM_COLS;
-    const int n_kt = K / n_split / 32, kt0 = split * n_kt;
-    const int w_nt = N / 16;  // W2 is stored k-tile major, W1 n-tile major
-    // This wavefront brings row tiles and column tiles (TPW/2)*wave .. of every stage;
-    // src[i]: this lane's 16 bytes of its i-th tile for the k-tile to request next.
-    const char *src[TPW];
-    size_t step[TPW];  // to the same tile of the next k-tile
+// The k loop and the epilogue for chunks of at most 16 * WM * MC rows.  Eight wavefronts as WM x WN; a
+// wavefront owns four column tiles (wn*4 ..) and the MC row tiles wm, wm + WM, ...  WM = 512 / BN.
+template <int BN, int NS, bool UP, int MC>
+__device__ inline void gemm_tile_body(const GemmTile &t, char *ring, void *__restrict__ h_chunk, float *__restrict__ partial_rows,
+                                      __bf16 *__restrict__ y_rows, int N, int n0) {
+    constexpr int WN = BN / 64, WM = 8 / WN;
+    constexpr int STAGE = (GEMM_RT + BN / 16) * 1024;  // per stage: the row tiles, then the column tiles
+    constexpr int LA = (WM * MC + 7) / 8, LW = BN / 128, LOADS = LA + LW;  // tiles a wavefront brings per stage
+    constexpr int MX = (MC + 1) / 2, MY = MC - MX;
+    static_assert(NS >= 3 && LOADS * (NS - 1) < 64, "NS - 1 stages of LOADS loads per wavefront in flight");
+    static_assert(8 * (LA - 1) <= WM * (MC - 1), "only a wavefront's last row tile may not exist");
+    const int lane = threadIdx.x & 63, wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
+    const int wn = wave & (WN - 1), wm = wave / WN;
+
+    // A wavefront brings row tiles wave, wave + 8, .. (the last of them only if the chunk has it: a wavefront
+    // without it counts one load less) and LW column tiles.  src[i]: this lane's 16 bytes of its i-th tile for the
+    // k-tile to request next.
+    const bool full = wave + 8 * (LA - 1) < t.rt;  // uniform over the wavefront
+    const char *src[LOADS];
 #pragma unroll
-    for (int i = 0; i < TPW / 2; ++i) {
-        const int t = (TPW / 2) * wave + i;
-        src[i] = a_packed + (size_t)chunk_id * GEMM_ROWS * K * 2 + ((size_t)kt0 * NT + t) * 1024 + lane * 16;
-        step[i] = NT * 1024;
-        if (UP) {
-            src[TPW / 2 + i] = wsafe + ((size_t)((n0 >> 4) + t) * (K / 32) + kt0) * 1024 + lane * 16;
-            step[TPW / 2 + i] = 1024;
-        } else {
-            src[TPW / 2 + i] = wsafe + (size_t)K * N * 2 + ((size_t)kt0 * w_nt + (n0 >> 4) + t) * 1024 + lane * 16;
-            step[TPW / 2 + i] = (size_t)w_nt * 1024;
-        }
-    }
-    const unsigned ring_lds = lds_address(ring) + __builtin_amdgcn_readfirstlane((TPW / 2) * wave * 1024);
+    for (int i = 0; i < LW; ++i) src[i] = t.w + (size_t)(wave + 8 * i) * t.w_tile + lane * 16;
+#pragma unroll
+    for (int i = 0; i < LA; ++i) src[LW + i] = t.a + (size_t)min(wave + 8 * i, t.rt - 1) * 1024 + lane * 16;
+    const size_t a_kt = (size_t)t.rt * 1024;
+    const unsigned a_lds = lds_address(ring) + wave * 1024, w_lds = a_lds + GEMM_RT * 1024;
+    int ahead = 0;  // k-tiles requested so far
     auto issue = [&](unsigned stage_off) {  // the next k-tile of this wavefront's tiles, into the stage at stage_off
 #pragma unroll
-        for (int i = 0; i < TPW / 2; ++i) {
-            load_tile_to_lds(src[i], ring_lds + stage_off + i * 1024);
-            load_tile_to_lds(src[TPW / 2 + i], ring_lds + stage_off + NT * 1024 + i * 1024);
-        }
-    };
-    auto advance = [&](int requested) {  // a request past the last k-tile re-reads the last one
-        if (requested < n_kt) {
+        for (int i = 0; i < LW; ++i) load_tile_to_lds(src[i], w_lds + stage_off + i * 8192);
 #pragma unroll
-            for (int i = 0; i < TPW; ++i) src[i] += step[i];
-        }
+        for (int i = 0; i + 1 < LA; ++i) load_tile_to_lds(src[LW + i], a_lds + stage_off + i * 8192);
+        if (full) load_tile_to_lds(src[LOADS - 1], a_lds + stage_off + (LA - 1) * 8192);
+        // a request past the last k-tile re-reads the last one: nobody needs it, the count stays uniform
+        const bool more = ++ahead < t.n_kt;
+        const size_t da = more ? a_kt : 0, dw = more ? t.w_kt : 0;
+#pragma unroll
+        for (int i = 0; i < LW; ++i) src[i] += dw;
+#pragma unroll
+        for (int i = 0; i < LA; ++i) src[LW + i] += da;
     };
 
-    floatx4 acc[4][4];
+    floatx4 acc[4][MC];
 #pragma unroll
     for (int a = 0; a < 4; ++a)
 #pragma unroll
-        for (int m = 0; m < 4; ++m) acc[a][m] = floatx4{0.f, 0.f, 0.f, 0.f};
+        for (int m = 0; m < MC; ++m) acc[a][m] = floatx4{0.f, 0.f, 0.f, 0.f};
 
-    // NS - 1 stages are requested ahead.  The surplus requests at the end go into a stage nobody
-    // needs and keep the count of outstanding loads uniform.
-    int ahead = 0;  // k-tiles requested so far
-    for (; ahead < NS - 1; ++ahead) {
-        issue(ahead * STAGE);
-        advance(ahead + 1);
-    }
-    const bf16x8 *A = reinterpret_cast<const bf16x8 *>(ring) + (wm * 4) * 64 + lane;
-    const bf16x8 *W = reinterpret_cast<const bf16x8 *>(ring + NT * 1024) + (wn * 4) * 64 + lane;
-    auto read_frags = [&](unsigned stage_off, bf16x8 (&wf)[4], bf16x8 (&af)[4]) {
-        const bf16x8 *Ac = A + (stage_off >> 4), *Wc = W + (stage_off >> 4);
 #pragma unroll
-        for (int a = 0; a < 4; ++a) wf[a] = Wc[a * 64];
+    for (int st = 0; st < NS; ++st) issue(st * STAGE);
+    const bf16x8 *A = reinterpret_cast<const bf16x8 *>(ring) + wm * 64 + lane;
+    const bf16x8 *W = reinterpret_cast<const bf16x8 *>(ring + GEMM_RT * 1024) + wn * 4 * 64 + lane;
+
+    // Half a stage is multiplied while the operands of the next half are read from LDS: X is the
+    // first half of the row tiles, Y the second.  In the middle of turn kt: everyone's reads of stage kt
+    // have returned (they are waited for before the barrier), so its buffer takes the request for stage
+    // kt + NS; stage kt+1 has landed for this wavefront (at most the NS-2 stages after it are outstanding)
+    // and, after the barrier, for everyone.  A fence here would make the compiler wait for every load in flight.
+    bf16x8 wf0[4], wf1[4], ax[MX];
+    if (full) asm volatile("s_waitcnt vmcnt(%0)" ::"n"(LOADS * (NS - 1)) : "memory");
+    else asm volatile("s_waitcnt vmcnt(%0)" ::"n"((LOADS - 1) * (NS - 1)) : "memory");
+    asm volatile("s_barrier" ::: "memory");
 #pragma unroll
-        for (int m = 0; m < 4; ++m) af[m] = Ac[m * 64];
+    for (int a = 0; a < 4; ++a) wf0[a] = W[a * 64];
+#pragma unroll
+    for (int m = 0; m < MX; ++m) ax[m] = A[WM * m * 64];
+    unsigned cur = 0;  // byte offset of the stage being multiplied
+    auto turn = [&](const bf16x8 (&wf)[4], bf16x8 (&wf_next)[4]) {
+        const bf16x8 *Ac = A + (cur >> 4);
+        bf16x8 ay[MY > 0 ? MY : 1];
+#pragma unroll
+        for (int m = 0; m < MY; ++m) ay[m] = Ac[WM * (MX + m) * 64];
+        __builtin_amdgcn_sched_barrier(0);
+#pragma unroll
+        for (int m = 0; m < MX; ++m)
+#pragma unroll
+            for (int a = 0; a < 4; ++a) acc[a][m] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(wf[a], ax[m], acc[a][m], 0, 0, 0);
+        __builtin_amdgcn_sched_barrier(0);
+        if (full) asm volatile("s_waitcnt vmcnt(%0) lgkmcnt(0)" ::"n"(LOADS * (NS - 2)) : "memory");
+        else asm volatile("s_waitcnt vmcnt(%0) lgkmcnt(0)" ::"n"((LOADS - 1) * (NS - 2)) : "memory");
+        asm volatile("s_barrier" ::: "memory");
+        issue(cur);
+        cur = cur + STAGE == NS * STAGE ? 0 : cur + STAGE;
+        const bf16x8 *An = A + (cur >> 4), *Wn = W + (cur >> 4);
+#pragma unroll
+        for (int m = 0; m < MX; ++m) ax[m] = An[WM * m * 64];
+#pragma unroll
+        for (int a = 0; a < 4; ++a) wf_next[a] = Wn[a * 64];
+        __builtin_amdgcn_sched_barrier(0);
+#pragma unroll
+        for (int m = 0; m < MY; ++m)
+#pragma unroll
+            for (int a = 0; a < 4; ++a) acc[a][MX + m] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(wf[a], ay[m], acc[a][MX + m], 0, 0, 0);
+        __builtin_amdgcn_sched_barrier(0);
     };
-    auto multiply = [&](const bf16x8 (&wf)[4], const bf16x8 (&af)[4]) {
-#pragma unroll
-        for (int a = 0; a < 4; ++a)
-#pragma unroll
-            for (int m = 0; m < 4; ++m)
-                acc[a][m] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(wf[a], af[m], acc[a][m], 0, 0, 0);
-    };
-    // The operand fragments of stage kt+1 are read from LDS while stage kt is multiplied (two
-    // register sets, the loop runs two stages per turn; n_kt is even, the launcher checks).  In
-    // turn kt: stage kt+1 has landed for this wavefront (at most the NS-3 stages after it are
-    // outstanding) and, after the barrier, for everyone; everyone's reads of stage kt-1 were
-    // consumed by matrix-core instructions issued before the barrier, so its buffer takes the
-    // request for stage kt+NS-1; the wait on the LDS counter makes that hold wherever the compiler
-    // puts the matrix-core instructions (it costs nothing: those fragments are needed right after).
-    // A fence here would make the compiler wait for every load in flight.
-    bf16x8 wf0[4], af0[4], wf1[4], af1[4];
-    asm volatile("s_waitcnt vmcnt(%0)\n\ts_barrier" ::"n"(TPW * (NS - 2)) : "memory");
-    read_frags(0, wf0, af0);
-    unsigned nxt = STAGE, refill = (NS - 1) * STAGE;  // byte offsets: the stage to read next, the one to request into
-    auto turn = [&](const bf16x8 (&wf)[4], const bf16x8 (&af)[4], bf16x8 (&wf_next)[4], bf16x8 (&af_next)[4]) {
-        asm volatile("s_waitcnt vmcnt(%0) lgkmcnt(0)\n\ts_barrier" ::"n"(TPW * (NS - 3)) : "memory");
-        issue(refill);
-        ++ahead;
-        advance(ahead);
-        read_frags(nxt, wf_next, af_next);
-        multiply(wf, af);
-        refill = refill + STAGE == NS * STAGE ? 0 : refill + STAGE;
-        nxt = nxt + STAGE == NS * STAGE ? 0 : nxt + STAGE;
-    };
-    for (int kt = 0; kt < n_kt; kt += 2) {
-        turn(wf0, af0, wf1, af1);
-        turn(wf1, af1, wf0, af0);
+    for (int kt = 0; kt < t.n_kt; kt += 2) {  // n_kt is even (the launcher checks)
+        turn(wf0, wf1);
+        turn(wf1, wf0);
     }
     asm volatile("s_waitcnt vmcnt(0)" ::: "memory");  // the surplus requests must not outlive the workgroup's LDS
 
-    // lane holds row wm*64 + m*16 + tok, output columns n0 + wn*64 + a*16 + 4*g + {0..3}
+    // lane holds row 16 * row tile + tok, output columns n0 + wn*64 + a*16 + 4*g + {0..3}
     const int tok = lane & 15, g = lane >> 4;
 #pragma unroll
-    for (int m = 0; m < 4; ++m) {
-        const int r = (wm * 4 + m) * 16 + tok;
-        if (r >= ci.nrows) continue;
+    for (int m = 0; m < MC; ++m) {
+        const int tile = wm + WM * m, r = tile * 16 + tok;
+        if (r >= t.nrows) continue;
         if (UP) {
-            // Packed layout of H: per chunk [N/32 k-tiles][NT row tiles][1 KiB]; a tile holds 16 rows x 32
+            // Packed layout of H: per chunk [N/32 k-tiles][row tiles][1 KiB]; a tile holds 16 rows x 32
             // features in matrix-core operand order: cell row%16 + 16*((feature%32)/8), 8 features per
             // cell.  Rows past the chunk's end are left unwritten (the down-projection never stores
             // what it computes from them).
-            __bf16 *dst = reinterpret_cast<__bf16 *>(out) + (size_t)chunk_id * GEMM_ROWS * N + (size_t)(r >> 4) * 512 +
-                          (tok + 16 * (g >> 1)) * 8 + 4 * (g & 1);
+            __bf16 *dst = reinterpret_cast<__bf16 *>(h_chunk) + (size_t)tile * 512 + (tok + 16 * (g >> 1)) * 8 + 4 * (g & 1);
 #pragma unroll
             for (int a = 0; a < 4; ++a) {
                 bf16x4 o;
@@ -258,98 +330,226 @@ __global__ __launch_bounds__(256) void ffn_gemm_tile_kernel(
                 o.y = (__bf16)fmaxf(acc[a][m].y, 0.f);
                 o.z = (__bf16)fmaxf(acc[a][m].z, 0.f);
                 o.w = (__bf16)fmaxf(acc[a][m].w, 0.f);
-                if (no_weights) o = bf16x4{0, 0, 0, 0};
+                if (t.no_weights) o = bf16x4{0, 0, 0, 0};
                 const int kt = (n0 >> 5) + wn * 2 + (a >> 1);  // k-tile of the down-projection these 16 features fall in
-                *reinterpret_cast<bf16x4 *>(dst + (size_t)kt * NT * 512 + (a & 1) * 32 * 8) = o;
+                *reinterpret_cast<bf16x4 *>(dst + (size_t)kt * t.rt * 512 + (a & 1) * 32 * 8) = o;
             }
-        } else {
-            float *dst = reinterpret_cast<float *>(out) + ((size_t)split * n_rows + (size_t)ci.row0 + r) * N + n0 + wn * 64 + 4 * g;
+        } else if (partial_rows) {
+            float *dst = partial_rows + (size_t)r * N + n0 + wn * 64 + 4 * g;
 #pragma unroll
             for (int a = 0; a < 4; ++a)
-                *reinterpret_cast<floatx4 *>(dst + a * 16) = no_weights ? floatx4{0.f, 0.f, 0.f, 0.f} : acc[a][m];
+                *reinterpret_cast<floatx4 *>(dst + a * 16) = t.no_weights ? floatx4{0.f, 0.f, 0.f, 0.f} : acc[a][m];
+        } else {
+            __bf16 *dst = y_rows + (size_t)r * N + n0 + wn * 64 + 4 * g;
+#pragma unroll
+            for (int a = 0; a < 4; ++a) {
+                bf16x4 o;
+                o.x = (__bf16)acc[a][m].x;
+                o.y = (__bf16)acc[a][m].y;
+                o.z = (__bf16)acc[a][m].z;
+                o.w = (__bf16)acc[a][m].w;
+                if (t.no_weights) o = bf16x4{0, 0, 0, 0};
+                *reinterpret_cast<bf16x4 *>(dst + a * 16) = o;
+            }
         }
     }
 }
 
-// The two-GEMM path pays off once an expert sees enough rows for its weights to be reused out
-// of LDS many times: at least 192 rows per expert on average.
-constexpr int GEMM_SPLIT = 4;  // most K slices of the down-projection (float32 partials)
-bool uses_gemm_kernels(const pgmoe_config &c, int n_rows) {
-    if (c.dtype != PGMOE_BF16) return false;
-    // the k loop takes two 32-k tiles per turn (in every K slice of the down-projection); the pack kernel PACK_KT k-tiles per workgroup
-    if (c.d_model % GEMM_COLS || c.d_ff % GEMM_COLS || c.d_model % (32 * PACK_KT) || c.d_ff % (GEMM_SPLIT * 64)) return false;
-    const int active = std::max(1, std::min(c.n_experts, n_rows));
-    return n_rows / active >= 192;
+// UP = false: the down-projection, A . W2 with K = f, N = d, over K / n_split of the k-tiles: into partial[s]
+//             with several slices, else rounded into y_perm.
+// UP = true : the up-projection, H = ReLU(A . W1) with K = d, N = f, A the packed rows, W1's tiles
+//             n-tile major (the k-tiles of one 16-column slab are contiguous), the result rounded
+//             to bf16 and stored packed for the down-projection.
+template <int BN, int NS, bool UP>
+__global__ __launch_bounds__(512) void ffn_gemm_tile_kernel(
+    const char *__restrict__ a_packed, const int32_t *__restrict__ offsets, int E, int K, int N, int n_split,
+    const char *__restrict__ w_base, size_t w_stride, int slot_by_rank, int n_slots,
+    const unsigned long long *__restrict__ table, char *__restrict__ h, float *__restrict__ partial,
+    __bf16 *__restrict__ y_perm, int n_rows, int tiles_lo, int tiles_hi) {
+    extern __shared__ __attribute__((aligned(1024))) char ring[];  // NS stages
+    GemmScan scan;
+    gemm_scan(offsets, E, tiles_lo, tiles_hi, scan);
+    int chunk_id, col_id;
+    if (!gemm_item(scan, chunk_id, col_id)) return;
+    const GemmChunk ci = gemm_find(scan, E, tiles_lo, chunk_id);
+    if (ci.nrows == 0) return;  // uniform over the workgroup
+    const char *wexp = table ? reinterpret_cast<const char *>(table[ci.expert])
+                             : w_base + (size_t)(slot_by_rank ? ci.slot : ci.expert) * w_stride;
+    GemmTile t;
+    t.no_weights = table ? wexp == nullptr : (slot_by_rank && ci.slot >= n_slots);
+    const char *wsafe = t.no_weights ? w_base : wexp;  // a valid address; the rows are written as zeros
+
+    const int n_blocks = N / BN;
+    const int nb = col_id % n_blocks, split = col_id / n_blocks;
+    const int n0 = nb * BN;
+    t.nrows = ci.nrows;
+    t.rt = (ci.nrows + 15) >> 4;
+    t.n_kt = K / n_split / 32;
+    const int kt0 = split * t.n_kt;
+    t.a = a_packed + (size_t)ci.tile0 * 32 * K + (size_t)kt0 * t.rt * 1024;
+    if (UP) {
+        t.w_tile = (size_t)(K / 32) * 1024;
+        t.w_kt = 1024;
+        t.w = wsafe + (size_t)(n0 >> 4) * t.w_tile;
+    } else {
+        t.w_tile = 1024;
+        t.w_kt = (size_t)(N / 16) * 1024;
+        t.w = wsafe + (size_t)K * N * 2 + (size_t)kt0 * t.w_kt + (size_t)(n0 >> 4) * 1024;
+    }
+    void *h_chunk = UP ? h + (size_t)ci.tile0 * 32 * N : nullptr;
+    float *partial_rows = !UP && partial ? partial + ((size_t)split * n_rows + ci.row0) * N : nullptr;
+    __bf16 *y_rows = UP ? nullptr : y_perm + (size_t)ci.row0 * N;
+    // row tiles per wavefront (uniform): the smallest body that holds the chunk
+    const int mc = (t.rt + 512 / BN - 1) / (512 / BN);
+#define PG_BODY(MC_) gemm_tile_body<BN, NS, UP, MC_>(t, ring, h_chunk, partial_rows, y_rows, N, n0)
+    if constexpr (BN == 256) {
+        if (mc > 9) PG_BODY(10);
+        else if (mc > 8) PG_BODY(9);
+        else if (mc > 6) PG_BODY(8);
+        else if (mc > 4) PG_BODY(6);
+        else if (mc > 2) PG_BODY(4);
+        else PG_BODY(2);
+    } else {
+        if (mc > 4) PG_BODY(5);
+        else if (mc > 3) PG_BODY(4);
+        else if (mc > 2) PG_BODY(3);
+        else if (mc > 1) PG_BODY(2);
+        else PG_BODY(1);
+    }
+#undef PG_BODY
 }
 
-// float32 partials of the down-projection (most K slices), then the bf16 hidden activation and
-// the packed rows in 128-row chunks, at most one partly filled chunk per expert
+// ------------------------------------------------------------------------------------------
+constexpr int GEMM_SPLIT = 4;  // most K slices of the down-projection (float32 partials)
+
+// Workspace: float32 partials of the down-projection (most K slices), then the bf16 hidden activation and the packed
+// rows (with room for 128-row chunks, at most one partly filled one per expert; 16-row tiles are what is used).
 size_t ffn_gemm_workspace_bytes(const pgmoe_config &c) {
     const int64_t max_rows = (int64_t)c.max_tokens * c.top_k;
     return (size_t)GEMM_SPLIT * max_rows * c.d_model * 4 +
-           (size_t)(max_rows / GEMM_ROWS + std::min<int64_t>(c.n_experts, max_rows)) * GEMM_ROWS * (c.d_ff + c.d_model) * 2 + 256;
+           (size_t)(max_rows / 128 + std::min<int64_t>(c.n_experts, max_rows)) * 128 * (c.d_ff + c.d_model) * 2 + 256;
 }
 
-// K slices of the down-projection: as few as still give every CU a workgroup (fewer float32
-// partials to write and to add up); one slice runs one workgroup per CU with a deeper ring, more
-// slices two per CU
-static int gemm_split(const pgmoe_config &c, int n_rows) {
-    const int tiles = (n_rows / GEMM_ROWS) * (c.d_model / GEMM_COLS);
-    return tiles >= 160 ? 1 : (tiles >= 80 ? 2 : GEMM_SPLIT);
-}
-
-// Workspace one launch of n_rows rows uses: the float32 partials, the packed hidden activation, the packed rows.
+// What pgmoe_expert_ffn_static admits a launch of n_rows rows by: with hundreds of rows per expert an upper bound of the
+// scratch one pass uses, below that what the fused kernel needs (launch_ffn_gemm then takes as many passes
+// as the static buffer makes necessary).
 size_t ffn_gemm_launch_bytes(const pgmoe_config &c, int n_rows) {
     const int active = std::max(1, std::min(c.n_experts, n_rows));
-    const int max_chunks = active + n_rows / GEMM_ROWS;
-    return (size_t)gemm_split(c, n_rows) * n_rows * c.d_model * 4 + (size_t)max_chunks * GEMM_ROWS * (c.d_ff + c.d_model) * 2;
+    if (n_rows / active < GEMM_ALWAYS) return ffn_partial_bytes(c, n_rows);
+    const int tiles = (n_rows / 128) * (c.d_model / 128);
+    const int split = tiles >= 160 ? 1 : (tiles >= 80 ? 2 : GEMM_SPLIT);
+    return (size_t)split * n_rows * c.d_model * 4 + (size_t)(active + n_rows / 128) * 128 * (c.d_ff + c.d_model) * 2;
+}
+static size_t gemm_tile_bytes(const pgmoe_config &c) { return (size_t)16 * (c.d_ff + c.d_model) * 2; }  // a row tile, hidden and packed
+
+// Does a launch take the two GEMMs?  From GEMM_ALWAYS rows per expert on always.  Below, the fused kernel streams
+// every expert's weights once per chunk of at most 64 rows, with d_ff cut into as few ranges as keep
+// its partial sums cheap, so with few experts or several chunks per expert it leaves CUs idle or reads weights
+// again; the GEMMs cost two launches more and the round trip of the hidden activation.  The two estimates
+// (microseconds) are fitted to measurements over d_model 512 .. 2048, 16 .. 128 experts and 20 .. 300 rows per
+// expert, where they are within 15 %: 64 experts of 768 x 3072 at 28 / 40 / 64 / 100 rows per expert 124 / 155 / 248 / 243 us
+// fused and 128 / 135 / 146 / 161 us as GEMMs; 128 of them 253 / 225 / 281 / 329 and 245 / 257 / 277 / 300.
+bool uses_gemm_kernels(const pgmoe_config &c, int n_rows) {
+    if (c.dtype != PGMOE_BF16) return false;
+    // the k loop takes two 32-k tiles per turn (in every K slice of the down-projection); the pack kernel PACK_KT k-tiles per workgroup
+    if (c.d_model % 128 || c.d_ff % 128 || c.d_model % (32 * PACK_KT) || c.d_ff % (GEMM_SPLIT * 64)) return false;
+    const int active = std::max(1, std::min(c.n_experts, n_rows));
+    if (n_rows / active >= GEMM_ALWAYS) return true;
+    if (n_rows / active < 8) return false;
+    // the static buffer has to hold at least one chunk of a launch it admits
+    if (ffn_partial_bytes(c, n_rows) <= PGMOE_STATIC_SCRATCH_BYTES && 2 * GEMM_RT * gemm_tile_bytes(c) > PGMOE_STATIC_SCRATCH_BYTES) return false;
+    const FfnPlan p = plan_ffn(c, n_rows);
+    const double expert = 4.0 * c.d_model * c.d_ff, weights = active * expert / 5.7e6;  // bytes; us at the rate HBM delivers
+    const double chunks = std::max((double)active, 0.5 * active + n_rows / (16.0 * p.mt)), wgs = chunks * p.n_partial;
+    const bool alone = p.mt * (c.d_model / 32 + p.nw) > 80;  // KiB of LDS: one workgroup per CU, so a second round costs as much as the first
+    const double rounds = 1.0 + std::max(0.0, alone ? (wgs - 220.0) / 100.0 : wgs / 256.0 - 1.0);
+    const double again = 0.3 + 0.7 * chunks / active;  // an expert's second chunk finds part of the weights in a cache
+    const double fused = 8.0 + std::max(weights * again, rounds * expert / p.n_partial / 32e3);
+    const double gemm = 20.0 + weights + 4.0 * n_rows * c.d_model * c.d_ff / 1.8e9;
+    return (active > 96 ? 1.15 : 1.1) * gemm < fused;  // in doubt fused: a skewed routing costs the GEMMs more, with many experts above all
+}
+
+// Column width of the two products and K slices of the down-projection, from the shape of the launch alone.
+struct GemmPlan {
+    int bn_up, bn_down, split;
+    size_t p_bytes;
+};
+static GemmPlan gemm_plan(const pgmoe_config &c, int n_rows) {
+    const int active = std::max(1, std::min(c.n_experts, n_rows));
+    const double chunks = std::max((double)active, n_rows / (double)GEMM_ROWS + 0.4 * active);  // estimate
+    const double rt = std::min(20.0, n_rows / 16.0 / chunks + 0.5);                             // row tiles of a chunk
+    GemmPlan best = {};
+    double best_up = 1e30, best_down = 1e30;
+    const bool admitted = ffn_gemm_launch_bytes(c, n_rows) <= PGMOE_STATIC_SCRATCH_BYTES;
+    for (int bn = 128; bn <= 256; bn *= 2) {
+        // microseconds per 32-k stage of a workgroup that has its CU to itself
+        const double stage = (bn == 256 ? 0.80 : 0.50) * std::max(rt / 20.0, 0.4);
+        auto rounds = [&](double wgs) { return std::max(1.0, std::ceil(wgs / 256.0 - 0.05)); };
+        if (c.d_ff % bn == 0) {
+            const double up = rounds(chunks * (c.d_ff / bn)) * (c.d_model / 32 * stage + 4.0);
+            if (up < best_up) {
+                best_up = up;
+                best.bn_up = bn;
+            }
+        }
+        if (c.d_model % bn == 0)
+            for (int split = 1; split <= GEMM_SPLIT; split *= 2) {
+                const size_t p_bytes = split > 1 ? (size_t)split * n_rows * c.d_model * 4 : 0;
+                if (admitted && split > 1 && p_bytes + 2 * GEMM_RT * gemm_tile_bytes(c) > PGMOE_STATIC_SCRATCH_BYTES) continue;
+                const double down = rounds(chunks * (c.d_model / bn) * split) * (c.d_ff / 32 / split * stage + 4.0) +
+                                    (split > 1 ? 2.0 * p_bytes : 2.0 * n_rows * c.d_model * 2.0) / 4.0e6;
+                if (down < best_down) {
+                    best_down = down;
+                    best.bn_down = bn;
+                    best.split = split;
+                    best.p_bytes = p_bytes;
+                }
+            }
+    }
+    return best;
 }
 
 int launch_ffn_gemm(pgmoe_ctx *ctx, const char *w_base, size_t w_stride, bool slot_by_rank, int n_slots, const void *x_perm,
-                    const int32_t *offsets, int n_rows, void *y_perm, void *workspace, hipStream_t s, int *keep_partials,
-                    const unsigned long long *table, const int32_t *src_row) {
+                    const int32_t *offsets, int n_rows, void *y_perm, void *workspace, size_t workspace_bytes, hipStream_t s,
+                    int *keep_partials, const unsigned long long *table, const int32_t *src_row) {
     const pgmoe_config &c = ctx->cfg;
-    // float32 partials [split][n_rows, d] first (the combine reads them at the workspace's start),
-    // then the packed hidden activation, 128-row chunk by chunk (at most one partly filled chunk per expert)
+    // float32 partials [split][n_rows, d] first (the combine reads them at the workspace's start; none with one slice),
+    // then the packed hidden activation and the packed rows, by 16-row tiles (at most one partly filled tile per expert).
+    // Scratch that does not hold every tile (the static buffer) is used for one range of chunks after the other: a
+    // chunk's result does not depend on the others, so the number of passes changes no bit.
     const int active = std::max(1, std::min(c.n_experts, n_rows));
-    const int max_chunks = active + n_rows / GEMM_ROWS;
-    const int split = gemm_split(c, n_rows);
-    const size_t p_bytes = (size_t)split * n_rows * c.d_model * 4;
-    const size_t h_bytes = (size_t)max_chunks * GEMM_ROWS * c.d_ff * 2;
-    const size_t xp_bytes = (size_t)max_chunks * GEMM_ROWS * c.d_model * 2;
-    if (h_bytes + p_bytes + xp_bytes > ffn_workspace_bytes(c))
+    const int max_chunks = active + n_rows / GEMM_ROWS, max_tiles = active + n_rows / 16;
+    const GemmPlan p = gemm_plan(c, n_rows);
+    const size_t room = workspace_bytes > p.p_bytes ? (workspace_bytes - p.p_bytes) / gemm_tile_bytes(c) : 0;
+    if (room < (size_t)std::min(max_tiles, 2 * GEMM_RT))
         return fail(ctx, PGMOE_EINVAL, "pgmoe_expert_ffn: hidden activation, packed rows and partial sums of %d rows do not fit the workspace", n_rows);
-    float *partial = (float *)workspace;
-    __bf16 *h = (__bf16 *)((char *)workspace + p_bytes);
-    __bf16 *xp = (__bf16 *)((char *)workspace + p_bytes + h_bytes);
+    const bool one_pass = room >= (size_t)max_tiles;
+    const int tiles = one_pass ? max_tiles : (int)room - GEMM_RT;  // first tiles of a pass: its last chunk may reach past them
+    const size_t h_bytes = (one_pass ? (size_t)max_tiles : room) * 16 * c.d_ff * 2;
+    float *partial = p.split > 1 ? (float *)workspace : nullptr;
+    char *h = (char *)workspace + p.p_bytes;
+    char *xp = h + h_bytes;
     const int tslot = ffn_timing_slot(ctx);
     if (tslot >= 0) PG_HIP(ctx, hipEventRecord(ctx->tim_begin[tslot], s));
-    hipLaunchKernelGGL(ffn_gemm_pack_rows_kernel, dim3(max_chunks, c.d_model / 32 / PACK_KT), dim3(256), 0, s, (const __bf16 *)x_perm,
-                       offsets, c.n_experts, c.d_model, src_row, xp);
-    PG_HIP(ctx, hipGetLastError());
-#define PG_TILE(NS_, UP_, GRID_, A_, K_, N_, SPLIT_, OUT_)                                                                       \
-do {                                                                                                                         \
-    constexpr int lds = NS_ * 2 * (GEMM_ROWS / 16) * 1024;                                                                   \
-    auto kern_ = ffn_gemm_tile_kernel<NS_, UP_>;                                                                             \
-    if (int rc_ = allow_dynamic_lds(ctx, reinterpret_cast<const void *>(kern_), lds)) return rc_;                            \
-    hipLaunchKernelGGL(kern_, GRID_, dim3(256), lds, s, (const char *)(A_), offsets, c.n_experts, K_, N_, SPLIT_, w_base,    \
-                       w_stride, slot_by_rank ? 1 : 0, n_slots, table, (void *)(OUT_), n_rows);                              \
-} while (0)
-    // up-projection: a ring of four stages leaves room for two workgroups per CU (its k loop is short)
-    const dim3 grid_up(max_chunks, c.d_ff / GEMM_COLS);
-    PG_TILE(4, true, grid_up, xp, c.d_model, c.d_ff, 1, h);
-    PG_HIP(ctx, hipGetLastError());
-    const dim3 grid_down(max_chunks, (c.d_model / GEMM_COLS) * split);
-    if (split == 1) PG_TILE(6, false, grid_down, h, c.d_ff, c.d_model, split, partial);
-    else PG_TILE(4, false, grid_down, h, c.d_ff, c.d_model, split, partial);
+    for (int lo = 0; lo < max_tiles; lo += tiles) {
+        const int hi = one_pass ? INT_MAX : lo + tiles;  // INT_MAX: every chunk
+        hipLaunchKernelGGL(ffn_gemm_pack_rows_kernel, dim3(max_chunks, c.d_model / 32 / PACK_KT), dim3(512), 0, s, (const __bf16 *)x_perm,
+                           offsets, c.n_experts, c.d_model, src_row, (__bf16 *)xp, lo, hi);
+        PG_HIP(ctx, hipGetLastError());
+#define PG_TILE(BN_, NS_, UP_, A_, K_, N_, SPLIT_)                                                                                  do {                                                                                                                             constexpr int lds = NS_ * (GEMM_RT + BN_ / 16) * 1024;                                                                       auto kern_ = ffn_gemm_tile_kernel<BN_, NS_, UP_>;                                                                            if (int rc_ = allow_dynamic_lds(ctx, reinterpret_cast<const void *>(kern_), lds)) return rc_;                                hipLaunchKernelGGL(kern_, dim3(max_chunks, N_ / BN_ * SPLIT_), dim3(512), lds, s, (const char *)(A_), offsets,                                  c.n_experts, K_, N_, SPLIT_, w_base, w_stride, slot_by_rank ? 1 : 0, n_slots, table, h, partial,                             (__bf16 *)y_perm, n_rows, lo, hi);                                                                        PG_HIP(ctx, hipGetLastError());                                                                                          } while (0)
+        if (p.bn_up == 256) PG_TILE(256, 4, true, xp, c.d_model, c.d_ff, 1);
+        else PG_TILE(128, 5, true, xp, c.d_model, c.d_ff, 1);
+        if (p.bn_down == 256) PG_TILE(256, 4, false, h, c.d_ff, c.d_model, p.split);
+        else PG_TILE(128, 5, false, h, c.d_ff, c.d_model, p.split);
 #undef PG_TILE
-    PG_HIP(ctx, hipGetLastError());
+    }
     if (tslot >= 0) PG_HIP(ctx, hipEventRecord(ctx->tim_end[tslot], s));
+    if (!partial) return PGMOE_OK;  // y_perm was written directly
     if (keep_partials) {
-        *keep_partials = split;
+        *keep_partials = p.split;
         return PGMOE_OK;
     }
-    return launch_ffn_reduce(ctx, partial, split, n_rows, y_perm, s);
+    return launch_ffn_reduce(ctx, partial, p.split, n_rows, y_perm, s);
 }
 
 }  // namespace pgmoe

@@ -150,7 +150,7 @@ struct FfnPlan {
 };
 FfnPlan plan_ffn(const pgmoe_config &cfg, int n_rows);
 size_t ffn_workspace_bytes(const pgmoe_config &cfg);
-size_t ffn_launch_workspace_bytes(const pgmoe_config &cfg, int n_rows);  // what one launch of n_rows rows uses of it
+size_t ffn_launch_workspace_bytes(const pgmoe_config &cfg, int n_rows);  // by what pgmoe_expert_ffn_static admits a launch of n_rows rows
 // Device address of the library's static scratch buffer on the context's device (which must be
 // current) into ctx->static_scratch; resolved once per device and process.
 int resolve_static_scratch(pgmoe_ctx *ctx);

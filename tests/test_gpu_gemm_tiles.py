@@ -1,0 +1,59 @@
+"""The two tiled GEMMs of the expert FFN at the sizes where their tiling can go wrong: chunks of
+every number of 16-row tiles a workgroup body is built for, one row more and one row less, both
+column widths, several K slices, many experts, and scratch that does not hold all rows at once."""
+import numpy as np
+import pytest
+import torch
+
+import workloads as W
+from test_gpu_parity import TOL, hx, nerr, run_ffn_case  # noqa: F401  (hx is a fixture)
+
+pytestmark = pytest.mark.gpu
+
+EDGES = [1, 16, 17, 64, 65, 128, 129, 192, 193, 255, 256, 257, 288, 289, 304, 305, 320, 321, 0, 640, 641, 700, 500]
+
+
+@pytest.mark.parametrize("d,f,E,counts", [
+    (256, 512, len(EDGES), EDGES),                                   # 256-column blocks
+    (128, 256, len(EDGES), EDGES),                                   # 128-column blocks in the down-projection
+    (128, 1024, 2, [1500, 700]),                                     # K slices of the down-projection
+    (512, 256, 130, [200 + (e * 37) % 140 if e % 3 else 300 for e in range(130)]),   # three rounds of 64 experts in the lookup
+    (512, 2048, 8, [9, 31, 8, 16, 17, 0, 33, 20]),                   # few rows per expert: chosen over the fused kernel
+    (2048, 256, 4, [60, 0, 80, 31]),
+])
+def test_expert_ffn_at_tile_edges(hx, d, f, E, counts):  # noqa: F811
+    H, B = hx
+    ctx = B.Context(B.make_config(d, f, E, 1, 1, sum(counts), B.BF16, flags=B.FLAG_HOST_ONLY))
+    name = ctx.ffn_kernel_name(sum(counts))
+    ctx.close()
+    print(f"gemm tiles: d={d} f={f} E={E} rows={sum(counts)} {name}", flush=True)
+    assert "gemm" in name
+    out, ref = run_ffn_case(H, B, "bf16", d, f, E, counts, seed=d + f + E)
+    offs = np.concatenate([[0], np.cumsum(counts)])
+    for e in range(E):   # an expert at a time, so that a wrong small one cannot hide behind a big one
+        if counts[e]:
+            assert nerr(out[offs[e]: offs[e + 1]], ref[offs[e]: offs[e + 1]]) <= TOL["bf16"], f"expert {e} ({counts[e]} rows)"
+
+
+@pytest.mark.parametrize("counts", [[120] * 16, [700, 0, 321, 5, 64, 100, 1, 16, 17, 90, 200, 33, 50, 150, 80, 93]])
+def test_static_scratch_takes_several_passes_and_gives_the_same_bits(hx, counts):  # noqa: F811
+    """A launch the static buffer admits but whose hidden activation it does not hold at once."""
+    H, B = hx
+    d, f, E, n = 128, 8192, 16, sum(counts)
+    assert (n // 16 + E) * 16 * (d + f) * 2 > B.STATIC_SCRATCH_BYTES
+    w = W.Workload("gemm_passes", 78, 1, d, f, E, 1, n, 1, "bf16", 0.0, False)
+    cfg = H.config_for(w)
+    store = H.ExpertStore(w, cfg, threads=4)
+    ctx = B.Context(cfg)
+    ctx.register_resident_experts(store.to_hbm(), store.expert_stride, store.block_stride)
+    assert "gemm" in ctx.ffn_kernel_name(n)
+    x = H.to_device(W.round_to_bf16(np.random.default_rng(5).standard_normal((n, d)).astype(np.float32)), "bf16")
+    offs = torch.from_numpy(np.concatenate([[0], np.cumsum(counts)]).astype(np.int32)).cuda()
+    ys = [torch.full((n, d), 7.0, dtype=torch.bfloat16, device="cuda") for _ in range(2)]
+    ws = torch.full((ctx.workspace_bytes,), 0x5A, dtype=torch.uint8, device="cuda")
+    ctx.expert_ffn(0, x, offs, n, ys[0], ws)
+    ctx.expert_ffn_static(0, x, offs, n, ys[1])
+    torch.cuda.synchronize()
+    assert torch.equal(ys[0].view(torch.int16), ys[1].view(torch.int16))
+    assert float(ys[0].float().abs().max()) not in (0.0, 7.0)
+    ctx.close()
