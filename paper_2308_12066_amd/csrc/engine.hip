@@ -571,7 +571,7 @@ static int gate_for_block(pgmoe_ctx *ctx, const pgmoe_step_buffers *io, int g, c
     return rc;
 }
 
-// Token grouping and expert FFN of one block inside pgmoe_stack_step.  bf16: only the integer
+// Token grouping and expert FFN of one block inside pgmoe_stack_step.  bf16 (and float32 of ordinary sizes): only the integer
 // half of the grouping runs (offsets, row_of and the inverse map grouped row -> token); the FFN
 // kernels read their rows of x through that map, so the gather kernel and the x_perm round trip
 // are skipped (same values, hence the same results as pgmoe_permute + pgmoe_expert_ffn).
@@ -580,7 +580,7 @@ static int group_and_run_experts(pgmoe_ctx *ctx, const pgmoe_step_buffers *io, i
                                  const FusedGate *gate = nullptr, bool *gate_done = nullptr) {
     const int nk = T * ctx->cfg.top_k;
     if (gate_done) *gate_done = false;
-    if (ctx->cfg.dtype != PGMOE_BF16) {
+    if (ctx->cfg.dtype != PGMOE_BF16 && !ffn_f32_reads_rows_in_place(ctx->cfg)) {
         int rc = pgmoe_permute(ctx, x, idx, T, io->x_perm, row_of, offs, stream);
         if (rc) return rc;
         return expert_ffn_impl(ctx, block, io->x_perm, offs, nk, io->y_perm, io->workspace, stream, n_partial);

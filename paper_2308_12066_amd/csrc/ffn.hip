@@ -22,7 +22,7 @@
 //   The weights are the A operand (v_mfma_f32_16x16x32_bf16, 16 features x 32 k) and the
 //   tokens the B operand, so each lane ends up with 4 consecutive features of one token.
 //
-// f32 path - plain float32 kernels (correctness configuration; no matrix cores).
+// f32 path - float32 matrix instructions (d_model and d_ff multiples of 4), else plain scalar kernels.
 #include <mutex>
 
 #include "ffn_common.h"
@@ -342,7 +342,149 @@ __global__ __launch_bounds__(256) void ffn_reduce_kernel(const float *__restrict
 }
 
 // ------------------------------------------------------------------------------------------
-// float32 path.  One workgroup per (row = blockIdx.x, 256 output columns = blockIdx.y); the row's expert and slot are
+// float32 path on the float32 matrix instruction (v_mfma_f32_16x16x4_f32: float32 products and sums).
+//
+// A workgroup takes up to 16*MT rows of one expert and 16*V columns; its NW wavefronts deal the reduction among
+// themselves in blocks of 16 k and add their sums in LDS in wavefront order (bit-reproducible).  The weights are
+// row-major, so nothing is transposed: lane l loads V neighbouring columns V*(l%16) .. of weight row 16*b + 4*(l/16) + s
+// and the four k of its token 4*(l/16) .. +3; instruction (s, j) then multiplies component j of the weights with component s
+// of the row, i.e. its output row i is column V*i + j, and every lane ends up with 4*V neighbouring columns of one token.
+// Bound by the weight stream (HBM); F32_DEPTH blocks of loads are in flight per wavefront.  One thread
+// per output column walking k by itself, which this replaces, re-read the weights once per row and paid a
+// memory latency every few k: 8 experts of 768 x 3072, 100 rows, 284 us + 836 us, now 18 + 32 (75 MB
+// of weights each; the second product has half the columns' workgroups, and its hidden rows share the CUs' request slots).
+constexpr int F32_DEPTH = 4;
+
+template <int V>
+struct F32Vec {
+    typedef float type __attribute__((ext_vector_type(V)));
+};
+template <>
+struct F32Vec<1> {
+    typedef float type;
+};
+template <int V>
+__device__ inline float f32_comp(const typename F32Vec<V>::type &v, int j) {
+    if constexpr (V == 1) return v;
+    else return v[j];
+}
+
+// out[rows, n0 .. n0 + 16*V) = (RELU) a[rows, K] . w[K, N] for the rows of one chunk; a_row0: row of a that is the chunk's
+// first (through src_row if given).  K % 4 == 0, N % V == 0.
+template <int V, int MT, int NW, bool RELU>
+__device__ inline void f32_tile(const float *__restrict__ a, const int32_t *__restrict__ src_row, const float *__restrict__ w,
+                                float *__restrict__ out, const ChunkInfo &ci, int K, int N, bool no_weights) {
+    typedef typename F32Vec<V>::type vec;
+    typedef __attribute__((address_space(1))) vec gvec;
+    __shared__ floatx4 sums[NW][V * MT][64];
+    const int lane = threadIdx.x & 63, wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
+    const int i16 = lane & 15, g = lane >> 4;
+    const int n0 = blockIdx.y * 16 * V;
+    const int col = n0 + V * i16;
+    const gvec *wp = (const gvec *)(w + (col < N ? col : 0));  // columns past the end: a valid address, never stored
+    const int wstep = N / V;                                   // vectors per weight row
+    const floatx4 *ap[MT];
+#pragma unroll
+    for (int m = 0; m < MT; ++m) {
+        const int r = m * 16 + i16, row = ci.row0 + (r < ci.nrows ? r : 0);  // rows past the end: a valid row, never stored
+        ap[m] = reinterpret_cast<const floatx4 *>(a + (size_t)(src_row ? src_row[row] : row) * K);
+    }
+    floatx4 acc[V][MT];
+#pragma unroll
+    for (int j = 0; j < V; ++j)
+#pragma unroll
+        for (int m = 0; m < MT; ++m) acc[j][m] = floatx4{0.f, 0.f, 0.f, 0.f};
+
+    const int n_blk = no_weights ? 0 : (K + 15) >> 4, quads = K >> 2;
+    vec wv[F32_DEPTH][4];
+    floatx4 av[F32_DEPTH][MT];
+    auto request = [&](int b, vec (&wb)[4], floatx4 (&ab)[MT]) {
+        const int q = min(4 * b + g, quads - 1);  // this lane's four k; past the end: the last ones, zeroed when used
+#pragma unroll
+        for (int s = 0; s < 4; ++s) wb[s] = wp[(size_t)(4 * q + s) * wstep];
+#pragma unroll
+        for (int m = 0; m < MT; ++m) ab[m] = ap[m][q];
+    };
+    if (n_blk > 0) {
+#pragma unroll
+        for (int p = 0; p < F32_DEPTH; ++p) {
+            if (wave + NW * p < n_blk) request(wave + NW * p, wv[p], av[p]);  // uniform over the wavefront, as below
+        }
+    }
+    for (int b0 = wave; b0 < n_blk; b0 += NW * F32_DEPTH) {
+#pragma unroll
+        for (int p = 0; p < F32_DEPTH; ++p) {
+            const int b = b0 + NW * p;
+            if (b >= n_blk) break;
+            const bool live = 4 * b + g < quads;  // false only past the end of K
+            vec wc[4];
+            floatx4 ac[MT];
+#pragma unroll
+            for (int s = 0; s < 4; ++s) wc[s] = live ? wv[p][s] : vec{};
+#pragma unroll
+            for (int m = 0; m < MT; ++m) ac[m] = live ? av[p][m] : floatx4{0.f, 0.f, 0.f, 0.f};
+            if (b + NW * F32_DEPTH < n_blk) request(b + NW * F32_DEPTH, wv[p], av[p]);
+#pragma unroll
+            for (int s = 0; s < 4; ++s)
+#pragma unroll
+                for (int j = 0; j < V; ++j)
+#pragma unroll
+                    for (int m = 0; m < MT; ++m)
+                        acc[j][m] = __builtin_amdgcn_mfma_f32_16x16x4f32(f32_comp<V>(wc[s], j), ac[m][s], acc[j][m], 0, 0, 0);
+        }
+    }
+#pragma unroll
+    for (int j = 0; j < V; ++j)
+#pragma unroll
+        for (int m = 0; m < MT; ++m) sums[wave][j * MT + m][lane] = acc[j][m];
+    __syncthreads();
+    // thread -> (row tile, lane, r): V neighbouring columns of one row
+    for (int o = threadIdx.x; o < MT * 256; o += NW * 64) {
+        const int r = o & 3, l = (o >> 2) & 63, m = o >> 8;
+        const int row = m * 16 + (l & 15), c = n0 + V * (4 * (l >> 4) + r);
+        if (row >= ci.nrows || c >= N) continue;
+        vec y;
+#pragma unroll
+        for (int j = 0; j < V; ++j) {
+            float t = sums[0][j * MT + m][l][r];
+#pragma unroll
+            for (int v = 1; v < NW; ++v) t += sums[v][j * MT + m][l][r];
+            if (RELU) t = fmaxf(t, 0.f);
+            if constexpr (V == 1) y = t;
+            else y[j] = t;
+        }
+        *reinterpret_cast<vec *>(out + (size_t)(ci.row0 + row) * N + c) = y;
+    }
+}
+
+template <int V, int MT, int NW>
+__global__ __launch_bounds__(NW * 64) void ffn_f32_hidden_kernel(const float *__restrict__ x_perm, const int32_t *__restrict__ src_row,
+                                                                 const int32_t *__restrict__ offsets, int E, int d, int f,
+                                                                 const char *__restrict__ w_base, size_t w_stride, int slot_by_rank,
+                                                                 int n_slots, const unsigned long long *__restrict__ table,
+                                                                 float *__restrict__ h) {
+    const ChunkInfo ci = find_chunk(offsets, E, 16 * MT, blockIdx.x);
+    if (ci.nrows == 0) return;  // uniform over the workgroup
+    const char *wexp = table ? reinterpret_cast<const char *>(table[ci.expert])
+                             : w_base + (size_t)(slot_by_rank ? ci.slot : ci.expert) * w_stride;
+    const bool no_weights = table ? wexp == nullptr : (slot_by_rank && ci.slot >= n_slots);  // no slot: rows are zeroed
+    f32_tile<V, MT, NW, true>(x_perm, src_row, reinterpret_cast<const float *>(wexp), h, ci, d, f, no_weights);
+}
+
+template <int V, int MT, int NW>
+__global__ __launch_bounds__(NW * 64) void ffn_f32_out_kernel(const float *__restrict__ h, const int32_t *__restrict__ offsets, int E,
+                                                              int d, int f, const char *__restrict__ w_base, size_t w_stride,
+                                                              int slot_by_rank, int n_slots,
+                                                              const unsigned long long *__restrict__ table, float *__restrict__ y_perm) {
+    const ChunkInfo ci = find_chunk(offsets, E, 16 * MT, blockIdx.x);
+    if (ci.nrows == 0) return;  // uniform over the workgroup
+    const char *wexp = table ? reinterpret_cast<const char *>(table[ci.expert])
+                             : w_base + (size_t)(slot_by_rank ? ci.slot : ci.expert) * w_stride;
+    const bool no_weights = table ? wexp == nullptr : (slot_by_rank && ci.slot >= n_slots);
+    f32_tile<V, MT, NW, false>(h, nullptr, reinterpret_cast<const float *>(wexp) + (size_t)d * f, y_perm, ci, f, d, no_weights);
+}
+
+// Any other float32 shape (d_model or d_ff not a multiple of 4, rows that cannot be read 16 bytes at a time).  One workgroup per (row = blockIdx.x, 256 output columns = blockIdx.y); the row's expert and slot are
 // found once per workgroup.
 __device__ inline void find_row_expert(const int32_t *offsets, int E, int row, int *expert, int *slot) {
     int e = 0, s = -1;
@@ -358,7 +500,7 @@ __device__ inline void find_row_expert(const int32_t *offsets, int E, int row, i
     *slot = s < 0 ? 0 : s;
 }
 
-__global__ __launch_bounds__(256) void ffn_f32_hidden_kernel(const float *__restrict__ x_perm,
+__global__ __launch_bounds__(256) void ffn_f32_hidden_scalar_kernel(const float *__restrict__ x_perm,
                                                               const int32_t *__restrict__ offsets, int E, int d, int f,
                                                               const char *__restrict__ w_base, size_t w_stride,
                                                               int slot_by_rank, int n_slots,
@@ -382,7 +524,7 @@ __global__ __launch_bounds__(256) void ffn_f32_hidden_kernel(const float *__rest
     h[(size_t)row * f + j] = fmaxf(acc, 0.f);
 }
 
-__global__ __launch_bounds__(256) void ffn_f32_out_kernel(const float *__restrict__ h, const int32_t *__restrict__ offsets,
+__global__ __launch_bounds__(256) void ffn_f32_out_scalar_kernel(const float *__restrict__ h, const int32_t *__restrict__ offsets,
                                                            int E, int d, int f, const char *__restrict__ w_base,
                                                            size_t w_stride, int slot_by_rank, int n_slots,
                                                            const unsigned long long *__restrict__ table,
@@ -572,6 +714,62 @@ static int launch_fused(pgmoe_ctx *ctx, const FfnPlan &p, const char *w_base, si
     return PGMOE_OK;
 }
 
+bool ffn_f32_reads_rows_in_place(const pgmoe_config &c) { return c.dtype == PGMOE_F32 && c.d_model % 4 == 0 && c.d_ff % 4 == 0; }
+
+static int launch_ffn_f32(pgmoe_ctx *ctx, const char *w_base, size_t w_stride, bool slot_by_rank, int n_slots, const float *x,
+                          const int32_t *offsets, int n_rows, float *y_perm, float *h, hipStream_t s,
+                          const unsigned long long *table, const int32_t *src_row) {
+    const pgmoe_config &c = ctx->cfg;
+    const int tslot = ffn_timing_slot(ctx);
+    if (tslot >= 0) PG_HIP(ctx, hipEventRecord(ctx->tim_begin[tslot], s));
+    if (ffn_f32_reads_rows_in_place(c)) {
+        // rows per workgroup by the rows an expert has (8 experts of 768 x 3072 with 12.5 rows each: 18 + 32 us with 16-row
+        // chunks, 28 + 41 with 32); columns per lane as many as still give (half of) the CUs a workgroup
+        const int active = std::max(1, std::min(c.n_experts, n_rows)), mean = (n_rows + active - 1) / active;
+        const int mt = mean <= 16 ? 1 : (mean <= 32 ? 2 : 4);
+        const int chunks = active + n_rows / (16 * mt);
+        auto cols = [&](int N) { return active * ((N + 63) / 64) >= 256 ? 4 : (active * ((N + 31) / 32) >= 128 ? 2 : 1); };
+#define PG_F32_HIDDEN(V_, MT_, NW_)                                                                                            \
+    hipLaunchKernelGGL((ffn_f32_hidden_kernel<V_, MT_, NW_>), dim3(chunks, (c.d_ff + 16 * V_ - 1) / (16 * V_)), dim3(NW_ * 64), 0, s, \
+                       x, src_row, offsets, c.n_experts, c.d_model, c.d_ff, w_base, w_stride, slot_by_rank ? 1 : 0, n_slots, table, h)
+#define PG_F32_OUT(V_, MT_, NW_)                                                                                               \
+    hipLaunchKernelGGL((ffn_f32_out_kernel<V_, MT_, NW_>), dim3(chunks, (c.d_model + 16 * V_ - 1) / (16 * V_)), dim3(NW_ * 64), 0, s, \
+                       h, offsets, c.n_experts, c.d_model, c.d_ff, w_base, w_stride, slot_by_rank ? 1 : 0, n_slots, table, y_perm)
+#define PG_F32(KERN_, N_)                                                                                                      \
+    do {                                                                                                                       \
+        const int v_ = cols(N_);                                                                                               \
+        if (mt == 1) {                                                                                                         \
+            if (v_ == 4) KERN_(4, 1, 8);                                                                                       \
+            else if (v_ == 2) KERN_(2, 1, 8);                                                                                  \
+            else KERN_(1, 1, 8);                                                                                               \
+        } else if (mt == 2) {                                                                                                  \
+            if (v_ == 4) KERN_(4, 2, 8);                                                                                       \
+            else if (v_ == 2) KERN_(2, 2, 8);                                                                                  \
+            else KERN_(1, 2, 8);                                                                                               \
+        } else {                                                                                                               \
+            if (v_ == 4) KERN_(4, 4, 4);                                                                                       \
+            else if (v_ == 2) KERN_(2, 4, 8);                                                                                  \
+            else KERN_(1, 4, 8);                                                                                               \
+        }                                                                                                                      \
+        PG_HIP(ctx, hipGetLastError());                                                                                        \
+    } while (0)
+        PG_F32(PG_F32_HIDDEN, c.d_ff);
+        PG_F32(PG_F32_OUT, c.d_model);
+#undef PG_F32
+#undef PG_F32_OUT
+#undef PG_F32_HIDDEN
+    } else {
+        hipLaunchKernelGGL(ffn_f32_hidden_scalar_kernel, dim3(n_rows, (c.d_ff + 255) / 256), dim3(256), 0, s, x, offsets, c.n_experts,
+                           c.d_model, c.d_ff, w_base, w_stride, slot_by_rank ? 1 : 0, n_slots, table, h);
+        PG_HIP(ctx, hipGetLastError());
+        hipLaunchKernelGGL(ffn_f32_out_scalar_kernel, dim3(n_rows, (c.d_model + 255) / 256), dim3(256), 0, s, h, offsets, c.n_experts,
+                           c.d_model, c.d_ff, w_base, w_stride, slot_by_rank ? 1 : 0, n_slots, table, y_perm);
+        PG_HIP(ctx, hipGetLastError());
+    }
+    if (tslot >= 0) PG_HIP(ctx, hipEventRecord(ctx->tim_end[tslot], s));
+    return PGMOE_OK;
+}
+
 int launch_ffn(pgmoe_ctx *ctx, const char *w_base, size_t w_stride, bool slot_by_rank, int n_slots, const void *x_perm,
                const int32_t *offsets, int n_rows, void *y_perm, void *workspace, hipStream_t s, int *keep_partials,
                const unsigned long long *table, const int32_t *src_row, const FusedGate *gate, bool *gate_done) {
@@ -579,20 +777,9 @@ int launch_ffn(pgmoe_ctx *ctx, const char *w_base, size_t w_stride, bool slot_by
     if (keep_partials) *keep_partials = 0;
     if (gate_done) *gate_done = false;
     if (n_rows == 0) return PGMOE_OK;
-    if (c.dtype == PGMOE_F32) {
-        float *h = (float *)workspace;
-        const int tslot = ffn_timing_slot(ctx);
-        if (tslot >= 0) PG_HIP(ctx, hipEventRecord(ctx->tim_begin[tslot], s));
-        hipLaunchKernelGGL(ffn_f32_hidden_kernel, dim3(n_rows, (c.d_ff + 255) / 256), dim3(256), 0, s,
-                           (const float *)x_perm, offsets, c.n_experts, c.d_model, c.d_ff, w_base, w_stride,
-                           slot_by_rank ? 1 : 0, n_slots, table, h);
-        PG_HIP(ctx, hipGetLastError());
-        hipLaunchKernelGGL(ffn_f32_out_kernel, dim3(n_rows, (c.d_model + 255) / 256), dim3(256), 0, s, h, offsets,
-                           c.n_experts, c.d_model, c.d_ff, w_base, w_stride, slot_by_rank ? 1 : 0, n_slots, table, (float *)y_perm);
-        PG_HIP(ctx, hipGetLastError());
-        if (tslot >= 0) PG_HIP(ctx, hipEventRecord(ctx->tim_end[tslot], s));
-        return PGMOE_OK;
-    }
+    if (c.dtype == PGMOE_F32)
+        return launch_ffn_f32(ctx, w_base, w_stride, slot_by_rank, n_slots, (const float *)x_perm, offsets, n_rows, (float *)y_perm,
+                              (float *)workspace, s, table, src_row);
     if (uses_gemm_kernels(c, n_rows))
         return launch_ffn_gemm(ctx, w_base, w_stride, slot_by_rank, n_slots, x_perm, offsets, n_rows, y_perm, workspace,
                                workspace == ctx->static_scratch ? PGMOE_STATIC_SCRATCH_BYTES : ffn_workspace_bytes(c), s, keep_partials,

@@ -155,6 +155,7 @@ size_t ffn_launch_workspace_bytes(const pgmoe_config &cfg, int n_rows);  // by w
 // current) into ctx->static_scratch; resolved once per device and process.
 int resolve_static_scratch(pgmoe_ctx *ctx);
 const char *ffn_kernel_name(const pgmoe_config &cfg, int n_rows);  // nullptr: no kernel is built for this launch
+bool ffn_f32_reads_rows_in_place(const pgmoe_config &c);         // float32: the expert kernels take the row -> token map
 bool ffn_supports_d_model(int d_model);                          // bf16: expert kernels are built for this d_model
 
 // Kernel launchers (each validates nothing: callers did).  All asynchronous on `s`.
@@ -187,7 +188,8 @@ struct FusedGate {
 int launch_ffn(pgmoe_ctx *ctx, const char *w_base, size_t w_stride, bool slot_by_rank, int n_slots, const void *x_perm,
                const int32_t *offsets, int n_rows, void *y_perm, void *workspace, hipStream_t s, int *keep_partials = nullptr,
                const unsigned long long *table = nullptr,  // table: per-expert weight addresses (0 = none), overrides w_base
-               const int32_t *src_row = nullptr,  // bf16 only: x_perm is the un-grouped x [T,d], grouped row r reads x[src_row[r]]
+               const int32_t *src_row = nullptr,  // x_perm is the un-grouped x [T,d], grouped row r reads x[src_row[r]] (bf16; float32
+                                                  // where ffn_f32_reads_rows_in_place says so)
                const FusedGate *gate = nullptr, bool *gate_done = nullptr);
 // p-lanes of the partial-sum reduction for P partials (fixes the order of the additions)
 inline int reduce_lanes(int P) { return P <= 2 ? 1 : (P <= 8 ? 4 : 16); }
