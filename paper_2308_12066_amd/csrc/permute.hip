@@ -4,14 +4,16 @@
 // step skips the gather: route_kernel also writes the inverse map (grouped row -> token) and the
 // expert kernels read their rows through it.
 //
-// route_kernel: one workgroup of 1024 threads; each of its 16 wavefronts owns one contiguous
+// route_kernel: workgroups of 1024 threads (one up to ROUTE_SINGLE entries); each of the 16 wavefronts owns one contiguous
 // range of the entries.  Pass 1 counts every range into a histogram of its own (LDS atomics:
 // integer, so order does not matter).  One thread per expert then turns the 16 histograms into
 // the start of every (wavefront, expert) run, and one wavefront scans the expert totals.  Pass 2
 // needs no further workgroup barrier: a wavefront walks its range in order, 64 entries at a time;
 // equal keys find each other with one ballot per key bit, which gives the stable rank inside the
 // 64, and the run's start moves on by the number of matches.  Everything is integer work and
-// bit-reproducible.
+// bit-reproducible.  The ballots are a serial chain per wavefront, 16 us for 16 k entries and 39 us for 32 k in one workgroup; counting
+// is not, so with more entries every workgroup counts all of them (no exchange between workgroups, no scratch) and places
+// only its own segment: 6 and 9 us.
 // gather_rows_kernel: one wavefront per entry, 16-byte copies.
 #include "pgmoe_internal.h"
 
@@ -19,19 +21,27 @@ namespace pgmoe {
 
 constexpr int ROUTE_THREADS = 1024;
 constexpr int ROUTE_WAVES = ROUTE_THREADS / 64;
+constexpr int ROUTE_COPIES = 4;  // histograms the lanes of a wavefront spread a popular expert's counts over
 
+// WIDE: several workgroups, each of which places one contiguous segment of the entries after counting all of them.
+template <bool WIDE>
 __global__ __launch_bounds__(ROUTE_THREADS) void route_kernel(const int32_t *__restrict__ idx, int n, int E, int k,
                                                                int32_t *__restrict__ row_of,
                                                                int32_t *__restrict__ offsets,
-                                                               int32_t *__restrict__ src_row, uint32_t *flags) {
+                                                               int32_t *__restrict__ src_row, uint32_t *flags, int segment) {
     __shared__ int run_start[ROUTE_WAVES][PGMOE_MAX_EXPERTS];  // pass 1: counts; then: next free row of the (wavefront, expert) run
     __shared__ int total[PGMOE_MAX_EXPERTS];                    // entries per expert, then the expert's first row
+    __shared__ int outside[WIDE ? 2 : 1][WIDE ? ROUTE_COPIES : 1][WIDE ? PGMOE_MAX_EXPERTS : 1];  // entries before / behind the segment
     static_assert(PGMOE_MAX_EXPERTS == 256, "four experts per lane in the scan below");
 
     const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
-    const int per = ((n + ROUTE_WAVES - 1) / ROUTE_WAVES + 63) & ~63;  // entries per wavefront, whole rounds of 64
-    const int lo = min(n, wave * per), hi = min(n, lo + per);
+    const int seg_lo = WIDE ? min(n, (int)blockIdx.x * segment) : 0, seg_hi = WIDE ? min(n, seg_lo + segment) : n;
+    const int per = ((seg_hi - seg_lo + ROUTE_WAVES - 1) / ROUTE_WAVES + 63) & ~63;  // entries per wavefront, whole rounds of 64
+    const int lo = min(seg_hi, seg_lo + wave * per), hi = min(seg_hi, lo + per);
     for (int i = tid; i < ROUTE_WAVES * PGMOE_MAX_EXPERTS; i += ROUTE_THREADS) (&run_start[0][0])[i] = 0;
+    if constexpr (WIDE) {
+        for (int i = tid; i < 2 * ROUTE_COPIES * PGMOE_MAX_EXPERTS; i += ROUTE_THREADS) (&outside[0][0][0])[i] = 0;
+    }
     __syncthreads();
 
     // the first ROUTE_KEEP rounds of a wavefront's range stay in registers for pass 2 (all of them up to
@@ -44,36 +54,58 @@ __global__ __launch_bounds__(ROUTE_THREADS) void route_kernel(const int32_t *__r
         kept[c] = i < hi ? idx[i] : 0;
     }
     bool bad = false;
-#pragma unroll
-    for (int c = 0; c < ROUTE_KEEP; ++c) {
-        const int i = lo + c * 64 + lane;
-        if (kept[c] < 0 || kept[c] >= E) {
-            bad = true;
-            kept[c] = kept[c] < 0 ? 0 : E - 1;
-        }
-        if (i < hi) atomicAdd(&run_start[wave][kept[c]], 1);
-    }
-    for (int i = lo + ROUTE_KEEP * 64 + lane; i < hi; i += 64) {
-        int e = idx[i];
+    auto clamped = [&](int e) {
         if (e < 0 || e >= E) {
             bad = true;
             e = e < 0 ? 0 : E - 1;
         }
-        atomicAdd(&run_start[wave][e], 1);
+        return e;
+    };
+#pragma unroll
+    for (int c = 0; c < ROUTE_KEEP; ++c) {
+        const int i = lo + c * 64 + lane;
+        kept[c] = clamped(kept[c]);
+        if (i < hi) atomicAdd(&run_start[wave][kept[c]], 1);
+    }
+    for (int i = lo + ROUTE_KEEP * 64 + lane; i < hi; i += 64) atomicAdd(&run_start[wave][clamped(idx[i])], 1);
+    if constexpr (WIDE) {
+        int(*mine)[PGMOE_MAX_EXPERTS] = nullptr;
+        for (int side = 0; side < 2; ++side) {
+            const int from = side ? seg_hi : 0, to = side ? n : seg_lo;
+            mine = outside[side];
+            for (int i0 = from; i0 < to; i0 += 8 * ROUTE_THREADS) {
+                int e[8];
+#pragma unroll
+                for (int u = 0; u < 8; ++u) {
+                    const int i = i0 + u * ROUTE_THREADS + tid;
+                    e[u] = i < to ? idx[i] : 0;
+                }
+#pragma unroll
+                for (int u = 0; u < 8; ++u)
+                    if (i0 + u * ROUTE_THREADS + tid < to) atomicAdd(&mine[lane & (ROUTE_COPIES - 1)][clamped(e[u])], 1);
+            }
+        }
     }
     if (__any(bad) && lane == 0) atomicOr(flags, kFlagBadIndex);
     __syncthreads();
 
     // per expert: counts of the wavefronts -> offsets of their runs inside the expert's group
     if (tid < PGMOE_MAX_EXPERTS) {
-        int run = 0;
+        int run = 0, behind = 0;
+        if constexpr (WIDE) {
+#pragma unroll
+            for (int c = 0; c < ROUTE_COPIES; ++c) {
+                run += outside[0][c][tid];
+                behind += outside[1][c][tid];
+            }
+        }
         if (tid < E)
             for (int w = 0; w < ROUTE_WAVES; ++w) {
                 const int c = run_start[w][tid];
                 run_start[w][tid] = run;
                 run += c;
             }
-        total[tid] = run;
+        total[tid] = run + behind;
     }
     __syncthreads();
     // exclusive scan of the expert totals by the first wavefront, four experts per lane
@@ -90,9 +122,9 @@ __global__ __launch_bounds__(ROUTE_THREADS) void route_kernel(const int32_t *__r
         for (int j = 0; j < 4; ++j) {
             const int e = 4 * lane + j;
             total[e] = first[j];
-            if (e < E) offsets[e] = first[j];
+            if (e < E && blockIdx.x == 0) offsets[e] = first[j];
         }
-        if (lane == 0) offsets[E] = n;
+        if (lane == 0 && blockIdx.x == 0) offsets[E] = n;
     }
     __syncthreads();
 
@@ -151,8 +183,18 @@ __global__ __launch_bounds__(256) void gather_rows_kernel(const char *__restrict
 int launch_route(pgmoe_ctx *ctx, const int32_t *idx, int T, int32_t *row_of, int32_t *offsets, int32_t *src_row,
                  hipStream_t s) {
     const pgmoe_config &c = ctx->cfg;
-    hipLaunchKernelGGL(route_kernel, dim3(1), dim3(ROUTE_THREADS), 0, s, idx, T * c.top_k, c.n_experts, c.top_k, row_of,
-                       offsets, src_row, ctx->dev_flags);
+    const int n = T * c.top_k;
+    // one workgroup while its wavefronts have at most two rounds each; beyond that segments of a round or more, on at most one
+    // workgroup per CU (each counts every entry)
+    constexpr int ROUTE_SINGLE = 2048, ROUTE_SEGMENT = 1024, ROUTE_MAX_GROUPS = 64;
+    if (n <= ROUTE_SINGLE) {
+        hipLaunchKernelGGL(route_kernel<false>, dim3(1), dim3(ROUTE_THREADS), 0, s, idx, n, c.n_experts, c.top_k, row_of, offsets, src_row,
+                           ctx->dev_flags, 0);
+    } else {
+        const int rounds = (n + ROUTE_SEGMENT * ROUTE_MAX_GROUPS - 1) / (ROUTE_SEGMENT * ROUTE_MAX_GROUPS), segment = rounds * ROUTE_SEGMENT;
+        hipLaunchKernelGGL(route_kernel<true>, dim3((n + segment - 1) / segment), dim3(ROUTE_THREADS), 0, s, idx, n, c.n_experts, c.top_k,
+                           row_of, offsets, src_row, ctx->dev_flags, segment);
+    }
     PG_HIP(ctx, hipGetLastError());
     return PGMOE_OK;
 }
