@@ -317,9 +317,9 @@ int pgmoe_combine(pgmoe_ctx *ctx, const void *y_perm, const int32_t *row_of, con
  * context's stream beside it (bf16 contexts).  All of this overlaps only if compute_stream,
  * copy_stream and the context's stream sit on different hardware queues: ask
  * pgmoe_check_streams() once at set-up.
- * With a resident store and pregate_distance 1, a decode-sized expert launch (up to 4 tokens, 8
- * or 16 experts) carries the pre-gate evaluated on the same hidden state as one extra workgroup:
- * results are those of the separate gate launch, bit for bit.
+ * With a resident store and pregate_distance 1, a decode-sized block (up to 128 tokens, bf16, n_experts a multiple of
+ * 8 up to 128) carries the pre-gate evaluated on the same hidden state in extra workgroups of its expert launch and its
+ * combine: results are those of the separate gate launch, bit for bit.
  * With pregate_distance N > 1 the gate that routes block g is evaluated on x_{max(0, g-N)}:
  * block 0 runs the gates of blocks 0..N on x_0 and queues their fetches back to back, block
  * i >= 1 runs the gate of block i+N; the last N blocks run none.  Arrays of pointers are host arrays of

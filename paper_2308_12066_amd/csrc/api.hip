@@ -4,6 +4,7 @@
 #include <algorithm>
 #include <new>
 
+#include "gate_small.h"
 #include "pgmoe_internal.h"
 
 namespace pgmoe {
@@ -211,6 +212,8 @@ int pgmoe_create(pgmoe_ctx **out, const pgmoe_config *cfg) {
         c->dev_unique = reinterpret_cast<int32_t *>(c->dev_copy_clock + 2 * (size_t)cfg->n_blocks);
         size_t n_idx = (size_t)cfg->max_tokens * cfg->top_k;
         if (rc == PGMOE_OK) H(hipMalloc((void **)&c->dev_src_row, (size_t)cfg->n_blocks * n_idx * sizeof(int32_t)), "hipMalloc(src_row)");
+        if (rc == PGMOE_OK && gate_planes_apply(*cfg, GATE_CARRY_TOKENS))
+            H(hipMalloc((void **)&c->gate_planes, gate_planes_floats(std::min(cfg->max_tokens, GATE_CARRY_TOKENS)) * sizeof(float)), "hipMalloc(gate planes)");
         if (rc == PGMOE_OK) H(hipHostMalloc((void **)&c->idx_staging, n_idx * sizeof(int32_t), hipHostMallocDefault), "hipHostMalloc(idx staging)");
         // idx_ready is the one event the host itself polls before it reads the staged indices (memcpy
         // mode): it keeps the default, system-scope release, so the copy before it is visible to the host
@@ -255,6 +258,7 @@ int pgmoe_destroy(pgmoe_ctx *c) {
         delete[] c->cache_parity;
         if (c->dev_flags) (void)hipFree(c->dev_flags);
         if (c->dev_src_row) (void)hipFree(c->dev_src_row);
+        if (c->gate_planes) (void)hipFree(c->gate_planes);
         if (c->idx_staging) (void)hipHostFree(c->idx_staging);
         if (c->idx_ready) (void)hipEventDestroy(c->idx_ready);
         if (c->step_start) (void)hipEventDestroy(c->step_start);

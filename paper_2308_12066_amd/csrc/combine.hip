@@ -2,6 +2,7 @@
 // experts): y[t] = sum_j prob[t,j] * y_perm[row_of[t*k+j]], gathered per token so that no
 // atomics are needed and the sum order (j ascending) is fixed.  Optionally also writes the
 // residual stand-in x_next = x_res + y that feeds the next MoE block.
+#include "gate_small.h"
 #include "pgmoe_internal.h"
 
 namespace pgmoe {
@@ -74,16 +75,22 @@ __global__ __launch_bounds__(256) void combine_scalar_kernel(const XT *__restric
 typedef float floatx4 __attribute__((ext_vector_type(4)));
 typedef __bf16 bf16x4 __attribute__((ext_vector_type(4)));
 
-template <int PL>
+// GATE: the first workgroups finish the pre-gate whose partial planes the expert launch left.
+template <int PL, bool GATE>
 __global__ __launch_bounds__(256) void combine_partials_kernel(const float *__restrict__ partial, int P, int n_rows,
                                                                 const int32_t *__restrict__ row_of,
                                                                 const float *__restrict__ prob, int d, int k,
                                                                 __bf16 *__restrict__ y, const __bf16 *__restrict__ x_res,
-                                                                __bf16 *__restrict__ x_next) {
+                                                                __bf16 *__restrict__ x_next, CarriedGate gate) {
+    const int tiles = GATE ? (gate.T + GM_TOK - 1) / GM_TOK : 0;
+    if (GATE && (int)blockIdx.x < tiles) {  // uniform over the workgroup
+        if (blockIdx.y == 0) gate_finish_body(gate, blockIdx.x);
+        return;
+    }
     // 256 threads = PL p-lanes x COLS float4 columns of one token (same split as ffn_reduce_kernel<PL>)
     constexpr int COLS = 256 / PL;
     __shared__ floatx4 sub[PL][COLS + 1];
-    const int t = blockIdx.x;
+    const int t = blockIdx.x - tiles;
     const int col = threadIdx.x % COLS, pl = threadIdx.x / COLS;
     const int c4 = blockIdx.y * COLS + col;
     const bool live = c4 < d / 4;
@@ -147,17 +154,30 @@ __global__ __launch_bounds__(256) void combine_partials_kernel(const float *__re
 }
 
 int launch_combine_partials(pgmoe_ctx *ctx, const float *partial, int P, int n_rows, const int32_t *row_of,
-                            const float *prob, int T, void *y, const void *x_res, void *x_next, hipStream_t s) {
+                            const float *prob, int T, void *y, const void *x_res, void *x_next, hipStream_t s, const FusedGate *gate) {
     const pgmoe_config &c = ctx->cfg;
     const int pl = reduce_lanes(P);
     const int cols = 256 / pl;
-    const dim3 grid(T, (c.d_model / 4 + cols - 1) / cols);
-#define PG_CP(PL_)                                                                                                   \
-    hipLaunchKernelGGL(combine_partials_kernel<PL_>, grid, dim3(256), 0, s, partial, P, n_rows, row_of, prob, c.d_model, \
-                       c.top_k, (__bf16 *)y, (const __bf16 *)x_res, (__bf16 *)x_next)
-    if (pl == 1) PG_CP(1);
-    else if (pl == 4) PG_CP(4);
-    else PG_CP(16);
+    CarriedGate cg = {};
+    if (gate) {
+        const bool route = gate_mfma_routes(c, gate->T);
+        cg = CarriedGate{(const __bf16 *)gate->x, (const __bf16 *)gate->w, gate->bias, gate->T, c.d_model, c.top_k, c.n_experts, gate->idx,
+                         gate->prob, ctx->dev_flags, route ? gate->row_of : nullptr, route ? gate->offsets : nullptr,
+                         route ? gate->src_row : nullptr, ctx->gate_planes};
+    }
+    const dim3 grid(T + (gate ? (gate->T + GM_TOK - 1) / GM_TOK : 0), (c.d_model / 4 + cols - 1) / cols);
+#define PG_CP(PL_, GATE_)                                                                                                     \
+    hipLaunchKernelGGL((combine_partials_kernel<PL_, GATE_>), grid, dim3(256), 0, s, partial, P, n_rows, row_of, prob, c.d_model, \
+                       c.top_k, (__bf16 *)y, (const __bf16 *)x_res, (__bf16 *)x_next, cg)
+    if (gate) {
+        if (pl == 1) PG_CP(1, true);
+        else if (pl == 4) PG_CP(4, true);
+        else PG_CP(16, true);
+    } else {
+        if (pl == 1) PG_CP(1, false);
+        else if (pl == 4) PG_CP(4, false);
+        else PG_CP(16, false);
+    }
 #undef PG_CP
     PG_HIP(ctx, hipGetLastError());
     return PGMOE_OK;

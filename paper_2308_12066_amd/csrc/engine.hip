@@ -17,6 +17,7 @@
 #include <chrono>
 #include <new>
 
+#include "gate_small.h"
 #include "pgmoe_internal.h"
 
 using namespace pgmoe;
@@ -414,7 +415,7 @@ int pgmoe_slot_address(pgmoe_ctx *ctx, int block, int slot, void **dev_out) {
 static int expert_ffn_impl(pgmoe_ctx *ctx, int block, const void *x_perm, const int32_t *expert_offsets, int n_rows,
                            void *y_perm, void *workspace, void *stream, int *keep_partials,
                            const int32_t *src_row = nullptr,  // src_row: x_perm holds the un-grouped rows (see launch_ffn)
-                           const FusedGate *gate = nullptr, bool *gate_done = nullptr) {  // resident store only (see launch_ffn)
+                           const FusedGate *gate = nullptr, GateCarried *gate_done = nullptr) {  // resident store only (see launch_ffn)
     const char *fn = "pgmoe_expert_ffn";
     if (!ctx) return fail(nullptr, PGMOE_EINVAL, "%s: ctx is NULL", fn);
     int rc = check_block(ctx, fn, block);
@@ -577,9 +578,9 @@ static int gate_for_block(pgmoe_ctx *ctx, const pgmoe_step_buffers *io, int g, c
 // are skipped (same values, hence the same results as pgmoe_permute + pgmoe_expert_ffn).
 static int group_and_run_experts(pgmoe_ctx *ctx, const pgmoe_step_buffers *io, int block, int T, const void *x,
                                  const int32_t *idx, int32_t *row_of, int32_t *offs, void *stream, int *n_partial,
-                                 const FusedGate *gate = nullptr, bool *gate_done = nullptr) {
+                                 const FusedGate *gate = nullptr, GateCarried *gate_done = nullptr) {
     const int nk = T * ctx->cfg.top_k;
-    if (gate_done) *gate_done = false;
+    if (gate_done) *gate_done = GATE_LEFT;
     if (ctx->cfg.dtype != PGMOE_BF16 && !ffn_f32_reads_rows_in_place(ctx->cfg)) {
         int rc = pgmoe_permute(ctx, x, idx, T, io->x_perm, row_of, offs, stream);
         if (rc) return rc;
@@ -685,8 +686,8 @@ int pgmoe_stack_step(pgmoe_ctx *ctx, const pgmoe_step_buffers *io, int T, void *
     const int N = ctx->distance;
     const int head = std::min(N, L - 1);
     // Resident store, pre-gate distance 1: nothing waits for a routing, so the pre-gate evaluated
-    // on x_i is offered to block i's expert launch, which carries it as one extra workgroup when
-    // it is a decode-sized launch with one of the smallest gates (one launch fewer per block);
+    // on x_i is offered to block i's expert launch: a decode-sized one carries the smallest gates whole and begins the others,
+    // which block i's combine then finishes (one launch fewer per block, the gate's latency beside the weights' stream);
     // a launch that cannot leaves it to a gate launch of its own right behind it.
     const bool carry_gate = ctx->store_mode == STORE_RESIDENT && N == 1 && c.dtype == PGMOE_BF16;
     if (ctx->pull_seq >= 0 && c.dtype == PGMOE_BF16) {
@@ -747,18 +748,19 @@ int pgmoe_stack_step(pgmoe_ctx *ctx, const pgmoe_step_buffers *io, int T, void *
         // combine kernel adds them itself (same order as the stand-alone reduction) and y_perm is skipped
         int n_partial = 0;
         const int g = i + N;
+        FusedGate fg = {};
+        GateCarried carried = GATE_LEFT;
         if (carry_gate && g < L) {
             const float *bias = io->gate_b ? io->gate_b[g] : nullptr;
             if (!aligned(x_at(i), 16) || !aligned(io->gate_w[g], 16) || !aligned(bias, 4))
                 return fail(ctx, PGMOE_EINVAL, "%s: misaligned hidden state, gate weight or bias of block %d", fn, g);
-            const FusedGate fg = {x_at(i), io->gate_w[g], bias, T, idx_at(g), prob_at(g), io->row_of + (size_t)g * nk,
-                                  io->expert_offsets + (size_t)g * (c.n_experts + 1),
-                                  ctx->dev_src_row + (size_t)g * c.max_tokens * c.top_k};
-            bool carried = false;
+            fg = FusedGate{x_at(i), io->gate_w[g], bias, T, idx_at(g), prob_at(g), io->row_of + (size_t)g * nk,
+                           io->expert_offsets + (size_t)g * (c.n_experts + 1), ctx->dev_src_row + (size_t)g * c.max_tokens * c.top_k};
             rc = group_and_run_experts(ctx, io, i, T, x_at(i), idx_at(i), row_of, offs, compute_stream, &n_partial, &fg, &carried);
             if (rc) return rc;
-            if (carried) ctx->routed[g] = true;  // the smallest-gate code groups the tokens as well
-            else rc = gate_for_block(ctx, io, g, x_at(i), T, compute_stream);
+            // a gate of one workgroup groups the tokens as well
+            if (carried == GATE_LEFT) rc = gate_for_block(ctx, io, g, x_at(i), T, compute_stream);
+            else ctx->routed[g] = carried == GATE_ROUTED || gate_mfma_routes(c, T);
         } else {
             rc = group_and_run_experts(ctx, io, i, T, x_at(i), idx_at(i), row_of, offs, compute_stream, &n_partial);
         }
@@ -766,7 +768,7 @@ int pgmoe_stack_step(pgmoe_ctx *ctx, const pgmoe_step_buffers *io, int T, void *
         void *y = io->y_blocks ? (char *)io->y_blocks + (size_t)i * xbytes : nullptr;
         if (n_partial > 0)
             rc = launch_combine_partials(ctx, (const float *)io->workspace, n_partial, (int)nk, row_of, prob_at(i), T, y,
-                                         x_at(i), x_at(i + 1), (hipStream_t)compute_stream);
+                                         x_at(i), x_at(i + 1), (hipStream_t)compute_stream, carried == GATE_STARTED ? &fg : nullptr);
         else
             rc = pgmoe_combine(ctx, io->y_perm, row_of, prob_at(i), T, y, x_at(i), x_at(i + 1), compute_stream);
         if (rc) return rc;

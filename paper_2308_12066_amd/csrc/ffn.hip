@@ -43,7 +43,8 @@ __global__ __launch_bounds__(NW * 64) void ffn_fused_kernel(
     const __bf16 *__restrict__ x_perm, const int32_t *__restrict__ offsets, int E, int f, int f_range,
     const char *__restrict__ w_base, size_t w_stride, int slot_by_rank, int n_slots,
     const unsigned long long *__restrict__ table, float *__restrict__ partial, __bf16 *__restrict__ y_perm, int n_rows,
-    const int32_t *__restrict__ src_row) {  // nullable: grouped row r is row src_row[r] of x_perm (rows not gathered yet)
+    const int32_t *__restrict__ src_row,  // nullable: grouped row r is row src_row[r] of x_perm (rows not gathered yet)
+    CarriedGate gate) {                   // gate.x != nullptr: grid row 0 runs its first half, the d_ff ranges follow
     constexpr int SUB = 16 * NW;      // d_ff columns per sub-slab
     constexpr int KTB = SUB / 32;     // k-tiles of phase B per sub-slab
     constexpr int NTD = KT * 2;       // n-tiles of the output (d_model / 16)
@@ -54,6 +55,13 @@ __global__ __launch_bounds__(NW * 64) void ffn_fused_kernel(
     extern __shared__ __attribute__((aligned(16))) char smem[];
 
     const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
+    int range = blockIdx.y;
+    if constexpr (NW == 4 && MT <= 2) {
+        if (gate.x != nullptr && range-- == 0) {  // uniform over the workgroup
+            for (int u = blockIdx.x; u < 2 * ((gate.T + GM_TOK - 1) / GM_TOK); u += gridDim.x) gate_planes_body(gate, u);
+            return;
+        }
+    }
 
     const ChunkInfo ci = find_chunk(offsets, E, 16 * MT, blockIdx.x);
     if (ci.nrows == 0) return;  // uniform over the workgroup
@@ -68,7 +76,7 @@ __global__ __launch_bounds__(NW * 64) void ffn_fused_kernel(
     const global_bf16x8 *w1 = (const global_bf16x8 *)wexp + lane;
     const global_bf16x8 *w2 = (const global_bf16x8 *)(wexp + (size_t)d * f * 2) + lane;
     const int n_sub = no_weights ? 0 : f_range / SUB;
-    const int fs0 = blockIdx.y * f_range;
+    const int fs0 = range * f_range;
 
     // tile i (0 <= i < NT, compile-time after unrolling) of sub-slab s
     auto tile_ptr = [&](int s, int i) -> const global_bf16x8 * {
@@ -168,7 +176,7 @@ __global__ __launch_bounds__(NW * 64) void ffn_fused_kernel(
         if (r >= ci.nrows) continue;
         const size_t row = (size_t)ci.row0 + r;
         if (partial) {
-            float *dst = partial + ((size_t)blockIdx.y * n_rows + row) * d + (wave * NTB) * 16 + 4 * q;
+            float *dst = partial + ((size_t)range * n_rows + row) * d + (wave * NTB) * 16 + 4 * q;
 #pragma unroll
             for (int a = 0; a < NTB; ++a) *reinterpret_cast<floatx4 *>(dst + a * 16) = yacc[a][m];
         } else {
@@ -186,17 +194,6 @@ __global__ __launch_bounds__(NW * 64) void ffn_fused_kernel(
     }
 }
 
-// The pre-gate a decode-sized launch carries (FusedGate with the types the kernel needs).
-struct DecodeGate {
-    const __bf16 *x, *w;
-    const float *bias;
-    int T, k, E;
-    int32_t *idx;
-    float *prob;
-    uint32_t *flags;
-    int32_t *row_of, *offsets, *src_row;
-};
-
 // Decode-sized variant (at most a few experts active, <= 16 rows each): one workgroup of four
 // wavefronts per (chunk, 32-column sub-slab of d_ff), every weight tile it needs requested before
 // anything else happens, so the kernel is one round of memory latency deep instead of a ring of
@@ -213,10 +210,12 @@ __global__ __launch_bounds__(256) void ffn_decode_kernel(
     const char *__restrict__ w_base, size_t w_stride, int slot_by_rank, int n_slots,
     const unsigned long long *__restrict__ table, float *__restrict__ partial, int n_rows,
     const int32_t *__restrict__ src_row,  // nullable: grouped row r is row src_row[r] of x_perm
-    DecodeGate gate) {            // gate.x != nullptr: workgroup (0, gridDim.y - 1) runs that gate instead of a sub-slab
+    CarriedGate gate) {           // gate.x != nullptr: the last grid row runs that gate (planes: its first half) instead of a sub-slab
     constexpr int d = KT * 32;
     if (gate.x != nullptr && blockIdx.y == gridDim.y - 1) {  // uniform over the workgroup
-        if (blockIdx.x == 0)
+        if (gate.planes)
+            for (int u = blockIdx.x; u < 2 * ((gate.T + GM_TOK - 1) / GM_TOK); u += gridDim.x) gate_planes_body(gate, u);
+        else if (blockIdx.x == 0)
             gate_small_dispatch(gate.E, gate.x, gate.w, gate.bias, gate.T, d, gate.k, gate.idx, gate.prob, nullptr, gate.flags,
                                 gate.row_of, gate.offsets, gate.src_row);
         return;
@@ -688,11 +687,30 @@ int launch_ffn_reduce(pgmoe_ctx *ctx, const float *partial, int P, int n_rows, v
     return PGMOE_OK;
 }
 
+// The gate a launch is asked to carry, as the kernels take it (x == nullptr: it cannot), and what becomes of it.
+static CarriedGate carry_gate(pgmoe_ctx *ctx, const FusedGate *gate, bool decode_kernel, bool partials_kept, GateCarried *done) {
+    const pgmoe_config &c = ctx->cfg;
+    CarriedGate g = {};
+    if (!gate) return g;
+    const bool small = decode_kernel && gate_small_applies(c, gate->T);
+    // the second half goes with the combine that adds the partial sums
+    if (!small && !(partials_kept && ctx->gate_planes && gate_planes_apply(c, gate->T))) return g;
+    const bool route = small || gate_mfma_routes(c, gate->T);
+    g = CarriedGate{(const __bf16 *)gate->x, (const __bf16 *)gate->w, gate->bias, gate->T, c.d_model, c.top_k, c.n_experts, gate->idx,
+                    gate->prob, ctx->dev_flags, route ? gate->row_of : nullptr, route ? gate->offsets : nullptr,
+                    route ? gate->src_row : nullptr, small ? nullptr : ctx->gate_planes};
+    *done = small ? GATE_ROUTED : GATE_STARTED;
+    return g;
+}
+
 template <int MT, int KT, int NW, int D>
 static int launch_fused(pgmoe_ctx *ctx, const FfnPlan &p, const char *w_base, size_t w_stride, bool slot_by_rank, int n_slots,
                         const void *x_perm, const int32_t *offsets, int n_rows, void *y_perm, void *workspace,
-                        hipStream_t s, int *keep_partials, const unsigned long long *table, const int32_t *src_row) {
+                        hipStream_t s, int *keep_partials, const unsigned long long *table, const int32_t *src_row, const FusedGate *gate,
+                        GateCarried *gate_done) {
     const pgmoe_config &c = ctx->cfg;
+    CarriedGate cg = {};
+    if (NW == 4 && MT <= 2) cg = carry_gate(ctx, gate, false, keep_partials && p.n_partial > 1, gate_done);
     const size_t lds = (size_t)MT * KT * 1024 + 2u * MT * (16 * NW / 32) * 1024;
     auto kern = ffn_fused_kernel<MT, KT, NW, D>;
     if (int rc = allow_dynamic_lds(ctx, reinterpret_cast<const void *>(kern), lds)) return rc;
@@ -701,9 +719,9 @@ static int launch_fused(pgmoe_ctx *ctx, const FfnPlan &p, const char *w_base, si
         return fail(ctx, PGMOE_EINVAL, "pgmoe_expert_ffn: %d partial sums of %d rows do not fit the workspace", p.n_partial, n_rows);
     const int tslot = ffn_timing_slot(ctx);
     if (tslot >= 0) PG_HIP(ctx, hipEventRecord(ctx->tim_begin[tslot], s));
-    hipLaunchKernelGGL(kern, dim3(p.max_chunks, p.n_partial), dim3(NW * 64), lds, s, (const __bf16 *)x_perm, offsets,
+    hipLaunchKernelGGL(kern, dim3(p.max_chunks, p.n_partial + (cg.x ? 1 : 0)), dim3(NW * 64), lds, s, (const __bf16 *)x_perm, offsets,
                        c.n_experts, c.d_ff, p.f_range, w_base, w_stride, slot_by_rank ? 1 : 0, n_slots, table, partial, (__bf16 *)y_perm,
-                       n_rows, src_row);
+                       n_rows, src_row, cg);
     PG_HIP(ctx, hipGetLastError());
     if (tslot >= 0) PG_HIP(ctx, hipEventRecord(ctx->tim_end[tslot], s));
     if (keep_partials) {
@@ -772,10 +790,10 @@ static int launch_ffn_f32(pgmoe_ctx *ctx, const char *w_base, size_t w_stride, b
 
 int launch_ffn(pgmoe_ctx *ctx, const char *w_base, size_t w_stride, bool slot_by_rank, int n_slots, const void *x_perm,
                const int32_t *offsets, int n_rows, void *y_perm, void *workspace, hipStream_t s, int *keep_partials,
-               const unsigned long long *table, const int32_t *src_row, const FusedGate *gate, bool *gate_done) {
+               const unsigned long long *table, const int32_t *src_row, const FusedGate *gate, GateCarried *gate_done) {
     const pgmoe_config &c = ctx->cfg;
     if (keep_partials) *keep_partials = 0;
-    if (gate_done) *gate_done = false;
+    if (gate_done) *gate_done = GATE_LEFT;
     if (n_rows == 0) return PGMOE_OK;
     if (c.dtype == PGMOE_F32)
         return launch_ffn_f32(ctx, w_base, w_stride, slot_by_rank, n_slots, (const float *)x_perm, offsets, n_rows, (float *)y_perm,
@@ -793,13 +811,8 @@ int launch_ffn(pgmoe_ctx *ctx, const char *w_base, size_t w_stride, bool slot_by
             return fail(ctx, PGMOE_EINVAL, "pgmoe_expert_ffn: %d partial sums of %d rows do not fit the workspace", p.n_partial, n_rows);
         const int tslot = ffn_timing_slot(ctx);
         if (tslot >= 0) PG_HIP(ctx, hipEventRecord(ctx->tim_begin[tslot], s));
-        // one more row of workgroups for the pre-gate this launch carries, if it is one the smallest-gate code serves
-        DecodeGate dg = {};
-        if (gate && gate_done && gate_small_applies(c, gate->T)) {
-            dg = DecodeGate{(const __bf16 *)gate->x, (const __bf16 *)gate->w, gate->bias, gate->T, c.top_k, c.n_experts, gate->idx,
-                            gate->prob, ctx->dev_flags, gate->row_of, gate->offsets, gate->src_row};
-            *gate_done = true;
-        }
+        // one more row of workgroups for the pre-gate this launch carries
+        const CarriedGate dg = carry_gate(ctx, gate, true, keep_partials != nullptr, gate_done);
         const dim3 grid(p.max_chunks, p.n_partial + (dg.x ? 1 : 0));
         const size_t lds = (size_t)kt * 1024 + 4096;
         if (kt == 24)
@@ -820,7 +833,7 @@ int launch_ffn(pgmoe_ctx *ctx, const char *w_base, size_t w_stride, bool slot_by
 #define X(MT_, KT_, NW_, D_)                                                                                                  \
     if (p.mt == MT_ && kt == KT_ && p.nw == NW_)                                                                              \
         return launch_fused<MT_, KT_, NW_, D_>(ctx, p, w_base, w_stride, slot_by_rank, n_slots, x_perm, offsets, n_rows, y_perm, \
-                                               workspace, s, keep_partials, table, src_row);
+                                               workspace, s, keep_partials, table, src_row, gate, gate_done);
     PG_FUSED_CASES(X)
 #undef X
     return fail(ctx, PGMOE_EINVAL, "pgmoe_expert_ffn: no bf16 kernel built for d_model=%d with %d-row chunks and %d wavefronts", c.d_model, 16 * p.mt, p.nw);

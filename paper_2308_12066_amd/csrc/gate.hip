@@ -167,11 +167,6 @@ __global__ __launch_bounds__(GS_THREADS) void gate_small_kernel(
 //     eight k-values of expert 8*n + q: that is a valid operand for the 16 experts
 //     {q, 8+q, 16+q, ...}, i.e. output column n of product q is expert 8*n + q.  Eight products
 //     cover 128 experts per k-tile; E = 256 takes a second pass.
-typedef __bf16 gbf16x8 __attribute__((ext_vector_type(8)));
-typedef float gfloatx4 __attribute__((ext_vector_type(4)));
-constexpr int GM_TOK = 16;  // tokens per workgroup
-constexpr int GATE_ROUTE_MAX = 256;  // most (token, choice) pairs the gate kernel groups by itself
-
 template <int NP, int NW>  // NP: passes of 128 experts (1: E <= 128, 2: E <= 256); NW: wavefronts that split d_model
 __global__ __launch_bounds__(NW * 64) void gate_topk_mfma_kernel(
     const __bf16 *__restrict__ x, const __bf16 *__restrict__ w, const float *__restrict__ bias, int T, int d, int E, int k,
@@ -300,7 +295,7 @@ static int launch_gate_mfma(pgmoe_ctx *ctx, const __bf16 *x, const __bf16 *w, co
     const int np = c.n_experts <= 128 ? 1 : 2;
     const dim3 grid((T + GM_TOK - 1) / GM_TOK);
     // grouping inside the gate kernel: one workgroup holds the whole batch and the selections fit
-    const bool route = row_of && offsets && src_row && grid.x == 1 && T * c.top_k <= GATE_ROUTE_MAX;
+    const bool route = row_of && offsets && src_row && gate_mfma_routes(c, T);
     if (!route) row_of = offsets = src_row = nullptr;
     if (routed) *routed = route;
     if (gate_small_applies(c, T)) {
@@ -330,7 +325,7 @@ int launch_gate(pgmoe_ctx *ctx, const void *x, const void *w, const float *bias,
                 float *prob, float *probs, hipStream_t s, int32_t *row_of, int32_t *offsets, int32_t *src_row, bool *routed) {
     const pgmoe_config &c = ctx->cfg;
     if (routed) *routed = false;
-    if (c.dtype == PGMOE_BF16 && c.n_experts % 8 == 0 && c.d_model % 32 == 0)
+    if (gate_mfma_applies(c))
         return launch_gate_mfma(ctx, (const __bf16 *)x, (const __bf16 *)w, bias, T, idx, prob, probs, s,
                                 row_of, offsets, src_row, routed);
     if (c.dtype == PGMOE_F32)

@@ -1,7 +1,7 @@
-// Device code shared by the gate kernels (gate.hip) and by the decode-sized expert-FFN kernel
-// (ffn.hip), which can carry the next block's pre-gate as one extra workgroup: reductions over a
-// group of 16 lanes, softmax / top-k, token grouping inside a workgroup, and the body of the
-// smallest gate (at most GS_TOK tokens, 8 or 16 experts).
+// Device code shared by the gate kernels (gate.hip) and by the launches of a decode-sized block that can carry the next
+// block's pre-gate in a few extra workgroups (expert FFN: ffn.hip, combine: combine.hip): reductions over a
+// group of 16 lanes, softmax / top-k, token grouping inside a workgroup, the body of the
+// smallest gate (at most GS_TOK tokens, 8 or 16 experts) and the matrix-core gate in two halves.
 #ifndef PGMOE_GATE_SMALL_H
 #define PGMOE_GATE_SMALL_H
 #include "pgmoe_internal.h"
@@ -244,10 +244,103 @@ __device__ inline void gate_small_dispatch(int E, const __bf16 *x, const __bf16 
 #undef PG_GS
 }
 
+typedef __bf16 gbf16x8 __attribute__((ext_vector_type(8)));
+typedef float gfloatx4 __attribute__((ext_vector_type(4)));
+constexpr int GM_TOK = 16;  // tokens per workgroup
+constexpr int GATE_ROUTE_MAX = 256;  // most (token, choice) pairs the gate kernel groups by itself
+
+// ------------------------------------------------------------------------------------------
+// The matrix-core gate (gate_topk_mfma_kernel, E <= 128) in two halves for a decode-sized block: its logits are sums of GATE_PLANES partial
+// planes, plane v over the k-tiles v, v + GATE_PLANES, ..; the first half, carried by the launch that streams the experts'
+// weights, leaves the planes in memory, the second, carried by the combine behind it, adds them in order and selects.
+// Nothing crosses workgroups inside a launch, and every sum is the one kernel's, so results are its bits.
+// Why: alone the gate is a chain of latencies (8 us for 16 tokens and 64 experts, 12 for 64 and 128) in front of every block;
+// here the first half ends long before the weights have been streamed and the second is as long as the combine.  As one
+// workgroup inside the expert launch the whole gate took longer than the experts and cost that kernel its registers.
+constexpr int GATE_PLANES = 8;
+constexpr int GATE_PLANE = 8 * 64 * 4;        // floats of one plane of 16 tokens: [product q][lane][r]
+constexpr int GATE_CARRY_TOKENS = 128;        // most tokens of a carried gate
+struct CarriedGate {
+    const __bf16 *x, *w;  // x == nullptr: none
+    const float *bias;
+    int T, d, k, E;
+    int32_t *idx;
+    float *prob;
+    uint32_t *flags;
+    int32_t *row_of, *offsets, *src_row;  // null: the tokens are grouped elsewhere
+    float *planes;                        // [token tile][GATE_PLANES][GATE_PLANE]
+};
+
+// First half, 256 threads: workgroup u < 2 * token tiles computes four planes of tile u / 2, one per wavefront.
+__device__ inline void gate_planes_body(const CarriedGate &c, int u) {
+    const int lane = threadIdx.x & 63, n = lane & 15, g = lane >> 4;
+    const int tile = u >> 1, plane = (u & 1) * 4 + (threadIdx.x >> 6);
+    const int t0 = tile * GM_TOK, nt = min(GM_TOK, c.T - t0), KT = c.d >> 5, ncv = c.E >> 3;
+    const __bf16 *xrow = c.x + (size_t)(t0 + (n < nt ? n : 0)) * c.d + 8 * g;  // rows past the batch: its first token, never used
+    const gbf16x8 *wcol = reinterpret_cast<const gbf16x8 *>(c.w) + min(n, ncv - 1);  // column vectors past E: the last one, never used
+    gfloatx4 acc[8];
+#pragma unroll
+    for (int q = 0; q < 8; ++q) acc[q] = gfloatx4{0.f, 0.f, 0.f, 0.f};
+#pragma unroll 1
+    for (int kt = plane; kt < KT; kt += GATE_PLANES) {
+        const gbf16x8 a = *reinterpret_cast<const gbf16x8 *>(xrow + kt * 32);
+        gbf16x8 rows[8];
+#pragma unroll
+        for (int j = 0; j < 8; ++j) rows[j] = wcol[(size_t)(kt * 32 + 8 * g + j) * ncv];
+#pragma unroll
+        for (int q = 0; q < 8; ++q) {
+            gbf16x8 cell;
+#pragma unroll
+            for (int j = 0; j < 8; ++j) cell[j] = rows[j][q];
+            acc[q] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(a, cell, acc[q], 0, 0, 0);
+        }
+    }
+    gfloatx4 *dst = reinterpret_cast<gfloatx4 *>(c.planes + ((size_t)tile * GATE_PLANES + plane) * GATE_PLANE) + lane;
+#pragma unroll
+    for (int q = 0; q < 8; ++q) dst[q * 64] = acc[q];
+}
+
+// Second half, 256 threads: the 16 tokens of a tile.
+__device__ inline void gate_finish_body(const CarriedGate &c, int tile) {
+    __shared__ float zs[GM_TOK * 128];
+    __shared__ int32_t r_idx[GATE_ROUTE_MAX], r_cnt[PGMOE_MAX_EXPERTS], r_off[PGMOE_MAX_EXPERTS];
+    const int t0 = tile * GM_TOK, nt = min(GM_TOK, c.T - t0);
+    const gfloatx4 *src = reinterpret_cast<const gfloatx4 *>(c.planes + (size_t)tile * GATE_PLANES * GATE_PLANE);
+    for (int o = threadIdx.x; o < GATE_PLANE / 4; o += 256) {
+        const int l = o & 63, e = 8 * (l & 15) + (o >> 6);
+        gfloatx4 v[GATE_PLANES];
+#pragma unroll
+        for (int p = 0; p < GATE_PLANES; ++p) v[p] = src[p * (GATE_PLANE / 4) + o];
+        const float b = c.bias && e < c.E ? c.bias[e] : 0.f;
+#pragma unroll
+        for (int r = 0; r < 4; ++r) {
+            float sum = v[0][r];
+#pragma unroll
+            for (int p = 1; p < GATE_PLANES; ++p) sum += v[p][r];
+            zs[(4 * (l >> 4) + r) * 128 + e] = sum + b;
+        }
+    }
+    __syncthreads();
+    const bool route = c.row_of != nullptr;
+    softmax_topk<8>(zs, 128, t0, nt, c.E, c.k, c.idx, c.prob, nullptr, c.flags, route ? r_idx : nullptr);
+    if (route) group_in_workgroup(r_idx, r_cnt, r_off, nt * c.k, c.E, c.k, 256, c.row_of, c.offsets, c.src_row);
+}
+
 // Host side: is (T tokens, this configuration) a gate the smallest-gate code serves?
 inline bool gate_small_applies(const pgmoe_config &c, int T) {
     return c.dtype == PGMOE_BF16 && T >= 1 && T <= GS_TOK && (c.n_experts == 8 || c.n_experts == 16) && c.d_model <= 8 * GS_THREADS;
 }
+
+// Host side: is this a gate the matrix-core code serves?
+inline bool gate_mfma_applies(const pgmoe_config &c) { return c.dtype == PGMOE_BF16 && c.n_experts % 8 == 0 && c.d_model % 32 == 0; }
+// Does one workgroup hold the whole batch, so that the gate can group the tokens itself?
+inline bool gate_mfma_routes(const pgmoe_config &c, int T) { return T <= GM_TOK && T * c.top_k <= GATE_ROUTE_MAX; }
+// Is it one that a decode-sized block can carry in two halves?
+inline bool gate_planes_apply(const pgmoe_config &c, int T) {
+    return gate_mfma_applies(c) && c.n_experts <= 128 && T <= GATE_CARRY_TOKENS && !gate_small_applies(c, T);
+}
+// Floats of scratch the planes take for T tokens.
+inline size_t gate_planes_floats(int T) { return (size_t)((T + GM_TOK - 1) / GM_TOK) * GATE_PLANES * GATE_PLANE; }
 
 }  // namespace pgmoe
 #endif  // PGMOE_GATE_SMALL_H

@@ -56,6 +56,7 @@ struct pgmoe_ctx {
     int32_t *dev_unique;   // [n_blocks] distinct experts found by the pull kernel (dev_flags + 64 bytes)
     unsigned long long *dev_copy_clock;  // [n_blocks][2] copy start / end of the block's last traced pull kernel (100 MHz ticks)
     int32_t *dev_src_row;  // [n_blocks][max_tokens * k] grouped row -> token, written by each block's routing
+    float *gate_planes = nullptr;  // partial logits between the two halves of a carried pre-gate (gate_small.h); null: none is ever carried so
     bool *routed;          // [n_blocks] host: this step's gate kernel already grouped the block's tokens
     // turn-taking of a stack step's migration kernels on the host link (see fetch.hip): position of
     // the next one in the step (-1: not inside a step), and the position of the step's last one
@@ -170,7 +171,7 @@ int launch_permute(pgmoe_ctx *ctx, const void *x, const int32_t *idx, int T, voi
 // The integer half of launch_permute; src_row (nullable) receives the inverse map grouped row -> token.
 int launch_route(pgmoe_ctx *ctx, const int32_t *idx, int T, int32_t *row_of, int32_t *offsets, int32_t *src_row,
                  hipStream_t s);
-// A pre-gate that an expert-FFN launch may carry as one extra workgroup (Sec. IV-B: the pre-gate
+// A pre-gate that an expert-FFN launch may carry in extra workgroups (Sec. IV-B: the pre-gate
 // of block i is evaluated on the same hidden state as block i's experts and needs nothing from
 // them, so the two can run side by side in one launch).  Only decode-sized launches do it.
 struct FusedGate {
@@ -182,21 +183,24 @@ struct FusedGate {
     float *prob;                    // [T, k] out
     int32_t *row_of, *offsets, *src_row;  // grouping of the routed block, out
 };
+// What became of it: left to the caller; begun (launch_combine_partials finishes it); evaluated and its tokens grouped.
+enum GateCarried { GATE_LEFT = 0, GATE_STARTED = 1, GATE_ROUTED = 2 };
 // keep_partials != nullptr: if the launch produces float32 partial sums, leave them in the
 // workspace unreduced and report their number there (0 = y_perm was written directly).
-// gate != nullptr: carry that gate if this launch can (then *gate_done = true), else leave it to the caller.
+// gate != nullptr: carry that gate if this launch can and say so in *gate_done (non-null then).
 int launch_ffn(pgmoe_ctx *ctx, const char *w_base, size_t w_stride, bool slot_by_rank, int n_slots, const void *x_perm,
                const int32_t *offsets, int n_rows, void *y_perm, void *workspace, hipStream_t s, int *keep_partials = nullptr,
                const unsigned long long *table = nullptr,  // table: per-expert weight addresses (0 = none), overrides w_base
                const int32_t *src_row = nullptr,  // x_perm is the un-grouped x [T,d], grouped row r reads x[src_row[r]] (bf16; float32
                                                   // where ffn_f32_reads_rows_in_place says so)
-               const FusedGate *gate = nullptr, bool *gate_done = nullptr);
+               const FusedGate *gate = nullptr, GateCarried *gate_done = nullptr);
 // p-lanes of the partial-sum reduction for P partials (fixes the order of the additions)
 inline int reduce_lanes(int P) { return P <= 2 ? 1 : (P <= 8 ? 4 : 16); }
 // Combine straight from P unreduced float32 partials [P][n_rows][d] (bf16 contexts only): same
 // arithmetic, in the same order, as ffn_reduce_kernel followed by launch_combine.
 int launch_combine_partials(pgmoe_ctx *ctx, const float *partial, int P, int n_rows, const int32_t *row_of,
-                            const float *prob, int T, void *y, const void *x_res, void *x_next, hipStream_t s);
+                            const float *prob, int T, void *y, const void *x_res, void *x_next, hipStream_t s,
+                            const FusedGate *gate = nullptr);  // gate: one the expert launch has begun; finished here
 // seq: position among the migration kernels of the running stack step (they take turns on the
 // host link in that order), -1 for a kernel that is not part of one; last: the step's last one
 // turn_timeout_ticks: bound of that wait in ticks of the 100 MHz clock (0 = the default of half a second)
