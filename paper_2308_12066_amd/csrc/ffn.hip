@@ -204,20 +204,24 @@ __global__ __launch_bounds__(NW * 64) void ffn_fused_kernel(
 // token map: asking for the map at kernel start and for x ahead of the weights, or right behind
 // them, was measured 0.5 and 0.3 us slower per launch (same box, alternating builds): whatever
 // delays the first weight request costs more than the late x saves.
-template <int KT>
+// One instantiation per kind of gate: with all of them in one kernel it took 288 registers and 352 bytes of scratch per lane (the 16-expert
+// gate still does), and fewer workgroups of neighbouring steps shared a CU (T = 4, 8 experts of 768 x 3072, six blocks: 56 us a
+// step with steps of several stacks in flight, now 48).
+enum DecodeGateKind { DECODE_NO_GATE, DECODE_SMALL_GATE_8, DECODE_SMALL_GATE_16, DECODE_GATE_PLANES };  // small: for 8 / 16 experts
+template <int KT, DecodeGateKind GATE>
 __global__ __launch_bounds__(256) void ffn_decode_kernel(
     const __bf16 *__restrict__ x_perm, const int32_t *__restrict__ offsets, int E, int f,
     const char *__restrict__ w_base, size_t w_stride, int slot_by_rank, int n_slots,
     const unsigned long long *__restrict__ table, float *__restrict__ partial, int n_rows,
     const int32_t *__restrict__ src_row,  // nullable: grouped row r is row src_row[r] of x_perm
-    CarriedGate gate) {           // gate.x != nullptr: the last grid row runs that gate (planes: its first half) instead of a sub-slab
+    CarriedGate gate) {           // the last grid row runs that gate (planes: its first half) instead of a sub-slab
     constexpr int d = KT * 32;
-    if (gate.x != nullptr && blockIdx.y == gridDim.y - 1) {  // uniform over the workgroup
-        if (gate.planes)
+    if (GATE != DECODE_NO_GATE && blockIdx.y == gridDim.y - 1) {  // uniform over the workgroup
+        if constexpr (GATE == DECODE_GATE_PLANES)
             for (int u = blockIdx.x; u < 2 * ((gate.T + GM_TOK - 1) / GM_TOK); u += gridDim.x) gate_planes_body(gate, u);
         else if (blockIdx.x == 0)
-            gate_small_dispatch(gate.E, gate.x, gate.w, gate.bias, gate.T, d, gate.k, gate.idx, gate.prob, nullptr, gate.flags,
-                                gate.row_of, gate.offsets, gate.src_row);
+gate_small_dispatch<GATE == DECODE_SMALL_GATE_8 ? 1 : 2>(gate.x, gate.w, gate.bias, gate.T, d, gate.k, gate.idx, gate.prob, nullptr,
+                                                                     gate.flags, gate.row_of, gate.offsets, gate.src_row);
         return;
     }
     constexpr int NTD = KT * 2;   // output n-tiles
@@ -815,12 +819,22 @@ int launch_ffn(pgmoe_ctx *ctx, const char *w_base, size_t w_stride, bool slot_by
         const CarriedGate dg = carry_gate(ctx, gate, true, keep_partials != nullptr, gate_done);
         const dim3 grid(p.max_chunks, p.n_partial + (dg.x ? 1 : 0));
         const size_t lds = (size_t)kt * 1024 + 4096;
-        if (kt == 24)
-            hipLaunchKernelGGL(ffn_decode_kernel<24>, grid, dim3(256), lds, s, (const __bf16 *)x_perm, offsets, c.n_experts, c.d_ff,
-                               w_base, w_stride, slot_by_rank ? 1 : 0, n_slots, table, partial, n_rows, src_row, dg);
-        else
-            hipLaunchKernelGGL(ffn_decode_kernel<32>, grid, dim3(256), lds, s, (const __bf16 *)x_perm, offsets, c.n_experts, c.d_ff,
-                               w_base, w_stride, slot_by_rank ? 1 : 0, n_slots, table, partial, n_rows, src_row, dg);
+#define PG_DECODE(KT_, GATE_)                                                                                                    \
+    hipLaunchKernelGGL((ffn_decode_kernel<KT_, GATE_>), grid, dim3(256), lds, s, (const __bf16 *)x_perm, offsets, c.n_experts, c.d_ff, \
+                       w_base, w_stride, slot_by_rank ? 1 : 0, n_slots, table, partial, n_rows, src_row, dg)
+        const DecodeGateKind kind = !dg.x ? DECODE_NO_GATE : (dg.planes ? DECODE_GATE_PLANES : (c.n_experts == 8 ? DECODE_SMALL_GATE_8 : DECODE_SMALL_GATE_16));
+        if (kt == 24) {
+            if (kind == DECODE_NO_GATE) PG_DECODE(24, DECODE_NO_GATE);
+            else if (kind == DECODE_SMALL_GATE_8) PG_DECODE(24, DECODE_SMALL_GATE_8);
+            else if (kind == DECODE_SMALL_GATE_16) PG_DECODE(24, DECODE_SMALL_GATE_16);
+            else PG_DECODE(24, DECODE_GATE_PLANES);
+        } else {
+            if (kind == DECODE_NO_GATE) PG_DECODE(32, DECODE_NO_GATE);
+            else if (kind == DECODE_SMALL_GATE_8) PG_DECODE(32, DECODE_SMALL_GATE_8);
+            else if (kind == DECODE_SMALL_GATE_16) PG_DECODE(32, DECODE_SMALL_GATE_16);
+            else PG_DECODE(32, DECODE_GATE_PLANES);
+        }
+#undef PG_DECODE
         PG_HIP(ctx, hipGetLastError());
         if (tslot >= 0) PG_HIP(ctx, hipEventRecord(ctx->tim_end[tslot], s));
         if (keep_partials) {

@@ -153,7 +153,8 @@ __global__ __launch_bounds__(GS_THREADS) void gate_small_kernel(
     int E, const __bf16 *__restrict__ x, const __bf16 *__restrict__ w, const float *__restrict__ bias, int T, int d, int k,
     int32_t *__restrict__ idx_out, float *__restrict__ prob_out, float *__restrict__ probs_out, uint32_t *flags,
     int32_t *__restrict__ row_of, int32_t *__restrict__ offsets, int32_t *__restrict__ src_row) {
-    gate_small_dispatch(E, x, w, bias, T, d, k, idx_out, prob_out, probs_out, flags, row_of, offsets, src_row);
+    if (E == 8) gate_small_dispatch<1>(x, w, bias, T, d, k, idx_out, prob_out, probs_out, flags, row_of, offsets, src_row);
+    else gate_small_dispatch<2>(x, w, bias, T, d, k, idx_out, prob_out, probs_out, flags, row_of, offsets, src_row);
 }
 
 // Matrix-core path (bf16, E a multiple of 8, d_model a multiple of 32): the gate is a skinny

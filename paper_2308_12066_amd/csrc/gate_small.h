@@ -227,20 +227,15 @@ __device__ inline void gate_small_body(
     group_in_workgroup(r_idx, r_cnt, r_off, T * k, E, k, GS_THREADS, row_of, offsets, src_row);
 }
 
-// Runs the smallest gate for (E, T) in the calling workgroup of GS_THREADS threads (uniform call).
-__device__ inline void gate_small_dispatch(int E, const __bf16 *x, const __bf16 *w, const float *bias, int T, int d, int k,
+// Runs the smallest gate for 8*EV experts and T tokens in the calling workgroup of GS_THREADS threads (uniform call).
+template <int EV>
+__device__ inline void gate_small_dispatch(const __bf16 *x, const __bf16 *w, const float *bias, int T, int d, int k,
                                            int32_t *idx_out, float *prob_out, float *probs_out, uint32_t *flags,
                                            int32_t *row_of, int32_t *offsets, int32_t *src_row) {
-#define PG_GS(EV_, NTOK_) gate_small_body<EV_, NTOK_>(x, w, bias, T, d, k, idx_out, prob_out, probs_out, flags, row_of, offsets, src_row)
-    if (E == 8) {
-        if (T == 1) PG_GS(1, 1);
-        else if (T == 2) PG_GS(1, 2);
-        else PG_GS(1, 4);
-    } else {
-        if (T == 1) PG_GS(2, 1);
-        else if (T == 2) PG_GS(2, 2);
-        else PG_GS(2, 4);
-    }
+#define PG_GS(NTOK_) gate_small_body<EV, NTOK_>(x, w, bias, T, d, k, idx_out, prob_out, probs_out, flags, row_of, offsets, src_row)
+    if (T == 1) PG_GS(1);
+    else if (T == 2) PG_GS(2);
+    else PG_GS(4);
 #undef PG_GS
 }
 
