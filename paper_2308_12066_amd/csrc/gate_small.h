@@ -54,14 +54,15 @@ __device__ inline void group_argmax(float &v, int &i) {
 // experts s, s+16, s+32, ...: NQ of them (compile time, E <= 16*NQ), fully unrolled without a
 // branch per slice (a skipped slice of a 16-slice version still costs its branch, some 60 clocks,
 // which is what a batch-1 gate with 8 experts then spends its time on).
-template <int NQ>
+// GROUP != 0: the calling wavefronts are GROUP threads of a larger workgroup, aligned to that number; else the whole workgroup.
+template <int NQ, int GROUP>
 __device__ inline void softmax_topk_n(const float *zs, int zstride, int t0, int nt, int E, int k,
                                       int32_t *__restrict__ idx_out, float *__restrict__ prob_out,
                                       float *__restrict__ probs_out, uint32_t *flags, int32_t *idx_lds) {
-    const int tid = threadIdx.x;
+    const int tid = GROUP ? threadIdx.x & (GROUP - 1) : threadIdx.x;
     const int sub = tid & 15, grp = tid >> 4;  // 16 lanes per group
     bool any_nan = false;
-    for (int tb = 0; tb < nt; tb += (int)blockDim.x / 16) {
+    for (int tb = 0; tb < nt; tb += (GROUP ? GROUP : (int)blockDim.x) / 16) {
         if (tb + (grp & ~3) >= nt) continue;  // none of this wavefront's four tokens exists (uniform over the wavefront)
         const int t = tb + grp;
         const bool live = t < nt;  // idle groups of a live wavefront just skip the writes
@@ -119,12 +120,12 @@ __device__ inline void softmax_topk_n(const float *zs, int zstride, int t0, int 
 }
 
 // MAXQ: the most slices the calling kernel can need (E <= 16*MAXQ there).
-template <int MAXQ = 16>
+template <int MAXQ = 16, int GROUP = 0>
 __device__ inline void softmax_topk(const float *zs, int zstride, int t0, int nt, int E, int k,
                                     int32_t *__restrict__ idx_out, float *__restrict__ prob_out,
                                     float *__restrict__ probs_out, uint32_t *flags,
                                     int32_t *idx_lds = nullptr) {  // nullable: LDS copy [nt*k] of the chosen indices
-#define PG_SOFTMAX(NQ_) softmax_topk_n<NQ_>(zs, zstride, t0, nt, E, k, idx_out, prob_out, probs_out, flags, idx_lds)
+#define PG_SOFTMAX(NQ_) softmax_topk_n<NQ_, GROUP>(zs, zstride, t0, nt, E, k, idx_out, prob_out, probs_out, flags, idx_lds)
     if (E <= 16) PG_SOFTMAX(1);  // uniform over the kernel
     else if (E <= 32) PG_SOFTMAX(2);
     else if (E <= 64) PG_SOFTMAX(4);
@@ -222,7 +223,7 @@ __device__ inline void gate_small_body(
     }
     __syncthreads();
     const bool route = row_of != nullptr;
-    softmax_topk_n<1>(zs, 16, 0, T, E, k, idx_out, prob_out, probs_out, flags, route ? r_idx : nullptr);
+    softmax_topk_n<1, 0>(zs, 16, 0, T, E, k, idx_out, prob_out, probs_out, flags, route ? r_idx : nullptr);
     if (!route) return;
     group_in_workgroup(r_idx, r_cnt, r_off, T * k, E, k, GS_THREADS, row_of, offsets, src_row);
 }
