@@ -345,13 +345,15 @@ static void launch_gate_t(const pgmoe_config &c, const XT *x, const XT *w, const
                            c.d_model, E, c.top_k, idx, prob, probs, flags);
         return;
     }
-    // tokens per workgroup: as few as keeps about 64 workgroups busy (each re-reads W from L2)
+    // tokens per workgroup: one while every workgroup has a CU to itself (each reads W whatever it serves), then more; the two-token
+    // kernel falls behind with many experts.  float32, one / two / four: 100 tokens of 1024 x 128 9.9 / 16.4 / -, 400 tokens of 768 x 8
+    // - / 7.7 / 14.6, of 2048 x 256 - / 80 / 55 us
 #define PG_GATE(TB_)                                                                                                  \
     hipLaunchKernelGGL((gate_topk_vec_kernel<XT, TB_>), dim3((T + TB_ - 1) / TB_), dim3(GATE_THREADS), 0, s, x, w, bias, T, \
                        c.d_model, E, c.top_k, idx, prob, probs, flags)
-    if (T <= 64) PG_GATE(1);
-    else if (T <= 128) PG_GATE(2);
-    else if (T <= 256) PG_GATE(4);
+    if (T <= 256) PG_GATE(1);
+    else if (T <= 512 && E <= 64) PG_GATE(2);
+    else if (T <= 1024) PG_GATE(4);
     else PG_GATE(8);
 #undef PG_GATE
 }
