@@ -354,7 +354,7 @@ __global__ __launch_bounds__(256) void ffn_reduce_kernel(const float *__restrict
 // of the row, i.e. its output row i is column V*i + j, and every lane ends up with 4*V neighbouring columns of one token.
 // Bound by the weight stream (HBM); F32_DEPTH blocks of loads are in flight per wavefront.  One thread
 // per output column walking k by itself, which this replaces, re-read the weights once per row and paid a
-// memory latency every few k: 8 experts of 768 x 3072, 100 rows, 284 us + 836 us, now 18 + 32 (75 MB
+// memory latency every few k: 8 experts of 768 x 3072, 100 rows, 284 us + 836 us, now 18 + 29 (75 MB
 // of weights each; the second product has half the columns' workgroups, and its hidden rows share the CUs' request slots).
 constexpr int F32_DEPTH = 4;
 
@@ -746,11 +746,13 @@ static int launch_ffn_f32(pgmoe_ctx *ctx, const char *w_base, size_t w_stride, b
     if (tslot >= 0) PG_HIP(ctx, hipEventRecord(ctx->tim_begin[tslot], s));
     if (ffn_f32_reads_rows_in_place(c)) {
         // rows per workgroup by the rows an expert has (8 experts of 768 x 3072 with 12.5 rows each: 18 + 32 us with 16-row
-        // chunks, 28 + 41 with 32); columns per lane as many as still give (half of) the CUs a workgroup
+        // chunks, 28 + 41 with 32); columns per lane: four (wide pieces of a weight row, the least share of the activations in what
+        // a CU has in flight) where a third of the CUs get a workgroup all the same and the experts see a few rows each (the FFN of 100 / 512
+        // rows over 8 experts 48.6 / 119 us against 54.4 / 137 with two; of 32 rows 45.8 against 38.7)
         const int active = std::max(1, std::min(c.n_experts, n_rows)), mean = (n_rows + active - 1) / active;
         const int mt = mean <= 16 ? 1 : (mean <= 32 ? 2 : 4);
         const int chunks = active + n_rows / (16 * mt);
-        auto cols = [&](int N) { return active * ((N + 63) / 64) >= 256 ? 4 : (active * ((N + 31) / 32) >= 128 ? 2 : 1); };
+        auto cols = [&](int N) { return active * ((N + 63) / 64) >= (mean >= 8 ? 96 : 256) ? 4 : (active * ((N + 31) / 32) >= 128 ? 2 : 1); };
 #define PG_F32_HIDDEN(V_, MT_, NW_)                                                                                            \
     hipLaunchKernelGGL((ffn_f32_hidden_kernel<V_, MT_, NW_>), dim3(chunks, (c.d_ff + 16 * V_ - 1) / (16 * V_)), dim3(NW_ * 64), 0, s, \
                        x, src_row, offsets, c.n_experts, c.d_model, c.d_ff, w_base, w_stride, slot_by_rank ? 1 : 0, n_slots, table, h)
