@@ -26,8 +26,10 @@ namespace pgmoe {
 //    weights runs at half of what it reaches alone (10 against 16 us for 38 MB beside / without the rows' tiles).
 //    Hence as many rows per weight tile as the registers hold (320: 160 accumulator registers of 246), no second
 //    chunk for an expert that has a few rows more than a power of two, and no request for a row tile the chunk lacks;
-//  * 8 experts of 768 x 3072, 4096 rows: 27 us up, 31 down (the vendor GEMM library: 27 + 41), of which the matrix cores
-//    alone take 21 and the load stream alone 21; random operands hold them to about 1.6 PFLOP/s;
+//  * 8 experts of 768 x 3072, 4096 rows: 31 us up, 36 down (33 and 35 before; the vendor GEMM library: 27 + 41). The matrix cores
+//    alone take 21 of the first and the load stream alone 21; random operands hold them to about 1.6 PFLOP/s.  512 rows per
+//    expert are two chunks each, 192 workgroups; chunks of at most 256 rows (75 -> 79 us a block) and 192-column blocks
+//    (73 -> 74) were no better;
 //  * matrix-core accumulators must be ordinary vector registers (build flag): with the accumulator-register form the
 //    register allocator copies accumulators about inside the k loop and every copy waits for the product before it;
 //  * one result straight in bf16 where no K slices are needed: the float32 partials of one slice cost the combine 14 us
