@@ -538,7 +538,16 @@ int launch_ffn_gemm(pgmoe_ctx *ctx, const char *w_base, size_t w_stride, bool sl
         hipLaunchKernelGGL(ffn_gemm_pack_rows_kernel, dim3(max_chunks, c.d_model / 32 / PACK_KT), dim3(512), 0, s, (const __bf16 *)x_perm,
                            offsets, c.n_experts, c.d_model, src_row, (__bf16 *)xp, lo, hi);
         PG_HIP(ctx, hipGetLastError());
-#define PG_TILE(BN_, NS_, UP_, A_, K_, N_, SPLIT_)                                                                                  do {                                                                                                                             constexpr int lds = NS_ * (GEMM_RT + BN_ / 16) * 1024;                                                                       auto kern_ = ffn_gemm_tile_kernel<BN_, NS_, UP_>;                                                                            if (int rc_ = allow_dynamic_lds(ctx, reinterpret_cast<const void *>(kern_), lds)) return rc_;                                hipLaunchKernelGGL(kern_, dim3(max_chunks, N_ / BN_ * SPLIT_), dim3(512), lds, s, (const char *)(A_), offsets,                                  c.n_experts, K_, N_, SPLIT_, w_base, w_stride, slot_by_rank ? 1 : 0, n_slots, table, h, partial,                             (__bf16 *)y_perm, n_rows, lo, hi);                                                                        PG_HIP(ctx, hipGetLastError());                                                                                          } while (0)
+#define PG_TILE(BN_, NS_, UP_, A_, K_, N_, SPLIT_)                                                                                 \
+    do {                                                                                                                           \
+        constexpr int lds = NS_ * (GEMM_RT + BN_ / 16) * 1024;                                                                     \
+        auto kern_ = ffn_gemm_tile_kernel<BN_, NS_, UP_>;                                                                          \
+        if (int rc_ = allow_dynamic_lds(ctx, reinterpret_cast<const void *>(kern_), lds)) return rc_;                              \
+        hipLaunchKernelGGL(kern_, dim3(max_chunks, N_ / BN_ * SPLIT_), dim3(512), lds, s, (const char *)(A_), offsets,             \
+                           c.n_experts, K_, N_, SPLIT_, w_base, w_stride, slot_by_rank ? 1 : 0, n_slots, table, h, partial,        \
+                           (__bf16 *)y_perm, n_rows, lo, hi);                                                                      \
+        PG_HIP(ctx, hipGetLastError());                                                                                            \
+    } while (0)
         if (p.bn_up == 256) PG_TILE(256, 4, true, xp, c.d_model, c.d_ff, 1);
         else PG_TILE(128, 5, true, xp, c.d_model, c.d_ff, 1);
         if (p.bn_down == 256) PG_TILE(256, 4, false, h, c.d_ff, c.d_model, p.split);
