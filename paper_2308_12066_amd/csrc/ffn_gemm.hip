@@ -195,12 +195,14 @@ __global__ __launch_bounds__(512) void ffn_gemm_pack_rows_kernel(
 // compiler cannot tell which stage a later LDS read belongs to and would wait for every load in
 // flight before it, which is exactly the prefetch.  Here the kernel counts its own loads (they
 // complete in order) and waits with explicit s_waitcnt vmcnt.  M0 (the LDS base of such a load)
-// is written inside the statement; nothing else in this kernel keeps a value in M0.
+// is written inside the statement; nothing else in this kernel keeps a value in M0.  The hardware needs one wait
+// state between a scalar write of M0 and a direct-to-LDS load (without it the tile may land at the address of the load
+// before); the compiler inserts it behind its own writes only, so the statement carries it.
 __device__ inline unsigned lds_address(const void *p) {
     return (unsigned)(size_t)(__attribute__((address_space(3))) const char *)p;
 }
 __device__ inline void load_tile_to_lds(const char *src_lane, unsigned lds_tile) {  // src_lane: this lane's 16 bytes
-    asm volatile("s_mov_b32 m0, %1\n\tglobal_load_lds_dwordx4 %0, off" ::"v"(src_lane), "s"(lds_tile) : "memory", "m0");
+    asm volatile("s_mov_b32 m0, %1\n\ts_nop 0\n\tglobal_load_lds_dwordx4 %0, off" ::"v"(src_lane), "s"(lds_tile) : "memory", "m0");
 }
 
 // What a workgroup of the tile kernel works on (all uniform).

@@ -1,0 +1,54 @@
+"""The device code inside libpgmoe.so, disassembled here: rules of the hardware that the compiler keeps
+for its own instructions but cannot keep inside an inline-assembly statement."""
+import os
+import re
+import subprocess
+
+import pytest
+
+from paper_2308_12066_amd import binding as B, build
+
+LLVM = os.path.join(os.path.dirname(os.path.dirname(os.path.realpath(build.HIPCC))), "llvm", "bin")
+
+
+@pytest.fixture(scope="module")
+def code_objects(tmp_path_factory):
+    """Paths of the gfx950 code objects the library carries, one per source file."""
+    objdump = os.path.join(LLVM, "llvm-objdump")
+    if not os.path.exists(objdump):
+        pytest.skip("no llvm-objdump")
+    folder = tmp_path_factory.mktemp("code")
+    lib = folder / "lib.so"
+    lib.write_bytes(open(B.LIB_PATH, "rb").read())
+    subprocess.run([objdump, "--offloading", str(lib)], check=True, stdout=subprocess.DEVNULL, cwd=folder)
+    objs = sorted(str(p) for p in folder.iterdir() if "gfx950" in p.name)
+    assert len(objs) == len(build.SOURCES)
+    return objs
+
+
+def writes_m0(instruction):
+    return re.match(r"s_\S+\s+m0\b", instruction) is not None
+
+
+def test_a_load_into_lds_leaves_a_wait_state_after_m0_is_written(code_objects):
+    """A direct-to-LDS load takes its LDS address from M0 and needs one instruction between a scalar write of
+    M0 and itself; without it the tile may land where the load before it put its own."""
+    seen, bad = 0, []
+    for obj in code_objects:
+        text = subprocess.run([os.path.join(LLVM, "llvm-objdump"), "-d", "--no-show-raw-insn", obj], check=True, capture_output=True, text=True).stdout
+        kernel, before = "", ""
+        for line in text.splitlines():
+            m = re.match(r"[0-9a-f]+ <(\S+)>:", line)
+            if m:
+                kernel, before = m.group(1), ""
+                continue
+            ins = line.split("//")[0].strip()
+            if not ins:
+                continue
+            if ins.startswith("global_load_lds") or (ins.startswith("buffer_load") and ins.endswith(" lds")):
+                seen += 1
+                if writes_m0(before):
+                    bad.append((kernel, before, ins))
+            before = ins
+    assert seen > 0
+    assert not bad, f"{len(bad)} of {seen} loads follow the write of M0 at once, the first in {bad[0]}"
