@@ -75,17 +75,23 @@ __global__ __launch_bounds__(256) void combine_scalar_kernel(const XT *__restric
 typedef float floatx4 __attribute__((ext_vector_type(4)));
 typedef __bf16 bf16x4 __attribute__((ext_vector_type(4)));
 
-// GATE: the first workgroups finish the pre-gate whose partial planes the expert launch left.
-template <int PL, bool GATE>
+// Gate: nothing, or CarriedGate: the first workgroups then finish the pre-gate whose partial planes the expert launch left.  The
+// variant without one has no such argument (64 bytes of arguments a launch, 160 with it: 8 experts of 768 x 3072, one token, six
+// blocks, each step waited for: 87.6 us a step on a slow host core, 90.3 with it).
+template <int PL, typename... Gate>
 __global__ __launch_bounds__(256) void combine_partials_kernel(const float *__restrict__ partial, int P, int n_rows,
                                                                 const int32_t *__restrict__ row_of,
                                                                 const float *__restrict__ prob, int d, int k,
                                                                 __bf16 *__restrict__ y, const __bf16 *__restrict__ x_res,
-                                                                __bf16 *__restrict__ x_next, CarriedGate gate) {
-    const int tiles = GATE ? (gate.T + GM_TOK - 1) / GM_TOK : 0;
-    if (GATE && (int)blockIdx.x < tiles) {  // uniform over the workgroup
-        if (blockIdx.y == 0) gate_finish_body(gate, blockIdx.x);
-        return;
+                                                                __bf16 *__restrict__ x_next, Gate... carried) {
+    int tiles = 0;
+    if constexpr (sizeof...(Gate) > 0) {
+        const CarriedGate &gate = the_gate(carried...);
+        tiles = (gate.T + GM_TOK - 1) / GM_TOK;
+        if ((int)blockIdx.x < tiles) {  // uniform over the workgroup
+            if (blockIdx.y == 0) gate_finish_body(gate, blockIdx.x);
+            return;
+        }
     }
     // 256 threads = PL p-lanes x COLS float4 columns of one token (same split as ffn_reduce_kernel<PL>)
     constexpr int COLS = 256 / PL;
@@ -158,26 +164,27 @@ int launch_combine_partials(pgmoe_ctx *ctx, const float *partial, int P, int n_r
     const pgmoe_config &c = ctx->cfg;
     const int pl = reduce_lanes(P);
     const int cols = 256 / pl;
-    CarriedGate cg = {};
-    if (gate) {
-        const bool route = gate_mfma_routes(c, gate->T);
-        cg = CarriedGate{(const __bf16 *)gate->x, (const __bf16 *)gate->w, gate->bias, gate->T, c.d_model, c.top_k, c.n_experts, gate->idx,
-                         gate->prob, ctx->dev_flags, route ? gate->row_of : nullptr, route ? gate->offsets : nullptr,
-                         route ? gate->src_row : nullptr, ctx->gate_planes};
-    }
     const dim3 grid(T + (gate ? (gate->T + GM_TOK - 1) / GM_TOK : 0), (c.d_model / 4 + cols - 1) / cols);
-#define PG_CP(PL_, GATE_)                                                                                                     \
-    hipLaunchKernelGGL((combine_partials_kernel<PL_, GATE_>), grid, dim3(256), 0, s, partial, P, n_rows, row_of, prob, c.d_model, \
+#define PG_CP(PL_)                                                                                                                  \
+    hipLaunchKernelGGL(combine_partials_kernel<PL_>, grid, dim3(256), 0, s, partial, P, n_rows, row_of, prob, c.d_model, c.top_k,      \
+                       (__bf16 *)y, (const __bf16 *)x_res, (__bf16 *)x_next)
+#define PG_CP_GATE(PL_)                                                                                                             \
+    hipLaunchKernelGGL((combine_partials_kernel<PL_, CarriedGate>), grid, dim3(256), 0, s, partial, P, n_rows, row_of, prob, c.d_model, \
                        c.top_k, (__bf16 *)y, (const __bf16 *)x_res, (__bf16 *)x_next, cg)
     if (gate) {
-        if (pl == 1) PG_CP(1, true);
-        else if (pl == 4) PG_CP(4, true);
-        else PG_CP(16, true);
+        const bool route = gate_mfma_routes(c, gate->T);
+        const CarriedGate cg = {(const __bf16 *)gate->x, (const __bf16 *)gate->w, gate->bias, gate->T, c.d_model, c.top_k, c.n_experts,
+                                gate->idx, gate->prob, ctx->dev_flags, route ? gate->row_of : nullptr, route ? gate->offsets : nullptr,
+                                route ? gate->src_row : nullptr, ctx->gate_planes};
+        if (pl == 1) PG_CP_GATE(1);
+        else if (pl == 4) PG_CP_GATE(4);
+        else PG_CP_GATE(16);
     } else {
-        if (pl == 1) PG_CP(1, false);
-        else if (pl == 4) PG_CP(4, false);
-        else PG_CP(16, false);
+        if (pl == 1) PG_CP(1);
+        else if (pl == 4) PG_CP(4);
+        else PG_CP(16);
     }
+#undef PG_CP_GATE
 #undef PG_CP
     PG_HIP(ctx, hipGetLastError());
     return PGMOE_OK;

@@ -266,6 +266,7 @@ struct CarriedGate {
     int32_t *row_of, *offsets, *src_row;  // null: the tokens are grouped elsewhere
     float *planes;                        // [token tile][GATE_PLANES][GATE_PLANE]
 };
+__device__ inline const CarriedGate &the_gate(const CarriedGate &gate) { return gate; }  // of a kernel whose last argument may be missing
 
 // First half, 256 threads: workgroup u < 2 * token tiles computes four planes of tile u / 2, one per wavefront.
 __device__ inline void gate_planes_body(const CarriedGate &c, int u) {

@@ -1,5 +1,6 @@
 """The device code inside libpgmoe.so, disassembled here: rules of the hardware that the compiler keeps
-for its own instructions but cannot keep inside an inline-assembly statement."""
+for its own instructions but cannot keep inside an inline-assembly statement, and what a launch that
+uses an option of a kernel must not cost the launches that do not."""
 import os
 import re
 import subprocess
@@ -52,3 +53,23 @@ def test_a_load_into_lds_leaves_a_wait_state_after_m0_is_written(code_objects):
             before = ins
     assert seen > 0
     assert not bad, f"{len(bad)} of {seen} loads follow the write of M0 at once, the first in {bad[0]}"
+
+
+def kernels(code_objects):
+    """{mangled name: {field: integer}} of the code objects' kernel metadata."""
+    out = {}
+    for obj in code_objects:
+        text = subprocess.run([os.path.join(LLVM, "llvm-readelf"), "--notes", obj], check=True, capture_output=True, text=True).stdout
+        for entry in re.split(r"\n  - (?=\.)", text)[1:]:
+            name = re.search(r"^\s*\.name:\s+'?(_Z\w+)", entry, re.M)
+            if name:
+                out[name.group(1)] = {k: int(v) for k, v in re.findall(r"^\s*\.(\w+):\s+(\d+)$", entry, re.M)}
+    return out
+
+
+def test_a_combine_without_a_carried_gate_has_no_arguments_of_one(code_objects):
+    """The host writes a launch's arguments one by one: the combine of a batch-1 block has 64 bytes of them."""
+    found = {n: k for n, k in kernels(code_objects).items() if "combine_partials_kernel" in n}
+    plain = {n: k["kernarg_segment_size"] for n, k in found.items() if "CarriedGate" not in n}
+    assert len(plain) == 3 and len(found) == 6, sorted(found)
+    assert max(plain.values()) <= 64, plain
