@@ -38,13 +38,18 @@ namespace pgmoe {
 // its NTB W2 tiles (phase B).  The tiles form one linear stream over all sub-slabs; tile g+D is
 // requested when tile g is consumed, so loads run ahead of the matrix cores across both phases
 // and across the LDS barrier between them.
-template <int MT, int KT, int NW, int D>
+//
+// Gate: nothing, or CarriedGate: grid row 0 then runs that gate's first half and the d_ff ranges follow.  A variant of its own, because
+// the gate's code costs the kernel registers (d_model 512, 16-row chunks: 170 with it, 148 without, i.e. two or three wavefronts per
+// SIMD; 64: 106 and 54) that a launch without a gate has no use for (64 experts of 512 x 2048, a block of 64 tokens: 56.8 us with the gate's
+// code in the kernel, 53.6 without).
+template <int MT, int KT, int NW, int D, typename... Gate>
 __global__ __launch_bounds__(NW * 64) void ffn_fused_kernel(
     const __bf16 *__restrict__ x_perm, const int32_t *__restrict__ offsets, int E, int f, int f_range,
     const char *__restrict__ w_base, size_t w_stride, int slot_by_rank, int n_slots,
     const unsigned long long *__restrict__ table, float *__restrict__ partial, __bf16 *__restrict__ y_perm, int n_rows,
     const int32_t *__restrict__ src_row,  // nullable: grouped row r is row src_row[r] of x_perm (rows not gathered yet)
-    CarriedGate gate) {                   // gate.x != nullptr: grid row 0 runs its first half, the d_ff ranges follow
+    Gate... carried) {
     constexpr int SUB = 16 * NW;      // d_ff columns per sub-slab
     constexpr int KTB = SUB / 32;     // k-tiles of phase B per sub-slab
     constexpr int NTD = KT * 2;       // n-tiles of the output (d_model / 16)
@@ -56,8 +61,10 @@ __global__ __launch_bounds__(NW * 64) void ffn_fused_kernel(
 
     const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
     int range = blockIdx.y;
-    if constexpr (NW == 4 && MT <= 2) {
-        if (gate.x != nullptr && range-- == 0) {  // uniform over the workgroup
+    if constexpr (sizeof...(Gate) > 0) {
+        static_assert(NW == 4, "the first half is 256 threads'");
+        const CarriedGate &gate = the_gate(carried...);
+        if (range-- == 0) {  // uniform over the workgroup
             for (int u = blockIdx.x; u < 2 * ((gate.T + GM_TOK - 1) / GM_TOK); u += gridDim.x) gate_planes_body(gate, u);
             return;
         }
@@ -713,19 +720,29 @@ static int launch_fused(pgmoe_ctx *ctx, const FfnPlan &p, const char *w_base, si
                         hipStream_t s, int *keep_partials, const unsigned long long *table, const int32_t *src_row, const FusedGate *gate,
                         GateCarried *gate_done) {
     const pgmoe_config &c = ctx->cfg;
+    constexpr bool CARRIES = NW == 4 && MT <= 2;  // decode-sized chunks
     CarriedGate cg = {};
-    if (NW == 4 && MT <= 2) cg = carry_gate(ctx, gate, false, keep_partials && p.n_partial > 1, gate_done);
+    if (CARRIES) cg = carry_gate(ctx, gate, false, keep_partials && p.n_partial > 1, gate_done);
     const size_t lds = (size_t)MT * KT * 1024 + 2u * MT * (16 * NW / 32) * 1024;
-    auto kern = ffn_fused_kernel<MT, KT, NW, D>;
-    if (int rc = allow_dynamic_lds(ctx, reinterpret_cast<const void *>(kern), lds)) return rc;
     float *partial = p.n_partial > 1 ? (float *)workspace : nullptr;
     if (partial && (size_t)p.n_partial * n_rows * c.d_model * 4 > ffn_workspace_bytes(c))
         return fail(ctx, PGMOE_EINVAL, "pgmoe_expert_ffn: %d partial sums of %d rows do not fit the workspace", p.n_partial, n_rows);
     const int tslot = ffn_timing_slot(ctx);
     if (tslot >= 0) PG_HIP(ctx, hipEventRecord(ctx->tim_begin[tslot], s));
-    hipLaunchKernelGGL(kern, dim3(p.max_chunks, p.n_partial + (cg.x ? 1 : 0)), dim3(NW * 64), lds, s, (const __bf16 *)x_perm, offsets,
-                       c.n_experts, c.d_ff, p.f_range, w_base, w_stride, slot_by_rank ? 1 : 0, n_slots, table, partial, (__bf16 *)y_perm,
-                       n_rows, src_row, cg);
+    auto launch = [&](auto kern, int rows, auto... carried) {
+        if (int rc = allow_dynamic_lds(ctx, reinterpret_cast<const void *>(kern), lds)) return rc;
+        hipLaunchKernelGGL(kern, dim3(p.max_chunks, rows), dim3(NW * 64), lds, s, (const __bf16 *)x_perm, offsets, c.n_experts, c.d_ff,
+                           p.f_range, w_base, w_stride, slot_by_rank ? 1 : 0, n_slots, table, partial, (__bf16 *)y_perm, n_rows, src_row,
+                           carried...);
+        return (int)PGMOE_OK;
+    };
+    int rc;
+    if constexpr (CARRIES) {
+        rc = cg.x ? launch(ffn_fused_kernel<MT, KT, NW, D, CarriedGate>, p.n_partial + 1, cg) : launch(ffn_fused_kernel<MT, KT, NW, D>, p.n_partial);
+    } else {
+        rc = launch(ffn_fused_kernel<MT, KT, NW, D>, p.n_partial);
+    }
+    if (rc) return rc;
     PG_HIP(ctx, hipGetLastError());
     if (tslot >= 0) PG_HIP(ctx, hipEventRecord(ctx->tim_end[tslot], s));
     if (keep_partials) {

@@ -73,3 +73,15 @@ def test_a_combine_without_a_carried_gate_has_no_arguments_of_one(code_objects):
     plain = {n: k["kernarg_segment_size"] for n, k in found.items() if "CarriedGate" not in n}
     assert len(plain) == 3 and len(found) == 6, sorted(found)
     assert max(plain.values()) <= 64, plain
+
+
+def test_a_fused_expert_launch_without_a_carried_gate_keeps_its_occupancy(code_objects):
+    """Wavefronts per SIMD (512 registers a lane, dealt out eight at a time, at most eight wavefronts) of the
+    variants that a launch without a gate runs; the gate's code would take one to four of them."""
+    waves = {}
+    for name, k in kernels(code_objects).items():
+        m = re.search(r"ffn_fused_kernelILi(\d+)ELi(\d+)ELi(\d+)E", name)
+        if m and "CarriedGate" not in name:
+            waves[tuple(map(int, m.groups()))] = min(8, 512 // (-(-k["vgpr_count"] // 8) * 8))
+    for case, want in {(1, 2, 4): 8, (2, 2, 4): 8, (1, 4, 4): 5, (1, 16, 4): 3}.items():    # (row tiles, d_model / 32, wavefronts)
+        assert waves.get(case, 0) >= want, (case, waves)
