@@ -292,3 +292,15 @@ def test_ffn_kernel_name_follows_the_launch_plan():
     assert name(16, d_model=768, d_ff=3072, n_experts=64, top_k=1, max_tokens=16) == "ffn_fused_kernel"
     assert name(4096, d_model=768, d_ff=3072, n_experts=8, top_k=1, max_tokens=4096) == "ffn_gemm_pack_rows_kernel+ffn_gemm_tile_kernel"   # ~512 rows per expert
     assert name(8, d_model=64, d_ff=256, n_experts=8, top_k=1, dtype=B.F32) == "ffn_f32_hidden_kernel+ffn_f32_out_kernel"
+
+
+@pytest.mark.parametrize("d,f,E,rows,gemm", [
+    (512, 2048, 1, 10, False), (512, 1024, 2, 20, False), (256, 512, 4, 48, False),     # too little work for three launches
+    (128, 8192, 256, 20480, False), (128, 8192, 64, 7168, False), (256, 1024, 128, 24320, False),   # the hidden activation's way through memory
+    (768, 3072, 128, 10240, False),                                                     # many experts: a skewed routing
+    (768, 3072, 8, 128, True), (768, 3072, 64, 6002, True), (1024, 4096, 128, 6144, True), (2048, 8192, 16, 320, True), (128, 8192, 4, 760, True),
+])
+def test_a_launch_takes_the_two_gemms_only_where_they_were_measured_faster(d, f, E, rows, gemm):
+    ctx = B.Context(cfg(d_model=d, d_ff=f, n_experts=E, top_k=1, max_tokens=rows))
+    assert ("gemm" in ctx.ffn_kernel_name(rows)) == gemm
+    ctx.close()
