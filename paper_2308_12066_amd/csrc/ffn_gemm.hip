@@ -450,11 +450,11 @@ static size_t gemm_tile_bytes(const pgmoe_config &c) { return (size_t)16 * (c.d_
 // every expert's weights once per chunk of at most 64 rows, with d_ff cut into as few ranges as keep
 // its partial sums cheap, so with few experts or several chunks per expert it leaves CUs idle or reads weights
 // again; the GEMMs cost two launches more and the round trip of the hidden activation, which is what bounds them where d_model is
-// small.  The two estimates (microseconds) are fitted to 813 launches timed both ways (d_model 128 .. 2048, d_ff 512 .. 8192, 1 .. 256
-// experts, 8 .. 190 rows per expert, even and skewed routing; both are within some 12 %): 64 experts of 768 x 3072 at 28 / 40 / 64 / 100
+// small.  The two estimates (microseconds) are fitted to 1317 launches timed both ways (d_model 128 .. 2048, d_ff 512 .. 8192, 1 .. 256
+// experts, 8 .. 190 rows per expert, even and skewed routing; both are within 11 % root mean square): 64 experts of 768 x 3072 at 28 / 40 / 64 / 100
 // rows per expert 124 / 155 / 248 / 243 us fused and 128 / 135 / 146 / 161 us as GEMMs; 128 of 1024 x 4096 at 48 rows 623 and 414; one of 512 x 2048
-// at 10 rows 19 and 26; 256 of 128 x 8192 at 80 rows 329 and 425; 128 of 256 x 1024 at 190 skewed rows 64 and 98.  By this rule eleven of the
-// 813 are more than 3 % slower than fused (115 of them by taking the GEMMs always) and 28 more than 3 % slower than as GEMMs.
+// at 10 rows 19 and 26; 256 of 128 x 8192 at 80 rows 329 and 425; 128 of 256 x 1024 at 190 skewed rows 64 and 98.  The rule's choices are
+// 1.49 times as fast as the fused kernel on the geometric mean, the better of the two each time would be 1.51.
 bool uses_gemm_kernels(const pgmoe_config &c, int n_rows) {
     if (c.dtype != PGMOE_BF16) return false;
     // the k loop takes two 32-k tiles per turn (in every K slice of the down-projection); the pack kernel PACK_KT k-tiles per workgroup
@@ -468,16 +468,18 @@ bool uses_gemm_kernels(const pgmoe_config &c, int n_rows) {
     const double expert = 4.0 * c.d_model * c.d_ff, weights = active * expert / 5.7e6;  // bytes; us at the rate HBM delivers
     const double chunks = std::max((double)active, 0.5 * active + n_rows / (16.0 * p.mt)), wgs = chunks * p.n_partial;
     const bool alone = p.mt * (c.d_model / 32 + p.nw) > 80;  // KiB of LDS: one workgroup per CU, so a second round costs as much as the first
-    const double rounds = 1.0 + std::max(0.0, alone ? (wgs - 220.0) / 100.0 : wgs / 256.0 - 1.0);
+    const double rounds = 1.0 + std::max(0.0, alone ? (wgs - 201.0) / 196.0 : wgs / 256.0 - 1.0);
     const double again = 0.3 + 0.7 * chunks / active;  // an expert's second chunk finds part of the weights in a cache
     // bytes per us of one workgroup's stream of weights: less the more rows it multiplies and the more workgroups there are
-    double rate = p.mt == 1 ? 115e3 : (p.mt == 2 ? 74e3 : (p.nw == 8 ? 74e3 : 55e3));
-    if (c.d_model >= 1024) rate *= p.nw == 8 ? 0.70 : 0.80;
-    rate *= std::pow(std::min(wgs, 256.0), -0.11);
-    const double fused = 12.0 + std::max(weights * again, rounds * expert / p.n_partial / rate);
-    const double gemm = 23.0 + 0.0013 * (c.d_model + c.d_ff) + std::max(weights + (double)n_rows * c.d_model * c.d_ff / 5e8, 1.9e-6 * n_rows * c.d_ff);
+    const bool wide = c.d_model >= 1024;
+    const double rate = p.mt == 1 ? 200e3 : (p.mt == 2 ? (wide ? 66e3 : 92e3) : (p.nw == 8 ? (wide ? 63e3 : 81e3) : 53e3));
+    const double decay = p.mt == 1 ? 0.31 : (p.mt == 2 ? (wide ? 0.05 : 0.16) : (p.nw == 8 ? (wide ? 0.137 : 0.164) : 0.087));
+    const double stream = rounds * expert / p.n_partial / (rate * std::pow(std::min(wgs, 256.0), -decay));
+    const double fused = 11.9 + (p.n_partial > 1 ? 4e-6 * p.n_partial * n_rows * c.d_model : 0.0) + std::max(0.91 * weights * again, stream);
+    const double gemm = 23.5 + 0.00091 * (c.d_model + c.d_ff) +
+                        std::max(0.89 * weights + (double)n_rows * c.d_model * c.d_ff / 3.36e8, 1.93e-6 * n_rows * c.d_ff);
     // in doubt fused: a skewed routing costs the GEMMs more, with many experts above all
-    const double margin = c.d_model <= 256 ? (active >= 64 ? 1.5 : 1.1) : (active >= 96 ? 1.2 : (active >= 32 ? 1.05 : 1.0));
+    const double margin = c.d_model <= 256 ? (active >= 64 ? 1.5 : 1.1) : (active >= 96 ? 1.1 : (active >= 32 ? 1.05 : 1.0));
     return margin * gemm < fused;
 }
 

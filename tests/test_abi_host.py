@@ -297,8 +297,8 @@ def test_ffn_kernel_name_follows_the_launch_plan():
 @pytest.mark.parametrize("d,f,E,rows,gemm", [
     (512, 2048, 1, 10, False), (512, 1024, 2, 20, False), (256, 512, 4, 48, False),     # too little work for three launches
     (128, 8192, 256, 20480, False), (128, 8192, 64, 7168, False), (256, 1024, 128, 24320, False),   # the hidden activation's way through memory
-    (768, 3072, 128, 10240, False),                                                     # many experts: a skewed routing
-    (768, 3072, 8, 128, True), (768, 3072, 64, 6002, True), (1024, 4096, 128, 6144, True), (2048, 8192, 16, 320, True), (128, 8192, 4, 760, True),
+    (768, 3072, 128, 2816, False),     # many experts, few rows: 232 us fused, 253 (at 80 rows 350 and 285 even, 294 and 361 skewed: no clear side, not tested)
+    (768, 3072, 8, 128, True), (768, 3072, 64, 2560, True), (768, 3072, 64, 6002, True), (1024, 4096, 128, 6144, True), (2048, 8192, 16, 320, True), (128, 8192, 4, 760, True),
 ])
 def test_a_launch_takes_the_two_gemms_only_where_they_were_measured_faster(d, f, E, rows, gemm):
     ctx = B.Context(cfg(d_model=d, d_ff=f, n_experts=E, top_k=1, max_tokens=rows))
