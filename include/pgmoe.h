@@ -275,8 +275,9 @@ int pgmoe_expert_ffn(pgmoe_ctx *ctx, int block, const void *x_perm, const int32_
  *   - A launch whose partial sums (with hundreds of rows per expert also the hidden activation) need
  *     more scratch than the buffer holds is refused with PGMOE_EINVAL and a
  *     text that names both sizes (decode-sized launches need a few MiB; 4096 rows over 8
- *     experts would need 82 MB: use pgmoe_expert_ffn with a workspace there).  Launches in between
- *     use the buffer for one part of their rows after the other.
+ *     experts of 768 x 3072 would need 52 MB: use pgmoe_expert_ffn with a workspace there).  A launch
+ *     in between, whose hidden activation alone does not fit, runs in several passes or through the
+ *     kernel that keeps it on the chip, and may be slower than pgmoe_expert_ffn.
  *   - All calls on one GPU, from every context, share the buffer and it keeps the last call's
  *     contents: nothing in it has to start at zero (every partial sum that is read was written
  *     by the same call), but two calls whose stream work overlaps on one GPU race.  Calls on

@@ -565,8 +565,8 @@ static int smallest_divisor_at_least(int n, int want) {
     return n;
 }
 
-// Geometry of the fused kernel for n_rows rows, from the shape of the launch alone.
-FfnPlan plan_ffn(const pgmoe_config &c, int n_rows) {
+// Geometry of the fused kernel for n_rows rows, from the shape of the launch alone.  slices: d_ff ranges the caller needs (0: the plan's choice).
+FfnPlan plan_ffn(const pgmoe_config &c, int n_rows, int slices) {
     FfnPlan p;
     const int E = c.n_experts;
     const int kt = c.d_model / 32;
@@ -578,7 +578,7 @@ FfnPlan plan_ffn(const pgmoe_config &c, int n_rows) {
     // the chip otherwise, 8 for the 64-row chunks (halves the accumulators per wavefront)
     int nw = 4;
     if (mt == 1 && active * (c.d_ff / 64) < 256 && (kt == 24 || kt == 32)) nw = 2;
-    if (mt == 4 && (kt == 24 || kt == 32) && c.d_ff % 128 == 0) nw = 8;
+    if (mt == 4 && (kt == 24 || kt == 32) && c.d_ff % (128 * std::max(1, slices)) == 0) nw = 8;
     if (mt == 4 && nw == 4 && kt > 24) mt = 2;
     if (mt == 2 && kt > 32) mt = 1;
     p.mt = mt;
@@ -596,6 +596,7 @@ FfnPlan plan_ffn(const pgmoe_config &c, int n_rows) {
         p.n_partial = 16;
         while (nsub % p.n_partial) --p.n_partial;
     }
+    if (slices) p.n_partial = slices;
     p.f_range = c.d_ff / p.n_partial;
     return p;
 }
@@ -821,11 +822,15 @@ int launch_ffn(pgmoe_ctx *ctx, const char *w_base, size_t w_stride, bool slot_by
     if (c.dtype == PGMOE_F32)
         return launch_ffn_f32(ctx, w_base, w_stride, slot_by_rank, n_slots, (const float *)x_perm, offsets, n_rows, (float *)y_perm,
                               (float *)workspace, s, table, src_row);
-    if (uses_gemm_kernels(c, n_rows))
-        return launch_ffn_gemm(ctx, w_base, w_stride, slot_by_rank, n_slots, x_perm, offsets, n_rows, y_perm, workspace,
-                               workspace == ctx->static_scratch ? PGMOE_STATIC_SCRATCH_BYTES : ffn_workspace_bytes(c), s, keep_partials,
-                               table, src_row);
-    const FfnPlan p = plan_ffn(c, n_rows);
+    int slices = 0;
+    if (uses_gemm_kernels(c, n_rows)) {
+        const size_t bytes = workspace == ctx->static_scratch ? PGMOE_STATIC_SCRATCH_BYTES : ffn_workspace_bytes(c);
+        slices = gemm_slices_for_fused(c, n_rows, bytes);
+        if (!slices)
+            return launch_ffn_gemm(ctx, w_base, w_stride, slot_by_rank, n_slots, x_perm, offsets, n_rows, y_perm, workspace, bytes, s,
+                                   keep_partials, table, src_row);
+    }
+    const FfnPlan p = plan_ffn(c, n_rows, slices);
     const int kt = c.d_model / 32;
     if (uses_decode_kernel(c, p)) {
         // a few experts with at most 16 rows each, one partial per 32-column sub-slab

@@ -109,6 +109,9 @@ bool uses_gemm_kernels(const pgmoe_config &c, int n_rows);
 size_t ffn_gemm_workspace_bytes(const pgmoe_config &c);
 // The scratch pgmoe_expert_ffn_static admits a two-GEMM launch of n_rows rows by.
 size_t ffn_gemm_launch_bytes(const pgmoe_config &c, int n_rows);
+// Launches of the two-GEMM path whose workspace does not hold every row at once: 0, or the number of d_ff ranges in which the fused
+// kernel runs them faster (with the same bits).
+int gemm_slices_for_fused(const pgmoe_config &c, int n_rows, size_t workspace_bytes);
 // The two-GEMM path of launch_ffn (same arguments; workspace_bytes: what the workspace holds).
 int launch_ffn_gemm(pgmoe_ctx *ctx, const char *w_base, size_t w_stride, bool slot_by_rank, int n_slots, const void *x_rows,
                     const int32_t *offsets, int n_rows, void *y_perm, void *workspace, size_t workspace_bytes, hipStream_t s,

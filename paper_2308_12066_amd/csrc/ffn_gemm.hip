@@ -434,9 +434,9 @@ size_t ffn_gemm_workspace_bytes(const pgmoe_config &c) {
            (size_t)(max_rows / 128 + std::min<int64_t>(c.n_experts, max_rows)) * 128 * (c.d_ff + c.d_model) * 2 + 256;
 }
 
-// What pgmoe_expert_ffn_static admits a launch of n_rows rows by: with hundreds of rows per expert an upper bound of the
-// scratch one pass uses, below that what the fused kernel needs (launch_ffn_gemm then takes as many passes
-// as the static buffer makes necessary).
+// What pgmoe_expert_ffn_static admits a launch of n_rows rows by (against PGMOE_STATIC_SCRATCH_BYTES; not what a launch uses).  A launch with
+// hundreds of rows per expert that it admits is planned to fit the buffer in one pass (gemm_plan); below that the figure is
+// what the fused kernel needs, and a launch that does not fit takes several passes or the fused kernel (gemm_slices_for_fused).
 size_t ffn_gemm_launch_bytes(const pgmoe_config &c, int n_rows) {
     const int active = std::max(1, std::min(c.n_experts, n_rows));
     if (n_rows / active < GEMM_ALWAYS) return ffn_partial_bytes(c, n_rows);
@@ -445,6 +445,27 @@ size_t ffn_gemm_launch_bytes(const pgmoe_config &c, int n_rows) {
     return (size_t)split * n_rows * c.d_model * 4 + (size_t)(active + n_rows / 128) * 128 * (c.d_ff + c.d_model) * 2;
 }
 static size_t gemm_tile_bytes(const pgmoe_config &c) { return (size_t)16 * (c.d_ff + c.d_model) * 2; }  // a row tile, hidden and packed
+
+// Microseconds of a fused launch of plan p, as fitted to measurements (see uses_gemm_kernels).
+static double fused_estimate(const pgmoe_config &c, int n_rows, const FfnPlan &p) {
+    const int active = std::max(1, std::min(c.n_experts, n_rows));
+    const double expert = 4.0 * c.d_model * c.d_ff, weights = active * expert / 5.7e6;  // bytes; us at the rate HBM delivers
+    const double chunks = std::max((double)active, 0.5 * active + n_rows / (16.0 * p.mt)), wgs = chunks * p.n_partial;
+    const bool alone = p.mt * (c.d_model / 32 + p.nw) > 80;  // KiB of LDS: one workgroup per CU, so a second round costs as much as the first
+    const double rounds = 1.0 + std::max(0.0, alone ? (wgs - 201.0) / 196.0 : wgs / 256.0 - 1.0);
+    const double again = 0.3 + 0.7 * chunks / active;  // an expert's second chunk finds part of the weights in a cache
+    // bytes per us of one workgroup's stream of weights: less the more rows it multiplies and the more workgroups there are
+    const bool wide = c.d_model >= 1024;
+    const double rate = p.mt == 1 ? 200e3 : (p.mt == 2 ? (wide ? 66e3 : 92e3) : (p.nw == 8 ? (wide ? 63e3 : 81e3) : 53e3));
+    const double decay = p.mt == 1 ? 0.31 : (p.mt == 2 ? (wide ? 0.05 : 0.16) : (p.nw == 8 ? (wide ? 0.137 : 0.164) : 0.087));
+    const double stream = rounds * expert / p.n_partial / (rate * std::pow(std::min(wgs, 256.0), -decay));
+    return 11.9 + (p.n_partial > 1 ? 4e-6 * p.n_partial * n_rows * c.d_model : 0.0) + std::max(0.91 * weights * again, stream);
+}
+// What the two GEMMs of a launch take beyond their launches and the latency of their k loops.
+static double gemm_estimate(const pgmoe_config &c, int n_rows) {
+    const int active = std::max(1, std::min(c.n_experts, n_rows));
+    return std::max(0.89 * active * 4.0 * c.d_model * c.d_ff / 5.7e6 + (double)n_rows * c.d_model * c.d_ff / 3.36e8, 1.93e-6 * n_rows * c.d_ff);
+}
 
 // Does a launch take the two GEMMs?  From GEMM_ALWAYS rows per expert on always.  Below, the fused kernel streams
 // every expert's weights once per chunk of at most 64 rows, with d_ff cut into as few ranges as keep
@@ -464,23 +485,10 @@ bool uses_gemm_kernels(const pgmoe_config &c, int n_rows) {
     if (n_rows / active < 8) return false;
     // the static buffer has to hold at least one chunk of a launch it admits
     if (ffn_partial_bytes(c, n_rows) <= PGMOE_STATIC_SCRATCH_BYTES && 2 * GEMM_RT * gemm_tile_bytes(c) > PGMOE_STATIC_SCRATCH_BYTES) return false;
-    const FfnPlan p = plan_ffn(c, n_rows);
-    const double expert = 4.0 * c.d_model * c.d_ff, weights = active * expert / 5.7e6;  // bytes; us at the rate HBM delivers
-    const double chunks = std::max((double)active, 0.5 * active + n_rows / (16.0 * p.mt)), wgs = chunks * p.n_partial;
-    const bool alone = p.mt * (c.d_model / 32 + p.nw) > 80;  // KiB of LDS: one workgroup per CU, so a second round costs as much as the first
-    const double rounds = 1.0 + std::max(0.0, alone ? (wgs - 201.0) / 196.0 : wgs / 256.0 - 1.0);
-    const double again = 0.3 + 0.7 * chunks / active;  // an expert's second chunk finds part of the weights in a cache
-    // bytes per us of one workgroup's stream of weights: less the more rows it multiplies and the more workgroups there are
-    const bool wide = c.d_model >= 1024;
-    const double rate = p.mt == 1 ? 200e3 : (p.mt == 2 ? (wide ? 66e3 : 92e3) : (p.nw == 8 ? (wide ? 63e3 : 81e3) : 53e3));
-    const double decay = p.mt == 1 ? 0.31 : (p.mt == 2 ? (wide ? 0.05 : 0.16) : (p.nw == 8 ? (wide ? 0.137 : 0.164) : 0.087));
-    const double stream = rounds * expert / p.n_partial / (rate * std::pow(std::min(wgs, 256.0), -decay));
-    const double fused = 11.9 + (p.n_partial > 1 ? 4e-6 * p.n_partial * n_rows * c.d_model : 0.0) + std::max(0.91 * weights * again, stream);
-    const double gemm = 23.5 + 0.00091 * (c.d_model + c.d_ff) +
-                        std::max(0.89 * weights + (double)n_rows * c.d_model * c.d_ff / 3.36e8, 1.93e-6 * n_rows * c.d_ff);
+    const double gemm = 23.5 + 0.00091 * (c.d_model + c.d_ff) + gemm_estimate(c, n_rows);
     // in doubt fused: a skewed routing costs the GEMMs more, with many experts above all
     const double margin = c.d_model <= 256 ? (active >= 64 ? 1.5 : 1.1) : (active >= 96 ? 1.1 : (active >= 32 ? 1.05 : 1.0));
-    return margin * gemm < fused;
+    return margin * gemm < fused_estimate(c, n_rows, plan_ffn(c, n_rows));
 }
 
 // Column width of the two products and K slices of the down-projection, from the shape of the launch alone.
@@ -509,7 +517,10 @@ static GemmPlan gemm_plan(const pgmoe_config &c, int n_rows) {
         if (c.d_model % bn == 0)
             for (int split = 1; split <= GEMM_SPLIT; split *= 2) {
                 const size_t p_bytes = split > 1 ? (size_t)split * n_rows * c.d_model * 4 : 0;
-                if (admitted && split > 1 && p_bytes + 2 * GEMM_RT * gemm_tile_bytes(c) > PGMOE_STATIC_SCRATCH_BYTES) continue;
+                // row tiles the static buffer has to hold beside them: with hundreds of rows per expert all (1280 rows over 4 experts of 1024 x 4096
+                // with two K slices 76 us, with four 69 but 108 in the static buffer's two passes), else those of a pass
+                const int hold = n_rows / active >= GEMM_ALWAYS ? active + n_rows / 16 : 2 * GEMM_RT;
+                if (admitted && split > 1 && p_bytes + hold * gemm_tile_bytes(c) > PGMOE_STATIC_SCRATCH_BYTES) continue;
                 const double down = rounds(chunks * (c.d_model / bn) * split) * (c.d_ff / 32 / split * stage + 4.0) +
                                     (split > 1 ? 2.0 * p_bytes : 2.0 * n_rows * c.d_model * 2.0) / 4.0e6;
                 if (down < best_down) {
@@ -523,30 +534,56 @@ static GemmPlan gemm_plan(const pgmoe_config &c, int n_rows) {
     return best;
 }
 
+// The scratch of a launch: float32 partials [split][n_rows, d] first (the combine reads them at the workspace's start; none with one
+// slice), then the packed hidden activation and the packed rows, by 16-row tiles (at most one partly filled tile per expert).
+// Scratch that does not hold every tile (the static buffer) is used for one range of chunks after the other: a
+// chunk's result does not depend on the others, so the number of passes changes no bit.
+struct GemmScratch {
+    int max_tiles;  // most row tiles of the launch
+    size_t room;    // row tiles the scratch holds behind the partials
+    bool one_pass;
+    int tiles;      // first tiles of a pass: its last chunk may reach past them
+};
+static GemmScratch gemm_scratch(const pgmoe_config &c, int n_rows, size_t p_bytes, size_t workspace_bytes) {
+    GemmScratch r;
+    r.max_tiles = std::max(1, std::min(c.n_experts, n_rows)) + n_rows / 16;
+    r.room = workspace_bytes > p_bytes ? (workspace_bytes - p_bytes) / gemm_tile_bytes(c) : 0;
+    r.one_pass = r.room >= (size_t)r.max_tiles;
+    r.tiles = r.one_pass ? r.max_tiles : (int)r.room - GEMM_RT;
+    return r;
+}
+
+// A pass costs its three launches and the latency of its k loops however few chunks it has, and a range of chunks seldom fills the chip, so a
+// launch of several passes can be slower than the fused kernel, which needs no scratch but the partials: it adds in the same order as
+// the GEMMs if d_ff is cut into as many ranges as they have K slices, and gives their bits.  Fitted to 75 launches of two passes or
+// more, even and skewed: 128 experts of 768 x 3072 at 128 rows each 485 us fused and 617 in passes, 32 of 512 x 8192 at 160 rows 265 and 947;
+// but 16 of 2048 x 8192 at 96 rows 1243 and 307, 24 of 1024 x 4096 at 128 rows 463 and 188.
+int gemm_slices_for_fused(const pgmoe_config &c, int n_rows, size_t workspace_bytes) {
+    const GemmPlan p = gemm_plan(c, n_rows);
+    const GemmScratch r = gemm_scratch(c, n_rows, p.p_bytes, workspace_bytes);
+    if (r.one_pass || r.tiles < 1) return 0;
+    const int passes = (r.max_tiles + r.tiles - 1) / r.tiles;
+    const double gemm = passes * (18.0 + 0.01 * (c.d_model + c.d_ff / p.split)) + gemm_estimate(c, n_rows);
+    return passes <= 6 && 1.1 * gemm < fused_estimate(c, n_rows, plan_ffn(c, n_rows, p.split)) ? 0 : p.split;
+}
+
 int launch_ffn_gemm(pgmoe_ctx *ctx, const char *w_base, size_t w_stride, bool slot_by_rank, int n_slots, const void *x_perm,
                     const int32_t *offsets, int n_rows, void *y_perm, void *workspace, size_t workspace_bytes, hipStream_t s,
                     int *keep_partials, const unsigned long long *table, const int32_t *src_row) {
     const pgmoe_config &c = ctx->cfg;
-    // float32 partials [split][n_rows, d] first (the combine reads them at the workspace's start; none with one slice),
-    // then the packed hidden activation and the packed rows, by 16-row tiles (at most one partly filled tile per expert).
-    // Scratch that does not hold every tile (the static buffer) is used for one range of chunks after the other: a
-    // chunk's result does not depend on the others, so the number of passes changes no bit.
-    const int active = std::max(1, std::min(c.n_experts, n_rows));
-    const int max_chunks = active + n_rows / GEMM_ROWS, max_tiles = active + n_rows / 16;
+    const int active = std::max(1, std::min(c.n_experts, n_rows)), max_chunks = active + n_rows / GEMM_ROWS;
     const GemmPlan p = gemm_plan(c, n_rows);
-    const size_t room = workspace_bytes > p.p_bytes ? (workspace_bytes - p.p_bytes) / gemm_tile_bytes(c) : 0;
-    if (room < (size_t)std::min(max_tiles, 2 * GEMM_RT))
+    const GemmScratch r = gemm_scratch(c, n_rows, p.p_bytes, workspace_bytes);
+    if (!r.one_pass && r.tiles < GEMM_RT)
         return fail(ctx, PGMOE_EINVAL, "pgmoe_expert_ffn: hidden activation, packed rows and partial sums of %d rows do not fit the workspace", n_rows);
-    const bool one_pass = room >= (size_t)max_tiles;
-    const int tiles = one_pass ? max_tiles : (int)room - GEMM_RT;  // first tiles of a pass: its last chunk may reach past them
-    const size_t h_bytes = (one_pass ? (size_t)max_tiles : room) * 16 * c.d_ff * 2;
+    const size_t h_bytes = (r.one_pass ? (size_t)r.max_tiles : r.room) * 16 * c.d_ff * 2;
     float *partial = p.split > 1 ? (float *)workspace : nullptr;
     char *h = (char *)workspace + p.p_bytes;
     char *xp = h + h_bytes;
     const int tslot = ffn_timing_slot(ctx);
     if (tslot >= 0) PG_HIP(ctx, hipEventRecord(ctx->tim_begin[tslot], s));
-    for (int lo = 0; lo < max_tiles; lo += tiles) {
-        const int hi = one_pass ? INT_MAX : lo + tiles;  // INT_MAX: every chunk
+    for (int lo = 0; lo < r.max_tiles; lo += r.tiles) {
+        const int hi = r.one_pass ? INT_MAX : lo + r.tiles;  // INT_MAX: every chunk
         hipLaunchKernelGGL(ffn_gemm_pack_rows_kernel, dim3(max_chunks, c.d_model / 32 / PACK_KT), dim3(512), 0, s, (const __bf16 *)x_perm,
                            offsets, c.n_experts, c.d_model, src_row, (__bf16 *)xp, lo, hi);
         PG_HIP(ctx, hipGetLastError());

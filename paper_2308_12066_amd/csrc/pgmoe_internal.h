@@ -149,7 +149,7 @@ struct FfnPlan {
     int n_partial;   // d_ff / f_range
     int max_chunks;  // upper bound of sum_e ceil(n_e / (16*mt))
 };
-FfnPlan plan_ffn(const pgmoe_config &cfg, int n_rows);
+FfnPlan plan_ffn(const pgmoe_config &cfg, int n_rows, int slices = 0);
 size_t ffn_workspace_bytes(const pgmoe_config &cfg);
 size_t ffn_launch_workspace_bytes(const pgmoe_config &cfg, int n_rows);  // by what pgmoe_expert_ffn_static admits a launch of n_rows rows
 // Device address of the library's static scratch buffer on the context's device (which must be

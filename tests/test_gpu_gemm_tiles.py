@@ -6,6 +6,7 @@ import pytest
 import torch
 
 import workloads as W
+from launch_count import kernel_launches
 from test_gpu_parity import TOL, hx, nerr, run_ffn_case  # noqa: F401  (hx is a fixture)
 
 pytestmark = pytest.mark.gpu
@@ -56,4 +57,38 @@ def test_static_scratch_takes_several_passes_and_gives_the_same_bits(hx, counts)
     torch.cuda.synchronize()
     assert torch.equal(ys[0].view(torch.int16), ys[1].view(torch.int16))
     assert float(ys[0].float().abs().max()) not in (0.0, 7.0)
+    ctx.close()
+
+
+@pytest.mark.parametrize("d,f,E,rows,launches", [
+    (2048, 1024, 40, 150, 6), (1024, 2304, 16, 150, 7),         # two passes of three launches (and a reduction of two K slices)
+    (512, 1792, 24, 190, 2), (768, 1280, 64, 150, 1),           # the fused kernel, in as many d_ff ranges as the GEMMs have K slices
+    (768, 4352, 10, 190, 2), (1024, 2816, 8, 190, 2),           # four ranges that are no multiple of the eight-wavefront kernel's sub-slab
+    (1024, 2048, 16, 190, 2), (128, 8192, 16, 120, 2),
+    (768, 1536, 8, 150, 4), (768, 3072, 64, 40, 3),             # everything at once, with two K slices and with one
+])
+def test_static_scratch_takes_the_faster_way_and_gives_the_workspace_bits(hx, d, f, E, rows, launches):  # noqa: F811
+    H, B = hx
+    g = np.random.default_rng(d + f + E)
+    counts = np.bincount(g.integers(0, E, size=E * rows), minlength=E)
+    counts[0], counts[-1] = counts[0] + counts[-1], 0
+    n = int(counts.sum())
+    gen = torch.Generator(device="cuda").manual_seed(d + f)
+    blobs = torch.empty((1, E, 2 * d * f), dtype=torch.bfloat16, device="cuda").normal_(0.0, 0.02, generator=gen)
+    x = torch.empty((n, d), dtype=torch.bfloat16, device="cuda").normal_(generator=gen)
+    offs = torch.from_numpy(np.concatenate([[0], np.cumsum(counts)]).astype(np.int32)).cuda()
+    ctx = B.Context(B.make_config(d, f, E, 1, 1, n, B.BF16))
+    ctx.register_resident_experts(blobs, 4 * d * f, 4 * d * f * E)
+    assert "gemm" in ctx.ffn_kernel_name(n)
+    print(f"static route: d={d} f={f} E={E} rows={n}", flush=True)
+    ys = [torch.full((n, d), 7.0, dtype=torch.bfloat16, device="cuda") for _ in range(2)]
+    ws = torch.full((ctx.workspace_bytes,), 0x5A, dtype=torch.uint8, device="cuda")
+    stream = torch.cuda.Stream()
+    torch.cuda.synchronize()
+    ctx.expert_ffn(0, x, offs, n, ys[0], ws, stream)
+    ctx.expert_ffn_static(0, x, offs, n, ys[1], stream)
+    torch.cuda.synchronize()
+    assert torch.equal(ys[0].view(torch.int16), ys[1].view(torch.int16))
+    assert 0.0 < float(ys[0].float().abs().max()) < 7.0
+    assert kernel_launches(lambda: ctx.expert_ffn_static(0, x, offs, n, ys[1], stream), stream) == launches
     ctx.close()
