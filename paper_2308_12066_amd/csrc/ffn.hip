@@ -630,7 +630,8 @@ static bool uses_decode_kernel(const pgmoe_config &c, const FfnPlan &p) {
 }
 
 const char *ffn_kernel_name(const pgmoe_config &c, int n_rows) {
-    if (c.dtype == PGMOE_F32) return "ffn_f32_hidden_kernel+ffn_f32_out_kernel";
+    if (c.dtype == PGMOE_F32)
+        return ffn_f32_reads_rows_in_place(c) ? "ffn_f32_hidden_kernel+ffn_f32_out_kernel" : "ffn_f32_hidden_scalar_kernel+ffn_f32_out_scalar_kernel";
     if (uses_gemm_kernels(c, n_rows)) return "ffn_gemm_pack_rows_kernel+ffn_gemm_tile_kernel";
     const FfnPlan p = plan_ffn(c, n_rows);
     if (uses_decode_kernel(c, p)) return "ffn_decode_kernel";

@@ -304,3 +304,12 @@ def test_a_launch_takes_the_two_gemms_only_where_they_were_measured_faster(d, f,
     ctx = B.Context(cfg(d_model=d, d_ff=f, n_experts=E, top_k=1, max_tokens=rows))
     assert ("gemm" in ctx.ffn_kernel_name(rows)) == gemm
     ctx.close()
+
+
+@pytest.mark.parametrize("d,f,scalar", [(64, 256, False), (4, 4, False), (30, 36, True), (32, 37, True), (33, 35, True)])
+def test_ffn_kernel_name_tells_the_float32_kernels_apart(d, f, scalar):
+    """d_model and d_ff that are multiples of four run on the matrix instruction, others on the scalar kernels."""
+    ctx = B.Context(cfg(d_model=d, d_ff=f, dtype=B.F32))
+    suffix = "_scalar" if scalar else ""
+    assert ctx.ffn_kernel_name(8) == f"ffn_f32_hidden{suffix}_kernel+ffn_f32_out{suffix}_kernel"
+    ctx.close()
