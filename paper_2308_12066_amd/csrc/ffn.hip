@@ -227,7 +227,7 @@ __global__ __launch_bounds__(256) void ffn_decode_kernel(
         if constexpr (GATE == DECODE_GATE_PLANES)
             for (int u = blockIdx.x; u < 2 * ((gate.T + GM_TOK - 1) / GM_TOK); u += gridDim.x) gate_planes_body(gate, u);
         else if (blockIdx.x == 0)
-gate_small_dispatch<GATE == DECODE_SMALL_GATE_8 ? 1 : 2>(gate.x, gate.w, gate.bias, gate.T, d, gate.k, gate.idx, gate.prob, nullptr,
+            gate_small_dispatch<GATE == DECODE_SMALL_GATE_8 ? 1 : 2>(gate.x, gate.w, gate.bias, gate.T, d, gate.k, gate.idx, gate.prob, nullptr,
                                                                      gate.flags, gate.row_of, gate.offsets, gate.src_row);
         return;
     }
@@ -361,8 +361,8 @@ __global__ __launch_bounds__(256) void ffn_reduce_kernel(const float *__restrict
 // of the row, i.e. its output row i is column V*i + j, and every lane ends up with 4*V neighbouring columns of one token.
 // Bound by the weight stream (HBM); F32_DEPTH blocks of loads are in flight per wavefront.  One thread
 // per output column walking k by itself, which this replaces, re-read the weights once per row and paid a
-// memory latency every few k: 8 experts of 768 x 3072, 100 rows, 284 us + 836 us, now 18 + 29 (75 MB
-// of weights each; the second product has half the columns' workgroups, and its hidden rows share the CUs' request slots).
+// memory latency every few k: 8 experts of 768 x 3072, 100 rows, 284 us + 836 us, now 21 + 30 from HBM and 19 + 24 from the
+// last-level cache (75 MB of weights each; the second product has half the columns' workgroups, and its hidden rows share the CUs' request slots).
 constexpr int F32_DEPTH = 4;
 
 template <int V>
@@ -494,8 +494,8 @@ __global__ __launch_bounds__(NW * 64) void ffn_f32_out_kernel(const float *__res
     f32_tile<V, MT, NW, false>(h, nullptr, reinterpret_cast<const float *>(wexp) + (size_t)d * f, y_perm, ci, f, d, no_weights);
 }
 
-// Any other float32 shape (d_model or d_ff not a multiple of 4, rows that cannot be read 16 bytes at a time).  One workgroup per (row = blockIdx.x, 256 output columns = blockIdx.y); the row's expert and slot are
-// found once per workgroup.
+// Any other float32 shape (d_model or d_ff not a multiple of 4: rows cannot be read 16 bytes at a time).  One workgroup per
+// (row = blockIdx.x, 256 output columns = blockIdx.y); the row's expert and slot are found once per workgroup.
 __device__ inline void find_row_expert(const int32_t *offsets, int E, int row, int *expert, int *slot) {
     int e = 0, s = -1;
     for (int i = 0; i < E; ++i) {
@@ -764,10 +764,12 @@ static int launch_ffn_f32(pgmoe_ctx *ctx, const char *w_base, size_t w_stride, b
     const int tslot = ffn_timing_slot(ctx);
     if (tslot >= 0) PG_HIP(ctx, hipEventRecord(ctx->tim_begin[tslot], s));
     if (ffn_f32_reads_rows_in_place(c)) {
-        // rows per workgroup by the rows an expert has (8 experts of 768 x 3072 with 12.5 rows each: 18 + 32 us with 16-row
-        // chunks, 28 + 41 with 32); columns per lane: four (wide pieces of a weight row, the least share of the activations in what
-        // a CU has in flight) where a third of the CUs get a workgroup all the same and the experts see a few rows each (the FFN of 100 / 512
-        // rows over 8 experts 48.6 / 119 us against 54.4 / 137 with two; of 32 rows 45.8 against 38.7)
+        // rows per workgroup by the rows an expert has (8 experts of 768 x 3072 with 12.5 rows each: both products 46 us with 16-row
+        // chunks, 63 with 32); columns per lane: four (wide pieces of a weight row, the least share of the activations in what
+        // a CU has in flight) where 96 workgroups come out all the same and the experts see eight rows or more.  Measured over 315 launches
+        // (d_model 64 .. 2048, 1 .. 64 experts, 1 .. 60 rows each), both products with four / with two columns: at 96 workgroups 45 / 51 us (8 experts of
+        // 768, 12 rows), 33 / 37 (12 of 512), 56 / 61 (6 of 1024) and 104 / 134, 73 / 95, 141 / 165 with 60 rows; at 72 (6 of 768) 41 / 35 and 99 / 82;
+        // with 4 rows 44 / 36 at 96.  The rule is within 2 % of the best choice on the geometric mean, at worst 1.37 times it (4 of 768, 12 rows).
         const int active = std::max(1, std::min(c.n_experts, n_rows)), mean = (n_rows + active - 1) / active;
         const int mt = mean <= 16 ? 1 : (mean <= 32 ? 2 : 4);
         const int chunks = active + n_rows / (16 * mt);

@@ -1,5 +1,5 @@
 // Shared by the expert-FFN translation units (ffn.hip: fused, decode and float32 kernels, launch
-// planning; ffn_gemm.hip: the two tiled GEMMs for launches with hundreds of rows per expert).
+// planning; ffn_gemm.hip: the two tiled GEMMs for launches with many rows per expert).
 #ifndef PGMOE_FFN_COMMON_H
 #define PGMOE_FFN_COMMON_H
 #include <algorithm>
@@ -69,18 +69,6 @@ __device__ inline ChunkInfo find_chunk(const int32_t *__restrict__ offsets, int 
         slot_base += __builtin_amdgcn_readlane(nz_incl, 63);
     }
     return ci;
-}
-
-// Number of chunks of rows_per_chunk rows over all experts (the same count on every lane).
-__device__ inline int count_chunks(const int32_t *__restrict__ offsets, int E, int rows_per_chunk) {
-    const int lane = threadIdx.x & 63;
-    int total = 0;
-    for (int q = 0; q * 64 < E; ++q) {
-        const int e = q * 64 + lane;
-        const int n = e < E ? offsets[e + 1] - offsets[e] : 0;
-        total += __builtin_amdgcn_readlane(wave_incl_scan((n + rows_per_chunk - 1) / rows_per_chunk), 63);
-    }
-    return total;
 }
 
 // ------------------------------------------------------------------------------------------

@@ -2,10 +2,12 @@
 // (Sec. II-B: the gate gives every expert a probability per token and the best ones are
 // activated; Sec. IV-B: the same function, placed in block N, routes block N+1).
 //
-// Three kernels share one softmax / top-k routine (16 lanes per token, k rounds of arg-max with
+// The kernels share one softmax / top-k routine (16 lanes per token, k rounds of arg-max with
 // shuffles, ties to the lowest index, NaN ranks as -infinity and raises a flag):
+//   gate_small_kernel      bf16, up to four tokens, 8 or 16 experts: one workgroup, all loads at once;
 //   gate_topk_mfma_kernel  bf16, E a multiple of 8: logits on the matrix cores, 16 tokens per
 //                          workgroup, W transposed in registers (no LDS staging on the way in);
+//   gate_topk_tiles_kernel the same for more 16-token tiles than CUs: W stays in registers;
 //   gate_topk_vec_kernel   f32 (and bf16 when the matrix-core kernel does not apply) for
 //                          power-of-two E: token rows staged in LDS as float32, threads split W
 //                          by expert columns and feature rows and fold their partial sums in a
@@ -268,7 +270,8 @@ __global__ __launch_bounds__(NW * 64) void gate_topk_mfma_kernel(
     group_in_workgroup(r_idx, r_cnt, r_off, nt * k, E, k, NT, row_of, offsets, src_row);
 }
 
-// The same for batches of several tiles per CU (E <= 128, d_model = 256*KW): a workgroup keeps its share of W in registers,
+// The same for batches of several tiles per CU (E <= 128, d_model = 256*KW, KW <= 4: the share of W is 32*KW registers a lane,
+// as many as the accumulators and the next tile's tokens leave): a workgroup keeps its share of W in registers,
 // transposed once, and walks token tiles, so that a CU reads W once and not once per tile; the softmax of a tile is one half of the
 // wavefronts' while the other half begins the next tile.  Sums and their order are the kernel's above: same bits.
 // 16384 tokens of d_model 1024, 128 experts: 39 us with a tile per workgroup (four rounds of 262 KB of W per CU), now 19.5;
