@@ -26,7 +26,8 @@ namespace pgmoe {
 //    weights runs at half of what it reaches alone (10 against 16 us for 38 MB beside / without the rows' tiles).
 //    Hence as many rows per weight tile as the registers hold (320: 160 accumulator registers of 246), no second
 //    chunk for an expert that has a few rows more than a power of two, and no request for a row tile the chunk lacks;
-//  * 8 experts of 768 x 3072, 4096 rows: 31 us up, 36 down (33 and 35 before; the vendor GEMM library: 27 + 41). The matrix cores
+//  * 8 experts of 768 x 3072, 4096 rows: 31 us up, 36 down with the weights from HBM, 29 and 34 from the last-level cache (33 and 35
+//    before; the vendor GEMM library: 27 + 41). The matrix cores
 //    alone take 21 of the first and the load stream alone 21; random operands hold them to about 1.6 PFLOP/s.  512 rows per
 //    expert are two chunks each, 192 workgroups; chunks of at most 256 rows (75 -> 79 us a block) and 192-column blocks
 //    (73 -> 74) were no better;
