@@ -453,19 +453,26 @@ static double fused_estimate(const pgmoe_config &c, int n_rows, const FfnPlan &p
     const double expert = 4.0 * c.d_model * c.d_ff, weights = active * expert / 5.7e6;  // bytes; us at the rate HBM delivers
     const double chunks = std::max((double)active, 0.5 * active + n_rows / (16.0 * p.mt)), wgs = chunks * p.n_partial;
     const bool alone = p.mt * (c.d_model / 32 + p.nw) > 80;  // KiB of LDS: one workgroup per CU, so a second round costs as much as the first
-    const double rounds = 1.0 + std::max(0.0, alone ? (wgs - 201.0) / 196.0 : wgs / 256.0 - 1.0);
+    const double rounds = 1.0 + (alone ? std::min(1.0, std::max(0.0, (wgs - 243.0) / 77.0)) + std::max(0.0, (wgs - 320.0) / 900.0) : std::max(0.0, wgs / 256.0 - 1.0));
     const double again = 0.3 + 0.7 * chunks / active;  // an expert's second chunk finds part of the weights in a cache
-    // bytes per us of one workgroup's stream of weights: less the more rows it multiplies and the more workgroups there are
-    const bool wide = c.d_model >= 1024;
-    const double rate = p.mt == 1 ? 200e3 : (p.mt == 2 ? (wide ? 66e3 : 92e3) : (p.nw == 8 ? (wide ? 63e3 : 81e3) : 53e3));
-    const double decay = p.mt == 1 ? 0.31 : (p.mt == 2 ? (wide ? 0.05 : 0.16) : (p.nw == 8 ? (wide ? 0.137 : 0.164) : 0.087));
+    // one workgroup's stream of weights, bytes per us: less the more rows it multiplies, and the more workgroups there are (decay)
+    double rate, decay;
+    if (p.mt == 1) rate = 188e3, decay = 0.29;
+    else if (p.mt == 2) {
+        if (c.d_model >= 1024) rate = 71e3, decay = 0.065;
+        else if (c.d_model >= 768) rate = 114e3, decay = 0.248;
+        else rate = 88e3, decay = 0.123;
+    } else if (p.nw == 8) {
+        if (c.d_model >= 1024) rate = 62e3, decay = 0.132;
+        else rate = 80e3, decay = 0.158;
+    } else rate = 55e3, decay = 0.09;
     const double stream = rounds * expert / p.n_partial / (rate * std::pow(std::min(wgs, 256.0), -decay));
-    return 11.9 + (p.n_partial > 1 ? 4e-6 * p.n_partial * n_rows * c.d_model : 0.0) + std::max(0.91 * weights * again, stream);
+    return 12.5 + (p.n_partial > 1 ? 4.2e-6 * p.n_partial * n_rows * c.d_model : 0.0) + std::max(0.90 * weights * again, stream);
 }
 // What the two GEMMs of a launch take beyond their launches and the latency of their k loops.
 static double gemm_estimate(const pgmoe_config &c, int n_rows) {
     const int active = std::max(1, std::min(c.n_experts, n_rows));
-    return std::max(0.89 * active * 4.0 * c.d_model * c.d_ff / 5.7e6 + (double)n_rows * c.d_model * c.d_ff / 3.36e8, 1.93e-6 * n_rows * c.d_ff);
+    return std::max(0.90 * active * 4.0 * c.d_model * c.d_ff / 5.7e6 + (double)n_rows * c.d_model * c.d_ff / 3.49e8, 1.94e-6 * n_rows * c.d_ff);
 }
 
 // Does a launch take the two GEMMs?  From GEMM_ALWAYS rows per expert on always.  Below, the fused kernel streams
@@ -486,7 +493,7 @@ bool uses_gemm_kernels(const pgmoe_config &c, int n_rows) {
     if (n_rows / active < 8) return false;
     // the static buffer has to hold at least one chunk of a launch it admits
     if (ffn_partial_bytes(c, n_rows) <= PGMOE_STATIC_SCRATCH_BYTES && 2 * GEMM_RT * gemm_tile_bytes(c) > PGMOE_STATIC_SCRATCH_BYTES) return false;
-    const double gemm = 23.5 + 0.00091 * (c.d_model + c.d_ff) + gemm_estimate(c, n_rows);
+    const double gemm = 23.5 + 0.00087 * (c.d_model + c.d_ff) + gemm_estimate(c, n_rows);
     // in doubt fused: a skewed routing costs the GEMMs more, with many experts above all
     const double margin = c.d_model <= 256 ? (active >= 64 ? 1.5 : 1.1) : (active >= 96 ? 1.1 : (active >= 32 ? 1.05 : 1.0));
     return margin * gemm < fused_estimate(c, n_rows, plan_ffn(c, n_rows));
