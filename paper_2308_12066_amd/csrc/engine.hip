@@ -415,7 +415,8 @@ int pgmoe_slot_address(pgmoe_ctx *ctx, int block, int slot, void **dev_out) {
 static int expert_ffn_impl(pgmoe_ctx *ctx, int block, const void *x_perm, const int32_t *expert_offsets, int n_rows,
                            void *y_perm, void *workspace, void *stream, int *keep_partials,
                            const int32_t *src_row = nullptr,  // src_row: x_perm holds the un-grouped rows (see launch_ffn)
-                           const FusedGate *gate = nullptr, GateCarried *gate_done = nullptr) {  // resident store only (see launch_ffn)
+                           const FusedGate *gate = nullptr, GateCarried *gate_done = nullptr,  // resident store only (see launch_ffn)
+                           const RowCombine *combine = nullptr) {
     const char *fn = "pgmoe_expert_ffn";
     if (!ctx) return fail(nullptr, PGMOE_EINVAL, "%s: ctx is NULL", fn);
     int rc = check_block(ctx, fn, block);
@@ -431,7 +432,7 @@ static int expert_ffn_impl(pgmoe_ctx *ctx, int block, const void *x_perm, const 
     if (ctx->store_mode == STORE_RESIDENT)
         return launch_ffn(ctx, ctx->store_base + (size_t)block * ctx->block_stride, ctx->expert_stride, false,
                           ctx->cfg.n_experts, x_perm, expert_offsets, n_rows, y_perm, workspace, s, keep_partials, nullptr,
-                          src_row, gate, gate_done);
+                          src_row, gate, gate_done, combine);
     const int gen = block % ctx->n_gen;
     if (ctx->fetched_block[gen] != block)
         return fail(ctx, PGMOE_ESTATE, "%s: block %d was not fetched (generation holds block %d)", fn, block, ctx->fetched_block[gen]);
@@ -441,7 +442,7 @@ static int expert_ffn_impl(pgmoe_ctx *ctx, int block, const void *x_perm, const 
     // a generation filled by pgmoe_fetch_all_experts is indexed by expert id, else by rank
     rc = launch_ffn(ctx, ctx->slot_pool + (size_t)gen * ctx->slots * ctx->expert_bytes, ctx->expert_bytes, !ctx->gen_all[gen],
                     ctx->slots, x_perm, expert_offsets, n_rows, y_perm, workspace, s, keep_partials,
-                    ctx->gen_table[gen] ? ctx->dev_table + (size_t)block * PGMOE_MAX_EXPERTS : nullptr, src_row);
+                    ctx->gen_table[gen] ? ctx->dev_table + (size_t)block * PGMOE_MAX_EXPERTS : nullptr, src_row, nullptr, nullptr, combine);
     if (rc) return rc;
     ctx->ffn_recorded[gen] = true;
     ctx->ffn_stream[gen] = s;
@@ -550,6 +551,25 @@ int pgmoe_check_streams(pgmoe_ctx *ctx, void *compute_stream, void *copy_stream,
     return PGMOE_OK;
 }
 
+// The gates of n (one or two) blocks from block g on, all on hidden state x, whose launch groups the blocks' tokens as well.
+static int gates_for_blocks(pgmoe_ctx *ctx, const pgmoe_step_buffers *io, int g, int n, const void *x, int T, void *stream) {
+    const pgmoe_config &c = ctx->cfg;
+    const size_t nk = (size_t)T * c.top_k;
+    FusedGate fg[2];
+    int blocks[2];
+    for (int i = 0; i < n; ++i) {
+        const int b = blocks[i] = g + i;
+        const float *bias = io->gate_b ? io->gate_b[b] : nullptr;
+        if (!aligned(x, 16) || !aligned(io->gate_w[b], 16) || !aligned(bias, 4))
+            return fail(ctx, PGMOE_EINVAL, "pgmoe_stack_step: misaligned hidden state, gate weight or bias of block %d", b);
+        fg[i] = FusedGate{x, io->gate_w[b], bias, T, io->topk_idx + (size_t)b * nk, io->topk_prob + (size_t)b * nk, io->row_of + (size_t)b * nk,
+                          io->expert_offsets + (size_t)b * (c.n_experts + 1), ctx->dev_src_row + (size_t)b * c.max_tokens * c.top_k};
+    }
+    const int rc = launch_gates_grouped(ctx, x, T, fg, n, blocks, (hipStream_t)stream);
+    for (int i = 0; i < n && rc == PGMOE_OK; ++i) ctx->routed[blocks[i]] = true;
+    return rc;
+}
+
 // The gate that routes block g, evaluated on hidden state x, inside pgmoe_stack_step.  For a
 // decode-sized bf16 batch the gate kernel also groups block g's tokens by expert (offsets, row_of,
 // inverse map) and routed[g] says so; pgmoe_stack_step has validated the buffers.
@@ -562,6 +582,7 @@ static int gate_for_block(pgmoe_ctx *ctx, const pgmoe_step_buffers *io, int g, c
     const float *bias = io->gate_b ? io->gate_b[g] : nullptr;
     if (!aligned(x, 16) || !aligned(io->gate_w[g], 16) || !aligned(bias, 4))
         return fail(ctx, PGMOE_EINVAL, "pgmoe_stack_step: misaligned hidden state, gate weight or bias of block %d", g);
+    if (gate_groups_tokens(c, T)) return gates_for_blocks(ctx, io, g, 1, x, T, stream);
     int32_t *row_of = io->row_of + (size_t)g * nk, *offs = io->expert_offsets + (size_t)g * (c.n_experts + 1);
     int32_t *src_row = ctx->dev_src_row + (size_t)g * c.max_tokens * c.top_k;
     int rc = launch_gate(ctx, x, io->gate_w[g], bias, T, io->topk_idx + (size_t)g * nk, io->topk_prob + (size_t)g * nk, nullptr,
@@ -578,7 +599,7 @@ static int gate_for_block(pgmoe_ctx *ctx, const pgmoe_step_buffers *io, int g, c
 // are skipped (same values, hence the same results as pgmoe_permute + pgmoe_expert_ffn).
 static int group_and_run_experts(pgmoe_ctx *ctx, const pgmoe_step_buffers *io, int block, int T, const void *x,
                                  const int32_t *idx, int32_t *row_of, int32_t *offs, void *stream, int *n_partial,
-                                 const FusedGate *gate = nullptr, GateCarried *gate_done = nullptr) {
+                                 const FusedGate *gate = nullptr, GateCarried *gate_done = nullptr, const RowCombine *combine = nullptr) {
     const int nk = T * ctx->cfg.top_k;
     if (gate_done) *gate_done = GATE_LEFT;
     if (ctx->cfg.dtype != PGMOE_BF16 && !ffn_f32_reads_rows_in_place(ctx->cfg)) {
@@ -591,8 +612,12 @@ static int group_and_run_experts(pgmoe_ctx *ctx, const pgmoe_step_buffers *io, i
         int rc = launch_route(ctx, idx, T, row_of, offs, src_row, (hipStream_t)stream);
         if (rc) return rc;
     }
-    return expert_ffn_impl(ctx, block, x, offs, nk, io->y_perm, io->workspace, stream, n_partial, src_row, gate, gate_done);
+    return expert_ffn_impl(ctx, block, x, offs, nk, io->y_perm, io->workspace, stream, n_partial, src_row, gate, gate_done, combine);
 }
+
+// One expert per token, float32: the second expert kernel has a token's whole result and writes the block's output and the next
+// hidden state itself (see launch_ffn).
+static bool rows_are_combined(const pgmoe_config &c) { return c.top_k == 1 && ffn_f32_reads_rows_in_place(c); }
 
 int pgmoe_stack_step(pgmoe_ctx *ctx, const pgmoe_step_buffers *io, int T, void *compute_stream, void *copy_stream) {
     const char *fn = "pgmoe_stack_step";
@@ -659,10 +684,14 @@ int pgmoe_stack_step(pgmoe_ctx *ctx, const pgmoe_step_buffers *io, int T, void *
             int32_t *row_of = io->row_of + (size_t)i * nk;
             int32_t *offs = io->expert_offsets + (size_t)i * (c.n_experts + 1);
             int n_partial = 0;
-            rc = group_and_run_experts(ctx, io, i, T, x_at(i), idx_at(i), row_of, offs, compute_stream, &n_partial);
-            if (rc) return rc;
             void *y = io->y_blocks ? (char *)io->y_blocks + (size_t)i * xbytes : nullptr;
-            if (n_partial > 0)
+            const RowCombine combine = {prob_at(i), (float *)y, (const float *)x_at(i), (float *)x_at(i + 1)};
+            const bool combined = rows_are_combined(c);
+            rc = group_and_run_experts(ctx, io, i, T, x_at(i), idx_at(i), row_of, offs, compute_stream, &n_partial, nullptr, nullptr,
+                                       combined ? &combine : nullptr);
+            if (rc) return rc;
+            if (combined) rc = PGMOE_OK;
+            else if (n_partial > 0)
                 rc = launch_combine_partials(ctx, (const float *)io->workspace, n_partial, (int)nk, row_of, prob_at(i), T, y,
                                              x_at(i), x_at(i + 1), (hipStream_t)compute_stream);
             else
@@ -723,6 +752,10 @@ int pgmoe_stack_step(pgmoe_ctx *ctx, const pgmoe_step_buffers *io, int T, void *
             rc = pgmoe_fetch_experts(ctx, g, idx_at(g), T, compute_stream, copy_stream, nullptr);
             if (rc) return rc;
         }
+    } else if (ctx->store_mode == STORE_RESIDENT && head == 1 && gate_groups_tokens(c, T)) {
+        // block 0's own gate and the pre-gate of block 1 read the same tokens: one launch
+        rc = gates_for_blocks(ctx, io, 0, 2, x_at(0), T, compute_stream);
+        if (rc) return rc;
     } else {
         for (int g = 0; g <= (carry_gate ? 0 : head); ++g) {
             rc = gate_for_block(ctx, io, g, x_at(0), T, compute_stream);
@@ -747,6 +780,9 @@ int pgmoe_stack_step(pgmoe_ctx *ctx, const pgmoe_step_buffers *io, int T, void *
         // grouping + FFN, then the weighted combine; when the FFN left float32 partial sums, the
         // combine kernel adds them itself (same order as the stand-alone reduction) and y_perm is skipped
         int n_partial = 0;
+        void *y = io->y_blocks ? (char *)io->y_blocks + (size_t)i * xbytes : nullptr;
+        const RowCombine combine = {prob_at(i), (float *)y, (const float *)x_at(i), (float *)x_at(i + 1)};
+        const bool combined = rows_are_combined(c);
         const int g = i + N;
         FusedGate fg = {};
         GateCarried carried = GATE_LEFT;
@@ -762,11 +798,12 @@ int pgmoe_stack_step(pgmoe_ctx *ctx, const pgmoe_step_buffers *io, int T, void *
             if (carried == GATE_LEFT) rc = gate_for_block(ctx, io, g, x_at(i), T, compute_stream);
             else ctx->routed[g] = carried == GATE_ROUTED || gate_mfma_routes(c, T);
         } else {
-            rc = group_and_run_experts(ctx, io, i, T, x_at(i), idx_at(i), row_of, offs, compute_stream, &n_partial);
+            rc = group_and_run_experts(ctx, io, i, T, x_at(i), idx_at(i), row_of, offs, compute_stream, &n_partial, nullptr, nullptr,
+                                       combined ? &combine : nullptr);
         }
         if (rc) return rc;
-        void *y = io->y_blocks ? (char *)io->y_blocks + (size_t)i * xbytes : nullptr;
-        if (n_partial > 0)
+        if (combined) rc = PGMOE_OK;
+        else if (n_partial > 0)
             rc = launch_combine_partials(ctx, (const float *)io->workspace, n_partial, (int)nk, row_of, prob_at(i), T, y,
                                          x_at(i), x_at(i + 1), (hipStream_t)compute_stream, carried == GATE_STARTED ? &fg : nullptr);
         else

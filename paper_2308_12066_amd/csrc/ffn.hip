@@ -379,11 +379,16 @@ __device__ inline float f32_comp(const typename F32Vec<V>::type &v, int j) {
     else return v[j];
 }
 
+__device__ inline const RowCombine &the_combine(const RowCombine &combine) { return combine; }
+
 // out[rows, n0 .. n0 + 16*V) = (RELU) a[rows, K] . w[K, N] for the rows of one chunk; a_row0: row of a that is the chunk's
 // first (through src_row if given).  K % 4 == 0, N % V == 0.
-template <int V, int MT, int NW, bool RELU>
+// Combine: nothing, or RowCombine: grouped row r is the one row of token tokens[r], whose weighted result and residual sum are written instead of out
+// (the arithmetic of combine_rows_kernel with one expert per token).
+template <int V, int MT, int NW, bool RELU, typename... Combine>
 __device__ inline void f32_tile(const float *__restrict__ a, const int32_t *__restrict__ src_row, const float *__restrict__ w,
-                                float *__restrict__ out, const ChunkInfo &ci, int K, int N, bool no_weights) {
+                                float *__restrict__ out, const ChunkInfo &ci, int K, int N, bool no_weights,
+                                const int32_t *__restrict__ tokens = nullptr, Combine... combine) {
     typedef typename F32Vec<V>::type vec;
     typedef __attribute__((address_space(1))) vec gvec;
     __shared__ floatx4 sums[NW][V * MT][64];
@@ -447,9 +452,22 @@ __device__ inline void f32_tile(const float *__restrict__ a, const int32_t *__re
     for (int j = 0; j < V; ++j)
 #pragma unroll
         for (int m = 0; m < MT; ++m) sums[wave][j * MT + m][lane] = acc[j][m];
-    __syncthreads();
     // thread -> (row tile, lane, r): V neighbouring columns of one row
-    for (int o = threadIdx.x; o < MT * 256; o += NW * 64) {
+    vec res[(MT * 256 + NW * 64 - 1) / (NW * 64)];
+    float p[(MT * 256 + NW * 64 - 1) / (NW * 64)];
+    if constexpr (sizeof...(Combine) > 0) {  // on their way while the sums meet
+        const RowCombine &rc = the_combine(combine...);
+#pragma unroll
+        for (int o = threadIdx.x, i = 0; o < MT * 256; o += NW * 64, ++i) {
+            const int l = (o >> 2) & 63, m = o >> 8, row = m * 16 + (l & 15), c = n0 + V * (4 * (l >> 4) + (o & 3));
+            const int t = tokens[ci.row0 + (row < ci.nrows ? row : 0)];
+            p[i] = rc.prob[t];
+            res[i] = *reinterpret_cast<const vec *>(rc.x_res + (size_t)t * N + (c < N ? c : 0));
+        }
+    }
+    __syncthreads();
+#pragma unroll
+    for (int o = threadIdx.x, i = 0; o < MT * 256; o += NW * 64, ++i) {
         const int r = o & 3, l = (o >> 2) & 63, m = o >> 8;
         const int row = m * 16 + (l & 15), c = n0 + V * (4 * (l >> 4) + r);
         if (row >= ci.nrows || c >= N) continue;
@@ -463,7 +481,25 @@ __device__ inline void f32_tile(const float *__restrict__ a, const int32_t *__re
             if constexpr (V == 1) y = t;
             else y[j] = t;
         }
-        *reinterpret_cast<vec *>(out + (size_t)(ci.row0 + row) * N + c) = y;
+        if constexpr (sizeof...(Combine) > 0) {
+            const RowCombine &rc = the_combine(combine...);
+            const size_t at = (size_t)tokens[ci.row0 + row] * N + c;
+            vec n;
+            if constexpr (V == 1) {
+                y = fmaf(p[i], y, 0.f);
+                n = res[i] + y;
+            } else {
+#pragma unroll
+                for (int j = 0; j < V; ++j) {
+                    y[j] = fmaf(p[i], y[j], 0.f);
+                    n[j] = res[i][j] + y[j];
+                }
+            }
+            if (rc.y) *reinterpret_cast<vec *>(rc.y + at) = y;
+            *reinterpret_cast<vec *>(rc.x_next + at) = n;
+        } else {
+            *reinterpret_cast<vec *>(out + (size_t)(ci.row0 + row) * N + c) = y;
+        }
     }
 }
 
@@ -481,17 +517,18 @@ __global__ __launch_bounds__(NW * 64) void ffn_f32_hidden_kernel(const float *__
     f32_tile<V, MT, NW, true>(x_perm, src_row, reinterpret_cast<const float *>(wexp), h, ci, d, f, no_weights);
 }
 
-template <int V, int MT, int NW>
+template <int V, int MT, int NW, typename... Combine>
 __global__ __launch_bounds__(NW * 64) void ffn_f32_out_kernel(const float *__restrict__ h, const int32_t *__restrict__ offsets, int E,
                                                               int d, int f, const char *__restrict__ w_base, size_t w_stride,
                                                               int slot_by_rank, int n_slots,
-                                                              const unsigned long long *__restrict__ table, float *__restrict__ y_perm) {
+                                                              const unsigned long long *__restrict__ table, float *__restrict__ y_perm,
+                                                              const int32_t *__restrict__ tokens, Combine... combine) {
     const ChunkInfo ci = find_chunk(offsets, E, 16 * MT, blockIdx.x);
     if (ci.nrows == 0) return;  // uniform over the workgroup
     const char *wexp = table ? reinterpret_cast<const char *>(table[ci.expert])
                              : w_base + (size_t)(slot_by_rank ? ci.slot : ci.expert) * w_stride;
     const bool no_weights = table ? wexp == nullptr : (slot_by_rank && ci.slot >= n_slots);
-    f32_tile<V, MT, NW, false>(h, nullptr, reinterpret_cast<const float *>(wexp) + (size_t)d * f, y_perm, ci, f, d, no_weights);
+    f32_tile<V, MT, NW, false>(h, nullptr, reinterpret_cast<const float *>(wexp) + (size_t)d * f, y_perm, ci, f, d, no_weights, tokens, combine...);
 }
 
 // Any other float32 shape (d_model or d_ff not a multiple of 4: rows cannot be read 16 bytes at a time).  One workgroup per
@@ -759,7 +796,7 @@ bool ffn_f32_reads_rows_in_place(const pgmoe_config &c) { return c.dtype == PGMO
 
 static int launch_ffn_f32(pgmoe_ctx *ctx, const char *w_base, size_t w_stride, bool slot_by_rank, int n_slots, const float *x,
                           const int32_t *offsets, int n_rows, float *y_perm, float *h, hipStream_t s,
-                          const unsigned long long *table, const int32_t *src_row) {
+                          const unsigned long long *table, const int32_t *src_row, const RowCombine *combine) {
     const pgmoe_config &c = ctx->cfg;
     const int tslot = ffn_timing_slot(ctx);
     if (tslot >= 0) PG_HIP(ctx, hipEventRecord(ctx->tim_begin[tslot], s));
@@ -777,9 +814,14 @@ static int launch_ffn_f32(pgmoe_ctx *ctx, const char *w_base, size_t w_stride, b
 #define PG_F32_HIDDEN(V_, MT_, NW_)                                                                                            \
     hipLaunchKernelGGL((ffn_f32_hidden_kernel<V_, MT_, NW_>), dim3(chunks, (c.d_ff + 16 * V_ - 1) / (16 * V_)), dim3(NW_ * 64), 0, s, \
                        x, src_row, offsets, c.n_experts, c.d_model, c.d_ff, w_base, w_stride, slot_by_rank ? 1 : 0, n_slots, table, h)
+#define PG_F32_OUT_ARGS(V_, MT_, NW_)                                                                                          \
+    dim3(chunks, (c.d_model + 16 * V_ - 1) / (16 * V_)), dim3(NW_ * 64), 0, s, h, offsets, c.n_experts, c.d_model, c.d_ff, w_base,    \
+        w_stride, slot_by_rank ? 1 : 0, n_slots, table, y_perm, src_row
 #define PG_F32_OUT(V_, MT_, NW_)                                                                                               \
-    hipLaunchKernelGGL((ffn_f32_out_kernel<V_, MT_, NW_>), dim3(chunks, (c.d_model + 16 * V_ - 1) / (16 * V_)), dim3(NW_ * 64), 0, s, \
-                       h, offsets, c.n_experts, c.d_model, c.d_ff, w_base, w_stride, slot_by_rank ? 1 : 0, n_slots, table, y_perm)
+    do {                                                                                                                       \
+        if (combine) hipLaunchKernelGGL((ffn_f32_out_kernel<V_, MT_, NW_, RowCombine>), PG_F32_OUT_ARGS(V_, MT_, NW_), *combine); \
+        else hipLaunchKernelGGL((ffn_f32_out_kernel<V_, MT_, NW_>), PG_F32_OUT_ARGS(V_, MT_, NW_));                            \
+    } while (0)
 #define PG_F32(KERN_, N_)                                                                                                      \
     do {                                                                                                                       \
         const int v_ = cols(N_);                                                                                               \
@@ -802,6 +844,7 @@ static int launch_ffn_f32(pgmoe_ctx *ctx, const char *w_base, size_t w_stride, b
         PG_F32(PG_F32_OUT, c.d_model);
 #undef PG_F32
 #undef PG_F32_OUT
+#undef PG_F32_OUT_ARGS
 #undef PG_F32_HIDDEN
     } else {
         hipLaunchKernelGGL(ffn_f32_hidden_scalar_kernel, dim3(n_rows, (c.d_ff + 255) / 256), dim3(256), 0, s, x, offsets, c.n_experts,
@@ -817,14 +860,15 @@ static int launch_ffn_f32(pgmoe_ctx *ctx, const char *w_base, size_t w_stride, b
 
 int launch_ffn(pgmoe_ctx *ctx, const char *w_base, size_t w_stride, bool slot_by_rank, int n_slots, const void *x_perm,
                const int32_t *offsets, int n_rows, void *y_perm, void *workspace, hipStream_t s, int *keep_partials,
-               const unsigned long long *table, const int32_t *src_row, const FusedGate *gate, GateCarried *gate_done) {
+               const unsigned long long *table, const int32_t *src_row, const FusedGate *gate, GateCarried *gate_done,
+               const RowCombine *combine) {
     const pgmoe_config &c = ctx->cfg;
     if (keep_partials) *keep_partials = 0;
     if (gate_done) *gate_done = GATE_LEFT;
     if (n_rows == 0) return PGMOE_OK;
     if (c.dtype == PGMOE_F32)
         return launch_ffn_f32(ctx, w_base, w_stride, slot_by_rank, n_slots, (const float *)x_perm, offsets, n_rows, (float *)y_perm,
-                              (float *)workspace, s, table, src_row);
+                              (float *)workspace, s, table, src_row, combine);
     int slices = 0;
     if (uses_gemm_kernels(c, n_rows)) {
         const size_t bytes = workspace == ctx->static_scratch ? PGMOE_STATIC_SCRATCH_BYTES : ffn_workspace_bytes(c);

@@ -12,6 +12,7 @@
 //                          power-of-two E: token rows staged in LDS as float32, threads split W
 //                          by expert columns and feature rows and fold their partial sums in a
 //                          fixed order (bit-reproducible);
+//   gate_topk_route_kernel the same for one or two gates of a small float32 batch, whose last workgroup also groups the tokens;
 //   gate_topk_kernel       the scalar version of that for any other E.
 #include <cstdlib>
 
@@ -83,9 +84,9 @@ __global__ __launch_bounds__(GATE_THREADS) void gate_topk_kernel(
 // threads sweep W in fully contiguous 4 KiB strides.  The RG partial sums per expert are folded
 // with a fixed butterfly inside the wavefront and then across the 4 wavefronts in order.
 template <typename XT, int TB>
-__global__ __launch_bounds__(GATE_THREADS) void gate_topk_vec_kernel(
+__device__ inline void gate_vec_body(
     const XT *__restrict__ x, const XT *__restrict__ w, const float *__restrict__ bias, int T, int d, int E, int k,
-    int32_t *__restrict__ idx_out, float *__restrict__ prob_out, float *__restrict__ probs_out, uint32_t *flags) {
+    int32_t *__restrict__ idx_out, float *__restrict__ prob_out, float *__restrict__ probs_out, uint32_t *flags, int32_t *idx_lds = nullptr) {
     __shared__ float xs[TB * GATE_DC];
     __shared__ float part[4 * TB * PGMOE_MAX_EXPERTS];
     __shared__ float zs[TB * PGMOE_MAX_EXPERTS];
@@ -147,7 +148,112 @@ __global__ __launch_bounds__(GATE_THREADS) void gate_topk_vec_kernel(
         zs[t * PGMOE_MAX_EXPERTS + e] = sum + (bias ? bias[e] : 0.f);
     }
     __syncthreads();
-    softmax_topk(zs, PGMOE_MAX_EXPERTS, t0, nt, E, k, idx_out, prob_out, probs_out, flags);
+    softmax_topk(zs, PGMOE_MAX_EXPERTS, t0, nt, E, k, idx_out, prob_out, probs_out, flags, idx_lds);
+}
+
+template <typename XT, int TB>
+__global__ __launch_bounds__(GATE_THREADS) void gate_topk_vec_kernel(
+    const XT *__restrict__ x, const XT *__restrict__ w, const float *__restrict__ bias, int T, int d, int E, int k,
+    int32_t *__restrict__ idx_out, float *__restrict__ prob_out, float *__restrict__ probs_out, uint32_t *flags) {
+    gate_vec_body<XT, TB>(x, w, bias, T, d, E, k, idx_out, prob_out, probs_out, flags);
+}
+
+// Gates of small batches that also group the tokens (what route_kernel does for larger ones), one or two of them on the same tokens (a
+// step's first two: block 0's own and the pre-gate of block 1).  A workgroup per token as above; whichever workgroup of a gate
+// ends last groups: the choices are written through to memory and counted, so there is no fence and nobody waits.  Bound by latency and
+// launches: a step of two float32 blocks of 64 x 256 (8 experts, 32 tokens) was ten launches and 34 us with steps of several stacks in flight, and is five
+// and 21 us with this kernel and the combine in the second expert kernel; one block of 768 x 3072, 100 tokens, 49.7 -> 47.8 us.
+struct RoutedGate {
+    const void *w;
+    const float *bias;
+    int32_t *idx;
+    float *prob;
+    int32_t *row_of, *offsets, *src_row;
+    int32_t *counter;  // zero; left zero
+};
+constexpr int GATE_ROUTE_ENTRIES = 512;  // most (token, choice) pairs
+
+// The grouping of n <= GATE_ROUTE_ENTRIES entries by 256 threads: entry tid + 256 * r is thread tid's r-th; entries of a wavefront are in order
+// inside a round and rounds follow each other, so a stable rank is: earlier entries of the round's earlier wavefronts, of
+// earlier rounds, and of lower lanes.
+__device__ inline void group_entries(const int32_t *__restrict__ idx, int n, int E, int k, int32_t *__restrict__ row_of,
+                                     int32_t *__restrict__ offsets, int32_t *__restrict__ src_row) {
+    constexpr int ROUNDS = GATE_ROUTE_ENTRIES / GATE_THREADS, RUNS = ROUNDS * 4;  // a run: 64 neighbouring entries
+    __shared__ int count[RUNS][PGMOE_MAX_EXPERTS];
+    __shared__ int first[PGMOE_MAX_EXPERTS + 1];
+    __shared__ int wave_total[4];
+    const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
+    int e[ROUNDS];
+#pragma unroll
+    for (int r = 0; r < ROUNDS; ++r) {
+        const int i = tid + r * GATE_THREADS;
+        e[r] = i < n ? __hip_atomic_load(idx + i, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT) : 0;
+    }
+#pragma unroll
+    for (int q = 0; q < RUNS; ++q) count[q][tid] = 0;
+    __syncthreads();
+#pragma unroll
+    for (int r = 0; r < ROUNDS; ++r)
+        if (tid + r * GATE_THREADS < n) atomicAdd(&count[r * 4 + wave][e[r]], 1);
+    __syncthreads();
+    int total = 0;  // thread tid: expert tid
+#pragma unroll
+    for (int q = 0; q < RUNS; ++q) {
+        const int c = count[q][tid];
+        count[q][tid] = total;
+        total += c;
+    }
+    int incl = total;
+#pragma unroll
+    for (int off = 1; off < 64; off <<= 1) {
+        const int o = __shfl_up(incl, off);
+        if (lane >= off) incl += o;
+    }
+    if (lane == 63) wave_total[wave] = incl;
+    __syncthreads();
+    int before = incl - total;
+    for (int q = 0; q < wave; ++q) before += wave_total[q];
+    first[tid] = before;
+    if (tid < E) offsets[tid] = before;
+    if (tid == 0) offsets[E] = n;
+    __syncthreads();
+    int nbits = 0;
+    while ((1 << nbits) < E) ++nbits;
+#pragma unroll
+    for (int r = 0; r < ROUNDS; ++r) {
+        const int i = tid + r * GATE_THREADS;
+        const bool valid = i < n;
+        unsigned long long peers = __ballot(valid);
+        for (int b = 0; b < nbits; ++b) {
+            const bool bit = (e[r] >> b) & 1;
+            const unsigned long long m = __ballot(bit);
+            peers &= bit ? m : ~m;
+        }
+        if (!valid) continue;
+        const int row = first[e[r]] + count[r * 4 + wave][e[r]] + __popcll(peers & ((1ull << lane) - 1ull));
+        row_of[i] = row;
+        src_row[row] = i / k;
+    }
+}
+
+template <typename XT>
+__global__ __launch_bounds__(GATE_THREADS) void gate_topk_route_kernel(const XT *__restrict__ x, int T, int d, int E, int k, uint32_t *flags,
+                                                                       RoutedGate g0, RoutedGate g1) {
+    __shared__ int32_t chosen[PGMOE_MAX_EXPERTS];
+    __shared__ int last;
+    const RoutedGate g = blockIdx.y ? g1 : g0;  // uniform
+    gate_vec_body<XT, 1>(x, (const XT *)g.w, g.bias, T, d, E, k, g.idx, g.prob, nullptr, flags, chosen);
+    __syncthreads();
+    const int tid = threadIdx.x;
+    for (int j = tid; j < k; j += GATE_THREADS)  // again, past this XCD's L2: the workgroup that groups may run on another
+        __hip_atomic_store(g.idx + (size_t)blockIdx.x * k + j, chosen[j], __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+    asm volatile("s_waitcnt vmcnt(0)" ::: "memory");
+    __syncthreads();
+    if (tid == 0) last = __hip_atomic_fetch_add(g.counter, 1, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT) == T - 1;
+    __syncthreads();
+    if (!last) return;  // uniform over the workgroup
+    if (tid == 0) __hip_atomic_store(g.counter, 0, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+    group_entries(g.idx, T * k, E, k, g.row_of, g.offsets, g.src_row);
 }
 
 // The smallest gate as a kernel of its own (its body lives in gate_small.h).
@@ -409,6 +515,24 @@ static int launch_gate_mfma(pgmoe_ctx *ctx, const __bf16 *x, const __bf16 *w, co
     if (np == 1) PG_GATE_MFMA(1, 8);
     else PG_GATE_MFMA(2, 4);
 #undef PG_GATE_MFMA
+    PG_HIP(ctx, hipGetLastError());
+    return PGMOE_OK;
+}
+
+// Gates the vector kernel serves with a workgroup per token and whose choices its last workgroup can group.
+bool gate_groups_tokens(const pgmoe_config &c, int T) {
+    const int E = c.n_experts;
+    return ffn_f32_reads_rows_in_place(c) && E >= 8 && E <= PGMOE_MAX_EXPERTS && (E & (E - 1)) == 0 && T <= 256 && T * c.top_k <= GATE_ROUTE_ENTRIES;
+}
+
+int launch_gates_grouped(pgmoe_ctx *ctx, const void *x, int T, const FusedGate *gates, int n, const int *blocks, hipStream_t s) {
+    const pgmoe_config &c = ctx->cfg;
+    RoutedGate g[2] = {};
+    for (int i = 0; i < n; ++i)
+        g[i] = RoutedGate{gates[i].w, gates[i].bias, gates[i].idx, gates[i].prob, gates[i].row_of, gates[i].offsets, gates[i].src_row,
+                          ctx->gate_counter + blocks[i]};
+    hipLaunchKernelGGL(gate_topk_route_kernel<float>, dim3(T, n), dim3(GATE_THREADS), 0, s, (const float *)x, T, c.d_model, c.n_experts,
+                       c.top_k, ctx->dev_flags, g[0], g[1]);
     PG_HIP(ctx, hipGetLastError());
     return PGMOE_OK;
 }

@@ -56,6 +56,7 @@ struct pgmoe_ctx {
     int32_t *dev_unique;   // [n_blocks] distinct experts found by the pull kernel (dev_flags + 64 bytes)
     unsigned long long *dev_copy_clock;  // [n_blocks][2] copy start / end of the block's last traced pull kernel (100 MHz ticks)
     int32_t *dev_src_row;  // [n_blocks][max_tokens * k] grouped row -> token, written by each block's routing
+    int32_t *gate_counter = nullptr;  // [n_blocks] workgroups of the block's gate that have ended (gate_topk_route_kernel); zero between launches
     float *gate_planes = nullptr;  // partial logits between the two halves of a carried pre-gate (gate_small.h); null: none is ever carried so
     bool *routed;          // [n_blocks] host: this step's gate kernel already grouped the block's tokens
     // turn-taking of a stack step's migration kernels on the host link (see fetch.hip): position of
@@ -185,6 +186,17 @@ struct FusedGate {
 };
 // What became of it: left to the caller; begun (launch_combine_partials finishes it); evaluated and its tokens grouped.
 enum GateCarried { GATE_LEFT = 0, GATE_STARTED = 1, GATE_ROUTED = 2 };
+// Float32: do the gates of a batch of T tokens group the tokens themselves?  Then launch_gates_grouped evaluates one or two gates on the same x
+// (gates[i].T and .x are not read) and groups their blocks' tokens.
+bool gate_groups_tokens(const pgmoe_config &c, int T);
+int launch_gates_grouped(pgmoe_ctx *ctx, const void *x, int T, const FusedGate *gates, int n, const int *blocks, hipStream_t s);
+// What a float32 expert launch with one expert per token can do with its results instead of leaving them in y_perm: the combine of the block.
+struct RowCombine {
+    const float *prob;   // [T]
+    float *y;            // [T, d] | nullptr
+    const float *x_res;  // [T, d]
+    float *x_next;       // [T, d]
+};
 // keep_partials != nullptr: if the launch produces float32 partial sums, leave them in the
 // workspace unreduced and report their number there (0 = y_perm was written directly).
 // gate != nullptr: carry that gate if this launch can and say so in *gate_done (non-null then).
@@ -193,7 +205,8 @@ int launch_ffn(pgmoe_ctx *ctx, const char *w_base, size_t w_stride, bool slot_by
                const unsigned long long *table = nullptr,  // table: per-expert weight addresses (0 = none), overrides w_base
                const int32_t *src_row = nullptr,  // x_perm is the un-grouped x [T,d], grouped row r reads x[src_row[r]] (bf16; float32
                                                   // where ffn_f32_reads_rows_in_place says so)
-               const FusedGate *gate = nullptr, GateCarried *gate_done = nullptr);
+               const FusedGate *gate = nullptr, GateCarried *gate_done = nullptr,
+               const RowCombine *combine = nullptr);  // float32, src_row given, one expert per token: done by this launch, y_perm is left alone
 // p-lanes of the partial-sum reduction for P partials (fixes the order of the additions)
 inline int reduce_lanes(int P) { return P <= 2 ? 1 : (P <= 8 ? 4 : 16); }
 // Combine straight from P unreduced float32 partials [P][n_rows][d] (bf16 contexts only): same

@@ -1,0 +1,50 @@
+"""Float32 stack steps whose gate launch groups the tokens and whose second expert kernel does the
+combine: the bits of the primitives called one by one, at the edges of what those launches take."""
+import pytest
+import torch
+
+import workloads as W
+from launch_count import kernel_launches
+from test_gpu_parity import hx, test_stack_step_equals_the_primitive_call_sequence as step_equals_primitives  # noqa: F401
+
+pytestmark = pytest.mark.gpu
+
+
+@pytest.mark.parametrize("T,d,f,E,k,L,offloaded", [
+    (1, 64, 256, 8, 1, 2, False), (64, 64, 256, 8, 1, 3, False), (65, 128, 256, 16, 1, 2, False),
+    (256, 64, 128, 64, 2, 2, False),                 # as many tokens and selections as a gate groups
+    (257, 64, 128, 64, 1, 2, False), (171, 64, 128, 8, 3, 2, False),    # a token, a selection more
+    (100, 128, 256, 256, 1, 1, False), (33, 64, 256, 8, 8, 2, False), (20, 64, 256, 12, 1, 2, False),   # every expert; no power of two
+    (50, 68, 132, 8, 1, 2, False), (40, 30, 36, 8, 1, 2, False),        # columns past a tile's end; rows that are no multiple of 16 bytes
+    (90, 256, 512, 8, 1, 2, False), (200, 512, 512, 8, 1, 1, False),    # 32- and 64-row chunks
+    (9, 64, 256, 8, 1, 3, True), (30, 64, 256, 8, 2, 3, True),
+])
+def test_f32_step_equals_the_primitives(hx, T, d, f, E, k, L, offloaded):  # noqa: F811
+    print(f"f32 step: T={T} d={d} f={f} E={E} k={k} L={L} offloaded={offloaded}", flush=True)
+    step_equals_primitives(hx, "f32", T, d, f, E, k, L, offloaded)
+
+
+@pytest.mark.parametrize("T,k,launches", [(32, 1, 5), (32, 2, 7), (300, 1, 8)])
+def test_f32_step_replayed_from_a_graph(hx, T, k, launches):  # noqa: F811
+    """Replays on new inputs, with eager steps in between: what a gate launch counts has to be zero again behind it."""
+    H, B = hx
+    w = W.Workload("f32_replay", 83, 2, 64, 256, 8, k, T, 1, "f32", 0.0, False)
+    stack = H.Stack(w, H.ExpertStore(w, H.config_for(w), threads=2))
+    stack.set_input(W.step_input(w, 0))
+    stack.step()
+    torch.cuda.synchronize()
+    assert kernel_launches(stack.step, stack.compute) == launches
+    graph = torch.cuda.CUDAGraph()
+    with torch.cuda.graph(graph, stream=stack.compute):
+        stack.step()
+    for n in range(4):
+        stack.set_input(W.step_input(w, n))
+        torch.cuda.synchronize()
+        graph.replay()
+        torch.cuda.synchronize()
+        got = [t.clone() for t in (stack.x_states, stack.y_blocks, stack.topk_idx, stack.row_of, stack.expert_offsets)]
+        stack.step()
+        torch.cuda.synchronize()
+        for a, b in zip(got, (stack.x_states, stack.y_blocks, stack.topk_idx, stack.row_of, stack.expert_offsets)):
+            assert torch.equal(a, b)
+    stack.close()
