@@ -17,7 +17,7 @@ ROOT = os.path.dirname(HERE)
 CSRC = os.path.join(HERE, "csrc")
 OBJ = os.path.join(HERE, "_build")
 LIB = os.path.join(HERE, "libpgmoe.so")
-SOURCES = ["api.hip", "gate.hip", "permute.hip", "ffn.hip", "ffn_gemm.hip", "combine.hip", "fetch.hip", "engine.hip"]
+SOURCES = ["api.hip", "gate.hip", "permute.hip", "ffn.hip", "ffn_gemm.hip", "ffn_decode_stack.hip", "combine.hip", "fetch.hip", "engine.hip"]
 
 HIPCC = os.environ.get("HIPCC", "/opt/rocm/bin/hipcc")
 FLAGS = [
@@ -71,7 +71,7 @@ def _check_resources(src: str, usage: dict) -> None:
 def _compile(src: str, force: bool) -> str:
     obj = os.path.join(OBJ, src.replace(".hip", ".o"))
     path = os.path.join(CSRC, src)
-    deps = [path, os.path.join(CSRC, "pgmoe_internal.h"), os.path.join(CSRC, "ffn_common.h"), os.path.join(CSRC, "gate_small.h"), os.path.join(ROOT, "include", "pgmoe.h")]
+    deps = [path, os.path.join(ROOT, "include", "pgmoe.h")] + [os.path.join(CSRC, h) for h in os.listdir(CSRC) if h.endswith(".h")]
     if not force and os.path.exists(obj) and all(os.path.getmtime(obj) >= os.path.getmtime(d) for d in deps):
         return obj
     r = subprocess.run([HIPCC, *FLAGS, "-c", path, "-o", obj], stderr=subprocess.PIPE, text=True)

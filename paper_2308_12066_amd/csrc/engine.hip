@@ -638,6 +638,7 @@ int pgmoe_stack_step(pgmoe_ctx *ctx, const pgmoe_step_buffers *io, int T, void *
     if (ctx->store_mode == STORE_NONE) return fail(ctx, PGMOE_ESTATE, "%s: no expert store registered", fn);
     if (ctx->host_only) return fail(ctx, PGMOE_ENODEVICE, "%s: context is host-only, nothing can be launched", fn);
     if (T == 0) return PGMOE_OK;
+    if (decode_stack_applies(ctx, T)) return launch_decode_stack(ctx, io, (hipStream_t)compute_stream);
     for (int b = 0; b < L; ++b) ctx->routed[b] = false;
     // the migrations of this step that run beside the compute stream (one per block in the pre-gated
     // and the prefetch-all schedule) take turns on the host link; whatever path leaves this

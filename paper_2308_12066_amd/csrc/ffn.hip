@@ -26,6 +26,7 @@
 #include <mutex>
 
 #include "ffn_common.h"
+#include "ffn_decode.h"
 #include "gate_small.h"
 
 namespace pgmoe {
@@ -231,88 +232,31 @@ __global__ __launch_bounds__(256) void ffn_decode_kernel(
                                                                      gate.flags, gate.row_of, gate.offsets, gate.src_row);
         return;
     }
-    constexpr int NTD = KT * 2;   // output n-tiles
-    constexpr int NA = KT / 2;    // phase-A tiles per wavefront
-    constexpr int NB = NTD / 4;   // phase-B tiles per wavefront
-    static_assert(KT % 2 == 0, "k split");
     extern __shared__ __attribute__((aligned(16))) char smem[];
-    const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
-    const int cw = wave & 1, ks = wave >> 1;
-
     const ChunkInfo ci = find_chunk(offsets, E, 16, blockIdx.x);
     if (ci.nrows == 0) return;  // uniform over the workgroup
     const char *wexp = table ? reinterpret_cast<const char *>(table[ci.expert])
                              : w_base + (size_t)(slot_by_rank ? ci.slot : ci.expert) * w_stride;
     const bool no_weights = table ? wexp == nullptr : (slot_by_rank && ci.slot >= n_slots);  // no slot: rows are zeroed
-    const int fs = blockIdx.y * 32;
-
-    bf16x8 ta[NA], tb[NB];
-    if (!no_weights) {
-        const global_bf16x8 *w1 = (const global_bf16x8 *)wexp + (((size_t)((fs >> 4) + cw) * KT) << 6) + lane;
-        const global_bf16x8 *w2 = (const global_bf16x8 *)(wexp + (size_t)d * f * 2) +
-                           (((size_t)(fs >> 5) * NTD + wave * NB) << 6) + lane;
-#pragma unroll
-        for (int i = 0; i < NA; ++i) ta[i] = w1[(size_t)(ks + 2 * i) << 6];
-#pragma unroll
-        for (int a = 0; a < NB; ++a) tb[a] = w2[(size_t)a << 6];
-    } else {
-#pragma unroll
-        for (int i = 0; i < NA; ++i) ta[i] = bf16x8{0, 0, 0, 0, 0, 0, 0, 0};
-#pragma unroll
-        for (int a = 0; a < NB; ++a) tb[a] = bf16x8{0, 0, 0, 0, 0, 0, 0, 0};
-    }
-
-    bf16x8 *xs = reinterpret_cast<bf16x8 *>(smem);                       // [KT][64] operand cells
-    floatx4 *hsum = reinterpret_cast<floatx4 *>(xs + (size_t)KT * 64);   // [2 k-halves][2 n-tiles][64]
-    {
-        constexpr int cells_per_row = d >> 3;
-        const uint4 *src = reinterpret_cast<const uint4 *>(x_perm);
-        uint4 *dst = reinterpret_cast<uint4 *>(xs);
-        for (int i = tid; i < 16 * cells_per_row; i += 256) {
-            const int m = i / cells_per_row, k8 = i - m * cells_per_row;
-            uint4 v = make_uint4(0, 0, 0, 0);
-            if (m < ci.nrows) {
-                const int row = ci.row0 + m;
-                v = src[(size_t)(src_row ? src_row[row] : row) * cells_per_row + k8];
+    decode_sub_slab<KT>(
+        smem, no_weights ? nullptr : wexp, f, blockIdx.y,
+        [&](bf16x8 *xs) {
+            constexpr int cells_per_row = d >> 3;
+            const uint4 *src = reinterpret_cast<const uint4 *>(x_perm);
+            uint4 *dst = reinterpret_cast<uint4 *>(xs);
+            for (int i = threadIdx.x; i < 16 * cells_per_row; i += 256) {
+                const int m = i / cells_per_row, k8 = i - m * cells_per_row;
+                uint4 v = make_uint4(0, 0, 0, 0);
+                if (m < ci.nrows) {
+                    const int row = ci.row0 + m;
+                    v = src[(size_t)(src_row ? src_row[row] : row) * cells_per_row + k8];
+                }
+                dst[((k8 >> 2) << 6) + m + 16 * (k8 & 3)] = v;
             }
-            dst[((k8 >> 2) << 6) + m + 16 * (k8 & 3)] = v;
-        }
-    }
-    lds_barrier();
-
-    // ---- phase A: 16 hidden features (n-tile cw of the sub-slab) over this wavefront's k-tiles
-    floatx4 hacc = floatx4{0.f, 0.f, 0.f, 0.f};
-#pragma unroll
-    for (int i = 0; i < NA; ++i)
-        hacc = __builtin_amdgcn_mfma_f32_16x16x32_bf16(ta[i], xs[((ks + 2 * i) << 6) + lane], hacc, 0, 0, 0);
-    hsum[(ks * 2 + cw) * 64 + lane] = hacc;
-    lds_barrier();
-
-    // ---- hidden activation as phase-B operand: lane (token lane%16, k-group g = lane/16) needs
-    // features 8g .. 8g+7 of the 32, i.e. n-tile g/2, accumulator rows 4*q' + r for q' = 2*(g%2), +1
-    const int tok = lane & 15, g = lane >> 4;
-    bf16x8 hfrag;
-    {
-        const int src = (g >> 1) * 64 + (2 * (g & 1)) * 16 + tok;
-        const floatx4 lo = hsum[src] + hsum[128 + src];
-        const floatx4 hi = hsum[src + 16] + hsum[128 + src + 16];
-        hfrag[0] = (__bf16)fmaxf(lo.x, 0.f);
-        hfrag[1] = (__bf16)fmaxf(lo.y, 0.f);
-        hfrag[2] = (__bf16)fmaxf(lo.z, 0.f);
-        hfrag[3] = (__bf16)fmaxf(lo.w, 0.f);
-        hfrag[4] = (__bf16)fmaxf(hi.x, 0.f);
-        hfrag[5] = (__bf16)fmaxf(hi.y, 0.f);
-        hfrag[6] = (__bf16)fmaxf(hi.z, 0.f);
-        hfrag[7] = (__bf16)fmaxf(hi.w, 0.f);
-    }
-
-    // ---- phase B: this wavefront's NB output n-tiles; lane holds token tok, columns 16*tile + 4*g + {0..3}
-    float *dst = partial + ((size_t)blockIdx.y * n_rows + (size_t)ci.row0 + tok) * d + (wave * NB) * 16 + 4 * g;
-#pragma unroll
-    for (int a = 0; a < NB; ++a) {
-        const floatx4 y = __builtin_amdgcn_mfma_f32_16x16x32_bf16(tb[a], hfrag, floatx4{0.f, 0.f, 0.f, 0.f}, 0, 0, 0);
-        if (tok < ci.nrows) *reinterpret_cast<floatx4 *>(dst + a * 16) = y;
-    }
+        },
+        [&](int column, int tok, const floatx4 &y) {
+            if (tok < ci.nrows) *reinterpret_cast<floatx4 *>(partial + ((size_t)blockIdx.y * n_rows + (size_t)ci.row0 + tok) * d + column) = y;
+        });
 }
 
 // y_perm[row][c] = bf16( sum_p partial[p][row][c] ).  A workgroup of 256 threads covers 256/PL
@@ -664,6 +608,10 @@ bool ffn_supports_d_model(int d_model) { return d_model % 32 == 0 && fused_case_
 static bool uses_decode_kernel(const pgmoe_config &c, const FfnPlan &p) {
     const int kt = c.d_model / 32;
     return p.mt == 1 && p.nw == 2 && p.n_partial == c.d_ff / 32 && (kt == 24 || kt == 32);
+}
+
+bool ffn_launch_is_decode_sized(const pgmoe_config &c, int n_rows) {
+    return c.dtype == PGMOE_BF16 && n_rows > 0 && !uses_gemm_kernels(c, n_rows) && uses_decode_kernel(c, plan_ffn(c, n_rows));
 }
 
 const char *ffn_kernel_name(const pgmoe_config &c, int n_rows) {

@@ -58,7 +58,7 @@ __device__ inline void group_argmax(float &v, int &i) {
 template <int NQ, int GROUP>
 __device__ inline void softmax_topk_n(const float *zs, int zstride, int t0, int nt, int E, int k,
                                       int32_t *__restrict__ idx_out, float *__restrict__ prob_out,
-                                      float *__restrict__ probs_out, uint32_t *flags, int32_t *idx_lds) {
+                                      float *__restrict__ probs_out, uint32_t *flags, int32_t *idx_lds, float *prob_lds = nullptr) {
     const int tid = GROUP ? threadIdx.x & (GROUP - 1) : threadIdx.x;
     const int sub = tid & 15, grp = tid >> 4;  // 16 lanes per group
     bool any_nan = false;
@@ -113,6 +113,7 @@ __device__ inline void softmax_topk_n(const float *zs, int zstride, int t0, int 
                 idx_out[tok * k + j] = bi;
                 prob_out[tok * k + j] = expf(bv - m) * inv;
                 if (idx_lds) idx_lds[t * k + j] = bi;
+                if (prob_lds) prob_lds[t * k + j] = expf(bv - m) * inv;
             }
         }
     }
@@ -175,27 +176,30 @@ constexpr int GS_TOK = 4;
 constexpr int GS_THREADS = 256;
 typedef __bf16 gs_bf16x8 __attribute__((ext_vector_type(8)));
 
-template <int EV, int NTOK>  // EV = E / 8 (1 or 2); NTOK = tokens the arithmetic is unrolled for (T <= NTOK <= GS_TOK)
-__device__ inline void gate_small_body(
-    const __bf16 *__restrict__ x, const __bf16 *__restrict__ w, const float *__restrict__ bias, int T, int d, int k,
+// x8(t, first): features first .. first + 7 of token t, asked for once W has been requested.  chosen(idx, prob): called by every thread with the choices
+// (LDS [T*k], only thread 0's own are sure to be there yet) before the tokens are grouped.
+template <int EV, int NTOK, typename Features, typename Chosen>  // EV = E / 8 (1 or 2); NTOK = tokens the arithmetic is unrolled for (T <= NTOK <= GS_TOK)
+__device__ inline void gate_small_rows(
+    Features x8, const __bf16 *__restrict__ w, const float *__restrict__ bias, int T, int d, int k,
     int32_t *__restrict__ idx_out, float *__restrict__ prob_out, float *__restrict__ probs_out, uint32_t *flags,
-    int32_t *__restrict__ row_of, int32_t *__restrict__ offsets, int32_t *__restrict__ src_row) {
+    int32_t *__restrict__ row_of, int32_t *__restrict__ offsets, int32_t *__restrict__ src_row, Chosen chosen) {
     constexpr int E = 8 * EV;
     constexpr int ROWS = GS_THREADS / 16;                // 16-lane rows in the workgroup
     __shared__ float part[ROWS][NTOK * E];
     __shared__ float zs[GS_TOK * 16];
     __shared__ int32_t r_idx[GS_TOK * E], r_cnt[E], r_off[E];
+    __shared__ float r_prob[GS_TOK * E];
     const int tid = threadIdx.x;
     const bool mine = 8 * tid < d;                       // d <= 8 * GS_THREADS (checked by the host)
     const int r0 = mine ? 8 * tid : 0;                   // idle threads read rows 0..7 and add nothing
     const float b = (bias && tid < NTOK * E) ? bias[tid % E] : 0.f;  // needed last, requested first
     gs_bf16x8 xv[NTOK], wv[8][EV];
 #pragma unroll
-    for (int t = 0; t < NTOK; ++t) xv[t] = *reinterpret_cast<const gs_bf16x8 *>(x + (size_t)(t < T ? t : 0) * d + r0);
-#pragma unroll
     for (int j = 0; j < 8; ++j)
 #pragma unroll
         for (int v = 0; v < EV; ++v) wv[j][v] = *reinterpret_cast<const gs_bf16x8 *>(w + (size_t)(r0 + j) * E + 8 * v);
+#pragma unroll
+    for (int t = 0; t < NTOK; ++t) xv[t] = x8(t < T ? t : 0, r0);
     float acc[NTOK][E];
 #pragma unroll
     for (int t = 0; t < NTOK; ++t)
@@ -223,9 +227,19 @@ __device__ inline void gate_small_body(
     }
     __syncthreads();
     const bool route = row_of != nullptr;
-    softmax_topk_n<1, 0>(zs, 16, 0, T, E, k, idx_out, prob_out, probs_out, flags, route ? r_idx : nullptr);
+    softmax_topk_n<1, 0>(zs, 16, 0, T, E, k, idx_out, prob_out, probs_out, flags, route ? r_idx : nullptr, r_prob);
+    chosen(r_idx, r_prob);
     if (!route) return;
     group_in_workgroup(r_idx, r_cnt, r_off, T * k, E, k, GS_THREADS, row_of, offsets, src_row);
+}
+
+template <int EV, int NTOK>
+__device__ inline void gate_small_body(
+    const __bf16 *__restrict__ x, const __bf16 *__restrict__ w, const float *__restrict__ bias, int T, int d, int k,
+    int32_t *__restrict__ idx_out, float *__restrict__ prob_out, float *__restrict__ probs_out, uint32_t *flags,
+    int32_t *__restrict__ row_of, int32_t *__restrict__ offsets, int32_t *__restrict__ src_row) {
+    gate_small_rows<EV, NTOK>([&](int t, int first) { return *reinterpret_cast<const gs_bf16x8 *>(x + (size_t)t * d + first); }, w, bias, T, d, k,
+                              idx_out, prob_out, probs_out, flags, row_of, offsets, src_row, [](const int32_t *, const float *) {});
 }
 
 // Runs the smallest gate for 8*EV experts and T tokens in the calling workgroup of GS_THREADS threads (uniform call).

@@ -21,6 +21,7 @@ constexpr int kSpareStreams = 6;  // most replacements of the context's own copy
 constexpr uint32_t kFlagNaN = 1u;
 constexpr uint32_t kFlagBadIndex = 2u;
 constexpr uint32_t kFlagNoSlot = 4u;
+constexpr uint32_t kFlagStalled = 8u;
 
 // Rows of one expert that a single FFN workgroup handles at once (bf16 path): 16 * MT.
 constexpr int kTileRows = 16;
@@ -57,6 +58,7 @@ struct pgmoe_ctx {
     unsigned long long *dev_copy_clock;  // [n_blocks][2] copy start / end of the block's last traced pull kernel (100 MHz ticks)
     int32_t *dev_src_row;  // [n_blocks][max_tokens * k] grouped row -> token, written by each block's routing
     int32_t *gate_counter = nullptr;  // [n_blocks] workgroups of the block's gate that have ended (gate_topk_route_kernel); zero between launches
+    char *decode_scratch = nullptr;  // of a one-launch step (ffn_decode_stack.hip); null: never taken
     float *gate_planes = nullptr;  // partial logits between the two halves of a carried pre-gate (gate_small.h); null: none is ever carried so
     bool *routed;          // [n_blocks] host: this step's gate kernel already grouped the block's tokens
     // turn-taking of a stack step's migration kernels on the host link (see fetch.hip): position of
@@ -207,6 +209,14 @@ int launch_ffn(pgmoe_ctx *ctx, const char *w_base, size_t w_stride, bool slot_by
                                                   // where ffn_f32_reads_rows_in_place says so)
                const FusedGate *gate = nullptr, GateCarried *gate_done = nullptr,
                const RowCombine *combine = nullptr);  // float32, src_row given, one expert per token: done by this launch, y_perm is left alone
+// Is a launch of n_rows rows the decode-sized kernel's?
+bool ffn_launch_is_decode_sized(const pgmoe_config &c, int n_rows);
+// A whole step of one token in one launch (ffn_decode_stack.hip), from DECODE_STACK_LEAST blocks on: with two and three blocks a step
+// that is waited for takes as long either way (8 experts of 768 x 3072: 32.0 against 32.6 us and 38.4 against 41.0; four blocks 45 against 79).
+constexpr int DECODE_STACK_LEAST = 4;
+size_t decode_stack_scratch_bytes(const pgmoe_config &c);
+bool decode_stack_applies(const pgmoe_ctx *ctx, int T);
+int launch_decode_stack(pgmoe_ctx *ctx, const pgmoe_step_buffers *io, hipStream_t s);
 // p-lanes of the partial-sum reduction for P partials (fixes the order of the additions)
 inline int reduce_lanes(int P) { return P <= 2 ? 1 : (P <= 8 ? 4 : 16); }
 // Combine straight from P unreduced float32 partials [P][n_rows][d] (bf16 contexts only): same
