@@ -33,7 +33,11 @@
  *   - Matrices are row-major.  T = tokens in this call, d = d_model, f = d_ff, E = n_experts,
  *     k = top_k.  Activations and gate weights have the context's dtype (float32 or
  *     bfloat16); probabilities are float32; indices are int32.  T = 0 is a valid no-op.
- *   - One context serves one stack on one device, from one host thread at a time.
+ *   - One context serves one stack on one device, from one host thread at a time.  The stream work of
+ *     its steps is ordered by the caller (one stream, or events), also where captured steps are
+ *     replayed: the row -> token maps, with a host store the expert slots too, are the context's.
+ *     Steps of one token in bfloat16 with 8 or 16 resident experts have no such state: several may be in
+ *     flight if each has pgmoe_step_buffers of its own.
  */
 #ifndef PGMOE_H
 #define PGMOE_H
@@ -138,7 +142,7 @@ const char *pgmoe_last_error(const pgmoe_ctx *ctx);
 
 /* Bytes of one expert blob (W1 then W2, contiguous): 2*d*f*sizeof(element). 0 if cfg invalid. */
 size_t pgmoe_expert_bytes(const pgmoe_config *cfg);
-/* Bytes of device scratch that pgmoe_expert_ffn() needs for up to max_tokens*k rows. */
+/* Bytes of device scratch that pgmoe_expert_ffn(), for up to max_tokens*k rows, and pgmoe_stack_step() need. */
 size_t pgmoe_workspace_bytes(const pgmoe_ctx *ctx);
 
 /* ---- expert weight layout (host) --------------------------------------------------
@@ -321,6 +325,8 @@ int pgmoe_combine(pgmoe_ctx *ctx, const void *y_perm, const int32_t *row_of, con
  * With a resident store and pregate_distance 1, a decode-sized block (up to 128 tokens, bf16, n_experts a multiple of
  * 8 up to 128) carries the pre-gate evaluated on the same hidden state in extra workgroups of its expert launch and its
  * combine: results are those of the separate gate launch, bit for bit.
+ * A step of one token with one of 8 or 16 resident bfloat16 experts per block can run as two launches, whatever its number of
+ * blocks; what those hand over lies in io->workspace, whose contents before the call do not matter.  Same results, bit for bit.
  * With pregate_distance N > 1 the gate that routes block g is evaluated on x_{max(0, g-N)}:
  * block 0 runs the gates of blocks 0..N on x_0 and queues their fetches back to back, block
  * i >= 1 runs the gate of block i+N; the last N blocks run none.  Arrays of pointers are host arrays of

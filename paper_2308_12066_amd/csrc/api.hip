@@ -213,10 +213,7 @@ int pgmoe_create(pgmoe_ctx **out, const pgmoe_config *cfg) {
         c->gate_counter = c->dev_unique + cfg->n_blocks;
         size_t n_idx = (size_t)cfg->max_tokens * cfg->top_k;
         if (rc == PGMOE_OK) H(hipMalloc((void **)&c->dev_src_row, (size_t)cfg->n_blocks * n_idx * sizeof(int32_t)), "hipMalloc(src_row)");
-        if (rc == PGMOE_OK && decode_stack_scratch_bytes(*cfg)) {
-            H(hipMalloc((void **)&c->decode_scratch, decode_stack_scratch_bytes(*cfg)), "hipMalloc(step scratch)");
-            if (rc == PGMOE_OK) H(hipMemset(c->decode_scratch, 0, decode_stack_scratch_bytes(*cfg)), "hipMemset(step scratch)");
-        }
+        c->decode_stack = decode_stack_workspace_bytes(*cfg) > 0;
         if (rc == PGMOE_OK && gate_planes_apply(*cfg, GATE_CARRY_TOKENS))
             H(hipMalloc((void **)&c->gate_planes, gate_planes_floats(std::min(cfg->max_tokens, GATE_CARRY_TOKENS)) * sizeof(float)), "hipMalloc(gate planes)");
         if (rc == PGMOE_OK) H(hipHostMalloc((void **)&c->idx_staging, n_idx * sizeof(int32_t), hipHostMallocDefault), "hipHostMalloc(idx staging)");
@@ -263,7 +260,6 @@ int pgmoe_destroy(pgmoe_ctx *c) {
         delete[] c->cache_parity;
         if (c->dev_flags) (void)hipFree(c->dev_flags);
         if (c->dev_src_row) (void)hipFree(c->dev_src_row);
-        if (c->decode_scratch) (void)hipFree(c->decode_scratch);
         if (c->gate_planes) (void)hipFree(c->gate_planes);
         if (c->idx_staging) (void)hipHostFree(c->idx_staging);
         if (c->idx_ready) (void)hipEventDestroy(c->idx_ready);
@@ -294,7 +290,7 @@ int pgmoe_destroy(pgmoe_ctx *c) {
 
 size_t pgmoe_workspace_bytes(const pgmoe_ctx *ctx) {
     if (!ctx) return 0;
-    return ffn_workspace_bytes(ctx->cfg);
+    return std::max(ffn_workspace_bytes(ctx->cfg), (decode_stack_workspace_bytes(ctx->cfg) + 255) & ~(size_t)255);
 }
 
 int pgmoe_pack_expert(const pgmoe_config *cfg, const void *w1, const void *w2, void *blob) {

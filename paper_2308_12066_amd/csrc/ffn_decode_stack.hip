@@ -1,8 +1,9 @@
-// A whole pre-gated stack step (Sec. IV-B wiring) of one token with one expert per block in one launch: smallest gates, decode-sized experts, every
+// A whole pre-gated stack step (Sec. IV-B wiring) of one token with one expert per block in two launches: smallest gates, decode-sized experts, every
 // expert resident (batch-1 decode of the 8- and 16-expert models).
 //
 // Block by block the step is a chain of two launches each, a dozen launches of a few microseconds that a host needs 45 to 57 us to
-// enqueue.  Here the workgroups of all blocks are one grid and hand over inside it:
+// enqueue.  Here the first launch is block 0's own gate, beside workgroups that clear the words the second one hands over with, and in the second
+// the workgroups of all blocks are one grid and hand over inside it:
 //   gate of block i+1 (one workgroup)   needs x_i;                                     leaves the expert of block i+1 and its probability
 //   experts of block i (one workgroup per 32-column sub-slab of d_ff)   need the expert to request its weights, then x_i;   leave partial sums
 //   combine of block i (one per 64 columns)                       needs the partial sums, probability and x_i;   leaves x_{i+1}
@@ -10,16 +11,18 @@
 //
 // Hand-over: what crosses workgroups is stored past the XCD's L2 and loaded past it, so there are no fences.  Routing and x travel as 64-bit words of
 // 32 bits of payload and a tag (number of the step and of the block) that whoever needs them polls until the tag is right: one store and one load.
-// The partial sums, 295 KB a block, are counted instead (polling them as tagged words held up what it waited for: 52 us a step).  Tags
-// and counts go on from step to step, so nothing is cleared.
+// The partial sums, 295 KB a block, are counted instead (polling them as tagged words held up what it waited for: 52 us a step).
+//
+// Everything a step shares lies in the workspace its caller brought, and the first launch clears it whatever the workspace held: steps with
+// buffers of their own have nothing in common, also those of one context on several streams or in several graphs.
 //
 // No workgroup waits for one that may not have started: work is drawn as tickets in the order above, and whoever holds a ticket waits for
 // lower ones only, so the lowest one still at work never waits, whatever else occupies the GPU.  Waits are bounded all the same (half a
-// second), after which the context's flags say that results are wrong.  The last workgroup to find no work left sets the tickets back and
-// counts the step, so a captured step replays.
+// second), after which the context's flags say that results are wrong.
 //
-// 8 experts of 768 x 3072, six blocks: 45 us on the GPU, 32 us a step with steps of several stacks in flight, 58 waited for; 55, 55 and 95 as
-// launches.  Bound by hand-overs: a block is two of them, about a microsecond each for the store and the load, around two
+// 8 experts of 768 x 3072, six blocks: 32 us a step with steps of several stacks in flight, 45 one after the other on a stream, 56 waited for;
+// 55, 58 and 73 as launches.  Clearing costs nothing beside block 0's gate: with state that was left ready by the step
+// before, all in one launch, it was 32 as well.  Bound by hand-overs: a block is two of them, about a microsecond each for the store and the load, around two
 // memory latencies of its own (weights are there when x is).  With more than one (token, expert) pair the launches are faster: a
 // first version that took up to fifteen pairs took 52, 93 and 92 us for two tokens, four tokens and two tokens of two experts, the
 // launches 56, 66 and 70.
@@ -38,12 +41,13 @@ constexpr unsigned long long STACK_PATIENCE = 50000000;  // half a second of the
 
 typedef uint32_t uint32x4 __attribute__((ext_vector_type(4)));
 
-// The context's scratch: ticket and step number, counters [STACK_BLOCKS][SPREAD] (a memory channel apart), tagged words of the routing (two a
-// block) and of x (even and odd blocks), partial sums of a block.
+// In the workspace: ticket, tagged words of the routing (two a block) and of x (even and odd blocks), counters [L][SPREAD] (a memory channel
+// apart), all of them zero when the step begins; then the partial sums of a block.
 struct StackScratch {
-    static constexpr int APART = 256;
-    static constexpr size_t COUNTERS = APART, ROUTING = COUNTERS + (size_t)STACK_BLOCKS * SPREAD * APART, X = ROUTING + STACK_BLOCKS * 2 * 8;
-    static size_t bytes(int d, int f) { return X + 2 * ((size_t)d / 2 * 8) + (size_t)(f / 32) * d * 4; }
+    static constexpr int APART = 256, ROUTING = APART, X = ROUTING + STACK_BLOCKS * 2 * 8;
+    __host__ __device__ static constexpr int counters(int d) { return X + 2 * (d / 2 * 8); }
+    __host__ __device__ static constexpr int cleared(int d, int L) { return counters(d) + L * SPREAD * APART; }  // the partial sums begin there
+    static size_t bytes(int d, int f, int L) { return cleared(d, L) + (size_t)(f / 32) * d * 4; }
 };
 
 struct DecodeStack {
@@ -54,7 +58,7 @@ struct DecodeStack {
     int32_t *row_of, *offsets, *src_row;  // [L], [L][E+1], [L][src_stride]
     const char *w_base;
     size_t w_stride, block_stride;
-    char *scratch;
+    char *scratch;  // the step's workspace
     uint32_t *flags;
     int f, L, src_stride;
     const __bf16 *gate_w[STACK_BLOCKS];
@@ -93,47 +97,54 @@ __device__ inline void take_pairs(__amdgpu_buffer_rsrc_t buf, Offset offset, uin
     }
 }
 
+// Block 0's gate and, in the other workgroups, the step's shared words set to zero.
+template <int EV>
+__global__ __launch_bounds__(GS_THREADS) void ffn_decode_stack_begin_kernel(
+    const __bf16 *__restrict__ x, const __bf16 *__restrict__ w, const float *__restrict__ bias, int d, int32_t *__restrict__ idx, float *__restrict__ prob,
+    uint32_t *flags, int32_t *__restrict__ row_of, int32_t *__restrict__ offsets, int32_t *__restrict__ src_row, uint4 *__restrict__ words, int n_words) {
+    if (blockIdx.x == 0) {
+        gate_small_body<EV, 1>(x, w, bias, 1, d, 1, idx, prob, nullptr, flags, row_of, offsets, src_row);
+        return;
+    }
+    const int i = (blockIdx.x - 1) * GS_THREADS + threadIdx.x;
+    if (i < n_words) words[i] = make_uint4(0, 0, 0, 0);
+}
+
 template <int KT, int EV>
 __global__ __launch_bounds__(256, 2) void ffn_decode_stack_kernel(DecodeStack s) {
     constexpr int d = KT * 32, E = 8 * EV, PL = 16, COLS = 256 / PL;  // p-lanes and float4 columns of a combine workgroup, as combine_partials_kernel<16>
     constexpr int n_combine = d / 4 / COLS;
     extern __shared__ __attribute__((aligned(16))) char smem[];
-    __shared__ uint32_t drawn, step;
+    __shared__ uint32_t drawn;
     __shared__ floatx4 sub[PL][COLS + 1];
     const int tid = threadIdx.x;
-    const int P = s.f / 32, per_block = 1 + P + n_combine;  // the last block has no gate, but block 0 two
+    const int P = s.f / 32, per_block = 1 + P + n_combine, tickets = s.L * per_block - 1;  // the last block has no gate
     uint32_t *ticket = reinterpret_cast<uint32_t *>(s.scratch);
     const __amdgpu_buffer_rsrc_t routing = buffer_at(s.scratch + StackScratch::ROUTING);
-    const __amdgpu_buffer_rsrc_t partial = buffer_at(s.scratch + StackScratch::X + 2 * (d / 2 * 8));
+    const __amdgpu_buffer_rsrc_t partial = buffer_at(s.scratch + StackScratch::cleared(d, s.L));
     auto x_words = [&](int i) { return buffer_at(s.scratch + StackScratch::X + (i & 1) * (d / 2 * 8)); };
-    auto done = [&](int i, int c) { return reinterpret_cast<uint32_t *>(s.scratch + StackScratch::COUNTERS) + (i * SPREAD + c) * (StackScratch::APART / 4); };
-    if (tid == 0) step = __hip_atomic_load(ticket + 1, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+    auto done = [&](int i, int c) { return reinterpret_cast<uint32_t *>(s.scratch + StackScratch::counters(d)) + (i * SPREAD + c) * (StackScratch::APART / 4); };
 #pragma unroll 1
     while (true) {
         __syncthreads();
         if (tid == 0) drawn = __hip_atomic_fetch_add(ticket, 1u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
         __syncthreads();
         int at = __builtin_amdgcn_readfirstlane(drawn);
-        if (at >= s.L * per_block) break;
-        const uint32_t steps = __builtin_amdgcn_readfirstlane(step);  // completed before this one
-        const uint32_t tags = (steps + 1) * (2 * STACK_BLOCKS);  // + i + 1: made by block i; + b: the routing of block b
-        int i = -1, what = 0;  // block; 0: gate of block i + 1, 1: experts, 2: combine
-        if (at > 0) {          // ticket 0: block 0's own gate
+        if (at >= tickets) break;
+        const int i = at / per_block;  // block
+        at -= i * per_block;
+        if (i == s.L - 1) at += 1;
+        int what = 0;  // 0: gate of block i + 1, 1: experts, 2: combine
+        if (at > 0) {
             at -= 1;
-            i = at / per_block;
-            at -= i * per_block;
-            if (i == s.L - 1) at += 1;
-            if (at > 0) {
-                at -= 1;
-                what = at < P ? 1 : 2;
-                if (what == 2) at -= P;
-            }
+            what = at < P ? 1 : 2;
+            if (what == 2) at -= P;
         }
-        // eight features of x_i, the first of them `first`
+        // eight features of x_i, the first of them `first`; x_i and the routing of block i, i > 0, have the tag i
         auto features = [&](int first, bool live) {
-            if (i <= 0) return *reinterpret_cast<const uint4 *>(s.x + first);
+            if (i == 0) return *reinterpret_cast<const uint4 *>(s.x + first);
             uint32_t a[2], b[2];
-            take_pairs<2>(x_words(i), [&](int n) { return first / 2 * 8 + n * 16; }, tags + i, live, a, b, s.flags);
+            take_pairs<2>(x_words(i), [&](int n) { return first / 2 * 8 + n * 16; }, i, live, a, b, s.flags);
             return make_uint4(a[0], b[0], a[1], b[1]);
         };
         if (what == 0) {
@@ -141,12 +152,17 @@ __global__ __launch_bounds__(256, 2) void ffn_decode_stack_kernel(DecodeStack s)
             gate_small_rows<EV, 1>([&](int, int first) { return __builtin_bit_cast(gs_bf16x8, features(first, 8 * tid < d)); }, s.gate_w[b], s.gate_b[b], 1,
                                    d, 1, s.idx + b, s.prob + b, nullptr, s.flags, s.row_of + b, s.offsets + b * (E + 1),
                                    s.src_row + (size_t)b * s.src_stride, [&](const int32_t *idx, const float *prob) {
-                                       if (tid == 0) put_pair(routing, b * 16, (uint32_t)idx[0], __float_as_uint(prob[0]), tags + b);
+                                       if (tid == 0) put_pair(routing, b * 16, (uint32_t)idx[0], __float_as_uint(prob[0]), b);
                                    });
             continue;
         }
         uint32_t expert[1], prob[1];
-        take_pairs<1>(routing, [&](int) { return i * 16; }, tags + i, true, expert, prob, s.flags);
+        if (i == 0) {
+            expert[0] = s.idx[0];
+            prob[0] = __float_as_uint(s.prob[0]);
+        } else {
+            take_pairs<1>(routing, [&](int) { return i * 16; }, i, true, expert, prob, s.flags);
+        }
         const int e = min(E - 1, (int)__builtin_amdgcn_readfirstlane(expert[0]));
         if (what == 1) {
             decode_sub_slab<KT>(
@@ -177,14 +193,14 @@ __global__ __launch_bounds__(256, 2) void ffn_decode_stack_kernel(DecodeStack s)
             res = reinterpret_cast<const bf16x4 *>(s.x)[c4];
         } else if (tid < 64) {  // all of it has been there since the experts began
             uint32_t a[1], b[1];
-            take_pairs<1>(x_words(i), [&](int) { return c4 * 16; }, tags + i, true, a, b, s.flags);
+            take_pairs<1>(x_words(i), [&](int) { return c4 * 16; }, i, true, a, b, s.flags);
             res = __builtin_bit_cast(bf16x4, make_uint2(a[0], b[0]));
         }
         {   // all partial sums of the block: every wavefront waits by itself
-            const int c = tid & 63, share = c < SPREAD ? (P - c + SPREAD - 1) / SPREAD : 0;
-            const uint32_t want = c < SPREAD ? (steps + 1) * share : 0;
+            const int c = tid & 63;
+            const uint32_t want = c < SPREAD ? (P - c + SPREAD - 1) / SPREAD : 0;
             const unsigned long long t0 = wall_clock64();
-            while (__any(c < SPREAD && (int)(__hip_atomic_load(done(i, c & (SPREAD - 1)), __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT) - want) < 0)) {
+            while (__any(c < SPREAD && __hip_atomic_load(done(i, c & (SPREAD - 1)), __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT) < want)) {
                 if (wall_clock64() - t0 > STACK_PATIENCE) {
                     if (c == 0) atomicOr(s.flags, kFlagStalled);
                     break;
@@ -219,26 +235,21 @@ __global__ __launch_bounds__(256, 2) void ffn_decode_stack_kernel(DecodeStack s)
                 x[c] = (__bf16)((float)res[c] + acc);
             }
             const uint2 words = __builtin_bit_cast(uint2, x);
-            if (i + 1 < s.L) put_pair(x_words(i + 1), c4 * 16, words.x, words.y, tags + i + 1);
+            if (i + 1 < s.L) put_pair(x_words(i + 1), c4 * 16, words.x, words.y, i + 1);
             reinterpret_cast<bf16x4 *>(const_cast<__bf16 *>(s.x) + (size_t)(i + 1) * d)[c4] = x;
             if (s.y) reinterpret_cast<bf16x4 *>(s.y + (size_t)i * d)[c4] = y;
         }
     }
-    // the last workgroup to find no work left: nobody draws or polls any more
-    if (tid == 0 && drawn == (uint32_t)(s.L * per_block) + gridDim.x - 1) {
-        __hip_atomic_store(ticket, 0u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
-        __hip_atomic_store(ticket + 1, step + 1, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
-    }
 }
 
-size_t decode_stack_scratch_bytes(const pgmoe_config &c) {
+size_t decode_stack_workspace_bytes(const pgmoe_config &c) {
     const bool may = c.dtype == PGMOE_BF16 && c.top_k == 1 && c.n_blocks >= DECODE_STACK_LEAST && c.n_blocks <= STACK_BLOCKS && gate_small_applies(c, 1) &&
                      ffn_launch_is_decode_sized(c, 1) && reduce_lanes(c.d_ff / 32) == 16;
-    return may ? StackScratch::bytes(c.d_model, c.d_ff) : 0;
+    return may ? StackScratch::bytes(c.d_model, c.d_ff, c.n_blocks) : 0;
 }
 
 bool decode_stack_applies(const pgmoe_ctx *ctx, int T) {
-    return T == 1 && ctx->decode_scratch && ctx->store_mode == STORE_RESIDENT && ctx->schedule == PGMOE_SCHED_PREGATED && ctx->distance == 1 &&
+    return T == 1 && ctx->decode_stack && ctx->store_mode == STORE_RESIDENT && ctx->schedule == PGMOE_SCHED_PREGATED && ctx->distance == 1 &&
            !ctx->trace && !ctx->tim_on && ctx->standin_us <= 0.f;
 }
 
@@ -255,7 +266,7 @@ int launch_decode_stack(pgmoe_ctx *ctx, const pgmoe_step_buffers *io, hipStream_
     s.w_base = ctx->store_base;
     s.w_stride = ctx->expert_stride;
     s.block_stride = ctx->block_stride;
-    s.scratch = ctx->decode_scratch;
+    s.scratch = (char *)io->workspace;
     s.flags = ctx->dev_flags;
     s.f = c.d_ff;
     s.L = c.n_blocks;
@@ -268,6 +279,11 @@ int launch_decode_stack(pgmoe_ctx *ctx, const pgmoe_step_buffers *io, hipStream_
     }
     const dim3 grid((unsigned)std::min(c.n_blocks, STACK_AHEAD) * (1 + c.d_ff / 32 + c.d_model / 64));
     const size_t lds = decode_lds_bytes(c.d_model / 32);
+    const int n_words = StackScratch::cleared(c.d_model, c.n_blocks) / 16;
+    hipLaunchKernelGGL(c.n_experts == 8 ? ffn_decode_stack_begin_kernel<1> : ffn_decode_stack_begin_kernel<2>, dim3(1 + (n_words + GS_THREADS - 1) / GS_THREADS),
+                       dim3(GS_THREADS), 0, stream, s.x, s.gate_w[0], s.gate_b[0], c.d_model, s.idx, s.prob, s.flags, s.row_of, s.offsets, s.src_row,
+                       (uint4 *)s.scratch, n_words);
+    PG_HIP(ctx, hipGetLastError());
 #define PG_STACK(KT_, EV_) hipLaunchKernelGGL((ffn_decode_stack_kernel<KT_, EV_>), grid, dim3(256), lds, stream, s)
     if (c.d_model == 768) {
         if (c.n_experts == 8) PG_STACK(24, 1);

@@ -58,7 +58,7 @@ struct pgmoe_ctx {
     unsigned long long *dev_copy_clock;  // [n_blocks][2] copy start / end of the block's last traced pull kernel (100 MHz ticks)
     int32_t *dev_src_row;  // [n_blocks][max_tokens * k] grouped row -> token, written by each block's routing
     int32_t *gate_counter = nullptr;  // [n_blocks] workgroups of the block's gate that have ended (gate_topk_route_kernel); zero between launches
-    char *decode_scratch = nullptr;  // of a one-launch step (ffn_decode_stack.hip); null: never taken
+    bool decode_stack = false;  // a step of one token can be ffn_decode_stack.hip's
     float *gate_planes = nullptr;  // partial logits between the two halves of a carried pre-gate (gate_small.h); null: none is ever carried so
     bool *routed;          // [n_blocks] host: this step's gate kernel already grouped the block's tokens
     // turn-taking of a stack step's migration kernels on the host link (see fetch.hip): position of
@@ -211,10 +211,11 @@ int launch_ffn(pgmoe_ctx *ctx, const char *w_base, size_t w_stride, bool slot_by
                const RowCombine *combine = nullptr);  // float32, src_row given, one expert per token: done by this launch, y_perm is left alone
 // Is a launch of n_rows rows the decode-sized kernel's?
 bool ffn_launch_is_decode_sized(const pgmoe_config &c, int n_rows);
-// A whole step of one token in one launch (ffn_decode_stack.hip), from DECODE_STACK_LEAST blocks on: with two and three blocks a step
-// that is waited for takes as long either way (8 experts of 768 x 3072: 32.0 against 32.6 us and 38.4 against 41.0; four blocks 45 against 79).
+// A whole step of one token in two launches (ffn_decode_stack.hip), from DECODE_STACK_LEAST blocks on: with two and three blocks a step
+// that is waited for takes as long either way (8 experts of 768 x 3072: 31.2 against 32.0 us and 37.7 against 40.8; four blocks 44 against 63).
+// With steps of four stacks in flight it would pay from one block on (8.3 against 12.0, 11.4 / 17.5, 10.1 / 24.4, 12.4 / 32.4 us for one to four).
 constexpr int DECODE_STACK_LEAST = 4;
-size_t decode_stack_scratch_bytes(const pgmoe_config &c);
+size_t decode_stack_workspace_bytes(const pgmoe_config &c);  // 0: never taken
 bool decode_stack_applies(const pgmoe_ctx *ctx, int T);
 int launch_decode_stack(pgmoe_ctx *ctx, const pgmoe_step_buffers *io, hipStream_t s);
 // p-lanes of the partial-sum reduction for P partials (fixes the order of the additions)

@@ -1,6 +1,6 @@
-"""The one-launch step of one token (batch-1 decode, experts resident) against the primitives called
+"""The two-launch step of one token (batch-1 decode, experts resident) against the primitives called
 one by one, bit for bit: numbers of blocks, widths, experts and sub-slabs at the edges of what it
-takes, steps one after the other, replayed from a graph, and the steps it leaves to launches."""
+takes, steps one after the other, several in flight, replayed from graphs, and the steps it leaves to launches."""
 import pytest
 import torch
 
@@ -26,19 +26,19 @@ def stack_of(H, T, d, f, E, k, L, max_tokens=None):
 ])
 def test_one_token_step(hx, T, d, f, E, k, L, one):  # noqa: F811
     H, B = hx
-    print(f"one-launch step: T={T} d={d} f={f} E={E} k={k} L={L}", flush=True)
+    print(f"two-launch step: T={T} d={d} f={f} E={E} k={k} L={L}", flush=True)
     w, stack = stack_of(H, T, d, f, E, k, L)
     stack.set_input(W.step_input(w, 0))
     stack.step()
     torch.cuda.synchronize()
-    assert (kernel_launches(stack.step, stack.compute) == 1) == one
+    assert (kernel_launches(stack.step, stack.compute) == 2) == one  # block 0's gate with the clearing, the rest
     stack.close()
     step_equals_primitives(hx, "bf16", T, d, f, E, k, L, False)
 
 
 def test_one_token_steps_follow_each_other_and_replay(hx):  # noqa: F811
-    """Tags and counts go on from step to step: many steps in a row, queued without a wait, then replays with eager
-    steps in between, each the same as in a context of its own; no wait has run out."""
+    """Many steps in a row, queued without a wait, then replays with eager steps in between, each the same as in a context
+    of its own; no wait has run out."""
     H, B = hx
     w, stack = stack_of(H, 1, 768, 3072, 8, 1, 6)
     other = H.Stack(w, stack.store)
@@ -92,3 +92,115 @@ def test_one_token_step_in_a_context_for_more(hx):  # noqa: F811
         torch.cuda.synchronize()
     roomy.close()
     tight.close()
+
+
+class Lane:
+    """A stream of its own and `n` one-token steps with inputs, outputs and (shared by the lane's steps) scratch of their own."""
+
+    def __init__(self, stack, n, first):
+        self.stack, self.stream, w, k = stack, torch.cuda.Stream(), stack.w, stack.w.top_k
+        new = lambda like, *shape: torch.zeros((n, *shape), dtype=like.dtype, device="cuda")  # noqa: E731
+        L, d, E = w.n_blocks, w.d_model, w.n_experts
+        self.out = (new(stack.x_states, L + 1, 1, d), new(stack.y_blocks, L, 1, d), new(stack.topk_idx, L, 1, k), new(stack.topk_prob, L, 1, k),
+                    new(stack.row_of, L, k), new(stack.expert_offsets, L, E + 1))
+        for i in range(n):
+            self.out[0][i, 0] = stack_input(w, first + i)
+        # what a step finds in its workspace is anybody's: here words that look like tags and counts of block 1
+        self.workspace = torch.full((stack.ctx.workspace_bytes // 4,), 1, dtype=torch.int32, device="cuda")
+        perm = torch.zeros((2, k, d), dtype=stack.x_states.dtype, device="cuda")
+        self.bufs = [stack.ctx.make_step_buffers(stack.gate_w, stack.gate_b, *(t[i] for t in self.out), perm[0], perm[1], self.workspace) for i in range(n)]
+        torch.cuda.synchronize()
+
+    def step(self, i):
+        self.stack.ctx.stack_step(self.bufs[i], 1, self.stream, self.stack.copy)
+
+    def clear(self):
+        self.out[0][:, 1:].zero_()
+        for t in self.out[1:]:
+            t.zero_()
+        torch.cuda.synchronize()
+
+
+def stack_input(w, n):
+    t = torch.from_numpy(W.step_input(w, n)).cuda()
+    return t if w.dtype == "f32" else t.bfloat16()
+
+
+def check_lanes(lanes, one_by_one):
+    """Every step of every lane, bit for bit, against the same step in a context that has nothing else in flight."""
+    for a, lane in enumerate(lanes):
+        n = len(lane.bufs)
+        alone = Lane(one_by_one, n, 0)
+        alone.out[0].copy_(lane.out[0])
+        alone.clear()
+        for i in range(n):
+            alone.step(i)
+            torch.cuda.synchronize()
+        for got, want in zip(lane.out, alone.out):
+            for i in range(n):
+                assert torch.equal(got[i], want[i]), f"lane {a}, step {i} of {n}"
+
+
+def lanes_in_flight(H, w, contexts, steps=16, lanes=3):
+    """Lanes dealt to `contexts` contexts, all their steps queued in turn without a wait, three times over."""
+    store = H.ExpertStore(w, H.config_for(w), threads=4)
+    stacks = [H.Stack(w, store) for _ in range(contexts)]
+    lanes = [Lane(stacks[a % contexts], steps, 100 * a) for a in range(lanes)]
+    alone = H.Stack(w, store)
+    alone.ctx.ffn_timing_begin(1)  # keeps the bf16 step to its separate launches
+    for _ in range(3):
+        for lane in lanes:
+            lane.clear()
+        for i in range(steps):
+            for lane in lanes:
+                lane.step(i)
+        torch.cuda.synchronize()
+        check_lanes(lanes, alone)
+    assert all(s.ctx.device_flags() == 0 for s in stacks)
+    alone.ctx.ffn_timing_end()
+    return stacks, lanes, alone
+
+
+@pytest.mark.parametrize("contexts", [1, 3])
+@pytest.mark.parametrize("d,f,E,L", [(768, 3072, 8, 6), (1024, 512, 16, 4)])
+def test_one_token_steps_in_flight_together(hx, d, f, E, L, contexts):  # noqa: F811
+    """Steps on streams of their own, of one context or of several, each with its own buffers and input, have nothing in common."""
+    H, B = hx
+    print(f"steps in flight: d={d} f={f} E={E} L={L} contexts={contexts}", flush=True)
+    stacks, lanes, alone = lanes_in_flight(H, W.Workload("decode_lanes", 84, L, d, f, E, 1, 1, 1, "bf16", 1.1, False), contexts)
+    assert kernel_launches(lambda: lanes[0].step(0), lanes[0].stream) == 2
+    for s in [*stacks, alone]:
+        s.close()
+
+
+def test_captured_one_token_steps_of_one_context_replay_together(hx):  # noqa: F811
+    H, B = hx
+    w = W.Workload("decode_lanes", 84, 6, 768, 3072, 8, 1, 1, 1, "bf16", 1.1, False)
+    stack = H.Stack(w, H.ExpertStore(w, H.config_for(w), threads=4))
+    alone = H.Stack(w, stack.store)
+    alone.ctx.ffn_timing_begin(1)
+    lanes = [Lane(stack, 4, 100 * a) for a in range(3)]
+    graphs = []
+    for lane in lanes:
+        graph = torch.cuda.CUDAGraph()
+        with torch.cuda.graph(graph, stream=lane.stream):
+            for i in range(4):
+                lane.step(i)
+        graphs.append(graph)
+    eager = Lane(stack, 4, 900)
+    for n in range(4):
+        for a, lane in enumerate([*lanes, eager]):
+            for i in range(4):
+                lane.out[0][i, 0] = stack_input(w, 1000 * n + 100 * a + i)
+            lane.clear()
+        for graph, lane in zip(graphs, lanes):
+            with torch.cuda.stream(lane.stream):
+                graph.replay()
+        for i in range(4):
+            eager.step(i)
+        torch.cuda.synchronize()
+        check_lanes([*lanes, eager], alone)
+    assert stack.ctx.device_flags() == 0
+    alone.ctx.ffn_timing_end()
+    stack.close()
+    alone.close()
