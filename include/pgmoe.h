@@ -435,7 +435,8 @@ int pgmoe_get_block_trace(pgmoe_ctx *ctx, int block, pgmoe_block_trace *out /* h
 /* Sticky device-side condition bits since the last call of this function (synchronises the
  * device): bit 0 = a NaN logit was seen by a gate, bit 1 = an expert index outside [0,E)
  * reached pgmoe_permute or the pull kernel, bit 2 = more distinct experts than slots,
- * bit 3 = workgroups of one pgmoe_stack_step launch waited half a second for each other in vain (its results are wrong). */
+ * bit 3 = workgroups of a one-token pgmoe_stack_step looked for each other's results a million times (half a second and
+ * more) in vain; from there on the outputs of this step and of one-token steps after it are NaN, until this function is called. */
 int pgmoe_device_flags(pgmoe_ctx *ctx, uint32_t *flags_out /* host */);
 
 #ifdef __cplusplus

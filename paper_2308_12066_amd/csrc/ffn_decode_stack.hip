@@ -17,8 +17,9 @@
 // buffers of their own have nothing in common, also those of one context on several streams or in several graphs.
 //
 // No workgroup waits for one that may not have started: work is drawn as tickets in the order above, and whoever holds a ticket waits for
-// lower ones only, so the lowest one still at work never waits, whatever else occupies the GPU.  Waits are bounded all the same (half a
-// second), after which the context's flags say that results are wrong.
+// lower ones only, so the lowest one still at work never waits, whatever else occupies the GPU.  Waits are bounded all the same, by the looks
+// taken and not by the clock, which goes on while the queue is not on the GPU; after that the context's flags say that results
+// are wrong, and whoever combines then leaves NaN.
 //
 // 8 experts of 768 x 3072, six blocks: 32 us a step with steps of several stacks in flight, 45 one after the other on a stream, 56 waited for;
 // 55, 58 and 73 as launches.  Clearing costs nothing beside block 0's gate: with state that was left ready by the step
@@ -37,7 +38,7 @@ constexpr int STACK_AHEAD = 2;    // blocks whose workgroups are there at once: 
                                   // block runs; more would only wait, in places that steps of other stacks could use
 constexpr int PAST_L2 = 16;       // cache policy of loads and stores: sc1
 constexpr int SPREAD = 8;         // counters of a block's finished expert workgroups, each of the form workgroup number % SPREAD
-constexpr unsigned long long STACK_PATIENCE = 50000000;  // half a second of the 100 MHz clock
+constexpr int STACK_PATIENCE = 1 << 20;  // most looks of a wait: half a second and more, each is a load past L2
 
 typedef uint32_t uint32x4 __attribute__((ext_vector_type(4)));
 
@@ -73,11 +74,15 @@ __device__ inline __amdgpu_buffer_rsrc_t buffer_at(const void *base) {
 __device__ inline void put_pair(__amdgpu_buffer_rsrc_t buf, int offset, uint32_t a, uint32_t b, uint32_t tag) {
     __builtin_amdgcn_raw_buffer_store_b128(uint32x4{a, tag, b, tag}, buf, offset, 0, PAST_L2);
 }
+// A wait of this wavefront has run out: known to whoever sees what this workgroup hands over next.
+__device__ inline void wait_failed(uint32_t *flags) {
+    if ((threadIdx.x & 63) == 0) atomicOr(flags, kFlagStalled);
+    asm volatile("s_waitcnt vmcnt(0)" ::: "memory");
+}
 // N pairs of tagged words per lane, at offset(n), polled until all of a wavefront's have the tag (lanes that are not `live` take what they get).
 template <int N, typename Offset>
 __device__ inline void take_pairs(__amdgpu_buffer_rsrc_t buf, Offset offset, uint32_t tag, bool live, uint32_t (&a)[N], uint32_t (&b)[N], uint32_t *flags) {
-    const unsigned long long t0 = wall_clock64();
-    while (true) {
+    for (int looks = 1;; ++looks) {
         uint32x4 v[N];
         bool there = true;
 #pragma unroll
@@ -89,10 +94,7 @@ __device__ inline void take_pairs(__amdgpu_buffer_rsrc_t buf, Offset offset, uin
             b[n] = v[n].z;
         }
         if (__all(there || !live)) return;
-        if (wall_clock64() - t0 > STACK_PATIENCE) {
-            if ((threadIdx.x & 63) == 0) atomicOr(flags, kFlagStalled);
-            return;
-        }
+        if (looks == STACK_PATIENCE) return wait_failed(flags);
         __builtin_amdgcn_s_sleep(1);
     }
 }
@@ -163,7 +165,7 @@ __global__ __launch_bounds__(256, 2) void ffn_decode_stack_kernel(DecodeStack s)
         } else {
             take_pairs<1>(routing, [&](int) { return i * 16; }, i, true, expert, prob, s.flags);
         }
-        const int e = min(E - 1, (int)__builtin_amdgcn_readfirstlane(expert[0]));
+        const int e = min((uint32_t)(E - 1), (uint32_t)__builtin_amdgcn_readfirstlane(expert[0]));
         if (what == 1) {
             decode_sub_slab<KT>(
                 smem, s.w_base + (size_t)i * s.block_stride + (size_t)e * s.w_stride, s.f, at,
@@ -199,16 +201,17 @@ __global__ __launch_bounds__(256, 2) void ffn_decode_stack_kernel(DecodeStack s)
         {   // all partial sums of the block: every wavefront waits by itself
             const int c = tid & 63;
             const uint32_t want = c < SPREAD ? (P - c + SPREAD - 1) / SPREAD : 0;
-            const unsigned long long t0 = wall_clock64();
-            while (__any(c < SPREAD && __hip_atomic_load(done(i, c & (SPREAD - 1)), __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT) < want)) {
-                if (wall_clock64() - t0 > STACK_PATIENCE) {
-                    if (c == 0) atomicOr(s.flags, kFlagStalled);
+            for (int looks = 1; __any(c < SPREAD && __hip_atomic_load(done(i, c & (SPREAD - 1)), __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT) < want);
+                 ++looks) {
+                if (looks == STACK_PATIENCE) {
+                    wait_failed(s.flags);
                     break;
                 }
                 __builtin_amdgcn_s_sleep(1);
             }
             asm volatile("" ::: "memory");
         }
+        const uint32_t flags = __hip_atomic_load(s.flags, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
         floatx4 sum = floatx4{0.f, 0.f, 0.f, 0.f};
         constexpr int U = 8;
         for (int p0 = pl; p0 < P; p0 += PL * U) {
@@ -226,7 +229,7 @@ __global__ __launch_bounds__(256, 2) void ffn_decode_stack_kernel(DecodeStack s)
             sum = sub[0][col];
 #pragma unroll
             for (int l = 1; l < PL; ++l) sum += sub[l][col];
-            const float p = __uint_as_float(prob[0]);
+            const float p = flags & kFlagStalled ? NAN : __uint_as_float(prob[0]);
             bf16x4 y, x;
 #pragma unroll
             for (int c = 0; c < 4; ++c) {

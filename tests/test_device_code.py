@@ -55,6 +55,19 @@ def test_a_load_into_lds_leaves_a_wait_state_after_m0_is_written(code_objects):
     assert not bad, f"{len(bad)} of {seen} loads follow the write of M0 at once, the first in {bad[0]}"
 
 
+def test_waits_of_the_one_token_step_read_no_clock(code_objects):
+    """Its workgroups wait for each other for a number of looks.  The clock goes on while other processes
+    have the GPU: a wait that it bounds may give up on its first look after a pause."""
+    seen = 0
+    for obj in code_objects:
+        text = subprocess.run([os.path.join(LLVM, "llvm-objdump"), "-d", "--no-show-raw-insn", obj], check=True, capture_output=True, text=True).stdout
+        for body in re.split(r"^[0-9a-f]+ (?=<)", text, flags=re.M):
+            if "ffn_decode_stack_kernel" in body.split("\n", 1)[0]:
+                seen += 1
+                assert not re.search(r"s_mem(real)?time|s_getreg_b32", body), body.split("\n", 1)[0]
+    assert seen == 4
+
+
 def kernels(code_objects):
     """{mangled name: {field: integer}} of the code objects' kernel metadata."""
     out = {}
