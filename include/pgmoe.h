@@ -36,8 +36,8 @@
  *   - One context serves one stack on one device, from one host thread at a time.  The stream work of
  *     its steps is ordered by the caller (one stream, or events), also where captured steps are
  *     replayed: the row -> token maps, with a host store the expert slots too, are the context's.
- *     Steps of one token in bfloat16 with 8 or 16 resident experts have no such state: several may be in
- *     flight if each has pgmoe_step_buffers of its own.
+ *     Steps of one token with resident experts, in float32 or with 8 or 16 of them in bfloat16, have no such state:
+ *     several may be in flight if each has pgmoe_step_buffers of its own.
  */
 #ifndef PGMOE_H
 #define PGMOE_H

@@ -169,7 +169,7 @@ struct RoutedGate {
     int32_t *idx;
     float *prob;
     int32_t *row_of, *offsets, *src_row;
-    int32_t *counter;  // zero; left zero
+    uint32_t *counter;  // of batches of this size; zero, left zero
 };
 constexpr int GATE_ROUTE_ENTRIES = 512;  // most (token, choice) pairs
 
@@ -249,10 +249,11 @@ __global__ __launch_bounds__(GATE_THREADS) void gate_topk_route_kernel(const XT 
         __hip_atomic_store(g.idx + (size_t)blockIdx.x * k + j, chosen[j], __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
     asm volatile("s_waitcnt vmcnt(0)" ::: "memory");
     __syncthreads();
-    if (tid == 0) last = __hip_atomic_fetch_add(g.counter, 1, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT) == T - 1;
+    // goes round after T workgroups: zero again behind any number of gates, in whatever order their workgroups came, and a
+    // gate of one workgroup is not told from another by it
+    if (tid == 0) last = atomicInc(g.counter, T - 1) == (uint32_t)T - 1;
     __syncthreads();
     if (!last) return;  // uniform over the workgroup
-    if (tid == 0) __hip_atomic_store(g.counter, 0, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
     group_entries(g.idx, T * k, E, k, g.row_of, g.offsets, g.src_row);
 }
 
@@ -522,7 +523,7 @@ static int launch_gate_mfma(pgmoe_ctx *ctx, const __bf16 *x, const __bf16 *w, co
 // Gates the vector kernel serves with a workgroup per token and whose choices its last workgroup can group.
 bool gate_groups_tokens(const pgmoe_config &c, int T) {
     const int E = c.n_experts;
-    return ffn_f32_reads_rows_in_place(c) && E >= 8 && E <= PGMOE_MAX_EXPERTS && (E & (E - 1)) == 0 && T <= 256 && T * c.top_k <= GATE_ROUTE_ENTRIES;
+    return ffn_f32_reads_rows_in_place(c) && E >= 8 && E <= PGMOE_MAX_EXPERTS && (E & (E - 1)) == 0 && T <= GATE_GROUP_TOKENS && T * c.top_k <= GATE_ROUTE_ENTRIES;
 }
 
 int launch_gates_grouped(pgmoe_ctx *ctx, const void *x, int T, const FusedGate *gates, int n, const int *blocks, hipStream_t s) {
@@ -530,7 +531,7 @@ int launch_gates_grouped(pgmoe_ctx *ctx, const void *x, int T, const FusedGate *
     RoutedGate g[2] = {};
     for (int i = 0; i < n; ++i)
         g[i] = RoutedGate{gates[i].w, gates[i].bias, gates[i].idx, gates[i].prob, gates[i].row_of, gates[i].offsets, gates[i].src_row,
-                          ctx->gate_counter + blocks[i]};
+                          ctx->gate_counter + (size_t)blocks[i] * gate_counters(c) + T - 1};
     hipLaunchKernelGGL(gate_topk_route_kernel<float>, dim3(T, n), dim3(GATE_THREADS), 0, s, (const float *)x, T, c.d_model, c.n_experts,
                        c.top_k, ctx->dev_flags, g[0], g[1]);
     PG_HIP(ctx, hipGetLastError());

@@ -57,7 +57,7 @@ struct pgmoe_ctx {
     int32_t *dev_unique;   // [n_blocks] distinct experts found by the pull kernel (dev_flags + 64 bytes)
     unsigned long long *dev_copy_clock;  // [n_blocks][2] copy start / end of the block's last traced pull kernel (100 MHz ticks)
     int32_t *dev_src_row;  // [n_blocks][max_tokens * k] grouped row -> token, written by each block's routing
-    int32_t *gate_counter = nullptr;  // [n_blocks] workgroups of the block's gate that have ended (gate_topk_route_kernel); zero between launches
+    uint32_t *gate_counter = nullptr;  // [n_blocks][gate_counters] workgroups of the block's gate of 1, 2, .. tokens that have ended (gate_topk_route_kernel)
     bool decode_stack = false;  // a step of one token can be ffn_decode_stack.hip's
     float *gate_planes = nullptr;  // partial logits between the two halves of a carried pre-gate (gate_small.h); null: none is ever carried so
     bool *routed;          // [n_blocks] host: this step's gate kernel already grouped the block's tokens
@@ -191,6 +191,10 @@ enum GateCarried { GATE_LEFT = 0, GATE_STARTED = 1, GATE_ROUTED = 2 };
 // Float32: do the gates of a batch of T tokens group the tokens themselves?  Then launch_gates_grouped evaluates one or two gates on the same x
 // (gates[i].T and .x are not read) and groups their blocks' tokens.
 bool gate_groups_tokens(const pgmoe_config &c, int T);
+constexpr int GATE_GROUP_TOKENS = 256;  // most tokens of such a batch
+inline size_t gate_counters(const pgmoe_config &c) {  // per block
+    return c.dtype == PGMOE_F32 ? (c.max_tokens < GATE_GROUP_TOKENS ? c.max_tokens : GATE_GROUP_TOKENS) : 0;
+}
 int launch_gates_grouped(pgmoe_ctx *ctx, const void *x, int T, const FusedGate *gates, int n, const int *blocks, hipStream_t s);
 // What a float32 expert launch with one expert per token can do with its results instead of leaving them in y_perm: the combine of the block.
 struct RowCombine {

@@ -5,6 +5,7 @@ import torch
 
 import workloads as W
 from launch_count import kernel_launches
+from test_gpu_decode_stack import lanes_in_flight
 from test_gpu_parity import hx, test_stack_step_equals_the_primitive_call_sequence as step_equals_primitives  # noqa: F401
 
 pytestmark = pytest.mark.gpu
@@ -48,3 +49,34 @@ def test_f32_step_replayed_from_a_graph(hx, T, k, launches):  # noqa: F811
         for a, b in zip(got, (stack.x_states, stack.y_blocks, stack.topk_idx, stack.row_of, stack.expert_offsets)):
             assert torch.equal(a, b)
     stack.close()
+
+
+@pytest.mark.parametrize("E,k,L,contexts", [(8, 1, 3, 1), (8, 2, 2, 1), (64, 1, 1, 1), (8, 1, 2, 3)])
+def test_one_token_f32_steps_in_flight_together(hx, E, k, L, contexts):  # noqa: F811
+    """Steps on streams of their own, each with its own buffers: no gate takes another's workgroup for its own."""
+    H, B = hx
+    print(f"f32 steps in flight: E={E} k={k} L={L} contexts={contexts}", flush=True)
+    stacks, lanes, alone = lanes_in_flight(H, W.Workload("f32_lanes", 85, L, 64, 256, E, k, 1, 1, "f32", 1.1, False), contexts)
+    for s in [*stacks, alone]:
+        s.close()
+
+
+def test_f32_batches_of_changing_size_in_one_context(hx):  # noqa: F811
+    """Each batch size's gates count for themselves."""
+    H, B = hx
+    w = W.Workload("f32_sizes", 86, 2, 64, 256, 8, 1, 256, 1, "f32", 0.0, False)
+    roomy = H.Stack(w, H.ExpertStore(w, H.config_for(w), threads=2))
+    for T in (256, 1, 33, 256, 2, 33, 1):
+        tight = H.Stack(w.replace(tokens=T), roomy.store)
+        x0 = W.step_input(w, T)[:T]
+        tight.set_input(x0)
+        tight.step()
+        roomy.x_states.reshape(-1)[: T * 64].copy_(tight.x_states[0].reshape(-1))
+        torch.cuda.synchronize()
+        for _ in range(2):
+            roomy.step(T=T)
+            torch.cuda.synchronize()
+            assert torch.equal(roomy.x_states.reshape(-1)[: 3 * T * 64], tight.x_states.reshape(-1)), T
+            assert torch.equal(roomy.row_of.reshape(-1)[: 2 * T], tight.row_of.reshape(-1)), T
+        tight.close()
+    roomy.close()
