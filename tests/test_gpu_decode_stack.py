@@ -37,16 +37,17 @@ def test_one_token_step(hx, T, d, f, E, k, L, one):  # noqa: F811
 
 
 def test_one_token_steps_follow_each_other_and_replay(hx):  # noqa: F811
-    """Many steps in a row, queued without a wait, then replays with eager steps in between, each the same as in a context
-    of its own; no wait has run out."""
+    """Many steps of different inputs in a row, queued without a wait, then replays with eager steps on another input in between, each
+    the same as in a context of its own; no wait has run out."""
     H, B = hx
     w, stack = stack_of(H, 1, 768, 3072, 8, 1, 6)
     other = H.Stack(w, stack.store)
     keep = lambda s: [t.clone() for t in (s.x_states, s.y_blocks, s.topk_idx, s.topk_prob, s.row_of, s.expert_offsets)]  # noqa: E731
+    row = Lane(stack, 40, 0)
     for n in range(40):
-        stack.set_input(W.step_input(w, n))
-        for _ in range(3):
-            stack.step()
+        row.step(n)
+    torch.cuda.synchronize()
+    check_lanes([row], other)
     want = {}
     for n in range(4):
         other.set_input(W.step_input(w, n))
@@ -58,16 +59,14 @@ def test_one_token_steps_follow_each_other_and_replay(hx):  # noqa: F811
     with torch.cuda.graph(graph, stream=stack.compute):
         stack.step()
     for n in (0, 1, 2, 3, 1):
-        stack.set_input(W.step_input(w, n))
-        torch.cuda.synchronize()
-        graph.replay()
-        torch.cuda.synchronize()
-        for a, b in zip(keep(stack), want[n]):
-            assert torch.equal(a, b)
-        stack.step()
-        torch.cuda.synchronize()
-        for a, b in zip(keep(stack), want[n]):
-            assert torch.equal(a, b)
+        for m, step in ((n, graph.replay), ((n + 1) % 4, stack.step)):
+            for t in (stack.x_states, stack.y_blocks, stack.topk_idx, stack.topk_prob, stack.row_of, stack.expert_offsets):
+                t.zero_()
+            stack.set_input(W.step_input(w, m))
+            step()
+            torch.cuda.synchronize()
+            for a, b in zip(keep(stack), want[m]):
+                assert torch.equal(a, b)
     assert stack.ctx.device_flags() == 0 and other.ctx.device_flags() == 0
     stack.close()
     other.close()
@@ -204,3 +203,58 @@ def test_captured_one_token_steps_of_one_context_replay_together(hx):  # noqa: F
     alone.ctx.ffn_timing_end()
     stack.close()
     alone.close()
+
+
+def same(a, b):
+    """Equal, with NaN in the same places."""
+    return torch.equal(a.isnan(), b.isnan()) and torch.equal(a.nan_to_num(), b.nan_to_num())
+
+
+def options_hold(H, B, w, reference):
+    """A step without y_blocks, one whose gates see a NaN logit and one of a hidden state with a NaN: the values of the same step made by
+    `reference(stack)`, another stack on the same experts that goes another way, and the NaN flag."""
+    store = H.ExpertStore(w, H.config_for(w), threads=4)
+    for bad_bias, bad_x in ((False, False), (True, False), (False, True)):
+        gates = [(gw, gb.copy()) for gw, gb in W.gate_tensors(w)]
+        assert not any((gates[0][1] == gb).all() for _, gb in gates[1:])  # every block's bias is another
+        if bad_bias:
+            for n, (_, gb) in enumerate(gates):
+                gb[n % w.n_experts] = float("nan")
+        x0 = W.step_input(w, 3)
+        if bad_x:
+            x0[-1, 5] = float("nan")
+        got = []
+        for other in (False, True):
+            stack = H.Stack(w, store, gates=gates)
+            x_in = torch.from_numpy(x0).cuda().to(stack.x_states.dtype)
+            stack.x_states[0].copy_(x_in)
+            torch.cuda.synchronize()
+            (reference if other else H.Stack.step)(stack)
+            torch.cuda.synchronize()
+            got.append([t.clone() for t in (stack.x_states, stack.y_blocks, stack.topk_idx, stack.topk_prob, stack.row_of, stack.expert_offsets)])
+            assert stack.ctx.device_flags() == (1 if bad_bias or bad_x else 0)
+            if not other:  # again, without the blocks' outputs
+                stack.x_states[1:].zero_()
+                stack.y_blocks.zero_()
+                bufs = stack.ctx.make_step_buffers(stack.gate_w, stack.gate_b, stack.x_states, None, stack.topk_idx, stack.topk_prob, stack.row_of,
+                                                   stack.expert_offsets, stack.x_perm, stack.y_perm, stack.workspace)
+                torch.cuda.synchronize()
+                stack.ctx.stack_step(bufs, w.tokens, stack.compute, stack.copy)
+                torch.cuda.synchronize()
+                assert same(stack.x_states, got[0][0]) and not stack.y_blocks.any()
+            stack.close()
+        for a, b in zip(*got):
+            assert same(a, b), (bad_bias, bad_x)
+        assert bool(got[0][0].isnan().any()) == bad_x
+
+
+@pytest.mark.parametrize("d,f,E,L", [(768, 320, 8, 5), (1024, 512, 16, 4)])
+def test_one_token_step_with_biases_without_outputs_and_with_nan(hx, d, f, E, L):  # noqa: F811
+    H, B = hx
+    print(f"options: d={d} f={f} E={E} L={L}", flush=True)
+
+    def launches(stack):
+        stack.ctx.ffn_timing_begin(1)
+        stack.step()
+
+    options_hold(H, B, W.Workload("decode_options", 87, L, d, f, E, 1, 1, 1, "bf16", 1.1, False), launches)

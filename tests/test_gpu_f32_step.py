@@ -5,7 +5,7 @@ import torch
 
 import workloads as W
 from launch_count import kernel_launches
-from test_gpu_decode_stack import lanes_in_flight
+from test_gpu_decode_stack import lanes_in_flight, options_hold
 from test_gpu_parity import hx, test_stack_step_equals_the_primitive_call_sequence as step_equals_primitives  # noqa: F401
 
 pytestmark = pytest.mark.gpu
@@ -38,16 +38,20 @@ def test_f32_step_replayed_from_a_graph(hx, T, k, launches):  # noqa: F811
     graph = torch.cuda.CUDAGraph()
     with torch.cuda.graph(graph, stream=stack.compute):
         stack.step()
+    other = H.Stack(w, stack.store)
+    out = lambda s: (s.x_states, s.y_blocks, s.topk_idx, s.topk_prob, s.row_of, s.expert_offsets)  # noqa: E731
     for n in range(4):
-        stack.set_input(W.step_input(w, n))
-        torch.cuda.synchronize()
-        graph.replay()
-        torch.cuda.synchronize()
-        got = [t.clone() for t in (stack.x_states, stack.y_blocks, stack.topk_idx, stack.row_of, stack.expert_offsets)]
-        stack.step()
-        torch.cuda.synchronize()
-        for a, b in zip(got, (stack.x_states, stack.y_blocks, stack.topk_idx, stack.row_of, stack.expert_offsets)):
-            assert torch.equal(a, b)
+        for m, step in ((n, graph.replay), (n + 10, stack.step)):
+            for t in out(stack):
+                t.zero_()
+            stack.set_input(W.step_input(w, m))
+            step()
+            other.set_input(W.step_input(w, m))
+            other.step()
+            torch.cuda.synchronize()
+            for a, b in zip(out(stack), out(other)):
+                assert torch.equal(a, b)
+    other.close()
     stack.close()
 
 
@@ -80,3 +84,22 @@ def test_f32_batches_of_changing_size_in_one_context(hx):  # noqa: F811
             assert torch.equal(roomy.row_of.reshape(-1)[: 2 * T], tight.row_of.reshape(-1)), T
         tight.close()
     roomy.close()
+
+
+@pytest.mark.parametrize("T,k,E,L", [(32, 1, 8, 3), (9, 2, 16, 2), (1, 1, 8, 2)])
+def test_f32_step_with_biases_without_outputs_and_with_nan(hx, T, k, E, L):  # noqa: F811
+    """Against the primitives called one by one."""
+    H, B = hx
+    print(f"f32 options: T={T} k={k} E={E} L={L}", flush=True)
+
+    def primitives(s):
+        ctx, nk = s.ctx, T * k
+        for i in range(L):
+            for g in ([0, 1] if i == 0 else [i + 1]):
+                if g < L:
+                    ctx.pregate_topk(s.x_states[i], s.gate_w[g], s.gate_b[g], T, s.topk_idx[g], s.topk_prob[g], None, s.compute)
+            ctx.permute(s.x_states[i], s.topk_idx[i], T, s.x_perm, s.row_of[i], s.expert_offsets[i], s.compute)
+            ctx.expert_ffn(i, s.x_perm, s.expert_offsets[i], nk, s.y_perm, s.workspace, s.compute)
+            ctx.combine(s.y_perm, s.row_of[i], s.topk_prob[i], T, s.y_blocks[i], s.x_states[i], s.x_states[i + 1], s.compute)
+
+    options_hold(H, B, W.Workload("f32_options", 88, L, 64, 256, E, k, T, 1, "f32", 1.1, False), primitives)

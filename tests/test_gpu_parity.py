@@ -925,16 +925,18 @@ def test_stacks_of_unusual_shapes_match_the_oracle(hx, dtype, T, d, f, E, k, L, 
 
 
 # ------------------------------------------------------------------------------ comparison schedules
-@pytest.mark.parametrize("schedule,fetch,offloaded", [
-    ("on_demand", "pull", True), ("on_demand", "memcpy", True), ("prefetch_all", "pull", True),
-    ("prefetch_all", "memcpy", True), ("on_demand", "-", False),
+@pytest.mark.parametrize("schedule,fetch,offloaded,dtype,k", [
+    ("on_demand", "pull", True, "bf16", 2), ("on_demand", "memcpy", True, "bf16", 2), ("prefetch_all", "pull", True, "bf16", 2),
+    ("prefetch_all", "memcpy", True, "bf16", 2), ("on_demand", "-", False, "bf16", 2),
+    # the second expert kernel combines
+    ("on_demand", "pull", True, "f32", 1), ("prefetch_all", "memcpy", True, "f32", 1), ("on_demand", "-", False, "f32", 1),
 ])
-def test_comparison_schedules_match_the_conventional_oracle(hx, schedule, fetch, offloaded):
+def test_comparison_schedules_match_the_conventional_oracle(hx, schedule, fetch, offloaded, dtype, k):
     """The paper's comparison systems on the same kernels: conventional wiring (every block routed
     by its own gate on its own input), experts fetched on demand or all prefetched; with a
     resident store this is the GPU-only design point."""
     H, B = hx
-    w = W.Workload("sched_case", 90, 4, 256, 512, 16, 2, 24, 1, "bf16", 1.1, offloaded)
+    w = W.Workload("sched_case", 90, 4, 256, 512, 16, k, 24, 1, dtype, 1.1, offloaded)
     stack, gates, cache = make_stack(H, w, threads=4, flags=B.FLAG_FETCH_MEMCPY if fetch == "memcpy" else 0)
     stack.ctx.set_schedule(B.SCHED_ON_DEMAND if schedule == "on_demand" else B.SCHED_PREFETCH_ALL)
     stack.ctx.fetch_timing(True)
