@@ -380,9 +380,11 @@ def run_workload(name, K, Wm, host_threads, with_cpu, cpu_steps, trace_steps, gp
         out["gpu_only"] = {"value": T * K / dt2, "unit": "tokens/s", "ms_per_step": 1e3 * dt2 / K,
                            "ffn_avg_launch_us": us2, "ffn_achieved_GBps": per_launch / (us2 * 1e-6) / 1e9,
                            "ffn_frac_of_hbm_peak": per_launch / (us2 * 1e-6) / 1e9 / HBM_PEAK_GBPS,
-                           "note": "same workload and routing with all experts resident in HBM (no migration); a "
-                                   "decode-sized expert launch here also carries the next block's pre-gate as one extra "
-                                   "workgroup, so its duration is that of the combined launch"}
+                           "note": "same workload and routing with all experts resident in HBM (no migration); ffn_* are of a "
+                                   "second pass with timing events around every expert launch, where a decode-sized one also "
+                                   "carries the next block's pre-gate as one extra workgroup; without events (value, ms_per_step) "
+                                   "a step of one token with one of 8 or 16 experts per block makes no such launches: its blocks "
+                                   "run in one launch behind block 0's gate"}
         if w.dtype == "bf16":
             # The expert-FFN kernel on its own: the primitive calls (pgmoe_permute, pgmoe_expert_ffn) over
             # the K steps' routings, block after block, so that every launch reads other experts than the

@@ -21,8 +21,8 @@
  *     "pinned" host memory obtained from hipHostMalloc.  The caller owns every buffer it
  *     passes and keeps it alive until the stream work that uses it has completed.  The
  *     library owns only the context: the expert slot pool, events and a small pinned
- *     staging area.  Allocation happens in set-up calls only: pgmoe_create() (flags, maps,
- *     events, staging), the first pgmoe_register_host_experts() on a context (slot pool and,
+ *     staging area.  Allocation happens in set-up calls only: pgmoe_create() (flags, counters, maps,
+ *     partial logits of carried gates, events, staging), the first pgmoe_register_host_experts() on a context (slot pool and,
  *     if configured, the expert cache), pgmoe_check_streams() (may create streams) and
  *     pgmoe_ffn_timing_begin() (its events).  The calls of the hot path (pgmoe_pregate_topk,
  *     pgmoe_fetch_experts, pgmoe_permute, pgmoe_expert_ffn, pgmoe_combine, pgmoe_stack_step)
@@ -35,7 +35,8 @@
  *     bfloat16); probabilities are float32; indices are int32.  T = 0 is a valid no-op.
  *   - One context serves one stack on one device, from one host thread at a time.  The stream work of
  *     its steps is ordered by the caller (one stream, or events), also where captured steps are
- *     replayed: the row -> token maps, with a host store the expert slots too, are the context's.
+ *     replayed: the row -> token maps and the partial logits of carried gates, with a host store the
+ *     expert slots too, are the context's.
  *     Steps of one token with resident experts, in float32 or with 8 or 16 of them in bfloat16, have no such state:
  *     several may be in flight if each has pgmoe_step_buffers of its own.
  */

@@ -22,7 +22,7 @@ SOURCES = ["api.hip", "gate.hip", "permute.hip", "ffn.hip", "ffn_gemm.hip", "ffn
 HIPCC = os.environ.get("HIPCC", "/opt/rocm/bin/hipcc")
 FLAGS = [
     "--offload-arch=gfx950", "-O3", "-std=c++17", "-fPIC", "-Wall", "-Wno-unused-function",
-    # the one inline-assembly statement (direct-to-LDS load) names M0 as clobbered, which the
+    # the inline-assembly statement of the direct-to-LDS load names M0 as clobbered, which the
     # compiler accepts with a warning about reserved registers
     "-Wno-inline-asm",
     # per-kernel register / scratch figures as remarks: checked below, kept in _build/

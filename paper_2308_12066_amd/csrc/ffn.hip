@@ -837,7 +837,7 @@ int launch_ffn(pgmoe_ctx *ctx, const char *w_base, size_t w_stride, bool slot_by
         // one more row of workgroups for the pre-gate this launch carries
         const CarriedGate dg = carry_gate(ctx, gate, true, keep_partials != nullptr, gate_done);
         const dim3 grid(p.max_chunks, p.n_partial + (dg.x ? 1 : 0));
-        const size_t lds = (size_t)kt * 1024 + 4096;
+        const size_t lds = decode_lds_bytes(kt);
 #define PG_DECODE(KT_, GATE_)                                                                                                    \
     hipLaunchKernelGGL((ffn_decode_kernel<KT_, GATE_>), grid, dim3(256), lds, s, (const __bf16 *)x_perm, offsets, c.n_experts, c.d_ff, \
                        w_base, w_stride, slot_by_rank ? 1 : 0, n_slots, table, partial, n_rows, src_row, dg)

@@ -24,9 +24,9 @@
 // 8 experts of 768 x 3072, six blocks: 32 us a step with steps of several stacks in flight, 45 one after the other on a stream, 56 waited for;
 // 55, 58 and 73 as launches.  Clearing costs nothing beside block 0's gate: with state that was left ready by the step
 // before, all in one launch, it was 32 as well.  Bound by hand-overs: a block is two of them, about a microsecond each for the store and the load, around two
-// memory latencies of its own (weights are there when x is).  With more than one (token, expert) pair the launches are faster: a
+// memory latencies of its own (weights are there when x is).  With more than one (token, expert) pair it does not pay: a
 // first version that took up to fifteen pairs took 52, 93 and 92 us for two tokens, four tokens and two tokens of two experts, the
-// launches 56, 66 and 70.
+// launches 56, 66 and 70; two tokens alone were little faster.
 #include "ffn_common.h"
 #include "ffn_decode.h"
 #include "gate_small.h"
