@@ -104,8 +104,8 @@ class Lane:
                     new(stack.row_of, L, k), new(stack.expert_offsets, L, E + 1))
         for i in range(n):
             self.out[0][i, 0] = stack_input(w, first + i)
-        # what a step finds in its workspace is anybody's: here words that look like tags and counts of block 1
-        self.workspace = torch.full((stack.ctx.workspace_bytes // 4,), 1, dtype=torch.int32, device="cuda")
+        # what a step finds in its workspace is anybody's: here words that look like tags and counts of block 1; some behind its end
+        self.workspace = torch.full((stack.ctx.workspace_bytes // 4 + 256,), 1, dtype=torch.int32, device="cuda")
         perm = torch.zeros((2, k, d), dtype=stack.x_states.dtype, device="cuda")
         self.bufs = [stack.ctx.make_step_buffers(stack.gate_w, stack.gate_b, *(t[i] for t in self.out), perm[0], perm[1], self.workspace) for i in range(n)]
         torch.cuda.synchronize()
@@ -129,6 +129,7 @@ def check_lanes(lanes, one_by_one):
     """Every step of every lane, bit for bit, against the same step in a context that has nothing else in flight."""
     for a, lane in enumerate(lanes):
         n = len(lane.bufs)
+        assert bool((lane.workspace[-256:] == 1).all())
         alone = Lane(one_by_one, n, 0)
         alone.out[0].copy_(lane.out[0])
         alone.clear()
