@@ -2,6 +2,8 @@
 // dense FFN, processes the tokens routed to it): the two products as two tiled GEMMs.
 #include <climits>
 #include <cmath>
+#include <type_traits>
+#include <utility>
 
 #include "ffn_common.h"
 
@@ -20,23 +22,25 @@ namespace pgmoe {
 // packed rows, the packed hidden activation the up-projection writes, and the pre-tiled weights).
 //
 // What bounds it and why the tile looks like this (measured on one MI355X):
-//  * large launches (128 experts of 1024 x 4096, 32768 rows): 322 us up, 361 us down, 454 and 464 with chunks of 128 rows
-//    and 128 columns before.  A CU keeps about 64 KiB of requests in flight whatever the ring holds (3, 4 and 5 stages
-//    are equal), and they return in order, so row tiles that L2 has wait behind weight tiles that HBM brings: the stream of
-//    weights runs at half of what it reaches alone (10 against 16 us for 38 MB beside / without the rows' tiles).
-//    Hence as many rows per weight tile as the registers hold (320: 160 accumulator registers of 246), no second
-//    chunk for an expert that has a few rows more than a power of two, and no request for a row tile the chunk lacks;
-//  * 8 experts of 768 x 3072, 4096 rows: 31 us up, 36 down with the weights from HBM, 29 and 34 from the last-level cache (33 and 35
-//    before; the vendor GEMM library: 27 + 41). The matrix cores
-//    alone take 21 of the first and the load stream alone 21; random operands hold them to about 1.6 PFLOP/s.  512 rows per
-//    expert are two chunks each, 192 workgroups; chunks of at most 256 rows (75 -> 79 us a block) and 192-column blocks
-//    (73 -> 74) were no better;
+//  * large launches (128 experts of 1024 x 4096, 32768 rows): power. The loop runs at 1.4 to 1.5 GHz and 1.2 PFLOP/s beside 4.8 TB/s of
+//    weights, where a loop of nothing but products on random operands reaches 1.7 at 1.7 GHz. 329 us up, 360 down (358 and 397 before the loop below);
+//    8 to 20 % of an item is its lookup, its first loads and its stores.  Hence as many rows per weight tile as the registers hold
+//    (320: 160 accumulator registers), no second chunk for an expert that has a few rows more than a power of two, and neither a
+//    request nor a product for a row tile the chunk lacks;
+//  * 8 experts of 768 x 3072, 4096 rows: 26.5 us up, 29.7 down with the weights in the last-level cache (30.5 and 34.6 before; the vendor GEMM
+//    library: 27 + 41).  A 32-k stage of 16 row tiles takes 0.62 us (0.76), 1170 clocks for 1024 of products: with a batch of LDS reads and
+//    loads behind every barrier it took 1540.  512 rows per expert are two chunks each, 192 workgroups; chunks of at most
+//    256 rows and 192-column blocks were no better;
+//  * few rows per expert: the stream of weights.  A chunk of one or two row tiles gets eight stages instead of four: a stage 0.46 -> 0.38 us;
 //  * matrix-core accumulators must be ordinary vector registers (build flag): with the accumulator-register form the
 //    register allocator copies accumulators about inside the k loop and every copy waits for the product before it;
 //  * one result straight in bf16 where no K slices are needed: the float32 partials of one slice cost the combine 14 us
 //    of 59 on the large launch.
 constexpr int GEMM_ROWS = 320;           // most rows of a chunk
 constexpr int GEMM_RT = GEMM_ROWS / 16;  // 16-row tiles of the largest chunk
+constexpr int GEMM_RING = 144 * 1024;    // bytes of LDS both operands pass through
+// A chunk's ring has the row tiles of the first of these that holds it: small chunks get more stages, not empty places.
+constexpr int GEMM_RING_TILES[] = {2, 8, GEMM_RT};
 
 // The chunks of an expert are of equal size (its rows dealt to as few chunks as hold them, in whole
 // 16-row tiles): 330 rows are two chunks of 176 and 154 rows, not 320 and 10, so no workgroup streams a whole
@@ -187,6 +191,15 @@ __global__ __launch_bounds__(512) void ffn_gemm_pack_rows_kernel(
                 dst[((size_t)(kt0 + k) * rt + wave + 8 * j) * 64 + cell] = live[j] ? v[j][k] : make_uint4(0, 0, 0, 0);
 }
 
+template <typename F, int... I>
+__device__ inline void static_for(F &&f, std::integer_sequence<int, I...>) {
+    (f(std::integral_constant<int, I>()), ...);
+}
+template <int N, typename F>
+__device__ inline void static_for(F &&f) {  // f(0) .. f(N - 1) with constants
+    static_for(f, std::make_integer_sequence<int, N>());
+}
+
 // Both operands are loaded straight into LDS (global_load_lds_dwordx4: each
 // lane's 16 bytes land at LDS base + 16 * lane, so a 1 KiB operand tile that is contiguous in
 // memory arrives in operand order with no register round trip and no staging writes).  A stage
@@ -202,8 +215,8 @@ __global__ __launch_bounds__(512) void ffn_gemm_pack_rows_kernel(
 __device__ inline unsigned lds_address(const void *p) {
     return (unsigned)(size_t)(__attribute__((address_space(3))) const char *)p;
 }
-__device__ inline void load_tile_to_lds(const char *src_lane, unsigned lds_tile) {  // src_lane: this lane's 16 bytes
-    asm volatile("s_mov_b32 m0, %1\n\ts_nop 0\n\tglobal_load_lds_dwordx4 %0, off" ::"v"(src_lane), "s"(lds_tile) : "memory", "m0");
+__device__ inline void load_tile_to_lds(const char *src, unsigned lane_off, unsigned lds_tile) {  // src: uniform; lane_off: 16 bytes a lane
+    asm volatile("s_mov_b32 m0, %2\n\ts_nop 0\n\tglobal_load_lds_dwordx4 %0, %1" ::"v"(lane_off), "s"(src), "s"(lds_tile) : "memory", "m0");
 }
 
 // What a workgroup of the tile kernel works on (all uniform).
@@ -216,105 +229,151 @@ struct GemmTile {
     bool no_weights;  // the expert got no slot: its rows are written as zeros
 };
 
-// The k loop and the epilogue for chunks of at most 16 * WM * MC rows.  Eight wavefronts as WM x WN; a
-// wavefront owns four column tiles (wn*4 ..) and the MC row tiles wm, wm + WM, ...  WM = 512 / BN.
-template <int BN, int NS, bool UP, int MC>
-__device__ inline void gemm_tile_body(const GemmTile &t, char *ring, void *__restrict__ h_chunk, float *__restrict__ partial_rows,
-                                      __bf16 *__restrict__ y_rows, int N, int n0) {
-    constexpr int WN = BN / 64, WM = 8 / WN;
-    constexpr int STAGE = (GEMM_RT + BN / 16) * 1024;  // per stage: the row tiles, then the column tiles
-    constexpr int LA = (WM * MC + 7) / 8, LW = BN / 128, LOADS = LA + LW;  // tiles a wavefront brings per stage
-    constexpr int MX = (MC + 1) / 2, MY = MC - MX;
-    static_assert(NS >= 3 && LOADS * (NS - 1) < 64, "NS - 1 stages of LOADS loads per wavefront in flight");
-    static_assert(8 * (LA - 1) <= WM * (MC - 1), "only a wavefront's last row tile may not exist");
-    const int lane = threadIdx.x & 63, wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
-    const int wn = wave & (WN - 1), wm = wave / WN;
+// The ring of a chunk of up to RTC row tiles: a stage is RTC row tiles, then BN / 16 column tiles.  NS is even (two turns of the k loop
+// share the weights' registers).
+template <int BN, int RTC>
+struct GemmRing {
+    static constexpr int STAGE = (RTC + BN / 16) * 1024, NS = GEMM_RING / STAGE / 2 * 2;
+};
 
-    // A wavefront brings row tiles wave, wave + 8, .. (the last of them only if the chunk has it: a wavefront
-    // without it counts one load less) and LW column tiles.  src[i]: this lane's 16 bytes of its i-th tile for the
-    // k-tile to request next.
-    const bool full = wave + 8 * (LA - 1) < t.rt;  // uniform over the wavefront
+// The k loop of one wavefront.  Eight wavefronts as WM x WN; a wavefront owns four column tiles (wn*4 ..) and the MC row tiles wm, wm + WM, ..
+// that the chunk has, and brings BN / 128 column tiles and LA row tiles (wave, wave + 8, ..) per stage.  Wavefronts of one workgroup run
+// different instantiations: what they share is the ring and the number of barriers.
+template <int BN, int RTC, int MC, int LA>
+__device__ inline void gemm_k_loop(const GemmTile &t, const char *ring, int wave, floatx4 (&acc)[4][MC > 0 ? MC : 1]) {
+    constexpr int STAGE = GemmRing<BN, RTC>::STAGE, NS = GemmRing<BN, RTC>::NS;
+    constexpr int WN = BN / 64, WM = 8 / WN, LW = BN / 128, LOADS = LA + LW;
+    constexpr int MX = (MC + 1) / 2, MY = MC - MX;
+    static_assert(NS >= 4 && LOADS * (NS - 1) < 64, "NS - 1 stages of LOADS loads per wavefront in flight");
+    const int lane = threadIdx.x & 63, wn = wave & (WN - 1), wm = wave / WN;
+
+    // src[i]: this wavefront's i-th tile (column tiles first) for the k-tile to request next (uniform)
     const char *src[LOADS];
 #pragma unroll
-    for (int i = 0; i < LW; ++i) src[i] = t.w + (size_t)(wave + 8 * i) * t.w_tile + lane * 16;
+    for (int i = 0; i < LW; ++i) src[i] = t.w + (size_t)(wave + 8 * i) * t.w_tile;
 #pragma unroll
-    for (int i = 0; i < LA; ++i) src[LW + i] = t.a + (size_t)min(wave + 8 * i, t.rt - 1) * 1024 + lane * 16;
+    for (int i = 0; i < LA; ++i) src[LW + i] = t.a + (size_t)(wave + 8 * i) * 1024;
     const size_t a_kt = (size_t)t.rt * 1024;
-    const unsigned a_lds = lds_address(ring) + wave * 1024, w_lds = a_lds + GEMM_RT * 1024;
-    int ahead = 0;  // k-tiles requested so far
-    auto issue = [&](unsigned stage_off) {  // the next k-tile of this wavefront's tiles, into the stage at stage_off
-#pragma unroll
-        for (int i = 0; i < LW; ++i) load_tile_to_lds(src[i], w_lds + stage_off + i * 8192);
-#pragma unroll
-        for (int i = 0; i + 1 < LA; ++i) load_tile_to_lds(src[LW + i], a_lds + stage_off + i * 8192);
-        if (full) load_tile_to_lds(src[LOADS - 1], a_lds + stage_off + (LA - 1) * 8192);
-        // a request past the last k-tile re-reads the last one: nobody needs it, the count stays uniform
-        const bool more = ++ahead < t.n_kt;
+    const unsigned a_lds = __builtin_amdgcn_readfirstlane(lds_address(ring)) + wave * 1024, w_lds = a_lds + RTC * 1024;
+    auto load = [&](int i, unsigned stage_off) {
+        load_tile_to_lds(src[i], lane * 16, (i < LW ? w_lds + i * 8192 : a_lds + (i - LW) * 8192) + stage_off);
+    };
+    auto advance = [&](bool more) {
         const size_t da = more ? a_kt : 0, dw = more ? t.w_kt : 0;
 #pragma unroll
-        for (int i = 0; i < LW; ++i) src[i] += dw;
-#pragma unroll
-        for (int i = 0; i < LA; ++i) src[LW + i] += da;
+        for (int i = 0; i < LOADS; ++i) src[i] += i < LW ? dw : da;
     };
+#pragma unroll
+    for (int st = 0; st < NS; ++st) {
+#pragma unroll
+        for (int i = 0; i < LOADS; ++i) load(i, st * STAGE);
+        advance(st + 1 < t.n_kt);  // fewer k-tiles than stages: the last one again, which nobody reads, so that the count stays uniform
+    }
 
-    floatx4 acc[4][MC];
+    const bf16x8 *A = reinterpret_cast<const bf16x8 *>(ring) + wm * 64 + lane;
+    const bf16x8 *W = reinterpret_cast<const bf16x8 *>(ring + RTC * 1024) + wn * 4 * 64 + lane;
+    bf16x8 wf0[4], wf1[4], ax[MX > 0 ? MX : 1];
+    asm volatile("s_waitcnt vmcnt(%0)" ::"n"(LOADS * (NS - 1)) : "memory");
+    asm volatile("s_barrier" ::: "memory");
+    if (MC > 0) {
+#pragma unroll
+        for (int a = 0; a < 4; ++a) wf0[a] = W[a * 64];
+#pragma unroll
+        for (int m = 0; m < MX; ++m) ax[m] = A[WM * m * 64];
+    }
+    unsigned cur = 0;  // byte offset of the stage being multiplied
+
+    // One k-tile.  X is the first half of the row tiles, Y the second; the operands of each half are read from LDS, and the loads
+    // issued, between the products of the half before, one at a time: in a batch they keep the matrix cores idle while eight wavefronts queue
+    // for LDS.  In the middle: everyone's reads of this stage have returned (they are waited for before the barrier), so its buffer takes the
+    // request for the k-tile NS further; the next stage has landed for this wavefront (at most AHEAD stages after it are
+    // outstanding) and, after the barrier, for everyone.  A fence here would make the compiler wait for every load in flight.
+    auto turn = [&](const bf16x8 (&wf)[4], bf16x8 (&wf_next)[4], auto ahead, auto request) {
+        constexpr int AHEAD = decltype(ahead)::value;  // negative: the last k-tile
+        constexpr bool REQUEST = decltype(request)::value;
+        const bf16x8 *Ac = A + (cur >> 4);
+        bf16x8 ay[MY > 0 ? MY : 1];
+        __builtin_amdgcn_sched_barrier(0);
+#pragma unroll
+        for (int i = 0; i < 4 * MX; ++i) {
+            acc[i & 3][i >> 2] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(wf[i & 3], ax[i >> 2], acc[i & 3][i >> 2], 0, 0, 0);
+            if (i < MY) ay[i] = Ac[WM * (MX + i) * 64];
+            __builtin_amdgcn_sched_barrier(0);
+        }
+        const unsigned freed = cur;
+        cur = cur + STAGE == NS * STAGE ? 0 : cur + STAGE;
+        if (AHEAD >= 0) {
+            asm volatile("s_waitcnt vmcnt(%0) lgkmcnt(0)" ::"n"(LOADS * (AHEAD > 0 ? AHEAD : 0)) : "memory");
+            asm volatile("s_barrier" ::: "memory");
+        }
+        const bf16x8 *An = A + (cur >> 4), *Wn = W + (cur >> 4);
+        constexpr int READS = AHEAD >= 0 && MC > 0 ? 4 + MX : 0, OPS = READS + (REQUEST ? LOADS : 0), MM = MY > 0 ? 4 * MY : 1;
+#pragma unroll
+        for (int i = 0; i < MM; ++i) {
+            if (MY > 0) acc[i & 3][MX + (i >> 2)] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(wf[i & 3], ay[i >> 2], acc[i & 3][MX + (i >> 2)], 0, 0, 0);
+#pragma unroll
+            for (int q = i * OPS / MM; q < (i + 1) * OPS / MM; ++q) {
+                if (q >= READS) load(q - READS, freed);
+                else if (q < 4) wf_next[q] = Wn[q * 64];
+                else ax[q - 4] = An[WM * (q - 4) * 64];
+            }
+            __builtin_amdgcn_sched_barrier(0);
+        }
+        if (REQUEST) advance(true);
+    };
+    using Steady = std::integral_constant<int, NS - 2>;
+    for (int kt = NS; kt < t.n_kt; kt += 2) {  // n_kt is even (the launcher checks)
+        turn(wf0, wf1, Steady(), std::true_type());
+        turn(wf1, wf0, Steady(), std::true_type());
+    }
+    // the last NS k-tiles (or all of fewer): everything is requested
+    static_for<NS / 2>([&](auto half) {
+        constexpr int j = 2 * decltype(half)::value;
+        if (j >= t.n_kt) return;  // uniform over the workgroup
+        turn(wf0, wf1, std::integral_constant<int, NS - 2 - j>(), std::false_type());
+        turn(wf1, wf0, std::integral_constant<int, NS - 3 - j>(), std::false_type());
+    });
+    asm volatile("s_waitcnt vmcnt(0)" ::: "memory");  // a surplus request must not outlive the workgroup's LDS
+}
+
+// Row tiles of wavefront `wave` among rt, and how many of them it brings per stage.
+template <int BN>
+constexpr int gemm_own_tiles(int rt, int wave) {
+    constexpr int WN = BN / 64, WM = 8 / WN;
+    return rt > wave / WN ? (rt - wave / WN + WM - 1) / WM : 0;
+}
+constexpr int gemm_brought_tiles(int rt, int wave) { return rt > wave ? (rt - wave + 7) / 8 : 0; }
+// Does a chunk of lo .. RTC row tiles have a wavefront with MC row tiles of its own that brings LA?
+template <int BN, int RTC, int MC, int LA>
+constexpr bool gemm_occurs(int lo) {
+    for (int rt = lo; rt <= RTC; ++rt)
+        for (int w = 0; w < 8; ++w)
+            if (gemm_own_tiles<BN>(rt, w) == MC && gemm_brought_tiles(rt, w) == LA) return true;
+    return false;
+}
+
+// Products and epilogue of one wavefront of a chunk of at most RTC row tiles (and more than the next smaller ring takes).
+template <int BN, bool UP, int MC>
+__device__ inline void gemm_tile_body(const GemmTile &t, const char *ring, int wave, void *__restrict__ h_chunk, float *__restrict__ partial_rows,
+                                      __bf16 *__restrict__ y_rows, int N, int n0) {
+    constexpr int WN = BN / 64, WM = 8 / WN;
+    const int lane = threadIdx.x & 63, wn = wave & (WN - 1), wm = wave / WN;
+    floatx4 acc[4][MC > 0 ? MC : 1];
 #pragma unroll
     for (int a = 0; a < 4; ++a)
 #pragma unroll
         for (int m = 0; m < MC; ++m) acc[a][m] = floatx4{0.f, 0.f, 0.f, 0.f};
-
-#pragma unroll
-    for (int st = 0; st < NS; ++st) issue(st * STAGE);
-    const bf16x8 *A = reinterpret_cast<const bf16x8 *>(ring) + wm * 64 + lane;
-    const bf16x8 *W = reinterpret_cast<const bf16x8 *>(ring + GEMM_RT * 1024) + wn * 4 * 64 + lane;
-
-    // Half a stage is multiplied while the operands of the next half are read from LDS: X is the
-    // first half of the row tiles, Y the second.  In the middle of turn kt: everyone's reads of stage kt
-    // have returned (they are waited for before the barrier), so its buffer takes the request for stage
-    // kt + NS; stage kt+1 has landed for this wavefront (at most the NS-2 stages after it are outstanding)
-    // and, after the barrier, for everyone.  A fence here would make the compiler wait for every load in flight.
-    bf16x8 wf0[4], wf1[4], ax[MX];
-    if (full) asm volatile("s_waitcnt vmcnt(%0)" ::"n"(LOADS * (NS - 1)) : "memory");
-    else asm volatile("s_waitcnt vmcnt(%0)" ::"n"((LOADS - 1) * (NS - 1)) : "memory");
-    asm volatile("s_barrier" ::: "memory");
-#pragma unroll
-    for (int a = 0; a < 4; ++a) wf0[a] = W[a * 64];
-#pragma unroll
-    for (int m = 0; m < MX; ++m) ax[m] = A[WM * m * 64];
-    unsigned cur = 0;  // byte offset of the stage being multiplied
-    auto turn = [&](const bf16x8 (&wf)[4], bf16x8 (&wf_next)[4]) {
-        const bf16x8 *Ac = A + (cur >> 4);
-        bf16x8 ay[MY > 0 ? MY : 1];
-#pragma unroll
-        for (int m = 0; m < MY; ++m) ay[m] = Ac[WM * (MX + m) * 64];
-        __builtin_amdgcn_sched_barrier(0);
-#pragma unroll
-        for (int m = 0; m < MX; ++m)
-#pragma unroll
-            for (int a = 0; a < 4; ++a) acc[a][m] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(wf[a], ax[m], acc[a][m], 0, 0, 0);
-        __builtin_amdgcn_sched_barrier(0);
-        if (full) asm volatile("s_waitcnt vmcnt(%0) lgkmcnt(0)" ::"n"(LOADS * (NS - 2)) : "memory");
-        else asm volatile("s_waitcnt vmcnt(%0) lgkmcnt(0)" ::"n"((LOADS - 1) * (NS - 2)) : "memory");
-        asm volatile("s_barrier" ::: "memory");
-        issue(cur);
-        cur = cur + STAGE == NS * STAGE ? 0 : cur + STAGE;
-        const bf16x8 *An = A + (cur >> 4), *Wn = W + (cur >> 4);
-#pragma unroll
-        for (int m = 0; m < MX; ++m) ax[m] = An[WM * m * 64];
-#pragma unroll
-        for (int a = 0; a < 4; ++a) wf_next[a] = Wn[a * 64];
-        __builtin_amdgcn_sched_barrier(0);
-#pragma unroll
-        for (int m = 0; m < MY; ++m)
-#pragma unroll
-            for (int a = 0; a < 4; ++a) acc[a][MX + m] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(wf[a], ay[m], acc[a][MX + m], 0, 0, 0);
-        __builtin_amdgcn_sched_barrier(0);
-    };
-    for (int kt = 0; kt < t.n_kt; kt += 2) {  // n_kt is even (the launcher checks)
-        turn(wf0, wf1);
-        turn(wf1, wf0);
-    }
-    asm volatile("s_waitcnt vmcnt(0)" ::: "memory");  // the surplus requests must not outlive the workgroup's LDS
+    constexpr int R0 = GEMM_RING_TILES[0], R1 = GEMM_RING_TILES[1], R2 = GEMM_RING_TILES[2];
+    const int kind = gemm_brought_tiles(t.rt, wave) + (t.rt <= R0 ? 0 : (t.rt <= R1 ? 4 : 8));
+    static_for<4>([&](auto la_) {
+        constexpr int LA = decltype(la_)::value;
+        if constexpr (gemm_occurs<BN, R0, MC, LA>(1))
+            if (kind == LA) gemm_k_loop<BN, R0, MC, LA>(t, ring, wave, acc);
+        if constexpr (gemm_occurs<BN, R1, MC, LA>(R0 + 1))
+            if (kind == 4 + LA) gemm_k_loop<BN, R1, MC, LA>(t, ring, wave, acc);
+        if constexpr (gemm_occurs<BN, R2, MC, LA>(R1 + 1))
+            if (kind == 8 + LA) gemm_k_loop<BN, R2, MC, LA>(t, ring, wave, acc);
+    });
 
     // lane holds row 16 * row tile + tok, output columns n0 + wn*64 + a*16 + 4*g + {0..3}
     const int tok = lane & 15, g = lane >> 4;
@@ -365,13 +424,13 @@ __device__ inline void gemm_tile_body(const GemmTile &t, char *ring, void *__res
 // UP = true : the up-projection, H = ReLU(A . W1) with K = d, N = f, A the packed rows, W1's tiles
 //             n-tile major (the k-tiles of one 16-column slab are contiguous), the result rounded
 //             to bf16 and stored packed for the down-projection.
-template <int BN, int NS, bool UP>
+template <int BN, bool UP>
 __global__ __launch_bounds__(512) void ffn_gemm_tile_kernel(
     const char *__restrict__ a_packed, const int32_t *__restrict__ offsets, int E, int K, int N, int n_split,
     const char *__restrict__ w_base, size_t w_stride, int slot_by_rank, int n_slots,
     const unsigned long long *__restrict__ table, char *__restrict__ h, float *__restrict__ partial,
     __bf16 *__restrict__ y_perm, int n_rows, int tiles_lo, int tiles_hi) {
-    extern __shared__ __attribute__((aligned(1024))) char ring[];  // NS stages
+    extern __shared__ __attribute__((aligned(1024))) char ring[];
     GemmScan scan;
     gemm_scan(offsets, E, tiles_lo, tiles_hi, scan);
     int chunk_id, col_id;
@@ -404,24 +463,17 @@ __global__ __launch_bounds__(512) void ffn_gemm_tile_kernel(
     void *h_chunk = UP ? h + (size_t)ci.tile0 * 32 * N : nullptr;
     float *partial_rows = !UP && partial ? partial + ((size_t)split * n_rows + ci.row0) * N : nullptr;
     __bf16 *y_rows = UP ? nullptr : y_perm + (size_t)ci.row0 * N;
-    // row tiles per wavefront (uniform): the smallest body that holds the chunk
-    const int mc = (t.rt + 512 / BN - 1) / (512 / BN);
-#define PG_BODY(MC_) gemm_tile_body<BN, NS, UP, MC_>(t, ring, h_chunk, partial_rows, y_rows, N, n0)
-    if constexpr (BN == 256) {
-        if (mc > 9) PG_BODY(10);
-        else if (mc > 8) PG_BODY(9);
-        else if (mc > 6) PG_BODY(8);
-        else if (mc > 4) PG_BODY(6);
-        else if (mc > 2) PG_BODY(4);
-        else PG_BODY(2);
-    } else {
-        if (mc > 4) PG_BODY(5);
-        else if (mc > 3) PG_BODY(4);
-        else if (mc > 2) PG_BODY(3);
-        else if (mc > 1) PG_BODY(2);
-        else PG_BODY(1);
-    }
+    const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6), own = gemm_own_tiles<BN>(t.rt, wave);
+    // A jump to the body: a chain of comparisons in front of every body would miss the instruction cache at each.
+    switch (own) {  // uniform over the wavefront
+#define PG_BODY(MC_)                                                                                                                \
+    case MC_:                                                                                                                       \
+        if constexpr (MC_ <= GEMM_RT / (512 / BN)) gemm_tile_body<BN, UP, MC_>(t, ring, wave, h_chunk, partial_rows, y_rows, N, n0); \
+        asm volatile("; %0 row tiles" ::"n"(MC_)); /* keeps the bodies' stores apart: merged, they would copy every accumulator */   \
+        return;
+        PG_BODY(0) PG_BODY(1) PG_BODY(2) PG_BODY(3) PG_BODY(4) PG_BODY(5) PG_BODY(6) PG_BODY(7) PG_BODY(8) PG_BODY(9) PG_BODY(10)
 #undef PG_BODY
+    }
 }
 
 // ------------------------------------------------------------------------------------------
@@ -595,20 +647,19 @@ int launch_ffn_gemm(pgmoe_ctx *ctx, const char *w_base, size_t w_stride, bool sl
         hipLaunchKernelGGL(ffn_gemm_pack_rows_kernel, dim3(max_chunks, c.d_model / 32 / PACK_KT), dim3(512), 0, s, (const __bf16 *)x_perm,
                            offsets, c.n_experts, c.d_model, src_row, (__bf16 *)xp, lo, hi);
         PG_HIP(ctx, hipGetLastError());
-#define PG_TILE(BN_, NS_, UP_, A_, K_, N_, SPLIT_)                                                                                 \
+#define PG_TILE(BN_, UP_, A_, K_, N_, SPLIT_)                                                                                 \
     do {                                                                                                                           \
-        constexpr int lds = NS_ * (GEMM_RT + BN_ / 16) * 1024;                                                                     \
-        auto kern_ = ffn_gemm_tile_kernel<BN_, NS_, UP_>;                                                                          \
-        if (int rc_ = allow_dynamic_lds(ctx, reinterpret_cast<const void *>(kern_), lds)) return rc_;                              \
-        hipLaunchKernelGGL(kern_, dim3(max_chunks, N_ / BN_ * SPLIT_), dim3(512), lds, s, (const char *)(A_), offsets,             \
+        auto kern_ = ffn_gemm_tile_kernel<BN_, UP_>;                                                                          \
+        if (int rc_ = allow_dynamic_lds(ctx, reinterpret_cast<const void *>(kern_), GEMM_RING)) return rc_;                              \
+        hipLaunchKernelGGL(kern_, dim3(max_chunks, N_ / BN_ * SPLIT_), dim3(512), GEMM_RING, s, (const char *)(A_), offsets,             \
                            c.n_experts, K_, N_, SPLIT_, w_base, w_stride, slot_by_rank ? 1 : 0, n_slots, table, h, partial,        \
                            (__bf16 *)y_perm, n_rows, lo, hi);                                                                      \
         PG_HIP(ctx, hipGetLastError());                                                                                            \
     } while (0)
-        if (p.bn_up == 256) PG_TILE(256, 4, true, xp, c.d_model, c.d_ff, 1);
-        else PG_TILE(128, 5, true, xp, c.d_model, c.d_ff, 1);
-        if (p.bn_down == 256) PG_TILE(256, 4, false, h, c.d_ff, c.d_model, p.split);
-        else PG_TILE(128, 5, false, h, c.d_ff, c.d_model, p.split);
+        if (p.bn_up == 256) PG_TILE(256, true, xp, c.d_model, c.d_ff, 1);
+        else PG_TILE(128, true, xp, c.d_model, c.d_ff, 1);
+        if (p.bn_down == 256) PG_TILE(256, false, h, c.d_ff, c.d_model, p.split);
+        else PG_TILE(128, false, h, c.d_ff, c.d_model, p.split);
 #undef PG_TILE
     }
     if (tslot >= 0) PG_HIP(ctx, hipEventRecord(ctx->tim_end[tslot], s));

@@ -36,6 +36,28 @@ def test_expert_ffn_at_tile_edges(hx, d, f, E, counts):  # noqa: F811
             assert nerr(out[offs[e]: offs[e + 1]], ref[offs[e]: offs[e + 1]]) <= TOL["bf16"], f"expert {e} ({counts[e]} rows)"
 
 
+# every number of row tiles a chunk can have (a wavefront's share, what it loads and the ring go by it), the last tile full, short and of one row
+EVERY = [16 * t - (0, 15, 6)[t % 3] for t in range(1, 21)]
+
+
+@pytest.mark.parametrize("d,f", [
+    (128, 256),     # fewer k-tiles than any ring has stages
+    (256, 768),     # as many as the ring of the largest chunks has, and 256-column blocks
+    (512, 2560),    # more than the deepest ring has: the steady loop and the tail
+])
+def test_every_number_of_row_tiles(hx, d, f):  # noqa: F811
+    H, B = hx
+    counts = EVERY + [320] * 6 + [t % 7 + 300 for t in EVERY]
+    ctx = B.Context(B.make_config(d, f, len(counts), 1, 1, sum(counts), B.BF16, flags=B.FLAG_HOST_ONLY))
+    assert "gemm" in ctx.ffn_kernel_name(sum(counts))
+    ctx.close()
+    print(f"gemm row tiles: d={d} f={f}", flush=True)
+    out, ref = run_ffn_case(H, B, "bf16", d, f, len(counts), counts, seed=d + f)
+    offs = np.concatenate([[0], np.cumsum(counts)])
+    for e in range(len(counts)):
+        assert nerr(out[offs[e]: offs[e + 1]], ref[offs[e]: offs[e + 1]]) <= TOL["bf16"], f"expert {e} ({counts[e]} rows)"
+
+
 @pytest.mark.parametrize("counts", [[120] * 16, [700, 0, 321, 5, 64, 100, 1, 16, 17, 90, 200, 33, 50, 150, 80, 93]])
 def test_static_scratch_takes_several_passes_and_gives_the_same_bits(hx, counts):  # noqa: F811
     """A launch the static buffer admits but whose hidden activation it does not hold at once."""
