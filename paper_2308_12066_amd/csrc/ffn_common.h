@@ -6,6 +6,7 @@
 #include <cstdlib>
 
 #include "pgmoe_internal.h"
+#include "wave.h"
 
 namespace pgmoe {
 
@@ -21,23 +22,6 @@ typedef __attribute__((address_space(1))) bf16x8 global_bf16x8;  // a load throu
 struct ChunkInfo {
     int expert, slot, row0, nrows;  // nrows == 0: chunk does not exist
 };
-
-// Inclusive prefix sum over the 64 lanes of a wavefront (all of them active) with data-parallel
-// primitives: four shifts inside each row of 16 lanes, then lane 15 of row 0 / 2 into row 1 / 3
-// and lane 31 into rows 2 and 3.  Six VALU operations instead of six trips through the LDS crossbar.
-template <int CTRL, int ROW_MASK>
-__device__ inline int dpp_or_zero(int v) {
-    return __builtin_amdgcn_update_dpp(0, v, CTRL, ROW_MASK, 0xf, false);  // lanes without a source get 0
-}
-__device__ inline int wave_incl_scan(int v) {
-    v += dpp_or_zero<0x111, 0xf>(v);  // row_shr:1
-    v += dpp_or_zero<0x112, 0xf>(v);  // row_shr:2
-    v += dpp_or_zero<0x114, 0xf>(v);  // row_shr:4
-    v += dpp_or_zero<0x118, 0xf>(v);  // row_shr:8
-    v += dpp_or_zero<0x142, 0xa>(v);  // row_bcast:15 -> rows 1 and 3
-    v += dpp_or_zero<0x143, 0xc>(v);  // row_bcast:31 -> rows 2 and 3
-    return v;
-}
 
 __device__ inline ChunkInfo find_chunk(const int32_t *__restrict__ offsets, int E, int rows_per_chunk, int chunk) {
     const int lane = threadIdx.x & 63;
