@@ -7,7 +7,7 @@
 //   gate_small_kernel      bf16, up to four tokens, 8 or 16 experts: one workgroup, all loads at once;
 //   gate_topk_mfma_kernel  bf16, E a multiple of 8: logits on the matrix cores, 16 tokens per
 //                          workgroup, W transposed in registers (no LDS staging on the way in);
-//   gate_topk_tiles_kernel the same for more 16-token tiles than CUs: W stays in registers;
+//   gate_topk_tiles_kernel the same for more than 128 tiles of 16 tokens: pairs of tiles, W stays in registers;
 //   gate_topk_vec_kernel   f32 (and bf16 when the matrix-core kernel does not apply) for
 //                          power-of-two E: token rows staged in LDS as float32, threads split W
 //                          by expert columns and feature rows and fold their partial sums in a
@@ -21,6 +21,7 @@
 
 namespace pgmoe {
 
+constexpr int GATE_ZS = 128 + 16;  // floats from one token's logits to the next: the four tokens of a wavefront on banks of their own
 constexpr int GATE_TB = 8;
 constexpr int GATE_DC = 1024;
 constexpr int GATE_THREADS = 256;
@@ -277,7 +278,12 @@ __global__ __launch_bounds__(GS_THREADS) void gate_small_kernel(
 //     eight k-values of expert 8*n + q: that is a valid operand for the 16 experts
 //     {q, 8+q, 16+q, ...}, i.e. output column n of product q is expert 8*n + q.  Eight products
 //     cover 128 experts per k-tile; E = 256 takes a second pass.
-template <int NP, int NW>  // NP: passes of 128 experts (1: E <= 128, 2: E <= 256); NW: wavefronts that split d_model
+// The expert of place o = [p][q][lane] of a plane of partial logits.
+__device__ inline int gate_expert_of(int o) { return 8 * ((o & 15) + 16 * (o >> 9)) + (o >> 6 & 7); }
+
+// NP: passes of 128 experts (1: E <= 128, 2: E <= 256); NW: wavefronts that split d_model; KW: k-tiles of a wavefront (d_model = 32 * NW * KW),
+// 0: any number of them
+template <int NP, int NW, int KW>
 __global__ __launch_bounds__(NW * 64) void gate_topk_mfma_kernel(
     const __bf16 *__restrict__ x, const __bf16 *__restrict__ w, const float *__restrict__ bias, int T, int d, int E, int k,
     int32_t *__restrict__ idx_out, float *__restrict__ prob_out, float *__restrict__ probs_out, uint32_t *flags,
@@ -300,50 +306,80 @@ __global__ __launch_bounds__(NW * 64) void gate_topk_mfma_kernel(
 #pragma unroll
         for (int q = 0; q < 8; ++q) acc[p][q] = gfloatx4{0.f, 0.f, 0.f, 0.f};
 
+    // the experts whose planes this thread adds: their bias is needed last and requested first
+    float b_of[NP * 8 / NW];
+#pragma unroll
+    for (int i = 0; i < NP * 8 / NW; ++i) {
+        const int e = gate_expert_of(tid + NT * i);
+        b_of[i] = bias && e < E ? bias[e] : 0.f;
+    }
     const __bf16 *xrow = x + (size_t)(t0 + (n < nt ? n : 0)) * d + 8 * g;  // rows past the batch read its first token; their logits are never used
-    // Register prefetch ring, PF k-tiles deep: the operands of k-tile i + PF are requested when
-    // k-tile i is consumed, so a wavefront pays the memory latency once, not once per k-tile.
+    // Register prefetch ring, PF k-tiles deep: the operands of a wavefront's k-tile i + PF are requested when
+    // k-tile i is consumed, so it pays the memory latency once, not once per k-tile.
     // Every request is an unconditional load from a clamped (always valid) address, so nothing
-    // makes the compiler wait for one load before it issues the next: a stage past the last
-    // k-tile reads the last one again and has its token operand zeroed when it is used (it adds
-    // nothing), column vectors past E read the last real one (their logits are never used).
-    constexpr int PF = NP == 1 ? 3 : 2;
+    // makes the compiler wait for one load before it issues the next: column vectors past E read the last real one (their logits are
+    // never used).  With a number of k-tiles known here none is requested that does not exist; else a stage past the last
+    // k-tile reads the last one again and has its token operand zeroed when it is used (it adds nothing), up to twice the loads:
+    // 4096 tokens of 1024 x 128 read 594 KB per workgroup that way, 264 KB now, 9.5 -> 7.5 us.
+    constexpr int PF = KW > 0 && NP == 1 ? (KW < 4 ? KW : 4) : (NP == 1 ? 3 : 2);
     const gbf16x8 zero8 = gbf16x8{0, 0, 0, 0, 0, 0, 0, 0};
     gbf16x8 a_buf[PF], rows_buf[PF][NP][8];
     auto request = [&](int kt, gbf16x8 &a, gbf16x8 (&rows)[NP][8]) {
-        const int ktc = min(kt, KT - 1);
-        a = *reinterpret_cast<const gbf16x8 *>(xrow + ktc * 32);
+        a = *reinterpret_cast<const gbf16x8 *>(xrow + kt * 32);
 #pragma unroll
         for (int p = 0; p < NP; ++p) {
             const int cv = min(n + 16 * p, ncv - 1);
-            const gbf16x8 *src = reinterpret_cast<const gbf16x8 *>(w + (size_t)(ktc * 32 + 8 * g) * E) + cv;
+            const gbf16x8 *src = reinterpret_cast<const gbf16x8 *>(w + (size_t)(kt * 32 + 8 * g) * E) + cv;
 #pragma unroll
             for (int j = 0; j < 8; ++j) rows[p][j] = src[(size_t)j * ncv];
         }
     };
+    auto transpose = [&](const gbf16x8 (&rows)[NP][8], gbf16x8 (&cells)[NP][8]) {
 #pragma unroll
-    for (int st = 0; st < PF; ++st) request(wave + NW * st, a_buf[st], rows_buf[st]);
-    // the instruction scheduler must not move these loads down to their uses to save registers
-    // (that would pay the memory latency once per stage): nothing crosses this point
-    __builtin_amdgcn_sched_barrier(0);
-    for (int kt0 = wave; kt0 < KT; kt0 += NW * PF) {
+        for (int p = 0; p < NP; ++p)
 #pragma unroll
-        for (int st = 0; st < PF; ++st) {
-            const gbf16x8 a = kt0 + NW * st < KT ? a_buf[st] : zero8;
+            for (int q = 0; q < 8; ++q)
+#pragma unroll
+                for (int j = 0; j < 8; ++j) cells[p][q][j] = rows[p][j][q];
+    };
+    auto multiply = [&](const gbf16x8 a, const gbf16x8 (&cells)[NP][8]) {
+#pragma unroll
+        for (int p = 0; p < NP; ++p)
+#pragma unroll
+            for (int q = 0; q < 8; ++q)
+                acc[p][q] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(a, cells[p][q], acc[p][q], 0, 0, 0);
+    };
+    // the instruction scheduler must not move the loads down to their uses to save registers
+    // (that would pay the memory latency once per stage): nothing crosses a scheduling barrier
+    if constexpr (KW > 0) {
+#pragma unroll
+        for (int i = 0; i < PF; ++i) request(wave + NW * i, a_buf[i], rows_buf[i]);
+        __builtin_amdgcn_sched_barrier(0);
+#pragma unroll
+        for (int i = 0; i < KW; ++i) {
+            const gbf16x8 a = a_buf[i % PF];
             gbf16x8 cells[NP][8];
+            transpose(rows_buf[i % PF], cells);
+            if (i + PF < KW) {
+                request(wave + NW * (i + PF), a_buf[i % PF], rows_buf[i % PF]);
+                __builtin_amdgcn_sched_barrier(0);
+            }
+            multiply(a, cells);
+        }
+    } else {
 #pragma unroll
-            for (int p = 0; p < NP; ++p)
+        for (int st = 0; st < PF; ++st) request(min(wave + NW * st, KT - 1), a_buf[st], rows_buf[st]);
+        __builtin_amdgcn_sched_barrier(0);
+        for (int kt0 = wave; kt0 < KT; kt0 += NW * PF) {
 #pragma unroll
-                for (int q = 0; q < 8; ++q)
-#pragma unroll
-                    for (int j = 0; j < 8; ++j) cells[p][q][j] = rows_buf[st][p][j][q];
-            request(kt0 + NW * (st + PF), a_buf[st], rows_buf[st]);
-            __builtin_amdgcn_sched_barrier(0);
-#pragma unroll
-            for (int p = 0; p < NP; ++p)
-#pragma unroll
-                for (int q = 0; q < 8; ++q)
-                    acc[p][q] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(a, cells[p][q], acc[p][q], 0, 0, 0);
+            for (int st = 0; st < PF; ++st) {
+                const gbf16x8 a = kt0 + NW * st < KT ? a_buf[st] : zero8;
+                gbf16x8 cells[NP][8];
+                transpose(rows_buf[st], cells);
+                request(min(kt0 + NW * (st + PF), KT - 1), a_buf[st], rows_buf[st]);
+                __builtin_amdgcn_sched_barrier(0);
+                multiply(a, cells);
+            }
         }
     }
     // lane holds tokens 4*g + r (r = 0..3), column n of product q = expert 8*(n + 16*p) + q.  The
@@ -355,14 +391,16 @@ __global__ __launch_bounds__(NW * 64) void gate_topk_mfma_kernel(
         for (int q = 0; q < 8; ++q)
             reinterpret_cast<gfloatx4 *>(part)[(((size_t)wave * NP + p) * 8 + q) * 64 + lane] = acc[p][q];
     __syncthreads();
-    constexpr int PLANE = NP * 8 * 4 * 64;  // floats per wavefront
-    for (int o = tid; o < PLANE; o += NT) {
-        const int r = o & 3, l = (o >> 2) & 63, q = (o >> 8) & 7, p = o >> 11;
-        const int e = 8 * ((l & 15) + 16 * p) + q, tokl = 4 * (l >> 4) + r;
-        float sum = part[o];
+    constexpr int PLACES = NP * 8 * 64;  // of four floats, per wavefront
 #pragma unroll
-        for (int wv = 1; wv < NW; ++wv) sum += part[wv * PLANE + o];
-        zs[tokl * ecols + e] = sum + ((bias && e < E) ? bias[e] : 0.f);
+    for (int i = 0; i < PLACES / NT; ++i) {
+        const int o = tid + NT * i;
+        const gfloatx4 *src = reinterpret_cast<const gfloatx4 *>(part) + o;
+        gfloatx4 sum = src[0];
+#pragma unroll
+        for (int wv = 1; wv < NW; ++wv) sum += src[wv * PLACES];
+#pragma unroll
+        for (int r = 0; r < 4; ++r) zs[(4 * (lane >> 4) + r) * ecols + gate_expert_of(o)] = sum[r] + b_of[i];
     }
     __syncthreads();
     // Decode-sized batch (the whole batch in this one workgroup, at most GATE_ROUTE_MAX
@@ -377,71 +415,77 @@ __global__ __launch_bounds__(NW * 64) void gate_topk_mfma_kernel(
     group_in_workgroup(r_idx, r_cnt, r_off, nt * k, E, k, NT, row_of, offsets, src_row);
 }
 
-// The same for batches of several tiles per CU (E <= 128, d_model = 256*KW, KW <= 4: the share of W is 32*KW registers a lane,
-// as many as the accumulators and the next tile's tokens leave): a workgroup keeps its share of W in registers,
-// transposed once, and walks token tiles, so that a CU reads W once and not once per tile; the softmax of a tile is one half of the
-// wavefronts' while the other half begins the next tile.  Sums and their order are the kernel's above: same bits.
-// 16384 tokens of d_model 1024, 128 experts: 39 us with a tile per workgroup (four rounds of 262 KB of W per CU), now 19.5;
-// 4200 tokens 19 -> 11.6.
+// The same for batches of many tiles (E <= 128, d_model = 256*KW, KW <= 4: the share of W is 32*KW registers a lane,
+// as many as the accumulators and the next tokens leave): a workgroup keeps its share of W in registers,
+// transposed once, and walks pairs of token tiles.  One tile alone is bound by its 264 KB of W (4600 clocks at the 64 bytes a clock of a CU's
+// path to L2) and by a softmax of half the wavefronts, each alone on its SIMD; a pair shares the first and fills the
+// second.  4096 tokens of 1024 x 128, passes of several streams: 9.5 us with a tile per workgroup and its surplus loads, now 5.7, where the
+// host's call is as long; 8192 11.6 -> 9.6 (single tiles walked); 16384 in a step 25 -> 22.  Sums and their order are the kernel's above: same bits.
 template <int KW>
 __global__ __launch_bounds__(512) void gate_topk_tiles_kernel(
     const __bf16 *__restrict__ x, const __bf16 *__restrict__ w, const float *__restrict__ bias, int T, int E, int k,
     int32_t *__restrict__ idx_out, float *__restrict__ prob_out, float *__restrict__ probs_out, uint32_t *flags) {
-    constexpr int NW = 8, d = 256 * KW, PLANE = 8 * 64 * 4;
+    constexpr int NW = 8, d = 256 * KW, PLACES = 8 * 64, PAIR = 2 * GM_TOK;
     extern __shared__ __attribute__((aligned(16))) char gsm[];
-    float *part = reinterpret_cast<float *>(gsm);  // [NW][PLANE]
-    float *zs = part + NW * PLANE;                 // [2][GM_TOK][128]
+    gfloatx4 *part = reinterpret_cast<gfloatx4 *>(gsm);             // [NW][PLACES]
+    float *zs = reinterpret_cast<float *>(part + NW * PLACES);      // [PAIR][GATE_ZS]
     const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
     const int n = lane & 15, g = lane >> 4;
-    const int ncv = E >> 3, tiles = (T + GM_TOK - 1) / GM_TOK;
+    const int ncv = E >> 3;
     gbf16x8 cells[KW][8], rows[KW][8];
     const gbf16x8 *wcol = reinterpret_cast<const gbf16x8 *>(w) + min(n, ncv - 1);  // column vectors past E: the last one, never used
 #pragma unroll
     for (int i = 0; i < KW; ++i)
 #pragma unroll
         for (int j = 0; j < 8; ++j) rows[i][j] = wcol[(size_t)((wave + NW * i) * 32 + 8 * g + j) * ncv];
-    gbf16x8 a[KW];
-    auto request = [&](int tile) {  // this wavefront's k-tiles of the tile's tokens; past the batch: its last token, never used
-        const __bf16 *xrow = x + (size_t)min(tile * GM_TOK + n, T - 1) * d + 8 * g;
+    gbf16x8 a[2][KW];
+    auto request = [&](int t0) {  // this wavefront's k-tiles of the pair's tokens; past the batch: its last token, never used
 #pragma unroll
-        for (int i = 0; i < KW; ++i) a[i] = *reinterpret_cast<const gbf16x8 *>(xrow + (wave + NW * i) * 32);
+        for (int u = 0; u < 2; ++u) {
+            const __bf16 *xrow = x + (size_t)min(t0 + u * GM_TOK + n, T - 1) * d + 8 * g;
+#pragma unroll
+            for (int i = 0; i < KW; ++i) a[u][i] = *reinterpret_cast<const gbf16x8 *>(xrow + (wave + NW * i) * 32);
+        }
     };
-    request(blockIdx.x);
-    const int e_of = 8 * (lane & 15) + wave;  // the expert this thread adds the planes of (product q = wave)
+    request(blockIdx.x * PAIR);
+    const int e_of = gate_expert_of(tid);  // the expert this thread adds the planes of
     const float b = bias && e_of < E ? bias[e_of] : 0.f;
+    __builtin_amdgcn_sched_barrier(0);
 #pragma unroll
     for (int i = 0; i < KW; ++i)
 #pragma unroll
         for (int q = 0; q < 8; ++q)
 #pragma unroll
             for (int j = 0; j < 8; ++j) cells[i][q][j] = rows[i][j][q];
-    int turn = 0;
-    for (int tile = blockIdx.x; tile < tiles; tile += gridDim.x, turn ^= 1) {
-        gfloatx4 acc[8];
+    for (int t0 = blockIdx.x * PAIR; t0 < T; t0 += gridDim.x * PAIR) {
+        gfloatx4 acc[2][8];
 #pragma unroll
-        for (int q = 0; q < 8; ++q) acc[q] = gfloatx4{0.f, 0.f, 0.f, 0.f};
+        for (int u = 0; u < 2; ++u)
 #pragma unroll
-        for (int i = 0; i < KW; ++i)
+            for (int q = 0; q < 8; ++q) acc[u][q] = gfloatx4{0.f, 0.f, 0.f, 0.f};
 #pragma unroll
-            for (int q = 0; q < 8; ++q) acc[q] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(a[i], cells[i][q], acc[q], 0, 0, 0);
-        if (tile + (int)gridDim.x < tiles) request(tile + gridDim.x);
+        for (int u = 0; u < 2; ++u)
 #pragma unroll
-        for (int q = 0; q < 8; ++q) reinterpret_cast<gfloatx4 *>(part)[(wave * 8 + q) * 64 + lane] = acc[q];
-        __syncthreads();
-        // thread (q = wave, lane) adds the planes' four floats of that place, in plane order
-        float *z = zs + turn * GM_TOK * 128;
-        {
-            const gfloatx4 *src = reinterpret_cast<const gfloatx4 *>(part) + wave * 64 + lane;
-            gfloatx4 sum = src[0];
+            for (int i = 0; i < KW; ++i)
 #pragma unroll
-            for (int v = 1; v < NW; ++v) sum += src[v * 8 * 64];
+                for (int q = 0; q < 8; ++q)
+                    acc[u][q] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(a[u][i], cells[i][q], acc[u][q], 0, 0, 0);
+        if (t0 + (int)gridDim.x * PAIR < T) request(t0 + gridDim.x * PAIR);
 #pragma unroll
-            for (int r = 0; r < 4; ++r) z[(4 * (lane >> 4) + r) * 128 + e_of] = sum[r] + b;
+        for (int u = 0; u < 2; ++u) {
+#pragma unroll
+            for (int q = 0; q < 8; ++q) part[wave * PLACES + q * 64 + lane] = acc[u][q];
+            __syncthreads();
+            // thread (q = wave, lane) adds the planes' four floats of that place, in plane order
+            gfloatx4 sum = part[tid];
+#pragma unroll
+            for (int v = 1; v < NW; ++v) sum += part[v * PLACES + tid];
+#pragma unroll
+            for (int r = 0; r < 4; ++r) zs[(u * GM_TOK + 4 * g + r) * GATE_ZS + e_of] = sum[r] + b;
+            __syncthreads();
         }
-        __syncthreads();
-        const int t0 = tile * GM_TOK;
-        if ((wave >> 2) == turn)  // uniform over the wavefront; the buffer is written again only two tiles later
-            softmax_topk<8, 256>(z, 128, t0, min(GM_TOK, T - t0), E, k, idx_out, prob_out, probs_out, flags);
+        // zs is written again only behind the first barrier of the next pair
+        softmax_topk<8>(zs, GATE_ZS, t0, min(PAIR, T - t0), E, k, idx_out, prob_out, probs_out, flags);
     }
 }
 
@@ -484,14 +528,15 @@ static int launch_gate_mfma(pgmoe_ctx *ctx, const __bf16 *x, const __bf16 *w, co
         PG_HIP(ctx, hipGetLastError());
         return PGMOE_OK;
     }
-    // more tiles than CUs: workgroups of several tiles each, as few as keep the rounds equal
-    if (np == 1 && grid.x > 256 && !route && c.d_model % 256 == 0 && c.d_model <= 1024) {
-        const int per = ((int)grid.x + 255) / 256;
-        const dim3 wgs((grid.x + per - 1) / per);
+    // More than 128 tiles: workgroups of pairs of tiles, as few as keep the rounds over the CUs equal. Below, half the CUs have room for
+    // a tile each and a call that is waited for ends sooner with one (4096 tokens 21.3 us against 22.9, of several streams 7.5 against 6.2).
+    if (np == 1 && grid.x > 128 && !route && c.d_model % 256 == 0 && c.d_model <= 1024) {
+        const int pairs = ((int)grid.x + 1) / 2, per = (pairs + 255) / 256;
+        const dim3 wgs((pairs + per - 1) / per);
 #define PG_GATE_TILES(KW_)                                                                                              \
     do {                                                                                                                \
         auto kern = gate_topk_tiles_kernel<KW_>;                                                                        \
-        constexpr size_t lds = (8 * 2048 + 2 * GM_TOK * 128) * sizeof(float);                                           \
+        constexpr size_t lds = (8 * 2048 + 2 * GM_TOK * GATE_ZS) * sizeof(float);                                       \
         if (int rc_ = allow_dynamic_lds(ctx, reinterpret_cast<const void *>(kern), lds)) return rc_;                    \
         hipLaunchKernelGGL(kern, wgs, dim3(512), lds, s, x, w, bias, T, c.n_experts, c.top_k, idx, prob, probs, ctx->dev_flags); \
     } while (0)
@@ -505,16 +550,28 @@ static int launch_gate_mfma(pgmoe_ctx *ctx, const __bf16 *x, const __bf16 *w, co
     }
     // eight wavefronts split d_model: with a three-deep prefetch ring each of them has all its
     // k-tiles (d_model <= 768) in flight at once, i.e. the kernel pays the memory latency once
-#define PG_GATE_MFMA(NP_, NW_)                                                                                          \
+#define PG_GATE_MFMA(NP_, NW_, KW_)                                                                                     \
     do {                                                                                                                \
-        auto kern = gate_topk_mfma_kernel<NP_, NW_>;                                                                    \
+        auto kern = gate_topk_mfma_kernel<NP_, NW_, KW_>;                                                               \
         const size_t lds = (size_t)(NW_ + 1) * GM_TOK * NP_ * 128 * sizeof(float); /* NW partial planes + the logits */ \
         if (int rc_ = allow_dynamic_lds(ctx, reinterpret_cast<const void *>(kern), lds)) return rc_;                    \
         hipLaunchKernelGGL(kern, grid, dim3(NW_ * 64), lds, s, x, w, bias, T, c.d_model, c.n_experts, c.top_k, idx, prob, probs, \
                            ctx->dev_flags, row_of, offsets, src_row);                                                   \
     } while (0)
-    if (np == 1) PG_GATE_MFMA(1, 8);
-    else PG_GATE_MFMA(2, 4);
+    if (np == 1) {
+        if (c.d_model == 256) PG_GATE_MFMA(1, 8, 1);
+        else if (c.d_model == 512) PG_GATE_MFMA(1, 8, 2);
+        else if (c.d_model == 768) PG_GATE_MFMA(1, 8, 3);
+        else if (c.d_model == 1024) PG_GATE_MFMA(1, 8, 4);
+        else if (c.d_model == 2048) PG_GATE_MFMA(1, 8, 8);
+        else PG_GATE_MFMA(1, 8, 0);
+    } else {
+        if (c.d_model == 512) PG_GATE_MFMA(2, 4, 4);
+        else if (c.d_model == 768) PG_GATE_MFMA(2, 4, 6);
+        else if (c.d_model == 1024) PG_GATE_MFMA(2, 4, 8);
+        else if (c.d_model == 2048) PG_GATE_MFMA(2, 4, 16);
+        else PG_GATE_MFMA(2, 4, 0);
+    }
 #undef PG_GATE_MFMA
     PG_HIP(ctx, hipGetLastError());
     return PGMOE_OK;
