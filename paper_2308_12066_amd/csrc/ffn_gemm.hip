@@ -352,6 +352,24 @@ constexpr bool gemm_occurs(int lo) {
     return false;
 }
 
+// Rounded results of two neighbouring column tiles: a lane of quarter g has columns 4g .. +3 of both and returns eight columns of one of them, 8 * (g / 2) ..
+// of the first (g even) or the second (g odd), by swapping halves with its neighbour quarter.  A row tile of the
+// hidden activation is then one contiguous store of 1 KiB, a row of the result 64 bytes at a time: the end of a down-projection item 5.3 -> 3.2 us.
+template <bool RELU>
+__device__ inline uint4 gemm_octet(const floatx4 even, const floatx4 odd) {
+    typedef unsigned uintx2 __attribute__((ext_vector_type(2)));
+    bf16x4 e, o;
+#pragma unroll
+    for (int j = 0; j < 4; ++j) {
+        e[j] = (__bf16)(RELU ? fmaxf(even[j], 0.f) : even[j]);
+        o[j] = (__bf16)(RELU ? fmaxf(odd[j], 0.f) : odd[j]);
+    }
+    const uintx2 eb = __builtin_bit_cast(uintx2, e), ob = __builtin_bit_cast(uintx2, o);
+    // odd quarters of the first operand change places with the even quarters of the second
+    const auto lo = __builtin_amdgcn_permlane16_swap(eb[0], ob[0], false, false), hi = __builtin_amdgcn_permlane16_swap(eb[1], ob[1], false, false);
+    return make_uint4(lo[0], hi[0], lo[1], hi[1]);
+}
+
 // Products and epilogue of one wavefront of a chunk of at most RTC row tiles (and more than the next smaller ring takes).
 template <int BN, bool UP, int MC>
 __device__ inline void gemm_tile_body(const GemmTile &t, const char *ring, int wave, void *__restrict__ h_chunk, float *__restrict__ partial_rows,
@@ -380,40 +398,28 @@ __device__ inline void gemm_tile_body(const GemmTile &t, const char *ring, int w
 #pragma unroll
     for (int m = 0; m < MC; ++m) {
         const int tile = wm + WM * m, r = tile * 16 + tok;
-        if (r >= t.nrows) continue;
-        if (UP) {
-            // Packed layout of H: per chunk [N/32 k-tiles][row tiles][1 KiB]; a tile holds 16 rows x 32
-            // features in matrix-core operand order: cell row%16 + 16*((feature%32)/8), 8 features per
-            // cell.  Rows past the chunk's end are left unwritten (the down-projection never stores
-            // what it computes from them).
-            __bf16 *dst = reinterpret_cast<__bf16 *>(h_chunk) + (size_t)tile * 512 + (tok + 16 * (g >> 1)) * 8 + 4 * (g & 1);
-#pragma unroll
-            for (int a = 0; a < 4; ++a) {
-                bf16x4 o;
-                o.x = (__bf16)fmaxf(acc[a][m].x, 0.f);
-                o.y = (__bf16)fmaxf(acc[a][m].y, 0.f);
-                o.z = (__bf16)fmaxf(acc[a][m].z, 0.f);
-                o.w = (__bf16)fmaxf(acc[a][m].w, 0.f);
-                if (t.no_weights) o = bf16x4{0, 0, 0, 0};
-                const int kt = (n0 >> 5) + wn * 2 + (a >> 1);  // k-tile of the down-projection these 16 features fall in
-                *reinterpret_cast<bf16x4 *>(dst + (size_t)kt * t.rt * 512 + (a & 1) * 32 * 8) = o;
-            }
-        } else if (partial_rows) {
+        if (!UP && partial_rows) {
+            if (r >= t.nrows) continue;
             float *dst = partial_rows + (size_t)r * N + n0 + wn * 64 + 4 * g;
 #pragma unroll
             for (int a = 0; a < 4; ++a)
                 *reinterpret_cast<floatx4 *>(dst + a * 16) = t.no_weights ? floatx4{0.f, 0.f, 0.f, 0.f} : acc[a][m];
-        } else {
-            __bf16 *dst = y_rows + (size_t)r * N + n0 + wn * 64 + 4 * g;
+            continue;
+        }
 #pragma unroll
-            for (int a = 0; a < 4; ++a) {
-                bf16x4 o;
-                o.x = (__bf16)acc[a][m].x;
-                o.y = (__bf16)acc[a][m].y;
-                o.z = (__bf16)acc[a][m].z;
-                o.w = (__bf16)acc[a][m].w;
-                if (t.no_weights) o = bf16x4{0, 0, 0, 0};
-                *reinterpret_cast<bf16x4 *>(dst + a * 16) = o;
+        for (int p = 0; p < 2; ++p) {  // two column tiles: every lane ends with eight neighbouring columns, 16 bytes a store instead of 8
+            const uint4 o = t.no_weights ? make_uint4(0, 0, 0, 0) : gemm_octet<UP>(acc[2 * p][m], acc[2 * p + 1][m]);
+            const int octet = 2 * (g & 1) + (g >> 1);  // of the 32 columns
+            if (r >= t.nrows) continue;
+            if (UP) {
+                // Packed layout of H: per chunk [N/32 k-tiles][row tiles][1 KiB]; a tile holds 16 rows x 32
+                // features in matrix-core operand order: cell row%16 + 16*((feature%32)/8), 8 features per
+                // cell.  Rows past the chunk's end are left unwritten (the down-projection never stores
+                // what it computes from them).
+                const int kt = (n0 >> 5) + wn * 2 + p;  // k-tile of the down-projection these 32 features are
+                reinterpret_cast<uint4 *>(h_chunk)[((size_t)kt * t.rt + tile) * 64 + tok + 16 * octet] = o;
+            } else {
+                *reinterpret_cast<uint4 *>(y_rows + (size_t)r * N + n0 + wn * 64 + p * 32 + 8 * octet) = o;
             }
         }
     }
