@@ -121,7 +121,9 @@ __device__ inline GemmChunk gemm_find(const GemmScan &s, int E, int tiles_lo, in
 // XCDs round-robin in launch order and every XCD has its own L2.  All column blocks of a chunk go to one XCD (they
 // share its rows), and so do G consecutive chunks, G being how many an expert has on average (they share its
 // weights); such groups are dealt round-robin, so that the large chunks of a popular expert do not all end up on
-// one XCD.  What is left over is cut into eight equal runs of items.
+// one XCD.  Where every expert has G chunks, all of a group take a column block before the next is begun: its weights are then read by
+// G workgroups side by side and not G times (16 experts of 2048 x 8192, 512 rows each: 522 -> 493 us a block; 8 of 1024 x 4096, 2048 rows each: 267 -> 263;
+// with unequal experts, whose groups straddle two, up to 9 % slower).  What is left over is cut into eight equal runs of items.
 // False: this workgroup has no item (uniform over the workgroup).
 __device__ inline bool gemm_item(const GemmScan &s, int &chunk_id, int &col_id) {
     const int gy = gridDim.y;
@@ -131,9 +133,11 @@ __device__ inline bool gemm_item(const GemmScan &s, int &chunk_id, int &col_id) 
     const int G = s.active > 0 ? (s.total + s.active - 1) / s.active : 1;
     const int full = s.total / (8 * G) * G;  // chunks per XCD dealt in groups
     if (turn < full * gy) {
-        const int lc = turn / gy;
-        col_id = turn - lc * gy;
-        chunk_id = (lc / G * 8 + xcd) * G + lc % G;
+        const int together = s.total == G * s.active ? G : 1;  // chunks that take turns at a column block
+        const int lc = turn / (together * gy), in = turn - lc * (together * gy);
+        col_id = in / together;
+        const int c = lc * together + in - col_id * together;
+        chunk_id = (c / G * 8 + xcd) * G + c % G;
         return true;
     }
     turn -= full * gy;
