@@ -124,29 +124,35 @@ __device__ inline GemmChunk gemm_find(const GemmScan &s, int E, int tiles_lo, in
 // one XCD.  Where every expert has G chunks, all of a group take a column block before the next is begun: its weights are then read by
 // G workgroups side by side and not G times (16 experts of 2048 x 8192, 512 rows each: 522 -> 493 us a block; 8 of 1024 x 4096, 2048 rows each: 267 -> 263;
 // with unequal experts, whose groups straddle two, up to 9 % slower).  What is left over is cut into eight equal runs of items.
-// False: this workgroup has no item (uniform over the workgroup).
-__device__ inline bool gemm_item(const GemmScan &s, int &chunk_id, int &col_id) {
-    const int gy = gridDim.y;
-    const int lin = blockIdx.y * gridDim.x + blockIdx.x;
-    const int xcd = lin & 7;
-    int turn = lin >> 3;
+// The items are the first total * gy workgroups of a launch in this order.
+// What a workgroup of the tile kernel needs to know is looked up once, by the kernel that packs the rows, and left as a record per item: with the
+// lookup in every workgroup (the prefix sums over the experts, five divisions) every item began a microsecond later: 512 rows for each of 8
+// experts of 768 x 3072 71.8 -> 70.2 us a block, 94 for 64 169 -> 166, 128 for 64 of 512 x 2048 115 -> 112.
+struct alignas(32) GemmItem {
+    const char *w;          // the expert's blob; null: it got no slot, its rows are written as zeros
+    int row0, nrows, tile0; // nrows == 0: no item
+    int col;                // column block and K slice
+};
+static_assert(sizeof(GemmItem) == 32, "two of a 64-byte line");
+__device__ inline int gemm_launch_order(const GemmScan &s, int chunk, int col, int gy) {
     const int G = s.active > 0 ? (s.total + s.active - 1) / s.active : 1;
     const int full = s.total / (8 * G) * G;  // chunks per XCD dealt in groups
-    if (turn < full * gy) {
-        const int together = s.total == G * s.active ? G : 1;  // chunks that take turns at a column block
-        const int lc = turn / (together * gy), in = turn - lc * (together * gy);
-        col_id = in / together;
-        const int c = lc * together + in - col_id * together;
-        chunk_id = (c / G * 8 + xcd) * G + c % G;
-        return true;
+    if (chunk < 8 * full) {
+        const int deal = chunk / G, k = chunk - deal * G, xcd = deal & 7, round = deal >> 3;
+        const int turn = s.total == G * s.active ? round * G * gy + col * G + k : (round * G + k) * gy + col;
+        return turn * 8 + xcd;
     }
-    turn -= full * gy;
-    const int rest = (s.total - 8 * full) * gy;
-    if (turn >= (rest >> 3) + (xcd < (rest & 7) ? 1 : 0)) return false;
-    const int item = xcd * (rest >> 3) + min(xcd, rest & 7) + turn;
-    chunk_id = 8 * full + item / gy;
-    col_id = item % gy;
-    return true;
+    const int rest = (s.total - 8 * full) * gy, run = rest >> 3, longer = rest & 7;  // the first `longer` XCDs get one item more
+    int item = (chunk - 8 * full) * gy + col, xcd, turn;
+    if (item < longer * (run + 1)) {
+        xcd = item / (run + 1);
+        turn = item - xcd * (run + 1);
+    } else {
+        item -= longer * (run + 1);
+        xcd = longer + item / run;
+        turn = item - (xcd - longer) * run;
+    }
+    return (full * gy + turn) * 8 + xcd;
 }
 
 // The rows of every chunk, gathered through the row -> token map and stored as the 1 KiB
@@ -161,10 +167,21 @@ constexpr int PACK_KT = 2;
 __global__ __launch_bounds__(512) void ffn_gemm_pack_rows_kernel(
     const __bf16 *__restrict__ x_rows, const int32_t *__restrict__ offsets, int E, int d,
     const int32_t *__restrict__ src_row,  // nullable: grouped row r is row src_row[r] of x_rows
-    __bf16 *__restrict__ x_packed, int tiles_lo, int tiles_hi) {
+    __bf16 *__restrict__ x_packed, int tiles_lo, int tiles_hi, const char *__restrict__ w_base, size_t w_stride, int slot_by_rank, int n_slots,
+    const unsigned long long *__restrict__ table, GemmItem *__restrict__ items, int gy_up, int gy_down) {
     GemmScan scan;
     gemm_scan(offsets, E, tiles_lo, tiles_hi, scan);
     const GemmChunk ci = gemm_find(scan, E, tiles_lo, blockIdx.x);
+    if (blockIdx.y == 0) {  // the records of this chunk's items, or of the items that a chunk of the launch at most would have
+        const char *w = table ? reinterpret_cast<const char *>(table[ci.expert]) : w_base + (size_t)(slot_by_rank ? ci.slot : ci.expert) * w_stride;
+        if (!table && slot_by_rank && ci.slot >= n_slots) w = nullptr;
+        for (int i = threadIdx.x; i < gy_up + gy_down; i += 512) {
+            const bool up = i < gy_up;
+            const int col = up ? i : i - gy_up, gy = up ? gy_up : gy_down;
+            const int at = ci.nrows ? gemm_launch_order(scan, blockIdx.x, col, gy) : blockIdx.x * gy + col;
+            items[(up ? 0 : (size_t)gridDim.x * gy_up) + at] = GemmItem{w, ci.row0, ci.nrows, ci.tile0, col};
+        }
+    }
     if (ci.nrows == 0) return;  // uniform over the workgroup
     const int rt = (ci.nrows + 15) >> 4;
     const int kt0 = blockIdx.y * PACK_KT;
@@ -436,26 +453,17 @@ __device__ inline void gemm_tile_body(const GemmTile &t, const char *ring, int w
 //             to bf16 and stored packed for the down-projection.
 template <int BN, bool UP>
 __global__ __launch_bounds__(512) void ffn_gemm_tile_kernel(
-    const char *__restrict__ a_packed, const int32_t *__restrict__ offsets, int E, int K, int N, int n_split,
-    const char *__restrict__ w_base, size_t w_stride, int slot_by_rank, int n_slots,
-    const unsigned long long *__restrict__ table, char *__restrict__ h, float *__restrict__ partial,
-    __bf16 *__restrict__ y_perm, int n_rows, int tiles_lo, int tiles_hi) {
+    const char *__restrict__ a_packed, const GemmItem *__restrict__ items, int K, int N, int n_split, const char *__restrict__ w_base,
+    char *__restrict__ h, float *__restrict__ partial, __bf16 *__restrict__ y_perm, int n_rows) {
     extern __shared__ __attribute__((aligned(1024))) char ring[];
-    GemmScan scan;
-    gemm_scan(offsets, E, tiles_lo, tiles_hi, scan);
-    int chunk_id, col_id;
-    if (!gemm_item(scan, chunk_id, col_id)) return;
-    const GemmChunk ci = gemm_find(scan, E, tiles_lo, chunk_id);
+    const GemmItem ci = items[blockIdx.x];
     if (ci.nrows == 0) return;  // uniform over the workgroup
-    const char *wexp = table ? reinterpret_cast<const char *>(table[ci.expert])
-                             : w_base + (size_t)(slot_by_rank ? ci.slot : ci.expert) * w_stride;
     GemmTile t;
-    t.no_weights = table ? wexp == nullptr : (slot_by_rank && ci.slot >= n_slots);
-    const char *wsafe = t.no_weights ? w_base : wexp;  // a valid address; the rows are written as zeros
+    t.no_weights = ci.w == nullptr;
+    const char *wsafe = t.no_weights ? w_base : ci.w;  // a valid address; the rows are written as zeros
 
     const int n_blocks = N / BN;
-    const int nb = col_id % n_blocks, split = col_id / n_blocks;
-    const int n0 = nb * BN;
+    const int split = n_split == 1 ? 0 : ci.col / n_blocks, n0 = (ci.col - split * n_blocks) * BN;
     t.nrows = ci.nrows;
     t.rt = (ci.nrows + 15) >> 4;
     t.n_kt = K / n_split / 32;
@@ -489,12 +497,20 @@ __global__ __launch_bounds__(512) void ffn_gemm_tile_kernel(
 // ------------------------------------------------------------------------------------------
 constexpr int GEMM_SPLIT = 4;  // most K slices of the down-projection (float32 partials)
 
-// Workspace: float32 partials of the down-projection (most K slices), then the bf16 hidden activation and the packed
-// rows (with room for 128-row chunks, at most one partly filled one per expert; 16-row tiles are what is used).
+static int gemm_max_chunks(const pgmoe_config &c, int64_t n_rows) {
+    return (int)(std::max<int64_t>(1, std::min<int64_t>(c.n_experts, n_rows)) + n_rows / GEMM_ROWS);
+}
+// The records of a launch's items (column blocks of the products, K slices); with 128 columns and every slice the most there can be.
+static size_t gemm_item_bytes(const pgmoe_config &c, int64_t n_rows, int bn_up = 128, int bn_down = 128, int split = GEMM_SPLIT) {
+    return (size_t)gemm_max_chunks(c, n_rows) * (c.d_ff / bn_up + c.d_model / bn_down * split) * sizeof(GemmItem);
+}
+
+// Workspace: float32 partials of the down-projection (most K slices), then the bf16 hidden activation, the packed
+// rows and the items' records (with room for 128-row chunks, at most one partly filled one per expert; 16-row tiles are what is used).
 size_t ffn_gemm_workspace_bytes(const pgmoe_config &c) {
     const int64_t max_rows = (int64_t)c.max_tokens * c.top_k;
     return (size_t)GEMM_SPLIT * max_rows * c.d_model * 4 +
-           (size_t)(max_rows / 128 + std::min<int64_t>(c.n_experts, max_rows)) * 128 * (c.d_ff + c.d_model) * 2 + 256;
+           (size_t)(max_rows / 128 + std::min<int64_t>(c.n_experts, max_rows)) * 128 * (c.d_ff + c.d_model) * 2 + gemm_item_bytes(c, max_rows) + 256;
 }
 
 // What pgmoe_expert_ffn_static admits a launch of n_rows rows by (against PGMOE_STATIC_SCRATCH_BYTES; not what a launch uses).  A launch with
@@ -554,7 +570,7 @@ bool uses_gemm_kernels(const pgmoe_config &c, int n_rows) {
     if (n_rows / active >= GEMM_ALWAYS) return true;
     if (n_rows / active < 8) return false;
     // the static buffer has to hold at least one chunk of a launch it admits
-    if (ffn_partial_bytes(c, n_rows) <= PGMOE_STATIC_SCRATCH_BYTES && 2 * GEMM_RT * gemm_tile_bytes(c) > PGMOE_STATIC_SCRATCH_BYTES) return false;
+    if (ffn_partial_bytes(c, n_rows) <= PGMOE_STATIC_SCRATCH_BYTES && 2 * GEMM_RT * gemm_tile_bytes(c) + gemm_item_bytes(c, n_rows) > PGMOE_STATIC_SCRATCH_BYTES) return false;
     const double gemm = 23.5 + 0.00087 * (c.d_model + c.d_ff) + gemm_estimate(c, n_rows);
     // in doubt fused: a skewed routing costs the GEMMs more, with many experts above all
     const double margin = c.d_model <= 256 ? (active >= 64 ? 1.5 : 1.1) : (active >= 96 ? 1.1 : (active >= 32 ? 1.05 : 1.0));
@@ -590,7 +606,7 @@ static GemmPlan gemm_plan(const pgmoe_config &c, int n_rows) {
                 // row tiles the static buffer has to hold beside them: with hundreds of rows per expert all (1280 rows over 4 experts of 1024 x 4096
                 // with two K slices 76 us, with four 69 but 108 in the static buffer's two passes), else those of a pass
                 const int hold = n_rows / active >= GEMM_ALWAYS ? active + n_rows / 16 : 2 * GEMM_RT;
-                if (admitted && split > 1 && p_bytes + hold * gemm_tile_bytes(c) > PGMOE_STATIC_SCRATCH_BYTES) continue;
+                if (admitted && split > 1 && p_bytes + hold * gemm_tile_bytes(c) + gemm_item_bytes(c, n_rows, 128, bn, split) > PGMOE_STATIC_SCRATCH_BYTES) continue;
                 const double down = rounds(chunks * (c.d_model / bn) * split) * (c.d_ff / 32 / split * stage + 4.0) +
                                     (split > 1 ? 2.0 * p_bytes : 2.0 * n_rows * c.d_model * 2.0) / 4.0e6;
                 if (down < best_down) {
@@ -605,19 +621,20 @@ static GemmPlan gemm_plan(const pgmoe_config &c, int n_rows) {
 }
 
 // The scratch of a launch: float32 partials [split][n_rows, d] first (the combine reads them at the workspace's start; none with one
-// slice), then the packed hidden activation and the packed rows, by 16-row tiles (at most one partly filled tile per expert).
+// slice), then the packed hidden activation and the packed rows, by 16-row tiles (at most one partly filled tile per expert), and the items' records.
 // Scratch that does not hold every tile (the static buffer) is used for one range of chunks after the other: a
 // chunk's result does not depend on the others, so the number of passes changes no bit.
 struct GemmScratch {
     int max_tiles;  // most row tiles of the launch
-    size_t room;    // row tiles the scratch holds behind the partials
+    size_t room;    // row tiles the scratch holds beside the partials and the items' records
     bool one_pass;
     int tiles;      // first tiles of a pass: its last chunk may reach past them
 };
-static GemmScratch gemm_scratch(const pgmoe_config &c, int n_rows, size_t p_bytes, size_t workspace_bytes) {
+static GemmScratch gemm_scratch(const pgmoe_config &c, int n_rows, const GemmPlan &p, size_t workspace_bytes) {
     GemmScratch r;
+    const size_t beside = p.p_bytes + gemm_item_bytes(c, n_rows, p.bn_up, p.bn_down, p.split);
     r.max_tiles = std::max(1, std::min(c.n_experts, n_rows)) + n_rows / 16;
-    r.room = workspace_bytes > p_bytes ? (workspace_bytes - p_bytes) / gemm_tile_bytes(c) : 0;
+    r.room = workspace_bytes > beside ? (workspace_bytes - beside) / gemm_tile_bytes(c) : 0;
     r.one_pass = r.room >= (size_t)r.max_tiles;
     r.tiles = r.one_pass ? r.max_tiles : (int)r.room - GEMM_RT;
     return r;
@@ -630,7 +647,7 @@ static GemmScratch gemm_scratch(const pgmoe_config &c, int n_rows, size_t p_byte
 // but 16 of 2048 x 8192 at 96 rows 1243 and 307, 24 of 1024 x 4096 at 128 rows 463 and 188.
 int gemm_slices_for_fused(const pgmoe_config &c, int n_rows, size_t workspace_bytes) {
     const GemmPlan p = gemm_plan(c, n_rows);
-    const GemmScratch r = gemm_scratch(c, n_rows, p.p_bytes, workspace_bytes);
+    const GemmScratch r = gemm_scratch(c, n_rows, p, workspace_bytes);
     if (r.one_pass || r.tiles < 1) return 0;
     const int passes = (r.max_tiles + r.tiles - 1) / r.tiles;
     const double gemm = passes * (18.0 + 0.01 * (c.d_model + c.d_ff / p.split)) + gemm_estimate(c, n_rows);
@@ -641,35 +658,37 @@ int launch_ffn_gemm(pgmoe_ctx *ctx, const char *w_base, size_t w_stride, bool sl
                     const int32_t *offsets, int n_rows, void *y_perm, void *workspace, size_t workspace_bytes, hipStream_t s,
                     int *keep_partials, const unsigned long long *table, const int32_t *src_row) {
     const pgmoe_config &c = ctx->cfg;
-    const int active = std::max(1, std::min(c.n_experts, n_rows)), max_chunks = active + n_rows / GEMM_ROWS;
+    const int max_chunks = gemm_max_chunks(c, n_rows);
     const GemmPlan p = gemm_plan(c, n_rows);
-    const GemmScratch r = gemm_scratch(c, n_rows, p.p_bytes, workspace_bytes);
+    const GemmScratch r = gemm_scratch(c, n_rows, p, workspace_bytes);
     if (!r.one_pass && r.tiles < GEMM_RT)
         return fail(ctx, PGMOE_EINVAL, "pgmoe_expert_ffn: hidden activation, packed rows and partial sums of %d rows do not fit the workspace", n_rows);
-    const size_t h_bytes = (r.one_pass ? (size_t)r.max_tiles : r.room) * 16 * c.d_ff * 2;
+    const size_t held = r.one_pass ? (size_t)r.max_tiles : r.room, h_bytes = held * 16 * c.d_ff * 2;
+    const int gy_up = c.d_ff / p.bn_up, gy_down = c.d_model / p.bn_down * p.split;
     float *partial = p.split > 1 ? (float *)workspace : nullptr;
     char *h = (char *)workspace + p.p_bytes;
     char *xp = h + h_bytes;
+    GemmItem *items = (GemmItem *)(h + held * gemm_tile_bytes(c));
     const int tslot = ffn_timing_slot(ctx);
     if (tslot >= 0) PG_HIP(ctx, hipEventRecord(ctx->tim_begin[tslot], s));
     for (int lo = 0; lo < r.max_tiles; lo += r.tiles) {
         const int hi = r.one_pass ? INT_MAX : lo + r.tiles;  // INT_MAX: every chunk
         hipLaunchKernelGGL(ffn_gemm_pack_rows_kernel, dim3(max_chunks, c.d_model / 32 / PACK_KT), dim3(512), 0, s, (const __bf16 *)x_perm,
-                           offsets, c.n_experts, c.d_model, src_row, (__bf16 *)xp, lo, hi);
+                           offsets, c.n_experts, c.d_model, src_row, (__bf16 *)xp, lo, hi, w_base, w_stride, slot_by_rank ? 1 : 0, n_slots, table, items,
+                           gy_up, gy_down);
         PG_HIP(ctx, hipGetLastError());
-#define PG_TILE(BN_, UP_, A_, K_, N_, SPLIT_)                                                                                 \
+#define PG_TILE(BN_, UP_, A_, ITEMS_, GY_, K_, N_, SPLIT_)                                                                         \
     do {                                                                                                                           \
-        auto kern_ = ffn_gemm_tile_kernel<BN_, UP_>;                                                                          \
-        if (int rc_ = allow_dynamic_lds(ctx, reinterpret_cast<const void *>(kern_), GEMM_RING)) return rc_;                              \
-        hipLaunchKernelGGL(kern_, dim3(max_chunks, N_ / BN_ * SPLIT_), dim3(512), GEMM_RING, s, (const char *)(A_), offsets,             \
-                           c.n_experts, K_, N_, SPLIT_, w_base, w_stride, slot_by_rank ? 1 : 0, n_slots, table, h, partial,        \
-                           (__bf16 *)y_perm, n_rows, lo, hi);                                                                      \
+        auto kern_ = ffn_gemm_tile_kernel<BN_, UP_>;                                                                               \
+        if (int rc_ = allow_dynamic_lds(ctx, reinterpret_cast<const void *>(kern_), GEMM_RING)) return rc_;                        \
+        hipLaunchKernelGGL(kern_, dim3(max_chunks * GY_), dim3(512), GEMM_RING, s, (const char *)(A_), ITEMS_, K_, N_, SPLIT_, w_base, h, partial, \
+                           (__bf16 *)y_perm, n_rows);                                                                              \
         PG_HIP(ctx, hipGetLastError());                                                                                            \
     } while (0)
-        if (p.bn_up == 256) PG_TILE(256, true, xp, c.d_model, c.d_ff, 1);
-        else PG_TILE(128, true, xp, c.d_model, c.d_ff, 1);
-        if (p.bn_down == 256) PG_TILE(256, false, h, c.d_ff, c.d_model, p.split);
-        else PG_TILE(128, false, h, c.d_ff, c.d_model, p.split);
+        if (p.bn_up == 256) PG_TILE(256, true, xp, items, gy_up, c.d_model, c.d_ff, 1);
+        else PG_TILE(128, true, xp, items, gy_up, c.d_model, c.d_ff, 1);
+        if (p.bn_down == 256) PG_TILE(256, false, h, items + (size_t)max_chunks * gy_up, gy_down, c.d_ff, c.d_model, p.split);
+        else PG_TILE(128, false, h, items + (size_t)max_chunks * gy_up, gy_down, c.d_ff, c.d_model, p.split);
 #undef PG_TILE
     }
     if (tslot >= 0) PG_HIP(ctx, hipEventRecord(ctx->tim_end[tslot], s));
