@@ -31,6 +31,13 @@
 
 namespace pgmoe {
 
+// An address that is the same for the whole wavefront, in scalar registers.
+__device__ inline const char *uniform_address(const void *p) {
+    const unsigned long long a = (unsigned long long)p;
+    const unsigned lo = __builtin_amdgcn_readfirstlane((unsigned)a), hi = __builtin_amdgcn_readfirstlane((unsigned)(a >> 32));
+    return (const char *)(((unsigned long long)hi << 32) | lo);
+}
+
 // MT: 16-row tiles per chunk; KT = d_model/32; NW: wavefronts per workgroup (sub-slab = 16*NW
 // d_ff columns); D: weight tiles (1 KiB each) a wavefront keeps in flight.
 //
@@ -305,8 +312,9 @@ __global__ __launch_bounds__(256) void ffn_reduce_kernel(const float *__restrict
 // of the row, i.e. its output row i is column V*i + j, and every lane ends up with 4*V neighbouring columns of one token.
 // Bound by the weight stream (HBM); F32_DEPTH blocks of loads are in flight per wavefront.  One thread
 // per output column walking k by itself, which this replaces, re-read the weights once per row and paid a
-// memory latency every few k: 8 experts of 768 x 3072, 100 rows, 284 us + 836 us, now 21 + 30 from HBM and 19 + 24 from the
-// last-level cache (75 MB of weights each; the second product has half the columns' workgroups, and its hidden rows share the CUs' request slots).
+// memory latency every few k: 8 experts of 768 x 3072, 100 rows, 284 us + 836 us, now 17 + 20 from the last-level cache (75 MB of weights each).
+// 18.4 + 23.7 while the requests were conditional: the compiler, which then cannot count them, waited for every load in flight once per round of blocks,
+// so the blocks came in batches with a memory latency between them.
 constexpr int F32_DEPTH = 4;
 
 template <int V>
@@ -323,6 +331,13 @@ __device__ inline float f32_comp(const typename F32Vec<V>::type &v, int j) {
     else return v[j];
 }
 
+template <int V>
+__device__ inline typename F32Vec<V>::type f32_load(__amdgpu_buffer_rsrc_t rsrc, int lane_off) {
+    if constexpr (V == 1) return __builtin_bit_cast(float, __builtin_amdgcn_raw_buffer_load_b32(rsrc, lane_off, 0, 0));
+    else if constexpr (V == 2) return __builtin_bit_cast(typename F32Vec<V>::type, __builtin_amdgcn_raw_buffer_load_b64(rsrc, lane_off, 0, 0));
+    else return __builtin_bit_cast(typename F32Vec<V>::type, __builtin_amdgcn_raw_buffer_load_b128(rsrc, lane_off, 0, 0));
+}
+
 __device__ inline const RowCombine &the_combine(const RowCombine &combine) { return combine; }
 
 // out[rows, n0 .. n0 + 16*V) = (RELU) a[rows, K] . w[K, N] for the rows of one chunk; a_row0: row of a that is the chunk's
@@ -334,20 +349,17 @@ __device__ inline void f32_tile(const float *__restrict__ a, const int32_t *__re
                                 float *__restrict__ out, const ChunkInfo &ci, int K, int N, bool no_weights,
                                 const int32_t *__restrict__ tokens = nullptr, Combine... combine) {
     typedef typename F32Vec<V>::type vec;
-    typedef __attribute__((address_space(1))) vec gvec;
     __shared__ floatx4 sums[NW][V * MT][64];
     const int lane = threadIdx.x & 63, wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
     const int i16 = lane & 15, g = lane >> 4;
     const int n0 = blockIdx.y * 16 * V;
     const int col = n0 + V * i16;
-    const gvec *wp = (const gvec *)(w + (col < N ? col : 0));  // columns past the end: a valid address, never stored
-    const int wstep = N / V;                                   // vectors per weight row
-    const floatx4 *ap[MT];
+    const char *weights = uniform_address(w);
+    const int row_bytes = N * 4;
+    int w_off[4];  // in a lane's offset, not the scalar one: that would move the descriptor's end, too
 #pragma unroll
-    for (int m = 0; m < MT; ++m) {
-        const int r = m * 16 + i16, row = ci.row0 + (r < ci.nrows ? r : 0);  // rows past the end: a valid row, never stored
-        ap[m] = reinterpret_cast<const floatx4 *>(a + (size_t)(src_row ? src_row[row] : row) * K);
-    }
+    for (int s = 0; s < 4; ++s) w_off[s] = (4 * g + s) * row_bytes + (col < N ? col : 0) * 4;  // columns past the end: valid ones, never stored
+    const floatx4 *ap[MT];
     floatx4 acc[V][MT];
 #pragma unroll
     for (int j = 0; j < V; ++j)
@@ -357,39 +369,64 @@ __device__ inline void f32_tile(const float *__restrict__ a, const int32_t *__re
     const int n_blk = no_weights ? 0 : (K + 15) >> 4, quads = K >> 2;
     vec wv[F32_DEPTH][4];
     floatx4 av[F32_DEPTH][MT];
-    auto request = [&](int b, vec (&wb)[4], floatx4 (&ab)[MT]) {
-        const int q = min(4 * b + g, quads - 1);  // this lane's four k; past the end: the last ones, zeroed when used
+    // Every request is made, also past the end of K, so that the compiler knows how many are in flight: behind conditional ones it waited for all.
+    // Weights past the end come from no memory, as zeros (the descriptor ends there); activations are the row's last ones, zeroed when used.
+    auto request_weights = [&](int b, vec (&wb)[4]) {
+        const int rows = __builtin_amdgcn_readfirstlane(max(0, min(16, K - 16 * b)));  // (the clamp alone would be a vector instruction)
+        const auto rsrc = __builtin_amdgcn_make_buffer_rsrc((void *)(weights + (size_t)min(16 * b, K) * row_bytes), 0, rows * row_bytes, 0x00020000);
 #pragma unroll
-        for (int s = 0; s < 4; ++s) wb[s] = wp[(size_t)(4 * q + s) * wstep];
-#pragma unroll
-        for (int m = 0; m < MT; ++m) ab[m] = ap[m][q];
+        for (int s = 0; s < 4; ++s) wb[s] = f32_load<V>(rsrc, w_off[s]);
     };
-    if (n_blk > 0) {
+    auto request_rows = [&](int b, floatx4 (&ab)[MT]) {
 #pragma unroll
-        for (int p = 0; p < F32_DEPTH; ++p) {
-            if (wave + NW * p < n_blk) request(wave + NW * p, wv[p], av[p]);  // uniform over the wavefront, as below
-        }
+        for (int m = 0; m < MT; ++m) ab[m] = ap[m][min(4 * b + g, quads - 1)];
+    };
+    auto multiply = [&](int b, const vec (&wb)[4], const floatx4 (&ab)[MT]) {
+        const bool live = 4 * b + g < quads;  // false only past the end of K
+#pragma unroll
+        for (int s = 0; s < 4; ++s)
+#pragma unroll
+            for (int j = 0; j < V; ++j)
+#pragma unroll
+                for (int m = 0; m < MT; ++m)
+                    acc[j][m] = __builtin_amdgcn_mfma_f32_16x16x4f32(f32_comp<V>(wb[s], j), live ? ab[m][s] : 0.f, acc[j][m], 0, 0, 0);
+    };
+    int row[MT];
+#pragma unroll
+    for (int m = 0; m < MT; ++m) {
+        const int r = m * 16 + i16;
+        row[m] = ci.row0 + (r < ci.nrows ? r : 0);  // rows past the end: a valid row, never stored
+        if (src_row) row[m] = src_row[row[m]];
     }
-    for (int b0 = wave; b0 < n_blk; b0 += NW * F32_DEPTH) {
+    __builtin_amdgcn_sched_barrier(0);
+    if (wave < n_blk) {  // uniform over the wavefront, as below
+#pragma unroll
+        for (int p = 0; p < F32_DEPTH; ++p) request_weights(wave + NW * p, wv[p]);
+        __builtin_amdgcn_sched_barrier(0);
+#pragma unroll
+        for (int m = 0; m < MT; ++m) ap[m] = reinterpret_cast<const floatx4 *>(a + (size_t)row[m] * K);  // the weights did not wait for it
+#pragma unroll
+        for (int p = 0; p < F32_DEPTH; ++p) request_rows(wave + NW * p, av[p]);
+        int b0 = wave;
+        auto round = [&]() {
+#pragma unroll
+            for (int p = 0; p < F32_DEPTH; ++p) {
+                multiply(b0 + NW * p, wv[p], av[p]);
+                __builtin_amdgcn_sched_barrier(0);
+                request_weights(b0 + NW * (p + F32_DEPTH), wv[p]);
+                request_rows(b0 + NW * (p + F32_DEPTH), av[p]);
+                __builtin_amdgcn_sched_barrier(0);
+            }
+            b0 += NW * F32_DEPTH;
+        };
+        if (b0 + NW * F32_DEPTH < n_blk) {
+            round();  // on its own: what it waits for lies in another order than in the rounds after it
+            while (b0 + NW * F32_DEPTH < n_blk) round();
+        }
 #pragma unroll
         for (int p = 0; p < F32_DEPTH; ++p) {
-            const int b = b0 + NW * p;
-            if (b >= n_blk) break;
-            const bool live = 4 * b + g < quads;  // false only past the end of K
-            vec wc[4];
-            floatx4 ac[MT];
-#pragma unroll
-            for (int s = 0; s < 4; ++s) wc[s] = live ? wv[p][s] : vec{};
-#pragma unroll
-            for (int m = 0; m < MT; ++m) ac[m] = live ? av[p][m] : floatx4{0.f, 0.f, 0.f, 0.f};
-            if (b + NW * F32_DEPTH < n_blk) request(b + NW * F32_DEPTH, wv[p], av[p]);
-#pragma unroll
-            for (int s = 0; s < 4; ++s)
-#pragma unroll
-                for (int j = 0; j < V; ++j)
-#pragma unroll
-                    for (int m = 0; m < MT; ++m)
-                        acc[j][m] = __builtin_amdgcn_mfma_f32_16x16x4f32(f32_comp<V>(wc[s], j), ac[m][s], acc[j][m], 0, 0, 0);
+            if (b0 + NW * p >= n_blk) break;
+            multiply(b0 + NW * p, wv[p], av[p]);
         }
     }
 #pragma unroll
@@ -397,16 +434,18 @@ __device__ inline void f32_tile(const float *__restrict__ a, const int32_t *__re
 #pragma unroll
         for (int m = 0; m < MT; ++m) sums[wave][j * MT + m][lane] = acc[j][m];
     // thread -> (row tile, lane, r): V neighbouring columns of one row
-    vec res[(MT * 256 + NW * 64 - 1) / (NW * 64)];
-    float p[(MT * 256 + NW * 64 - 1) / (NW * 64)];
-    if constexpr (sizeof...(Combine) > 0) {  // on their way while the sums meet
+    constexpr int OUT = (MT * 256 + NW * 64 - 1) / (NW * 64);
+    vec res[OUT];
+    float prob[OUT];
+    int token[OUT];
+    if constexpr (sizeof...(Combine) > 0) {  // on their way while the sums meet (ahead of the products they delayed the first weights)
         const RowCombine &rc = the_combine(combine...);
 #pragma unroll
         for (int o = threadIdx.x, i = 0; o < MT * 256; o += NW * 64, ++i) {
             const int l = (o >> 2) & 63, m = o >> 8, row = m * 16 + (l & 15), c = n0 + V * (4 * (l >> 4) + (o & 3));
-            const int t = tokens[ci.row0 + (row < ci.nrows ? row : 0)];
-            p[i] = rc.prob[t];
-            res[i] = *reinterpret_cast<const vec *>(rc.x_res + (size_t)t * N + (c < N ? c : 0));
+            token[i] = tokens[ci.row0 + (row < ci.nrows ? row : 0)];
+            prob[i] = rc.prob[token[i]];
+            res[i] = *reinterpret_cast<const vec *>(rc.x_res + (size_t)token[i] * N + (c < N ? c : 0));
         }
     }
     __syncthreads();
@@ -427,15 +466,15 @@ __device__ inline void f32_tile(const float *__restrict__ a, const int32_t *__re
         }
         if constexpr (sizeof...(Combine) > 0) {
             const RowCombine &rc = the_combine(combine...);
-            const size_t at = (size_t)tokens[ci.row0 + row] * N + c;
+            const size_t at = (size_t)token[i] * N + c;
             vec n;
             if constexpr (V == 1) {
-                y = fmaf(p[i], y, 0.f);
+                y = fmaf(prob[i], y, 0.f);
                 n = res[i] + y;
             } else {
 #pragma unroll
                 for (int j = 0; j < V; ++j) {
-                    y[j] = fmaf(p[i], y[j], 0.f);
+                    y[j] = fmaf(prob[i], y[j], 0.f);
                     n[j] = res[i][j] + y[j];
                 }
             }
@@ -759,6 +798,9 @@ static int launch_ffn_f32(pgmoe_ctx *ctx, const char *w_base, size_t w_stride, b
         const int mt = mean <= 16 ? 1 : (mean <= 32 ? 2 : 4);
         const int chunks = active + n_rows / (16 * mt);
         auto cols = [&](int N) { return active * ((N + 63) / 64) >= (mean >= 8 ? 96 : 256) ? 4 : (active * ((N + 31) / 32) >= 128 ? 2 : 1); };
+        // twice the wavefronts per workgroup where each CU has one workgroup at most and a wavefront still keeps its four blocks in flight: 8 experts of
+        // 768 x 3072 with 12 rows each, steps from HBM 46.8 -> 43.8 us; 16 of 1024 x 4096 with 4 rows 115 -> 108
+        auto wide = [&](int N, int K) { return active * ((N + 63) / 64) <= 256 && K >= 16 * 16 * F32_DEPTH; };
 #define PG_F32_HIDDEN(V_, MT_, NW_)                                                                                            \
     hipLaunchKernelGGL((ffn_f32_hidden_kernel<V_, MT_, NW_>), dim3(chunks, (c.d_ff + 16 * V_ - 1) / (16 * V_)), dim3(NW_ * 64), 0, s, \
                        x, src_row, offsets, c.n_experts, c.d_model, c.d_ff, w_base, w_stride, slot_by_rank ? 1 : 0, n_slots, table, h)
@@ -770,11 +812,12 @@ static int launch_ffn_f32(pgmoe_ctx *ctx, const char *w_base, size_t w_stride, b
         if (combine) hipLaunchKernelGGL((ffn_f32_out_kernel<V_, MT_, NW_, RowCombine>), PG_F32_OUT_ARGS(V_, MT_, NW_), *combine); \
         else hipLaunchKernelGGL((ffn_f32_out_kernel<V_, MT_, NW_>), PG_F32_OUT_ARGS(V_, MT_, NW_));                            \
     } while (0)
-#define PG_F32(KERN_, N_)                                                                                                      \
+#define PG_F32(KERN_, N_, K_)                                                                                                    \
     do {                                                                                                                       \
         const int v_ = cols(N_);                                                                                               \
         if (mt == 1) {                                                                                                         \
-            if (v_ == 4) KERN_(4, 1, 8);                                                                                       \
+            if (v_ == 4 && wide(N_, K_)) KERN_(4, 1, 16);                                                                      \
+            else if (v_ == 4) KERN_(4, 1, 8);                                                                                  \
             else if (v_ == 2) KERN_(2, 1, 8);                                                                                  \
             else KERN_(1, 1, 8);                                                                                               \
         } else if (mt == 2) {                                                                                                  \
@@ -788,8 +831,8 @@ static int launch_ffn_f32(pgmoe_ctx *ctx, const char *w_base, size_t w_stride, b
         }                                                                                                                      \
         PG_HIP(ctx, hipGetLastError());                                                                                        \
     } while (0)
-        PG_F32(PG_F32_HIDDEN, c.d_ff);
-        PG_F32(PG_F32_OUT, c.d_model);
+        PG_F32(PG_F32_HIDDEN, c.d_ff, c.d_model);
+        PG_F32(PG_F32_OUT, c.d_model, c.d_ff);
 #undef PG_F32
 #undef PG_F32_OUT
 #undef PG_F32_OUT_ARGS

@@ -58,3 +58,13 @@ def test_f32_block_reads_its_rows_in_place(hx, T, d, f, E, k, offloaded):  # noq
         y = R.block(xs[i], o["p"], o["idx"], {int(e): cache[(i, int(e))] for e in np.unique(o["idx"])}, w.d_ff)
         assert nerr(ys[i][ok], y[ok]) <= TOL["f32"], f"block {i}"
     stack.close()
+
+
+@pytest.mark.parametrize("d,f,E,counts", [
+    (768, 1024, 8, [12, 16, 9, 1, 17, 12, 12, 17]),     # sixteen wavefronts in the second product, each with its four blocks of 16 k and no more
+    (772, 1028, 8, [12, 16, 9, 0, 17, 12, 13, 17]),     # a block of four k past them, columns past a tile's end
+    (832, 2064, 12, [8, 9] * 6),                        # a second round of blocks for the first wavefront only
+    (64, 4100, 16, [3] * 16),                           # many rounds, the last one short
+])
+def test_f32_expert_ffn_over_rounds_of_requests(hx, d, f, E, counts):  # noqa: F811
+    test_f32_expert_ffn_at_tile_edges(hx, d, f, E, counts)
