@@ -48,9 +48,8 @@ __device__ inline const char *uniform_address(const void *p) {
 // and across the LDS barrier between them.
 //
 // Gate: nothing, or CarriedGate: grid row 0 then runs that gate's first half and the d_ff ranges follow.  A variant of its own, because
-// the gate's code costs the kernel registers (d_model 512, 16-row chunks: 170 with it, 148 without, i.e. two or three wavefronts per
-// SIMD; 64: 106 and 54) that a launch without a gate has no use for (64 experts of 512 x 2048, a block of 64 tokens: 56.8 us with the gate's
-// code in the kernel, 53.6 without).
+// the gate's code costs small kernels registers (d_model 64: 106 with it, 48 without) that a launch without a gate has no use for.
+constexpr int FUSED_PINNED = 0x6;  // what the scheduler may move past a request: scalar and vector arithmetic, not products, loads or LDS reads
 template <int MT, int KT, int NW, int D, typename... Gate>
 __global__ __launch_bounds__(NW * 64) void ffn_fused_kernel(
     const __bf16 *__restrict__ x_perm, const int32_t *__restrict__ offsets, int E, int f, int f_range,
@@ -67,7 +66,7 @@ __global__ __launch_bounds__(NW * 64) void ffn_fused_kernel(
     static_assert(NTD % NW == 0 && SUB % 32 == 0, "tile split");
     extern __shared__ __attribute__((aligned(16))) char smem[];
 
-    const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
+    const int tid = threadIdx.x, lane = tid & 63, wave = __builtin_amdgcn_readfirstlane(tid >> 6);
     int range = blockIdx.y;
     if constexpr (sizeof...(Gate) > 0) {
         static_assert(NW == 4, "the first half is 256 threads'");
@@ -85,27 +84,38 @@ __global__ __launch_bounds__(NW * 64) void ffn_fused_kernel(
                              : w_base + (size_t)(slot_by_rank ? ci.slot : ci.expert) * w_stride;
     const bool no_weights = table ? wexp == nullptr : (slot_by_rank && ci.slot >= n_slots);  // no slot: rows are zeroed
 
-    // weights are addressed as global memory explicitly: the blob's address may come out of the
-    // cache's pointer table, and a load the compiler cannot prove global becomes a flat load, which
-    // also counts on the LDS wait counter and would drain the prefetch ring at every LDS read
-    const global_bf16x8 *w1 = (const global_bf16x8 *)wexp + lane;
-    const global_bf16x8 *w2 = (const global_bf16x8 *)(wexp + (size_t)d * f * 2) + lane;
     const int n_sub = no_weights ? 0 : f_range / SUB;
     const int fs0 = range * f_range;
 
     // tile i (0 <= i < NT, compile-time after unrolling) of sub-slab s
-    auto tile_ptr = [&](int s, int i) -> const global_bf16x8 * {
+    // A wavefront's tiles of sub-slab s: scalar addresses, to which a lane adds its 16 bytes, through descriptors of up to four tiles.  Past the last
+    // sub-slab these are empty: requests for tiles there read no memory, so every request is made and the compiler knows how many loads are in
+    // flight at any point.  With requests that depended on s it waited for all of them towards the end of every sub-slab, and it moved them down to
+    // where it waited: 64 experts of 1024 x 4096, 2000 skewed rows 278 -> 237 us a block, 128 experts 1500 rows 413 -> 397, 128 rows 130 -> 122.
+    const char *const w1 = uniform_address(wexp), *const w2 = w1 + (size_t)d * f * 2;
+    struct Slab {
+        const char *a, *b;
+        int window;  // bytes of a descriptor
+    };
+    auto slab = [&](int s) {
         const int fs = fs0 + s * SUB;
-        if (i < NT_A) return w1 + (((size_t)((fs >> 4) + wave) * KT + i) << 6);
-        const int j = i - NT_A, kb = j / NTB, a = j - kb * NTB;
-        return w2 + (((size_t)((fs >> 5) + kb) * NTD + wave * NTB + a) << 6);
+        return Slab{w1 + ((size_t)((fs >> 4) + wave) * KT << 10), w2 + ((size_t)((fs >> 5) * NTD + wave * NTB) << 10), s < n_sub ? 4096 : 0};
+    };
+    auto load_tile = [&](const Slab &sl, int i) -> bf16x8 {
+        const int j = i - NT_A, kb = j / NTB, a = j - kb * NTB, in_run = i < NT_A ? i : a;
+        const char *run = i < NT_A ? sl.a : sl.b + ((size_t)(kb * NTD) << 10);
+        const auto rsrc = __builtin_amdgcn_make_buffer_rsrc((void *)(run + ((size_t)(in_run & ~3) << 10)), 0, sl.window, 0x00020000);
+        return __builtin_bit_cast(bf16x8, __builtin_amdgcn_raw_buffer_load_b128(rsrc, lane * 16 + ((in_run & 3) << 10), 0, 0));
     };
 
+    static_assert(D <= NT && NT % D == 0, "the ring reaches into the next sub-slab at most, where a tile finds the place that was filled for it");
+    // The 64-row chunks of d_model 768 leave it to the compiler: a launch of theirs that fills the chip is paced by HBM, which the pauses do not slow (128 experts of
+    // 768 x 3072, 4096 rows: 231 us a block, 234 with the steady stream).
+    constexpr bool STEADY = !(NW == 8 && KT == 24);
     bf16x8 ring[D];
+    Slab now = slab(0);
 #pragma unroll
-    for (int g = 0; g < D; ++g) {
-        if (g / NT < n_sub) ring[g] = *tile_ptr(g / NT, g % NT);
-    }
+    for (int g = 0; g < D; ++g) ring[g] = load_tile(now, g);
 
     bf16x8 *xs = reinterpret_cast<bf16x8 *>(smem);   // [MT][KT][64] operand cells
     bf16x8 *hs = xs + (size_t)MT * KT * 64;          // [2][MT][KTB][64]
@@ -133,25 +143,39 @@ __global__ __launch_bounds__(NW * 64) void ffn_fused_kernel(
 #pragma unroll
         for (int m = 0; m < MT; ++m) yacc[a][m] = floatx4{0.f, 0.f, 0.f, 0.f};
 
+    // The rows' operand cells are read from LDS AHEAD tiles before their products.
+    constexpr int AHEAD = KT < 4 ? 1 : (MT == 1 ? 4 : (MT == 2 || NW == 8 ? 2 : 1));
+    static_assert(AHEAD <= NT_A && AHEAD <= NT_B, "the cells of the next sub-slab replace none that is still to be used");
+    bf16x8 xa[AHEAD + 1][MT];
+    constexpr int HB = MT * NTB >= 32 ? 1 : 2;  // hidden cells of the next k-tile, too, where the accumulators leave registers for them
+#pragma unroll
+    for (int i = 0; i < AHEAD; ++i)
+#pragma unroll
+        for (int m = 0; m < MT; ++m) xa[i][m] = xs[((m * KT + i) << 6) + lane];
+
     const int q = lane >> 4;
     for (int s = 0; s < n_sub; ++s) {
+        const Slab next = slab(s + 1);
         floatx4 hacc[MT];
 #pragma unroll
         for (int m = 0; m < MT; ++m) hacc[m] = floatx4{0.f, 0.f, 0.f, 0.f};
-        bf16x8 hfrag[MT];
+        bf16x8 hfrag[HB][MT];
         const bf16x8 *hb = hs + (size_t)(s & 1) * MT * KTB * 64;
-#pragma unroll
-        for (int i = 0; i < NT; ++i) {
+        static_for<NT>([&](auto tile) {
+            constexpr int i = decltype(tile)::value;
             const bf16x8 v = ring[i % D];
-            {   // request tile g + D of the stream
-                const int ds = (i + D) / NT, ii = (i + D) % NT;
-                if (s + ds < n_sub) ring[i % D] = *tile_ptr(s + ds, ii);
+            // request tile g + D of the stream; where STEADY it stays where it is written
+            if (STEADY || i + D < NT || s + 1 < n_sub) ring[i % D] = load_tile(i + D < NT ? now : next, (i + D) % NT);
+            if constexpr ((i + AHEAD) % NT < NT_A) {
+#pragma unroll
+                for (int m = 0; m < MT; ++m) xa[(i + AHEAD) % NT % (AHEAD + 1)][m] = xs[((m * KT + (i + AHEAD) % NT) << 6) + lane];
             }
-            if (i < NT_A) {
+            if constexpr (STEADY) __builtin_amdgcn_sched_barrier(FUSED_PINNED);
+            if constexpr (i < NT_A) {
                 // ---- phase A: hidden features [fs + 16*wave, +16) over the full d_model reduction
 #pragma unroll
                 for (int m = 0; m < MT; ++m)
-                    hacc[m] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(v, xs[((m * KT + i) << 6) + lane], hacc[m], 0, 0, 0);
+                    hacc[m] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(v, xa[i % (AHEAD + 1)][m], hacc[m], 0, 0, 0);
                 if (i == NT_A - 1) {
                     // ReLU, round to bf16, store as phase-B operand: feature 16*wave + 4*q + r is
                     // k-tile wave/2, k-group 2*(wave%2) + q/2, position 4*(q%2) + r of token lane%16
@@ -171,16 +195,21 @@ __global__ __launch_bounds__(NW * 64) void ffn_fused_kernel(
                 }
             } else {
                 // ---- phase B: y[:, wave's columns] += H_sub . W2[fs .. fs+SUB, wave's columns]
-                const int j = i - NT_A, kb = j / NTB, a = j - kb * NTB;
-                if (a == 0) {
+                constexpr int j = i - NT_A, kb = j / NTB, a = j - kb * NTB;
+                if (a == 0 && (HB == 1 || kb == 0)) {
 #pragma unroll
-                    for (int m = 0; m < MT; ++m) hfrag[m] = hb[((m * KTB + kb) << 6) + lane];
+                    for (int m = 0; m < MT; ++m) hfrag[0][m] = hb[((m * KTB + kb) << 6) + lane];
+                }
+                if (HB > 1 && a == 0 && kb + 1 < KTB) {
+#pragma unroll
+                    for (int m = 0; m < MT; ++m) hfrag[(kb + 1) % HB][m] = hb[((m * KTB + kb + 1) << 6) + lane];
                 }
 #pragma unroll
                 for (int m = 0; m < MT; ++m)
-                    yacc[a][m] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(v, hfrag[m], yacc[a][m], 0, 0, 0);
+                    yacc[a][m] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(v, hfrag[kb % HB][m], yacc[a][m], 0, 0, 0);
             }
-        }
+        });
+        now = next;
     }
 
     // ---- epilogue: lane holds token (lane%16) of tile m, output columns 16*(wave*NTB+a) + 4*q + {0..3}
@@ -626,9 +655,9 @@ FfnPlan plan_ffn(const pgmoe_config &c, int n_rows, int slices) {
 // list for a d_model that appears in it (pgmoe_create refuses any other d_model for bf16).
 #define PG_FUSED_CASES(X)                                                                                   \
     X(1, 2, 4, 4) X(1, 4, 4, 8) X(1, 8, 4, 16) X(1, 16, 4, 16) X(1, 24, 4, 16) X(1, 32, 4, 16) X(1, 64, 4, 16) \
-    X(1, 24, 2, 24) X(1, 32, 2, 24)                                                                         \
-    X(2, 2, 4, 4) X(2, 4, 4, 8) X(2, 8, 4, 16) X(2, 16, 4, 16) X(2, 24, 4, 16) X(2, 32, 4, 16)              \
-    X(4, 2, 4, 4) X(4, 4, 4, 8) X(4, 8, 4, 16) X(4, 16, 4, 16) X(4, 24, 4, 16) X(4, 24, 8, 8) X(4, 32, 8, 8)
+    X(1, 24, 2, 16) X(1, 32, 2, 16)                                                                         \
+    X(2, 2, 4, 4) X(2, 4, 4, 8) X(2, 8, 4, 16) X(2, 16, 4, 16) X(2, 24, 4, 16) X(2, 32, 4, 8)              \
+    X(4, 2, 4, 4) X(4, 4, 4, 8) X(4, 8, 4, 16) X(4, 16, 4, 8) X(4, 24, 4, 8) X(4, 24, 8, 8) X(4, 32, 8, 4)
 
 static bool fused_case_built(int mt, int kt, int nw) {
 #define X(MT_, KT_, NW_, D_) \
@@ -749,7 +778,10 @@ static int launch_fused(pgmoe_ctx *ctx, const FfnPlan &p, const char *w_base, si
     constexpr bool CARRIES = NW == 4 && MT <= 2;  // decode-sized chunks
     CarriedGate cg = {};
     if (CARRIES) cg = carry_gate(ctx, gate, false, keep_partials && p.n_partial > 1, gate_done);
-    const size_t lds = (size_t)MT * KT * 1024 + 2u * MT * (16 * NW / 32) * 1024;
+    // No more than two workgroups of four wavefronts per CU: the dispatcher fills a CU before it takes the next, and a few hundred workgroups
+    // at three per CU leave CUs idle (64 experts of 512 x 2048, 64 tokens, six blocks: 201 us a step, 184 with two).
+    constexpr size_t TWO_PER_CU = 54 * 1024;
+    const size_t lds = std::max(KT >= 16 && NW == 4 ? TWO_PER_CU : 0, (size_t)MT * KT * 1024 + 2u * MT * (16 * NW / 32) * 1024);
     float *partial = p.n_partial > 1 ? (float *)workspace : nullptr;
     if (partial && (size_t)p.n_partial * n_rows * c.d_model * 4 > ffn_workspace_bytes(c))
         return fail(ctx, PGMOE_EINVAL, "pgmoe_expert_ffn: %d partial sums of %d rows do not fit the workspace", p.n_partial, n_rows);

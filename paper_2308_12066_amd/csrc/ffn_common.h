@@ -4,6 +4,8 @@
 #define PGMOE_FFN_COMMON_H
 #include <algorithm>
 #include <cstdlib>
+#include <type_traits>
+#include <utility>
 
 #include "pgmoe_internal.h"
 #include "wave.h"
@@ -14,6 +16,15 @@ typedef __bf16 bf16x8 __attribute__((ext_vector_type(8)));
 typedef __bf16 bf16x4 __attribute__((ext_vector_type(4)));
 typedef float floatx4 __attribute__((ext_vector_type(4)));
 typedef __attribute__((address_space(1))) bf16x8 global_bf16x8;  // a load through this is a global_load, never flat
+
+template <typename F, int... I>
+__device__ inline void static_for(F &&f, std::integer_sequence<int, I...>) {
+    (f(std::integral_constant<int, I>()), ...);
+}
+template <int N, typename F>
+__device__ inline void static_for(F &&f) {  // f(0) .. f(N - 1) with constants
+    static_for(f, std::make_integer_sequence<int, N>());
+}
 
 // ------------------------------------------------------------------------------------------
 // Which (expert, row range, slot) does chunk number `chunk` cover?  Chunks are numbered expert

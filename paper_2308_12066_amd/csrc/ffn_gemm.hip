@@ -3,7 +3,6 @@
 #include <climits>
 #include <cmath>
 #include <type_traits>
-#include <utility>
 
 #include "ffn_common.h"
 
@@ -210,15 +209,6 @@ __global__ __launch_bounds__(512) void ffn_gemm_pack_rows_kernel(
         for (int k = 0; k < PACK_KT; ++k)
             if (wave + 8 * j < rt)
                 dst[((size_t)(kt0 + k) * rt + wave + 8 * j) * 64 + cell] = live[j] ? v[j][k] : make_uint4(0, 0, 0, 0);
-}
-
-template <typename F, int... I>
-__device__ inline void static_for(F &&f, std::integer_sequence<int, I...>) {
-    (f(std::integral_constant<int, I>()), ...);
-}
-template <int N, typename F>
-__device__ inline void static_for(F &&f) {  // f(0) .. f(N - 1) with constants
-    static_for(f, std::make_integer_sequence<int, N>());
 }
 
 // Both operands are loaded straight into LDS (global_load_lds_dwordx4: each
