@@ -109,9 +109,10 @@ __global__ __launch_bounds__(NW * 64) void ffn_fused_kernel(
     };
 
     static_assert(D <= NT && NT % D == 0, "the ring reaches into the next sub-slab at most, where a tile finds the place that was filled for it");
-    // The 64-row chunks of d_model 768 leave it to the compiler: a launch of theirs that fills the chip is paced by HBM, which the pauses do not slow (128 experts of
-    // 768 x 3072, 4096 rows: 231 us a block, 234 with the steady stream).
-    constexpr bool STEADY = !(NW == 8 && KT == 24);
+    // The 64-row chunks of d_model 768, and d_model 512, leave it to the compiler: launches of theirs that fill the chip are paced by HBM, which the pauses do not
+    // slow (128 experts of 768 x 3072, 4096 rows: 231 us a block, 234 with the steady stream; 256 of 512 x 2048, 3000 rows: 214 and 218), and the steady
+    // stream's registers cost d_model 512 a wavefront per SIMD.
+    constexpr bool STEADY = KT != 16 && !(NW == 8 && KT == 24);
     bf16x8 ring[D];
     Slab now = slab(0);
 #pragma unroll
@@ -778,10 +779,7 @@ static int launch_fused(pgmoe_ctx *ctx, const FfnPlan &p, const char *w_base, si
     constexpr bool CARRIES = NW == 4 && MT <= 2;  // decode-sized chunks
     CarriedGate cg = {};
     if (CARRIES) cg = carry_gate(ctx, gate, false, keep_partials && p.n_partial > 1, gate_done);
-    // No more than two workgroups of four wavefronts per CU: the dispatcher fills a CU before it takes the next, and a few hundred workgroups
-    // at three per CU leave CUs idle (64 experts of 512 x 2048, 64 tokens, six blocks: 201 us a step, 184 with two).
-    constexpr size_t TWO_PER_CU = 54 * 1024;
-    const size_t lds = std::max(KT >= 16 && NW == 4 ? TWO_PER_CU : 0, (size_t)MT * KT * 1024 + 2u * MT * (16 * NW / 32) * 1024);
+    const size_t lds = (size_t)MT * KT * 1024 + 2u * MT * (16 * NW / 32) * 1024;
     float *partial = p.n_partial > 1 ? (float *)workspace : nullptr;
     if (partial && (size_t)p.n_partial * n_rows * c.d_model * 4 > ffn_workspace_bytes(c))
         return fail(ctx, PGMOE_EINVAL, "pgmoe_expert_ffn: %d partial sums of %d rows do not fit the workspace", p.n_partial, n_rows);
