@@ -779,7 +779,9 @@ static int launch_fused(pgmoe_ctx *ctx, const FfnPlan &p, const char *w_base, si
     constexpr bool CARRIES = NW == 4 && MT <= 2;  // decode-sized chunks
     CarriedGate cg = {};
     if (CARRIES) cg = carry_gate(ctx, gate, false, keep_partials && p.n_partial > 1, gate_done);
-    const size_t lds = (size_t)MT * KT * 1024 + 2u * MT * (16 * NW / 32) * 1024;
+    // Launches that carry a gate are a few hundred workgroups, which at three per CU leave CUs idle: two (64 experts of 512 x 2048, 64 tokens, six blocks: 184 us a
+    // step, 197 with three).
+    const size_t lds = std::max<size_t>(KT == 16 && cg.x ? 54 * 1024 : 0, (size_t)MT * KT * 1024 + 2u * MT * (16 * NW / 32) * 1024);
     float *partial = p.n_partial > 1 ? (float *)workspace : nullptr;
     if (partial && (size_t)p.n_partial * n_rows * c.d_model * 4 > ffn_workspace_bytes(c))
         return fail(ctx, PGMOE_EINVAL, "pgmoe_expert_ffn: %d partial sums of %d rows do not fit the workspace", p.n_partial, n_rows);
