@@ -98,3 +98,13 @@ def test_a_fused_expert_launch_without_a_carried_gate_keeps_its_occupancy(code_o
             waves[tuple(map(int, m.groups()))] = min(8, 512 // (-(-k["vgpr_count"] // 8) * 8))
     for case, want in {(1, 2, 4): 8, (2, 2, 4): 8, (1, 4, 4): 5, (1, 16, 4): 3}.items():    # (row tiles, d_model / 32, wavefronts)
         assert waves.get(case, 0) >= want, (case, waves)
+
+
+def test_latency_bound_kernels_have_no_stack_frame(code_objects):
+    """The batch-1 stack and the matrix-core gates of up to 128 experts: a frame makes every workgroup wait for scratch memory to be set up, and
+    it is there because registers ran out."""
+    found = kernels(code_objects)
+    names = [n for n in found if re.search(r"ffn_decode_stack|gate_small_kernel|gate_topk_mfma_kernelILi1E|gate_topk_tiles_kernel", n)]
+    assert len(names) == 4 + 2 + 1 + 6 + 4, sorted(names)
+    framed = {n: found[n]["private_segment_fixed_size"] for n in names if found[n]["private_segment_fixed_size"]}
+    assert not framed
