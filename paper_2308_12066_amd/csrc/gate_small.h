@@ -22,12 +22,6 @@ template <int N>
 __device__ inline float row_ror(float v) {
     return __int_as_float(row_ror<N>(__float_as_int(v)));
 }
-__device__ inline float group_max(float m) {
-    m = fmaxf(m, row_ror<8>(m));
-    m = fmaxf(m, row_ror<4>(m));
-    m = fmaxf(m, row_ror<2>(m));
-    return fmaxf(m, row_ror<1>(m));
-}
 __device__ inline float group_sum(float s) {  // fixed order: bit-reproducible
     s += row_ror<8>(s);
     s += row_ror<4>(s);
@@ -62,16 +56,15 @@ __device__ inline float sort_value(int key) { return __int_as_float(key ^ (key >
 // A round of arg-max is a maximum over sort keys, then the lowest index among the keys that equal it, each over the lane's slices and by
 // rotation: one operation a step, where (value, index) pairs took seven. With 128 experts and two choices that was 5000
 // of the 18500 clocks of a gate.
-// GROUP != 0: the calling wavefronts are GROUP threads of a larger workgroup, aligned to that number; else the whole workgroup.
-template <int NQ, int GROUP>
+template <int NQ>
 __device__ inline void softmax_topk_n(const float *zs, int zstride, int t0, int nt, int E, int k,
                                       int32_t *__restrict__ idx_out, float *__restrict__ prob_out,
                                       float *__restrict__ probs_out, uint32_t *flags, int32_t *idx_lds, float *prob_lds = nullptr) {
-    const int tid = GROUP ? threadIdx.x & (GROUP - 1) : threadIdx.x;
+    const int tid = threadIdx.x;
     const int sub = tid & 15, grp = tid >> 4;  // 16 lanes per group
     constexpr int NONE = INT_MIN;              // key of an expert that does not exist or has been chosen
     int nans = 0;
-    for (int tb = 0; tb < nt; tb += (GROUP ? GROUP : (int)blockDim.x) / 16) {
+    for (int tb = 0; tb < nt; tb += (int)blockDim.x / 16) {
         if (tb + (grp & ~3) >= nt) continue;  // none of this wavefront's four tokens exists (uniform over the wavefront)
         const int t = tb + grp;
         const bool live = t < nt;  // idle groups of a live wavefront work on its first token and skip the writes
@@ -135,12 +128,12 @@ __device__ inline void softmax_topk_n(const float *zs, int zstride, int t0, int 
 }
 
 // MAXQ: the most slices the calling kernel can need (E <= 16*MAXQ there).
-template <int MAXQ = 16, int GROUP = 0>
+template <int MAXQ = 16>
 __device__ inline void softmax_topk(const float *zs, int zstride, int t0, int nt, int E, int k,
                                     int32_t *__restrict__ idx_out, float *__restrict__ prob_out,
                                     float *__restrict__ probs_out, uint32_t *flags,
                                     int32_t *idx_lds = nullptr) {  // nullable: LDS copy [nt*k] of the chosen indices
-#define PG_SOFTMAX(NQ_) softmax_topk_n<NQ_, GROUP>(zs, zstride, t0, nt, E, k, idx_out, prob_out, probs_out, flags, idx_lds)
+#define PG_SOFTMAX(NQ_) softmax_topk_n<NQ_>(zs, zstride, t0, nt, E, k, idx_out, prob_out, probs_out, flags, idx_lds)
     if (E <= 16) PG_SOFTMAX(1);  // uniform over the kernel
     else if (E <= 32) PG_SOFTMAX(2);
     else if (E <= 64) PG_SOFTMAX(4);
@@ -282,7 +275,7 @@ __device__ inline void gate_small_rows(
     }
     __syncthreads();
     const bool route = row_of != nullptr;
-    softmax_topk_n<1, 0>(zs, 16, 0, T, E, k, idx_out, prob_out, probs_out, flags, route ? r_idx : nullptr, r_prob);
+    softmax_topk_n<1>(zs, 16, 0, T, E, k, idx_out, prob_out, probs_out, flags, route ? r_idx : nullptr, r_prob);
     chosen(r_idx, r_prob);
     if (!route) return;
     group_in_workgroup(r_idx, r_cnt, r_off, T * k, E, k, GS_THREADS, row_of, offsets, src_row);
