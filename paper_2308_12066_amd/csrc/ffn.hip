@@ -101,22 +101,30 @@ __global__ __launch_bounds__(NW * 64) void ffn_fused_kernel(
         const int fs = fs0 + s * SUB;
         return Slab{w1 + ((size_t)((fs >> 4) + wave) * KT << 10), w2 + ((size_t)((fs >> 5) * NTD + wave * NTB) << 10), s < n_sub ? 4096 : 0};
     };
+    // The 16-row chunks of d_model 256 keep plain conditional loads: their launches are of about four workgroups per CU, for which the steady stream has no
+    // registers (128 experts of 256 x 1024, one row each: 29.0 us so, 31.3 steady, 30.1 steady with eight tiles in flight; of 256 x 4096, 128 skewed rows 38.1,
+    // 44.3 and 37.2, three rows each 86.5, 92.6 and 92.1).
+    constexpr bool PLAIN = MT == 1 && KT == 8;
     auto load_tile = [&](const Slab &sl, int i) -> bf16x8 {
         const int j = i - NT_A, kb = j / NTB, a = j - kb * NTB, in_run = i < NT_A ? i : a;
         const char *run = i < NT_A ? sl.a : sl.b + ((size_t)(kb * NTD) << 10);
+        if constexpr (PLAIN) return *(const global_bf16x8 *)(run + ((size_t)in_run << 10) + lane * 16);
         const auto rsrc = __builtin_amdgcn_make_buffer_rsrc((void *)(run + ((size_t)(in_run & ~3) << 10)), 0, sl.window, 0x00020000);
         return __builtin_bit_cast(bf16x8, __builtin_amdgcn_raw_buffer_load_b128(rsrc, lane * 16 + ((in_run & 3) << 10), 0, 0));
     };
 
+    // Tiles in flight: sixteen for a wavefront of 16-row chunks, eight where the accumulators of 32 and 64 rows would leave fewer wavefronts per SIMD (d_model 256:
+    // 18 rows for each of 64 experts of 256 x 1024 25.2 us with sixteen, 16.3 with eight; 45 for each of 128 47.2 and 33.7).
     static_assert(D <= NT && NT % D == 0, "the ring reaches into the next sub-slab at most, where a tile finds the place that was filled for it");
     // The 64-row chunks of d_model 768, and d_model 512, leave it to the compiler: launches of theirs that fill the chip are paced by HBM, which the pauses do not
     // slow (128 experts of 768 x 3072, 4096 rows: 231 us a block, 234 with the steady stream; 256 of 512 x 2048, 3000 rows: 214 and 218), and the steady
     // stream's registers cost d_model 512 a wavefront per SIMD.
-    constexpr bool STEADY = KT != 16 && !(NW == 8 && KT == 24);
+    constexpr bool STEADY = !PLAIN && KT != 16 && !(NW == 8 && KT == 24);
     bf16x8 ring[D];
     Slab now = slab(0);
 #pragma unroll
-    for (int g = 0; g < D; ++g) ring[g] = load_tile(now, g);
+    for (int g = 0; g < D; ++g)
+        if (!PLAIN || n_sub > 0) ring[g] = load_tile(now, g);
 
     bf16x8 *xs = reinterpret_cast<bf16x8 *>(smem);   // [MT][KT][64] operand cells
     bf16x8 *hs = xs + (size_t)MT * KT * 64;          // [2][MT][KTB][64]
@@ -145,10 +153,10 @@ __global__ __launch_bounds__(NW * 64) void ffn_fused_kernel(
         for (int m = 0; m < MT; ++m) yacc[a][m] = floatx4{0.f, 0.f, 0.f, 0.f};
 
     // The rows' operand cells are read from LDS AHEAD tiles before their products.
-    constexpr int AHEAD = KT < 4 ? 1 : (MT == 1 ? 4 : (MT == 2 || NW == 8 ? 2 : 1));
+    constexpr int AHEAD = KT < 4 ? 1 : (KT == 8 ? 2 : (MT == 1 ? 4 : (MT == 2 || NW == 8 ? 2 : 1)));
     static_assert(AHEAD <= NT_A && AHEAD <= NT_B, "the cells of the next sub-slab replace none that is still to be used");
     bf16x8 xa[AHEAD + 1][MT];
-    constexpr int HB = MT * NTB >= 32 ? 1 : 2;  // hidden cells of the next k-tile, too, where the accumulators leave registers for them
+    constexpr int HB = MT * NTB >= 32 || KT == 8 ? 1 : 2;  // hidden cells of the next k-tile, too, where the accumulators leave registers for them
 #pragma unroll
     for (int i = 0; i < AHEAD; ++i)
 #pragma unroll
@@ -657,8 +665,8 @@ FfnPlan plan_ffn(const pgmoe_config &c, int n_rows, int slices) {
 #define PG_FUSED_CASES(X)                                                                                   \
     X(1, 2, 4, 4) X(1, 4, 4, 8) X(1, 8, 4, 16) X(1, 16, 4, 16) X(1, 24, 4, 16) X(1, 32, 4, 16) X(1, 64, 4, 16) \
     X(1, 24, 2, 16) X(1, 32, 2, 16)                                                                         \
-    X(2, 2, 4, 4) X(2, 4, 4, 8) X(2, 8, 4, 16) X(2, 16, 4, 16) X(2, 24, 4, 16) X(2, 32, 4, 8)              \
-    X(4, 2, 4, 4) X(4, 4, 4, 8) X(4, 8, 4, 16) X(4, 16, 4, 8) X(4, 24, 4, 8) X(4, 24, 8, 8) X(4, 32, 8, 4)
+    X(2, 2, 4, 4) X(2, 4, 4, 8) X(2, 8, 4, 8) X(2, 16, 4, 16) X(2, 24, 4, 16) X(2, 32, 4, 8)              \
+    X(4, 2, 4, 4) X(4, 4, 4, 8) X(4, 8, 4, 8) X(4, 16, 4, 8) X(4, 24, 4, 8) X(4, 24, 8, 8) X(4, 32, 8, 4)
 
 static bool fused_case_built(int mt, int kt, int nw) {
 #define X(MT_, KT_, NW_, D_) \

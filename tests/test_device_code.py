@@ -108,3 +108,13 @@ def test_latency_bound_kernels_have_no_stack_frame(code_objects):
     assert len(names) == 4 + 2 + 1 + 6 + 4, sorted(names)
     framed = {n: found[n]["private_segment_fixed_size"] for n in names if found[n]["private_segment_fixed_size"]}
     assert not framed
+
+
+def test_fused_expert_launches_of_d_model_256_keep_their_occupancy(code_objects):
+    """Launches of d_model 256 have a few small workgroups per CU: wavefronts per SIMD by rows per chunk."""
+    waves = {}
+    for name, k in kernels(code_objects).items():
+        m = re.search(r"ffn_fused_kernelILi(\d+)ELi8ELi4E", name)
+        if m:
+            waves.setdefault(int(m.group(1)), []).append(min(8, 512 // (-(-k["vgpr_count"] // 8) * 8)))
+    assert {mt: min(w) for mt, w in waves.items() if mt < 4} == {1: 4, 2: 4} and min(waves[4]) >= 2, waves
