@@ -116,10 +116,9 @@ __global__ __launch_bounds__(NW * 64) void ffn_fused_kernel(
     // Tiles in flight: sixteen for a wavefront of 16-row chunks, eight where the accumulators of 32 and 64 rows would leave fewer wavefronts per SIMD (d_model 256:
     // 18 rows for each of 64 experts of 256 x 1024 25.2 us with sixteen, 16.3 with eight; 45 for each of 128 47.2 and 33.7).
     static_assert(D <= NT && NT % D == 0, "the ring reaches into the next sub-slab at most, where a tile finds the place that was filled for it");
-    // The 64-row chunks of d_model 768, and d_model 512, leave it to the compiler: launches of theirs that fill the chip are paced by HBM, which the pauses do not
-    // slow (128 experts of 768 x 3072, 4096 rows: 231 us a block, 234 with the steady stream; 256 of 512 x 2048, 3000 rows: 214 and 218), and the steady
-    // stream's registers cost d_model 512 a wavefront per SIMD.
-    constexpr bool STEADY = !PLAIN && KT != 16 && !(NW == 8 && KT == 24);
+    // The 16- and 32-row chunks of d_model 512 leave it to the compiler: launches of theirs that fill the chip are paced by HBM, which the pauses do not
+    // slow (256 experts of 512 x 2048, 3000 rows: 214 us a block, 218 with the steady stream), and the steady stream's registers cost a wavefront per SIMD.
+    constexpr bool STEADY = !PLAIN && (KT != 16 || MT == 4);
     bf16x8 ring[D];
     Slab now = slab(0);
 #pragma unroll
@@ -152,11 +151,15 @@ __global__ __launch_bounds__(NW * 64) void ffn_fused_kernel(
 #pragma unroll
         for (int m = 0; m < MT; ++m) yacc[a][m] = floatx4{0.f, 0.f, 0.f, 0.f};
 
-    // The rows' operand cells are read from LDS AHEAD tiles before their products.
-    constexpr int AHEAD = KT < 4 ? 1 : (KT == 8 ? 2 : (MT == 1 ? 4 : (MT == 2 || NW == 8 ? 2 : 1)));
+    // The rows' operand cells are read from LDS AHEAD tiles before their products, or with 0 where the compiler puts it: in the largest chunks of d_model 512
+    // and 768 and at d_model 2048 the registers are worth more as they are (128 experts of 512 x 2048, some 50 rows each: 182 us with reads ahead and
+    // conditional requests, 113 steady and without; 128 of 768 x 3072, 28 skewed rows 254 and 242, 256 of 768 x 1536, 27 skewed rows 301 and 264; 4 of
+    // 2048 x 8192, 10 rows each, three launches at a time 55.3 and 53.7).
+    constexpr bool AS_IT_COMES = (MT == 4 && (KT == 16 || (KT == 24 && NW == 8))) || KT == 64;
+    constexpr int AHEAD = AS_IT_COMES ? 0 : (KT < 4 ? 1 : (KT == 8 ? 2 : (MT == 1 ? 4 : (MT == 2 || NW == 8 ? 2 : 1))));
     static_assert(AHEAD <= NT_A && AHEAD <= NT_B, "the cells of the next sub-slab replace none that is still to be used");
     bf16x8 xa[AHEAD + 1][MT];
-    constexpr int HB = MT * NTB >= 32 || KT == 8 ? 1 : 2;  // hidden cells of the next k-tile, too, where the accumulators leave registers for them
+    constexpr int HB = MT * NTB >= 32 || KT == 8 || AS_IT_COMES ? 1 : 2;  // hidden cells of the next k-tile, too, where the accumulators leave registers for them
 #pragma unroll
     for (int i = 0; i < AHEAD; ++i)
 #pragma unroll
@@ -175,7 +178,7 @@ __global__ __launch_bounds__(NW * 64) void ffn_fused_kernel(
             const bf16x8 v = ring[i % D];
             // request tile g + D of the stream; where STEADY it stays where it is written
             if (STEADY || i + D < NT || s + 1 < n_sub) ring[i % D] = load_tile(i + D < NT ? now : next, (i + D) % NT);
-            if constexpr ((i + AHEAD) % NT < NT_A) {
+            if constexpr (AHEAD > 0 && (i + AHEAD) % NT < NT_A) {
 #pragma unroll
                 for (int m = 0; m < MT; ++m) xa[(i + AHEAD) % NT % (AHEAD + 1)][m] = xs[((m * KT + (i + AHEAD) % NT) << 6) + lane];
             }
@@ -184,7 +187,7 @@ __global__ __launch_bounds__(NW * 64) void ffn_fused_kernel(
                 // ---- phase A: hidden features [fs + 16*wave, +16) over the full d_model reduction
 #pragma unroll
                 for (int m = 0; m < MT; ++m)
-                    hacc[m] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(v, xa[i % (AHEAD + 1)][m], hacc[m], 0, 0, 0);
+                    hacc[m] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(v, AHEAD > 0 ? xa[i % (AHEAD + 1)][m] : xs[((m * KT + i) << 6) + lane], hacc[m], 0, 0, 0);
                 if (i == NT_A - 1) {
                     // ReLU, round to bf16, store as phase-B operand: feature 16*wave + 4*q + r is
                     // k-tile wave/2, k-group 2*(wave%2) + q/2, position 4*(q%2) + r of token lane%16
