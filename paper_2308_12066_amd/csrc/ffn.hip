@@ -790,16 +790,26 @@ static int launch_fused(pgmoe_ctx *ctx, const FfnPlan &p, const char *w_base, si
     constexpr bool CARRIES = NW == 4 && MT <= 2;  // decode-sized chunks
     CarriedGate cg = {};
     if (CARRIES) cg = carry_gate(ctx, gate, false, keep_partials && p.n_partial > 1, gate_done);
-    // Launches that carry a gate are a few hundred workgroups, which at three per CU leave CUs idle: two (64 experts of 512 x 2048, 64 tokens, six blocks: 184 us a
-    // step, 197 with three).
-    const size_t lds = std::max<size_t>(KT == 16 && cg.x ? 54 * 1024 : 0, (size_t)MT * KT * 1024 + 2u * MT * (16 * NW / 32) * 1024);
+    // The dispatcher fills a CU before the next one, so a kernel of which two find room on a CU leaves CUs idle in a launch that has a workgroup for each. Two
+    // kernels take more LDS than they use in launches of 256 workgroups at most, the even case that the shape says; each alone was what their registers once made it:
+    // 128 experts of 512 x 2048, 30 rows each 123 us with two, 101 alone, 24 uneven rows 123 and 100 (30 skewed rows, which are more workgroups: 126 and 138);
+    // 32 of 768 x 3072, 12 and 16 uneven rows 75 and 64, 88 and 66.  Not the others: 16 of 1024 x 4096, 9 rows each 67 and 73, 16 of 256 x 1024, 3 rows 8.9 and 10.3.
+    constexpr size_t needed = (size_t)MT * KT * 1024 + 2u * MT * (16 * NW / 32) * 1024, half = 82 * 1024;
+    constexpr bool crowded = (MT == 2 && KT == 24) || (MT == 4 && KT == 16);
+    const int gate_wgs = cg.x ? 2 * ((gate->T + GM_TOK - 1) / GM_TOK) : 0, active = std::max(1, std::min(c.n_experts, n_rows));
+    const bool alone = crowded && std::max((double)active, 0.5 * active + n_rows / (16.0 * MT)) * p.n_partial + gate_wgs <= 256;
+    // With a carried gate the 16-row chunks of d_model 512 leave room for three, but two are right for more of the launches (six blocks of 512 x 2048, two / three: 64 experts,
+    // 16 tokens 125 / 130 us; 128 experts, 64 tokens 303 / 315, 128 tokens of two experts 548 / 567; 64 skewed experts, 64 tokens 190 / 203). Where
+    // between 512 and 768 workgroups come out three are: 64 experts, 64 tokens 273 / 261, 48 experts 253 / 236; the shape alone does not tell.
+    const size_t lds = std::max<size_t>(alone ? half : (KT == 16 && cg.x ? 54 * 1024 : 0), needed);
     float *partial = p.n_partial > 1 ? (float *)workspace : nullptr;
     if (partial && (size_t)p.n_partial * n_rows * c.d_model * 4 > ffn_workspace_bytes(c))
         return fail(ctx, PGMOE_EINVAL, "pgmoe_expert_ffn: %d partial sums of %d rows do not fit the workspace", p.n_partial, n_rows);
     const int tslot = ffn_timing_slot(ctx);
     if (tslot >= 0) PG_HIP(ctx, hipEventRecord(ctx->tim_begin[tslot], s));
     auto launch = [&](auto kern, int rows, auto... carried) {
-        if (int rc = allow_dynamic_lds(ctx, reinterpret_cast<const void *>(kern), lds)) return rc;
+        // the limit is raised once, so for the most that any launch of the kernel takes
+        if (int rc = allow_dynamic_lds(ctx, reinterpret_cast<const void *>(kern), crowded ? std::max(lds, half) : lds)) return rc;
         hipLaunchKernelGGL(kern, dim3(p.max_chunks, rows), dim3(NW * 64), lds, s, (const __bf16 *)x_perm, offsets, c.n_experts, c.d_ff,
                            p.f_range, w_base, w_stride, slot_by_rank ? 1 : 0, n_slots, table, partial, (__bf16 *)y_perm, n_rows, src_row,
                            carried...);

@@ -2,7 +2,9 @@
 weights end the store."""
 import numpy as np
 import pytest
+import torch
 
+from launch_count import kernel_nodes
 from test_gpu_parity import TOL, hx, nerr, run_ffn_case  # noqa: F401  (hx is a fixture)
 
 pytestmark = pytest.mark.gpu
@@ -26,3 +28,26 @@ def test_fused_expert_kernel_over_sub_slabs(hx, d, f, E, counts):  # noqa: F811
     for e in range(E):
         if counts[e]:
             assert nerr(out[offs[e]: offs[e + 1]], ref[offs[e]: offs[e + 1]]) <= TOL["bf16"], f"expert {e} ({counts[e]} rows)"
+
+
+@pytest.mark.parametrize("d,f,E,rows,alone", [
+    (512, 2048, 128, 30, True), (512, 2048, 128, 50, False),        # 64-row chunks: 256 workgroups, more experts than one chunk holds the rows of
+    (768, 3072, 32, 12, True), (768, 3072, 64, 18, False),          # 32-row chunks: 256 and 384 workgroups
+    (1024, 4096, 16, 9, False), (256, 1024, 16, 3, False),          # kernels that do not mind
+])
+def test_a_launch_with_a_workgroup_per_cu_keeps_them_apart(hx, d, f, E, rows, alone):  # noqa: F811
+    """By the LDS it takes: of a CU's 160 KiB more than half, or what it needs."""
+    H, B = hx
+    print(f"fused, workgroups per CU: d={d} f={f} E={E} rows={rows}", flush=True)
+    n = E * rows
+    ctx = B.Context(B.make_config(d, f, E, 1, 1, n, B.BF16))
+    blobs = torch.zeros((E, 2 * d * f), dtype=torch.bfloat16, device="cuda")
+    ctx.register_resident_experts(blobs, 4 * d * f, 4 * d * f * E)
+    assert ctx.ffn_kernel_name(n) == "ffn_fused_kernel"
+    x, y = (torch.zeros((n, d), dtype=torch.bfloat16, device="cuda") for _ in range(2))
+    offs = (torch.arange(E + 1, device="cuda") * rows).to(torch.int32)
+    ws, stream = torch.zeros(ctx.workspace_bytes, dtype=torch.uint8, device="cuda"), torch.cuda.Stream()
+    ctx.expert_ffn(0, x, offs, n, y, ws, stream)     # not captured first: the kernels are loaded
+    nodes = kernel_nodes(lambda: ctx.expert_ffn(0, x, offs, n, y, ws, stream), stream)
+    assert (nodes[0].lds > 80 * 1024) == alone, nodes[0].lds
+    ctx.close()
