@@ -68,3 +68,12 @@ def test_f32_block_reads_its_rows_in_place(hx, T, d, f, E, k, offloaded):  # noq
 ])
 def test_f32_expert_ffn_over_rounds_of_requests(hx, d, f, E, counts):  # noqa: F811
     test_f32_expert_ffn_at_tile_edges(hx, d, f, E, counts)
+
+
+@pytest.mark.parametrize("d,f,E,counts", [
+    (4, 12, 3, [1, 0, 2]), (60, 68, 4, [9, 40, 100, 3]),                        # less than a block for each wavefront
+    (500, 512, 2, [20, 30]), (508, 516, 2, [5, 12]), (512, 508, 3, [40, 1, 60]),  # a block short of a full round of eight wavefronts, a full one, one past it
+    (252, 256, 32, [40] * 32), (256, 260, 32, [40, 60] * 16),                    # the same of four
+])
+def test_f32_expert_ffn_at_the_first_full_round(hx, d, f, E, counts):  # noqa: F811
+    test_f32_expert_ffn_at_tile_edges(hx, d, f, E, counts)
