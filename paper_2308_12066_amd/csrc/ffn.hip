@@ -876,9 +876,11 @@ static int launch_ffn_f32(pgmoe_ctx *ctx, const char *w_base, size_t w_stride, b
         const int mt = mean <= 16 ? 1 : (mean <= 32 ? 2 : 4);
         const int chunks = active + n_rows / (16 * mt);
         auto cols = [&](int N) { return active * ((N + 63) / 64) >= (mean >= 8 ? 96 : 256) ? 4 : (active * ((N + 31) / 32) >= 128 ? 2 : 1); };
-        // twice the wavefronts per workgroup where each CU has one workgroup at most and a wavefront still keeps its four blocks in flight: 8 experts of
-        // 768 x 3072 with 12 rows each, steps from HBM 46.8 -> 43.8 us; 16 of 1024 x 4096 with 4 rows 115 -> 108
-        auto wide = [&](int N, int K) { return active * ((N + 63) / 64) <= 256 && K >= 16 * 16 * F32_DEPTH; };
+        // twice the wavefronts per workgroup where half the CUs have one at most and a wavefront still keeps its four blocks in flight: 8 experts of
+        // 768 x 3072 with 12 rows each, steps from HBM 46.8 -> 43.8 us. With one for every CU they gain or lose little in a launch by itself and lose where
+        // those of several streams meet (eight / sixteen, three streams: 4 experts of 1024 x 4096, 8 rows each 31.9 / 34.0 us, one row 27.5 / 31.1; 8 of
+        // 2048 x 1024, one row 23.5 / 29.3; by themselves 45.8 / 48.4, 38.0 / 37.8 and 31.0 / 33.0).
+        auto wide = [&](int N, int K) { return active * ((N + 63) / 64) <= 128 && K >= 16 * 16 * F32_DEPTH; };
 #define PG_F32_HIDDEN(V_, MT_, NW_)                                                                                            \
     hipLaunchKernelGGL((ffn_f32_hidden_kernel<V_, MT_, NW_>), dim3(chunks, (c.d_ff + 16 * V_ - 1) / (16 * V_)), dim3(NW_ * 64), 0, s, \
                        x, src_row, offsets, c.n_experts, c.d_model, c.d_ff, w_base, w_stride, slot_by_rank ? 1 : 0, n_slots, table, h)
