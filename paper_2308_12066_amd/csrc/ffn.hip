@@ -357,6 +357,7 @@ __global__ __launch_bounds__(256) void ffn_reduce_kernel(const float *__restrict
 // 18.4 + 23.7 while the requests were conditional: the compiler, which then cannot count them, waited for every load in flight once per round of blocks,
 // so the blocks came in batches with a memory latency between them.
 constexpr int F32_DEPTH = 4;
+constexpr size_t F32_ALONE = 52 * 1024;  // of LDS beside the 32 KiB of a workgroup of 64 rows, 16 columns and eight wavefronts: more than half a CU's
 
 template <int V>
 struct F32Vec {
@@ -881,16 +882,27 @@ static int launch_ffn_f32(pgmoe_ctx *ctx, const char *w_base, size_t w_stride, b
         // those of several streams meet (eight / sixteen, three streams: 4 experts of 1024 x 4096, 8 rows each 31.9 / 34.0 us, one row 27.5 / 31.1; 8 of
         // 2048 x 1024, one row 23.5 / 29.3; by themselves 45.8 / 48.4, 38.0 / 37.8 and 31.0 / 33.0).
         auto wide = [&](int N, int K) { return active * ((N + 63) / 64) <= 128 && K >= 16 * 16 * F32_DEPTH; };
-#define PG_F32_HIDDEN(V_, MT_, NW_)                                                                                            \
-    hipLaunchKernelGGL((ffn_f32_hidden_kernel<V_, MT_, NW_>), dim3(chunks, (c.d_ff + 16 * V_ - 1) / (16 * V_)), dim3(NW_ * 64), 0, s, \
-                       x, src_row, offsets, c.n_experts, c.d_model, c.d_ff, w_base, w_stride, slot_by_rank ? 1 : 0, n_slots, table, h)
-#define PG_F32_OUT_ARGS(V_, MT_, NW_)                                                                                          \
-    dim3(chunks, (c.d_model + 16 * V_ - 1) / (16 * V_)), dim3(NW_ * 64), 0, s, h, offsets, c.n_experts, c.d_model, c.d_ff, w_base,    \
-        w_stride, slot_by_rank ? 1 : 0, n_slots, table, y_perm, src_row
-#define PG_F32_OUT(V_, MT_, NW_)                                                                                               \
-    do {                                                                                                                       \
-        if (combine) hipLaunchKernelGGL((ffn_f32_out_kernel<V_, MT_, NW_, RowCombine>), PG_F32_OUT_ARGS(V_, MT_, NW_), *combine); \
-        else hipLaunchKernelGGL((ffn_f32_out_kernel<V_, MT_, NW_>), PG_F32_OUT_ARGS(V_, MT_, NW_));                            \
+        // A workgroup of 64 rows and 16 columns leaves room for a second one on its CU, and the dispatcher fills a CU before the next: launches with a workgroup
+        // for each CU take more LDS than half of one (4 experts of 768 x 3072, 40 rows each: 72.6 us with two on a CU, 57.2 alone; one of them, three
+        // streams 20.4 and 15.1; but 2 of 256 x 512, 1000 rows each, which are 1000 workgroups, 30.2 and 37.4). The estimate of
+        // the chunks is up to half a chunk of an expert's too high: 272.
+        const double full_chunks = std::max((double)active, 0.5 * active + n_rows / (16.0 * mt));
+        auto spare_lds = [&](int v, int rows16, int N) -> size_t { return v == 1 && rows16 == 4 && full_chunks * ((N + 15) / 16) <= 272 ? F32_ALONE : 0; };
+#define PG_F32_LAUNCH(N_, V_, MT_, NW_, KERN_, ...)                                                                             \
+    do {                                                                                                                        \
+        auto kern_ = KERN_;                                                                                                     \
+        const size_t lds_ = spare_lds(V_, MT_, N_);                                                                             \
+        if (int rc_ = allow_dynamic_lds(ctx, reinterpret_cast<const void *>(kern_), lds_)) return rc_;                          \
+        hipLaunchKernelGGL(kern_, dim3(chunks, (N_ + 16 * V_ - 1) / (16 * V_)), dim3(NW_ * 64), lds_, s, __VA_ARGS__);          \
+    } while (0)
+#define PG_F32_HIDDEN(V_, MT_, NW_)                                                                                             \
+    PG_F32_LAUNCH(c.d_ff, V_, MT_, NW_, (ffn_f32_hidden_kernel<V_, MT_, NW_>), x, src_row, offsets, c.n_experts, c.d_model, c.d_ff, w_base, \
+                  w_stride, slot_by_rank ? 1 : 0, n_slots, table, h)
+#define PG_F32_OUT_ARGS h, offsets, c.n_experts, c.d_model, c.d_ff, w_base, w_stride, slot_by_rank ? 1 : 0, n_slots, table, y_perm, src_row
+#define PG_F32_OUT(V_, MT_, NW_)                                                                                                \
+    do {                                                                                                                        \
+        if (combine) PG_F32_LAUNCH(c.d_model, V_, MT_, NW_, (ffn_f32_out_kernel<V_, MT_, NW_, RowCombine>), PG_F32_OUT_ARGS, *combine); \
+        else PG_F32_LAUNCH(c.d_model, V_, MT_, NW_, (ffn_f32_out_kernel<V_, MT_, NW_>), PG_F32_OUT_ARGS);                       \
     } while (0)
 #define PG_F32(KERN_, N_, K_)                                                                                                    \
     do {                                                                                                                       \
@@ -916,6 +928,7 @@ static int launch_ffn_f32(pgmoe_ctx *ctx, const char *w_base, size_t w_stride, b
 #undef PG_F32
 #undef PG_F32_OUT
 #undef PG_F32_OUT_ARGS
+#undef PG_F32_LAUNCH
 #undef PG_F32_HIDDEN
     } else {
         hipLaunchKernelGGL(ffn_f32_hidden_scalar_kernel, dim3(n_rows, (c.d_ff + 255) / 256), dim3(256), 0, s, x, offsets, c.n_experts,

@@ -7,6 +7,7 @@ import torch
 
 import workloads as W
 from oracle import reference as R
+from launch_count import kernel_nodes
 from test_gpu_parity import TOL, hx, nerr, run_ffn_case  # noqa: F401  (hx is a fixture)
 
 pytestmark = pytest.mark.gpu
@@ -77,3 +78,25 @@ def test_f32_expert_ffn_over_rounds_of_requests(hx, d, f, E, counts):  # noqa: F
 ])
 def test_f32_expert_ffn_at_the_first_full_round(hx, d, f, E, counts):  # noqa: F811
     test_f32_expert_ffn_at_tile_edges(hx, d, f, E, counts)
+
+
+@pytest.mark.parametrize("d,f,E,rows,alone", [
+    (768, 3072, 4, 40, (False, True)),      # the second product: 192 workgroups of 64 rows and 16 columns
+    (768, 3072, 1, 40, (True, True)), (512, 2048, 1, 100, (True, True)),
+    (256, 512, 2, 1000, (False, False)), (768, 3072, 8, 40, (False, False)),
+])
+def test_a_float32_launch_with_a_workgroup_per_cu_keeps_them_apart(hx, d, f, E, rows, alone):  # noqa: F811
+    """By the LDS it takes beside what its sums need."""
+    H, B = hx
+    print(f"f32, workgroups per CU: d={d} f={f} E={E} rows={rows}", flush=True)
+    n = E * rows
+    ctx = B.Context(B.make_config(d, f, E, 1, 1, n, B.F32))
+    blobs = torch.zeros((E, 2 * d * f), dtype=torch.float32, device="cuda")
+    ctx.register_resident_experts(blobs, 8 * d * f, 8 * d * f * E)
+    x, y = (torch.zeros((n, d), dtype=torch.float32, device="cuda") for _ in range(2))
+    offs = (torch.arange(E + 1, device="cuda") * rows).to(torch.int32)
+    ws, stream = torch.zeros(ctx.workspace_bytes, dtype=torch.uint8, device="cuda"), torch.cuda.Stream()
+    ctx.expert_ffn(0, x, offs, n, y, ws, stream)     # not captured first: the kernels are loaded
+    nodes = kernel_nodes(lambda: ctx.expert_ffn(0, x, offs, n, y, ws, stream), stream)
+    assert tuple(k.lds > 0 for k in nodes) == alone
+    ctx.close()
