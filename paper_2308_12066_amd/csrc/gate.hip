@@ -7,7 +7,7 @@
 //   gate_small_kernel      bf16, up to four tokens, 8 or 16 experts: one workgroup, all loads at once;
 //   gate_topk_mfma_kernel  bf16, E a multiple of 8: logits on the matrix cores, 16 tokens per
 //                          workgroup, W transposed in registers (no LDS staging on the way in);
-//   gate_topk_tiles_kernel the same for more than 128 tiles of 16 tokens: pairs of tiles, W stays in registers;
+//   gate_topk_tiles_kernel the same for more than 224 tiles of 16 tokens: pairs of tiles, W stays in registers;
 //   gate_topk_vec_kernel   f32 (and bf16 when the matrix-core kernel does not apply) for
 //                          power-of-two E: token rows staged in LDS as float32, threads split W
 //                          by expert columns and feature rows and fold their partial sums in a
@@ -419,8 +419,8 @@ __global__ __launch_bounds__(NW * 64) void gate_topk_mfma_kernel(
 // as many as the accumulators and the next tokens leave): a workgroup keeps its share of W in registers,
 // transposed once, and walks pairs of token tiles.  One tile alone is bound by its 264 KB of W (4600 clocks at the 64 bytes a clock of a CU's
 // path to L2) and by a softmax of half the wavefronts, each alone on its SIMD; a pair shares the first and fills the
-// second.  4096 tokens of 1024 x 128, passes of several streams: 9.5 us with a tile per workgroup and its surplus loads, now 5.7, where the
-// host's call is as long; 8192 11.6 -> 9.6 (single tiles walked); 16384 in a step 25 -> 22.  Sums and their order are the kernel's above: same bits.
+// second, and leaves half the CUs to others, but takes longer by itself.  4096 tokens of 1024 x 128, launches of three streams: 6.3 us with a tile per workgroup, 4.7
+// so (9.6 before either); by itself 7.2 and 9.3.  16384 in a step 22.  Sums and their order are the kernel's above: same bits.
 template <int KW>
 __global__ __launch_bounds__(512) void gate_topk_tiles_kernel(
     const __bf16 *__restrict__ x, const __bf16 *__restrict__ w, const float *__restrict__ bias, int T, int E, int k,
@@ -528,9 +528,11 @@ static int launch_gate_mfma(pgmoe_ctx *ctx, const __bf16 *x, const __bf16 *w, co
         PG_HIP(ctx, hipGetLastError());
         return PGMOE_OK;
     }
-    // More than 128 tiles: workgroups of pairs of tiles, as few as keep the rounds over the CUs equal. Below, half the CUs have room for
-    // a tile each and a call that is waited for ends sooner with one (4096 tokens 21.3 us against 22.9, of several streams 7.5 against 6.2).
-    if (np == 1 && grid.x > 128 && !route && c.d_model % 256 == 0 && c.d_model <= 1024) {
+    // More tiles than seven CUs of eight: workgroups of pairs of tiles, as few as keep the rounds over the CUs equal. Below, a tile for each CU ends sooner and
+    // launches of several streams share the chip either way; from there on they queue for it (tiles / pairs, 1024 x 128, by itself | waited for | three
+    // streams: 2049 tokens 6.5 / 9.0 | 19.5 / 21.6 | 4.7 / 4.3 us, 3584 6.8 / 9.2 | 19.8 / 22.2 | 5.3 / 4.5, 3840 6.9 / 9.3 | 19.9 / 22.3 | 5.9 / 4.4; 768 x 64: 2049
+    // 5.1 / 6.7 | 17.9 / 19.6 | 4.5 / 4.4, 4096 5.1 / 6.7 | 18.1 / 19.6 | 4.6 / 4.3). Up to 4096 tokens that favours several streams over a call by itself.
+    if (np == 1 && grid.x > 224 && !route && c.d_model % 256 == 0 && c.d_model <= 1024) {
         const int pairs = ((int)grid.x + 1) / 2, per = (pairs + 255) / 256;
         const dim3 wgs((pairs + per - 1) / per);
 #define PG_GATE_TILES(KW_)                                                                                              \
@@ -548,8 +550,8 @@ static int launch_gate_mfma(pgmoe_ctx *ctx, const __bf16 *x, const __bf16 *w, co
         PG_HIP(ctx, hipGetLastError());
         return PGMOE_OK;
     }
-    // eight wavefronts split d_model: with a three-deep prefetch ring each of them has all its
-    // k-tiles (d_model <= 768) in flight at once, i.e. the kernel pays the memory latency once
+    // With up to 128 experts eight wavefronts split d_model, and up to d_model 1024 each has all of its four k-tiles at most in flight at once, i.e. the kernel
+    // pays the memory latency once; with more experts four wavefronts have two k-tiles each in flight.
 #define PG_GATE_MFMA(NP_, NW_, KW_)                                                                                     \
     do {                                                                                                                \
         auto kern = gate_topk_mfma_kernel<NP_, NW_, KW_>;                                                               \

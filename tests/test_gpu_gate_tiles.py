@@ -16,7 +16,9 @@ pytestmark = pytest.mark.gpu
                                            (9001, 768, 120, 2, False), (12295, 768, 16, 2, True), (16400, 1024, 72, 1, False),
                                            # pairs of tiles: the second missing, of one token, whole; one pair a workgroup and several
                                            (2049, 1024, 128, 2, True), (2064, 768, 64, 1, True), (2065, 512, 8, 2, True), (2080, 256, 128, 5, False),
-                                           (8191, 768, 128, 2, True), (8225, 1024, 128, 2, True)])
+                                           (8191, 768, 128, 2, True), (8225, 1024, 128, 2, True),
+                                           # the last without pairs; the second of the last pair of one token, whole, missing, almost whole
+                                           (3584, 1024, 128, 2, True), (3585, 1024, 128, 2, True), (3600, 768, 64, 1, True), (3601, 512, 8, 2, True), (3615, 256, 128, 5, False)])
 def test_many_tiles_give_the_bits_of_single_ones(hx, T, d, E, k, probs):  # noqa: F811
     H, B = hx
     print(f"gate tiles: T={T} d={d} E={E} k={k}", flush=True)
