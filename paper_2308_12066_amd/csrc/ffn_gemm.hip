@@ -120,9 +120,11 @@ __device__ inline GemmChunk gemm_find(const GemmScan &s, int E, int tiles_lo, in
 // XCDs round-robin in launch order and every XCD has its own L2.  All column blocks of a chunk go to one XCD (they
 // share its rows), and so do G consecutive chunks, G being how many an expert has on average (they share its
 // weights); such groups are dealt round-robin, so that the large chunks of a popular expert do not all end up on
-// one XCD.  Where every expert has G chunks, all of a group take a column block before the next is begun: its weights are then read by
-// G workgroups side by side and not G times (16 experts of 2048 x 8192, 512 rows each: 522 -> 493 us a block; 8 of 1024 x 4096, 2048 rows each: 267 -> 263;
-// with unequal experts, whose groups straddle two, up to 9 % slower).  What is left over is cut into eight equal runs of items.
+// one XCD.  Where the experts have G chunks each on the mean, with nothing over, all of a group take a column block before the next is begun: its weights are then
+// read by G workgroups side by side and not G times (16 experts of 2048 x 8192, 512 rows each: 522 -> 493 us a block; 8 of 1024 x 4096, 2048 rows each: 267 -> 263).
+// Experts of one and three chunks pass for two each by that, and their groups straddle; it costs as much as it gives (by column block / chunk after chunk: 200 and 900
+// rows for 32 experts of 1024 x 4096 310 / 300 us with three streams, 314 / 312 by itself, for 8 of 2048 x 8192 260 / 262 and 322 / 337, 300 rows for fifteen of
+// 768 x 3072 and 5420 for one 122 / 124). With a remainder the order was up to 9 % slower.  What is left over is cut into eight equal runs of items.
 // The items are the first total * gy workgroups of a launch in this order.
 // What a workgroup of the tile kernel needs to know is looked up once, by the kernel that packs the rows, and left as a record per item: with the
 // lookup in every workgroup (the prefix sums over the experts, five divisions) every item began a microsecond later: 512 rows for each of 8
