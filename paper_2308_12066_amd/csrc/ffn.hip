@@ -884,10 +884,9 @@ static int launch_ffn_f32(pgmoe_ctx *ctx, const char *w_base, size_t w_stride, b
         auto wide = [&](int N, int K) { return active * ((N + 63) / 64) <= 128 && K >= 16 * 16 * F32_DEPTH; };
         // A workgroup of 64 rows and 16 columns leaves room for a second one on its CU, and the dispatcher fills a CU before the next: launches with a workgroup
         // for each CU take more LDS than half of one (4 experts of 768 x 3072, 40 rows each: 72.6 us with two on a CU, 57.2 alone; one of them, three
-        // streams 20.4 and 15.1; but 2 of 256 x 512, 1000 rows each, which are 1000 workgroups, 30.2 and 37.4). The estimate of
-        // the chunks is up to half a chunk of an expert's too high: 272.
-        const double full_chunks = std::max((double)active, 0.5 * active + n_rows / (16.0 * mt));
-        auto spare_lds = [&](int v, int rows16, int N) -> size_t { return v == 1 && rows16 == 4 && full_chunks * ((N + 15) / 16) <= 272 ? F32_ALONE : 0; };
+        // streams 20.4 and 15.1; but 2 of 256 x 512, 1000 rows each, which are 1000 workgroups, 30.2 and 37.4).
+        const double full_chunks = active == 1 ? (n_rows + 16 * mt - 1) / (16 * mt) : std::max((double)active, 0.5 * active + n_rows / (16.0 * mt));
+        auto spare_lds = [&](int v, int rows16, int N) -> size_t { return v == 1 && rows16 == 4 && full_chunks * ((N + 15) / 16) <= 256 ? F32_ALONE : 0; };
 #define PG_F32_LAUNCH(N_, V_, MT_, NW_, KERN_, ...)                                                                             \
     do {                                                                                                                        \
         auto kern_ = KERN_;                                                                                                     \
