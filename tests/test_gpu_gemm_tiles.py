@@ -6,7 +6,7 @@ import pytest
 import torch
 
 import workloads as W
-from launch_count import kernel_launches
+from launch_count import kernel_launches, kernel_nodes
 from test_gpu_parity import TOL, hx, nerr, run_ffn_case  # noqa: F401  (hx is a fixture)
 
 pytestmark = pytest.mark.gpu
@@ -15,8 +15,8 @@ EDGES = [1, 16, 17, 64, 65, 128, 129, 192, 193, 255, 256, 257, 288, 289, 304, 30
 
 
 @pytest.mark.parametrize("d,f,E,counts", [
-    (256, 512, len(EDGES), EDGES),                                   # 256-column blocks
-    (128, 256, len(EDGES), EDGES),                                   # 128-column blocks in the down-projection
+    (256, 512, len(EDGES), EDGES),                                   # 128-column blocks in both products
+    (128, 256, len(EDGES), EDGES),
     (128, 1024, 2, [1500, 700]),                                     # K slices of the down-projection
     (512, 256, 130, [200 + (e * 37) % 140 if e % 3 else 300 for e in range(130)]),   # three rounds of 64 experts in the lookup
     (512, 2048, 8, [9, 31, 8, 16, 17, 0, 33, 20]),                   # few rows per expert: chosen over the fused kernel
@@ -38,23 +38,41 @@ def test_expert_ffn_at_tile_edges(hx, d, f, E, counts):  # noqa: F811
 
 # every number of row tiles a chunk can have (a wavefront's share, what it loads and the ring go by it), the last tile full, short and of one row
 EVERY = [16 * t - (0, 15, 6)[t % 3] for t in range(1, 21)]
+LARGE = EVERY + [320] * 6 + [t % 7 + 300 for t in EVERY]
 
 
-@pytest.mark.parametrize("d,f", [
-    (128, 256),     # fewer k-tiles than any ring has stages
-    (256, 768),     # as many as the ring of the largest chunks has, and 256-column blocks
-    (512, 2560),    # more than the deepest ring has: the steady loop and the tail
+@pytest.mark.parametrize("d,f,counts,columns_up,columns_down,slices", [
+    (128, 256, LARGE, 128, 128, 1),     # four k-tiles up, eight down; the rings have 4, 8 and 14 stages
+    (256, 768, LARGE, 256, 128, 1),
+    (512, 2560, LARGE, 256, 128, 1),    # more k-tiles than the deepest ring: the steady loop and the tail
+    (768, 256, LARGE, 128, 256, 1),     # wide column blocks in the down-projection, over the rings of up to 2, 8 and 20 row tiles
+    (1024, 512, LARGE, 128, 256, 1),
+    (256, 768, EVERY, 128, 128, 2), (256, 2048, EVERY, 256, 128, 4),
+    (512, 4096, EVERY + [5] * 16, 256, 256, 2), (256, 8192, EVERY + [5] * 16, 256, 256, 4),
+    (256, 256, [320], 128, 128, 4),     # two k-tiles a slice, fewer than the four stages of the largest chunks' ring: surplus requests
+    (256, 256, [600, 16, 100], 128, 128, 2),    # four, fewer than the eight and fourteen of the smaller ones'
 ])
-def test_every_number_of_row_tiles(hx, d, f):  # noqa: F811
+def test_every_number_of_row_tiles(hx, d, f, counts, columns_up, columns_down, slices):  # noqa: F811
     H, B = hx
-    counts = EVERY + [320] * 6 + [t % 7 + 300 for t in EVERY]
-    ctx = B.Context(B.make_config(d, f, len(counts), 1, 1, sum(counts), B.BF16, flags=B.FLAG_HOST_ONLY))
-    assert "gemm" in ctx.ffn_kernel_name(sum(counts))
+    E, n = len(counts), sum(counts)
+    print(f"gemm row tiles: d={d} f={f} E={E} rows={n}", flush=True)
+    ctx = B.Context(B.make_config(d, f, E, 1, 1, n, B.BF16))
+    assert "gemm" in ctx.ffn_kernel_name(n)
+    # the launch is of the kind it is here for: column blocks and K slices out of its grids
+    blobs, x, y = torch.zeros((E, 2 * d * f), dtype=torch.bfloat16, device="cuda"), *(torch.zeros((n, d), dtype=torch.bfloat16, device="cuda") for _ in range(2))
+    ctx.register_resident_experts(blobs, 4 * d * f, 4 * d * f * E)
+    offs = torch.from_numpy(np.concatenate([[0], np.cumsum(counts)]).astype(np.int32)).cuda()
+    ws, stream = torch.zeros(ctx.workspace_bytes, dtype=torch.uint8, device="cuda"), torch.cuda.Stream()
+    torch.cuda.synchronize()
+    ctx.expert_ffn(0, x, offs, n, y, ws, stream)     # not captured first: the kernels are loaded
+    nodes = kernel_nodes(lambda: ctx.expert_ffn(0, x, offs, n, y, ws, stream), stream)
     ctx.close()
-    print(f"gemm row tiles: d={d} f={f}", flush=True)
-    out, ref = run_ffn_case(H, B, "bf16", d, f, len(counts), counts, seed=d + f)
+    chunks = E + n // 320
+    assert [k.grid[0] for k in nodes[:3]] == [chunks, chunks * f // columns_up, chunks * d // columns_down * slices]
+    assert len(nodes) == (4 if slices > 1 else 3)
+    out, ref = run_ffn_case(H, B, "bf16", d, f, E, counts, seed=d + f)
     offs = np.concatenate([[0], np.cumsum(counts)])
-    for e in range(len(counts)):
+    for e in range(E):
         assert nerr(out[offs[e]: offs[e + 1]], ref[offs[e]: offs[e + 1]]) <= TOL["bf16"], f"expert {e} ({counts[e]} rows)"
 
 
