@@ -102,7 +102,7 @@ __global__ __launch_bounds__(NW * 64) void ffn_fused_kernel(
         return Slab{w1 + ((size_t)((fs >> 4) + wave) * KT << 10), w2 + ((size_t)((fs >> 5) * NTD + wave * NTB) << 10), s < n_sub ? 4096 : 0};
     };
     // The 16-row chunks of d_model 256 keep plain conditional loads: their launches are of about four workgroups per CU, for which the steady stream has no
-    // registers (128 experts of 256 x 1024, one row each: 29.0 us so, 31.3 steady, 30.1 steady with eight tiles in flight; of 256 x 4096, 128 skewed rows 38.1,
+    // registers (128 experts of 256 x 1024, one row each: 29.8 us so, 31.3 steady, 30.1 steady with eight tiles in flight; of 256 x 4096, 128 skewed rows 38.1,
     // 44.3 and 37.2, three rows each 86.5, 92.6 and 92.1).
     constexpr bool PLAIN = MT == 1 && KT == 8;
     auto load_tile = [&](const Slab &sl, int i) -> bf16x8 {

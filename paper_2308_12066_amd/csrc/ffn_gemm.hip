@@ -21,11 +21,12 @@ namespace pgmoe {
 // packed rows, the packed hidden activation the up-projection writes, and the pre-tiled weights).
 //
 // What bounds it and why the tile looks like this (measured on one MI355X):
-//  * large launches (128 experts of 1024 x 4096, 32768 rows): power. The loop runs at 1.4 to 1.5 GHz and 1.2 PFLOP/s beside 4.8 TB/s of
-//    weights, where a loop of nothing but products on random operands reaches 1.7 at 1.7 GHz. 329 us up, 360 down (358 and 397 before the loop below);
-//    8 to 20 % of an item is its lookup, its first loads and its stores.  Hence as many rows per weight tile as the registers hold
-//    (320: 160 accumulator registers), no second chunk for an expert that has a few rows more than a power of two, and neither a
-//    request nor a product for a row tile the chunk lacks;
+//  * large launches (128 experts of 1024 x 4096, 32768 rows): the stream of weights, 1.07 GB a product, beside the products it feeds.
+//    289 us up and 314 down, 0.95 and 0.88 PFLOP/s, at 5.0 and 4.6 TB/s read and written; what is read past L2 is 1.02 and 1.03 times the operands,
+//    so no column block fetches its chunk's rows again; the matrix cores are busy 46 and 40 % of the time, at 2.0 to 2.1 GHz (counters of passes
+//    that are waited for; the loop below took 329 and 360 us where the one before it took 358 and 397).  Hence as many rows per weight tile as the
+//    registers hold (320: 160 accumulator registers), no second chunk for an expert that has a few rows more than a power of two, and neither
+//    a request nor a product for a row tile the chunk lacks;
 //  * 8 experts of 768 x 3072, 4096 rows: 26.5 us up, 29.7 down with the weights in the last-level cache (30.5 and 34.6 before; the vendor GEMM
 //    library: 27 + 41).  A 32-k stage of 16 row tiles takes 0.62 us (0.76), 1170 clocks for 1024 of products: with a batch of LDS reads and
 //    loads behind every barrier it took 1540.  512 rows per expert are two chunks each, 192 workgroups; chunks of at most
@@ -549,11 +550,11 @@ static double gemm_estimate(const pgmoe_config &c, int n_rows) {
 // every expert's weights once per chunk of at most 64 rows, with d_ff cut into as few ranges as keep
 // its partial sums cheap, so with few experts or several chunks per expert it leaves CUs idle or reads weights
 // again; the GEMMs cost two launches more and the round trip of the hidden activation, which is what bounds them where d_model is
-// small.  The two estimates (microseconds) are fitted to 1317 launches timed both ways (d_model 128 .. 2048, d_ff 512 .. 8192, 1 .. 256
-// experts, 8 .. 190 rows per expert, even and skewed routing; both are within 11 % root mean square): 64 experts of 768 x 3072 at 28 / 40 / 64 / 100
-// rows per expert 124 / 155 / 248 / 243 us fused and 128 / 135 / 146 / 161 us as GEMMs; 128 of 1024 x 4096 at 48 rows 623 and 414; one of 512 x 2048
-// at 10 rows 19 and 26; 256 of 128 x 8192 at 80 rows 329 and 425; 128 of 256 x 1024 at 190 skewed rows 64 and 98.  The rule's choices are
-// 1.49 times as fast as the fused kernel on the geometric mean, the better of the two each time would be 1.51.
+// small.  The two estimates (microseconds) were fitted to 1317 launches of earlier loops of both, timed both ways (d_model 128 .. 2048, d_ff 512 .. 8192, 1 .. 256
+// experts, 8 .. 190 rows per expert, even and skewed routing), and hold for the present ones: over 170 launches of the same ranges, captured, one
+// behind the other, the rule's choices are 1.47 times as fast as the fused kernel on the geometric mean, the better of the two each time would be 1.49
+// (worst: 48 experts of 256 x 1024, 77 skewed rows each, 36 us and 20 fused; 96 of 256 x 3072, 159 rows each, fused 156 and 118). With three streams of
+// launches 1.15 and 1.22: few experts of d_model 512 and less take 14 us as three launches and 7 to 9 fused, whose launches overlap.
 bool uses_gemm_kernels(const pgmoe_config &c, int n_rows) {
     if (c.dtype != PGMOE_BF16) return false;
     // the k loop takes two 32-k tiles per turn (in every K slice of the down-projection); the pack kernel PACK_KT k-tiles per workgroup
@@ -582,7 +583,8 @@ static GemmPlan gemm_plan(const pgmoe_config &c, int n_rows) {
     double best_up = 1e30, best_down = 1e30;
     const bool admitted = ffn_gemm_launch_bytes(c, n_rows) <= PGMOE_STATIC_SCRATCH_BYTES;
     for (int bn = 128; bn <= 256; bn *= 2) {
-        // microseconds per 32-k stage of a workgroup that has its CU to itself
+        // microseconds per 32-k stage of a workgroup that has its CU to itself: prices from before a chunk's ring went by its size (0.64 and 0.32 here for sixteen
+        // and two row tiles of 256 columns, which then took 0.76 and 0.46 and now take 0.62 and 0.38)
         const double stage = (bn == 256 ? 0.80 : 0.50) * std::max(rt / 20.0, 0.4);
         auto rounds = [&](double wgs) { return std::max(1.0, std::ceil(wgs / 256.0 - 0.05)); };
         if (c.d_ff % bn == 0) {
