@@ -9,7 +9,7 @@ expert FFNs and weighted combine, for all L blocks of the stack.  Inputs (hidden
 every step, gate weights) are resident in HBM before the timed region; the expert store is in
 pinned host memory (offloaded workloads) or in HBM (resident workloads), as the workload says.
 
-Prints ONE JSON line.  The headline numbers are those of --workload (default: the largest
+Prints ONE JSON line, a few kilobytes long, and before it, on stderr, the whole record (schedules, sweeps, every other workload's figures).  The headline numbers are those of --workload (default: the largest
 configuration, the Switch-Large-128 decode stack with top-1 routing, 25.8 GB of experts in pinned
 host memory); --also adds abbreviated results of other workloads under "other_workloads" (same
 measurement, fewer steps); the top-2 run of the same model shares the headline's expert store.
@@ -622,6 +622,31 @@ def activated_expert_sweep(host_threads, steps):
             "steps": steps, "by_top_k": {str(k): rows[str(k)] for k in W.SWEEP_K}}
 
 
+LINE_KEYS = ("metric", "value", "unit", "n_gpus", "steps", "warmup", "ms_per_step", "higher_is_better", "scaling", "vs_baseline", "dtype", "data", "config",
+             "ms_per_token", "ms_per_token_per_layer", "block_latency_us", "roofline", "host_link", "streams", "overlap", "gpu_only", "migration_engines",
+             "expert_cache", "systems", "cpu_baseline", "measured_peaks")
+LINE_OTHER_KEYS = ("value", "unit", "steps", "ms_per_step", "block_latency_us")
+
+
+def line_of(record):
+    """What is printed as the one line of the result: the workload's own figures to six digits, of the others the headline and the expert kernel's
+    share of its peak.  Whoever keeps the last few kilobytes of a log has all of it; the whole record goes to stderr before it."""
+    def short(v):
+        if isinstance(v, float):
+            return float(f"{v:.6g}")
+        if isinstance(v, dict):
+            return {k: short(x) for k, x in v.items() if k != "note"}
+        return [short(x) for x in v] if isinstance(v, list) else v
+
+    out = {k: record[k] for k in LINE_KEYS if k in record}
+    if record.get("other_workloads"):
+        out["other_workloads"] = {}
+        for n, r in record["other_workloads"].items():
+            o = out["other_workloads"][n] = {k: r[k] for k in LINE_OTHER_KEYS if k in r}
+            o["roofline"] = {k: r["roofline"][k] for k in ("bound", "kernel", "avg_launch_us", "frac") if k in r.get("roofline", {})}
+    return json.dumps(short(out))
+
+
 def main():
     ap = argparse.ArgumentParser()
     ap.add_argument("--gpus", type=int, default=1)
@@ -703,7 +728,8 @@ def main():
         out["other_workloads"][n] = {k: r[k] for k in keep if k in r}
     if not args.no_sweep_k and not args.main_only:
         out["activated_expert_sweep"] = activated_expert_sweep(args.host_threads, args.sweep_steps)
-    print(json.dumps(out), flush=True)
+    log("[bench] record: " + json.dumps(out))
+    print(line_of(out), flush=True)
 
 
 if __name__ == "__main__":

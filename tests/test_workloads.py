@@ -100,3 +100,24 @@ def test_bench_refuses_more_than_one_gpu():
     root = os.path.dirname(os.path.dirname(os.path.abspath(__file__)))
     r = subprocess.run([sys.executable, os.path.join(root, "bench.py"), "--gpus", "2"], capture_output=True, text=True, timeout=120)
     assert r.returncode != 0 and "ONE GPU" in r.stderr and r.stdout.strip() == ""
+
+
+def test_the_benchmark_line_is_short_and_whole():
+    """Logs keep the last kilobytes of a run: 8000 characters hold the line with every workload, and what it must have is in it."""
+    import json
+
+    import bench
+    roofline = {"bound": "hbm", "kernel": "ffn_fused_kernel", "avg_launch_us": 82.123456789, "frac": 0.64123456789, "unit": "GB/s", "traffic": None}
+    record = {k: 1.23456789012 for k in bench.LINE_KEYS}
+    record.update(metric="tokens/s", unit="tokens/s", vs_baseline=None, higher_is_better=True, config={"workload": "w" * 120}, roofline=roofline,
+                  overlap={"hidden_frac": 1 / 3, "note": "n" * 2000}, activated_expert_sweep={"by_top_k": "s" * 4000},
+                  other_workloads={f"workload{i}": {"value": 1e6 / 7, "unit": "tokens/s", "steps": 4, "ms_per_step": 1 / 3, "roofline": roofline,
+                                                    "gpu_only": {"note": "n" * 3000}} for i in range(7)})
+    text = bench.line_of(record)
+    line = json.loads(text)
+    assert len(text) < 8000 and "\n" not in text
+    assert all(k in line for k in ("metric", "value", "unit", "n_gpus", "steps", "warmup", "ms_per_step", "higher_is_better", "scaling", "vs_baseline", "dtype",
+                                   "data", "config"))
+    assert line["vs_baseline"] is None and line["value"] == 1.23457 and line["overlap"] == {"hidden_frac": 0.333333}
+    assert line["other_workloads"]["workload3"] == {"value": 142857.0, "unit": "tokens/s", "steps": 4, "ms_per_step": 0.333333,
+                                                    "roofline": {"bound": "hbm", "kernel": "ffn_fused_kernel", "avg_launch_us": 82.1235, "frac": 0.641235}}
