@@ -114,9 +114,10 @@ __global__ __launch_bounds__(NW * 64) void ffn_fused_kernel(
     };
 
     // Tiles in flight: sixteen for a wavefront of 16-row chunks, eight where the accumulators of 32 and 64 rows would leave fewer wavefronts per SIMD (d_model 256:
-    // 18 rows for each of 64 experts of 256 x 1024 25.2 us with sixteen, 16.3 with eight; 45 for each of 128 47.2 and 33.7), four for the eight wavefronts of 64-row
-    // chunks, which HBM paces (128 experts of 768 x 3072, three streams: 4096 rows 231.2 us with eight, 230.6 with four, 28 skewed rows each 244.3 and 239.9,
-    // 32 uneven ones 221.8 and 218.7, the one launch that conditional requests served better, 214.8).
+    // 18 rows for each of 64 experts of 256 x 1024 25.2 us with sixteen, 16.3 with eight; 45 for each of 128 47.2 and 33.7), four for the eight wavefronts of the
+    // 64-row chunks of 1024 and two of 768, which HBM paces: rows that lie evenly pass with few tiles in flight, skewed ones want more (three streams, conditional requests with
+    // eight / steady ones with two / four / eight: 128 experts of 768 x 3072, 4096 rows 231.3 / 227.8 / 231.3 / 231.2 us, 32 uneven rows each 215.8 / 216.3 /
+    // 219.4 / 221.8, 28 skewed ones 253.8 / 243.9 / 240.8 / 244.3, 4096 skewed ones 260.5 / 246.6 / 240.7 / 242.7).
     static_assert(D <= NT && NT % D == 0, "the ring reaches into the next sub-slab at most, where a tile finds the place that was filled for it");
     // The 16- and 32-row chunks of d_model 512 leave it to the compiler: launches of theirs that fill the chip are paced by HBM, which the pauses do not
     // slow (256 experts of 512 x 2048, 3000 rows: 214 us a block, 218 with the steady stream), and the steady stream's registers cost a wavefront per SIMD.
@@ -155,7 +156,7 @@ __global__ __launch_bounds__(NW * 64) void ffn_fused_kernel(
 
     // The rows' operand cells are read from LDS AHEAD tiles before their products, or with 0 where the compiler puts it: in the largest chunks of d_model 512
     // and 768 and at d_model 2048 the registers are worth more as they are (128 experts of 512 x 2048, some 50 rows each: 182 us with reads ahead and
-    // conditional requests, 113 steady and without; 128 of 768 x 3072, 28 skewed rows 253 and 239, 256 of 768 x 1536, 27 skewed rows 300 and 265; 4 of
+    // conditional requests, 113 steady and without; 128 of 768 x 3072, 28 skewed rows 253 and 244, 256 of 768 x 1536, 27 skewed rows 302 and 281; 4 of
     // 2048 x 8192, 10 rows each, three launches at a time 55.3 and 53.7).
     constexpr bool AS_IT_COMES = (MT == 4 && (KT == 16 || (KT == 24 && NW == 8))) || KT == 64;
     constexpr int AHEAD = AS_IT_COMES ? 0 : (KT < 4 ? 1 : (KT == 8 ? 2 : (MT == 1 ? 4 : (MT == 2 || NW == 8 ? 2 : 1))));
@@ -697,7 +698,7 @@ FfnPlan plan_ffn(const pgmoe_config &c, int n_rows, int slices) {
     X(1, 2, 4, 4) X(1, 4, 4, 8) X(1, 8, 4, 16) X(1, 16, 4, 16) X(1, 24, 4, 16) X(1, 32, 4, 16) X(1, 64, 4, 16) \
     X(1, 24, 2, 16) X(1, 32, 2, 16)                                                                         \
     X(2, 2, 4, 4) X(2, 4, 4, 8) X(2, 8, 4, 8) X(2, 16, 4, 16) X(2, 24, 4, 16) X(2, 32, 4, 8)              \
-    X(4, 2, 4, 4) X(4, 4, 4, 8) X(4, 8, 4, 8) X(4, 16, 4, 8) X(4, 24, 4, 8) X(4, 24, 8, 4) X(4, 32, 8, 4)
+    X(4, 2, 4, 4) X(4, 4, 4, 8) X(4, 8, 4, 8) X(4, 16, 4, 8) X(4, 24, 4, 8) X(4, 24, 8, 2) X(4, 32, 8, 4)
 
 static bool fused_case_built(int mt, int kt, int nw) {
 #define X(MT_, KT_, NW_, D_) \
